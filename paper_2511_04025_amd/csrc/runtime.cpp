@@ -131,18 +131,41 @@ int normalize_opts(const shh_opts *in, shh_opts *out) {
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-#ifndef SHH_TZ
-#define SHH_TZ 32
-#endif
-// z planes per stencil workgroup (the z-march length)
-static int tz_for(int n) { return n < SHH_TZ ? n : SHH_TZ; }
+// z planes per stencil workgroup (the z-march length) of an n^3 grid.  One
+// design's six load cases are tiles x runs x 6 workgroups on 512 places (two
+// workgroups on each of 256 CUs); a workgroup of tz planes takes about tz + 3
+// layer times (two planes of halo and the pipeline's start).  The length is the
+// even one, at most 64, with the smallest sum of the time of one design alone
+// (whole rounds over the places) and twice that in a large batch (rounds
+// shared): short runs where the grid would leave the chip idle (48^3: 6 planes,
+// where 32 ran 96 workgroups: a Jacobi pass at 45^3 61 -> 27 us, a design at
+// 24^3 in FP64 27.6 -> 19.9 ms), balanced rounds on larger grids (128^3: 26,
+// where 32 left the third round at 6 %).  It depends on the grid and precision
+// alone, so a design's result does not depend on its batch.
+static int tz_for(int n, int prec) {
+  constexpr long long places = 512;
+  const int w = prec == SHH_PREC_FP64 ? 0 : 1;
+  const int X = w ? Tile<float>::X : Tile<double>::X, Y = w ? Tile<float>::Y : Tile<double>::Y;
+  const long long tiles = (long long)((n + X - 1) / X) * ((n + Y - 1) / Y) * NRHS;
+  int best = 2;
+  double best_cost = -1.0;
+  for (int tz = 2; tz <= n + 1 && tz <= 64; tz += 2) {
+    const long long groups = tiles * ((n + tz - 1) / tz);
+    const double cost = (double((groups + places - 1) / places) + 2.0 * double(groups) / places) * (tz + 3);
+    if (best_cost < 0.0 || cost <= best_cost) {  // of equal costs the longer run: less halo
+      best = tz;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
 
 Layout make_layout(int n, int N, int K, int prec, bool save, bool vectors, int solver) {
   Layout L{};
   L.vectors = vectors;
   const long long nn = (long long)n * n * n;
   const int nb = 2 * K + 1;
-  const int tz_runs = (n + tz_for(n) - 1) / tz_for(n);
+  const int tz = tz_for(n, prec), tz_runs = (n + tz - 1) / tz;
   const int tiles = std::max(((n + Tile<float>::X - 1) / Tile<float>::X) * ((n + Tile<float>::Y - 1) / Tile<float>::Y),
                              ((n + Tile<double>::X - 1) / Tile<double>::X) * ((n + Tile<double>::Y - 1) / Tile<double>::Y)) *
                     tz_runs;
@@ -241,7 +264,7 @@ int slot_init(Slot &s, char *base, hipStream_t st) {
   h.n = n;
   h.prec = prec;
   h.nn = (long long)n * n * n;
-  h.tz = tz_for(n);
+  h.tz = tz_for(n, prec);
   h.tiles_z = (n + h.tz - 1) / h.tz;
   h.tiles_x[0] = (n + Tile<double>::X - 1) / Tile<double>::X;
   h.tiles_y[0] = (n + Tile<double>::Y - 1) / Tile<double>::Y;
