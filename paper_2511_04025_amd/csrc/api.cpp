@@ -386,6 +386,7 @@ int32_t shh_apply_stiffness(int32_t n, int32_t precision, const double *d_E, dou
   g.nblocks = s.host.ntiles[precision == SHH_PREC_MIXED ? 1 : 0] * nrhs;
   SHH_HIP(hipMemcpyAsync(seg_mem, &g, sizeof(g), hipMemcpyHostToDevice, st));
   LaunchArgs la{(const Segment *)seg_mem, 1, g.nblocks};
+  la.split_evenly();
   SHH_HIP(launch_stencil_apply(la, precision, st));
   SHH_HIP(hipStreamSynchronize(st));
   return SHH_OK;
@@ -435,6 +436,7 @@ int32_t shh_load_vectors(int32_t n, const double *d_E, double nu, double *d_f, v
   g.flag = RES_INIT;
   SHH_HIP(hipMemcpyAsync(seg_mem, &g, sizeof(g), hipMemcpyHostToDevice, st));
   LaunchArgs la{(const Segment *)seg_mem, 1, g.nblocks};
+  la.split_evenly();
   SHH_HIP(launch_stencil_resid(la, SHH_PREC_FP64, st));
   SHH_HIP(hipStreamSynchronize(st));
   return SHH_OK;

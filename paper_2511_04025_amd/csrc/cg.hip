@@ -239,32 +239,30 @@ __global__ __launch_bounds__(VEC_THREADS) void zero_kernel(LaunchArgs la) {
   }
 }
 
-static int padded_grid(int total) { return ((total + 7) / 8) * 8; }
-
 hipError_t launch_finish_resid(const LaunchArgs &la, int prec, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  if (prec == 0) finish_resid_kernel<double><<<padded_grid(la.total), VEC_THREADS, 0, st>>>(la);
-  else finish_resid_kernel<float><<<padded_grid(la.total), VEC_THREADS, 0, st>>>(la);
+  if (prec == 0) finish_resid_kernel<double><<<la.grid(), VEC_THREADS, 0, st>>>(la);
+  else finish_resid_kernel<float><<<la.grid(), VEC_THREADS, 0, st>>>(la);
   return hipGetLastError();
 }
 
 hipError_t launch_scalar(const LaunchArgs &la, int phase, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  scalar_kernel<<<padded_grid(la.total), VEC_THREADS, 0, st>>>(la, phase);
+  scalar_kernel<<<la.grid(), VEC_THREADS, 0, st>>>(la, phase);
   return hipGetLastError();
 }
 
 hipError_t launch_fold(const LaunchArgs &la, int prec, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  if (prec == 0) fold_kernel<double><<<padded_grid(la.total), VEC_THREADS, 0, st>>>(la);
-  else fold_kernel<float><<<padded_grid(la.total), VEC_THREADS, 0, st>>>(la);
+  if (prec == 0) fold_kernel<double><<<la.grid(), VEC_THREADS, 0, st>>>(la);
+  else fold_kernel<float><<<la.grid(), VEC_THREADS, 0, st>>>(la);
   return hipGetLastError();
 }
 
 hipError_t launch_zero_vectors(const LaunchArgs &la, int prec, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  if (prec == 0) zero_kernel<double><<<padded_grid(la.total), VEC_THREADS, 0, st>>>(la);
-  else zero_kernel<float><<<padded_grid(la.total), VEC_THREADS, 0, st>>>(la);
+  if (prec == 0) zero_kernel<double><<<la.grid(), VEC_THREADS, 0, st>>>(la);
+  else zero_kernel<float><<<la.grid(), VEC_THREADS, 0, st>>>(la);
   return hipGetLastError();
 }
 

@@ -179,20 +179,24 @@ enum { SMG_DIR = 0, SMG_STEP1 = 1, SMG_POST = 2, SMG_LAST = 3, SMG_RES = 4, SMG_
 #define SHH_SEL_DEG0 2
 #endif
 
+// Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on
+// XCD b % 8).  Each XCD takes a contiguous run of logical workgroups, so that
+// neighbouring tiles (shared halos) and the six load cases of one tile (shared
+// moduli) meet in the same L2.
+constexpr int NXCD = 8;
 struct LaunchArgs {
   const Segment *segs;
   int nseg;
-  int total;            // logical workgroups (before padding to a multiple of 8)
+  int total;            // logical workgroups
+  int per;              // workgroups launched per XCD (the longest run)
+  int start[NXCD + 1];  // XCD x takes logical workgroups [start[x], start[x + 1])
+  // runs of equal length, for workgroups of equal cost
+  void split_evenly() {
+    per = (total + NXCD - 1) / NXCD;
+    for (int x = 0; x <= NXCD; ++x) start[x] = x * per < total ? x * per : total;
+  }
+  int grid() const { return NXCD * per; }
 };
-
-// Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on
-// XCD b % 8).  Give each XCD a contiguous run of logical workgroups so that
-// neighbouring tiles (shared halos) and the six load cases of one tile (shared
-// moduli) meet in the same L2.
-__device__ __forceinline__ int logical_block(int b, int grid) {
-  const int per = grid >> 3;  // grid is a multiple of 8
-  return (b & 7) * per + (b >> 3);
-}
 
 struct Work {
   SlotDev *slot;
@@ -213,8 +217,8 @@ __device__ __forceinline__ const SHH_CONST T *to_const(const T *p) {
 }
 
 __device__ __forceinline__ bool decode_work(const LaunchArgs &a, Work &w) {
-  const int L = logical_block(blockIdx.x, gridDim.x);
-  if (L >= a.total) return false;
+  const int xcd = blockIdx.x & (NXCD - 1), L = a.start[xcd] + int(blockIdx.x / NXCD);
+  if (L >= a.start[xcd + 1]) return false;
   const SHH_CONST Segment *segs = to_const(a.segs);
   int lo = 0, hi = a.nseg - 1;
   while (lo < hi) {  // last segment with first <= L

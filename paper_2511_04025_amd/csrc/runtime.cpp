@@ -381,8 +381,30 @@ void Solver::set_segment_memory(char *d_mem, size_t bytes) {
   for (auto &v : host_segs_) v.clear();
 }
 
+// Divide the workgroups among the XCDs in order, each taking its share of the
+// cost: grids of different sizes march z-runs of different lengths, and equal
+// counts left the XCDs of the long runs behind (a batch of 64^3, 96^3 and 128^3
+// designs ran 5 to 7 % slower).
+static void split_by_cost(const std::vector<Segment> &segs, const std::vector<int> &cost, LaunchArgs &la) {
+  long long all = 0;
+  for (size_t i = 0; i < segs.size(); ++i) all += (long long)segs[i].nblocks * cost[i];
+  la.per = 0;
+  la.start[0] = 0;
+  size_t i = 0;
+  long long before = 0;  // cost of the segments before i
+  for (int x = 1; x <= NXCD; ++x) {
+    const long long upto = (all * x + NXCD - 1) / NXCD;
+    while (i < segs.size() && before + (long long)segs[i].nblocks * cost[i] < upto)
+      before += (long long)segs[i].nblocks * cost[i], ++i;
+    la.start[x] = i < segs.size() ? segs[i].first + int((upto - before + cost[i] - 1) / cost[i]) : la.total;
+    la.start[x] = std::min(la.start[x], la.total);
+    la.per = std::max(la.per, la.start[x] - la.start[x - 1]);
+  }
+}
+
 int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs &la) {
   std::vector<Segment> segs;
+  std::vector<int> cost;  // of one workgroup of each segment
   int first = 0;
   for (Slot *s : slots) {
     Segment g;
@@ -411,9 +433,11 @@ int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_r
     g.nblocks = units * g.nrhs;
     first += g.nblocks;
     segs.push_back(g);
+    cost.push_back(per_tile ? std::min(s->host.tz, s->host.n) + 3 : 1);
   }
   la.nseg = int(segs.size());
   la.total = first;
+  split_by_cost(segs, cost, la);
   const size_t bytes = sizeof(Segment) * segs.size();
   if (bytes > seg_cap_) return SHH_WORKSPACE_TOO_SMALL;
   Segment *dst = (Segment *)(seg_mem_ + (size_t)k * seg_cap_);

@@ -668,11 +668,9 @@ void stencil_kernel(LaunchArgs la) {
   }
 }
 
-static int padded_grid(int total) { return ((total + 7) / 8) * 8; }
-
 hipError_t launch_stencil_pcg(const LaunchArgs &la, int prec, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  const int g = padded_grid(la.total);
+  const int g = la.grid();
   if (prec == 0) stencil_kernel<double, double, MODE_PCG><<<g, Tile<double>::THREADS, 0, st>>>(la);
   else stencil_kernel<float, float, MODE_PCG><<<g, Tile<float>::THREADS, 0, st>>>(la);
   return hipGetLastError();
@@ -680,7 +678,7 @@ hipError_t launch_stencil_pcg(const LaunchArgs &la, int prec, hipStream_t st) {
 
 hipError_t launch_stencil_resid(const LaunchArgs &la, int prec, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  const int g = padded_grid(la.total);
+  const int g = la.grid();
   if (prec == 0) stencil_kernel<double, double, MODE_RESID><<<g, Tile<double>::THREADS, 0, st>>>(la);
   else stencil_kernel<double, float, MODE_RESID><<<g, Tile<double>::THREADS, 0, st>>>(la);
   return hipGetLastError();
@@ -688,7 +686,7 @@ hipError_t launch_stencil_resid(const LaunchArgs &la, int prec, hipStream_t st) 
 
 hipError_t launch_stencil_apply(const LaunchArgs &la, int prec, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  const int g = padded_grid(la.total);
+  const int g = la.grid();
   if (prec == 0) stencil_kernel<double, double, MODE_APPLY><<<g, Tile<double>::THREADS, 0, st>>>(la);
   else stencil_kernel<float, float, MODE_APPLY><<<g, Tile<float>::THREADS, 0, st>>>(la);
   return hipGetLastError();
@@ -696,7 +694,7 @@ hipError_t launch_stencil_apply(const LaunchArgs &la, int prec, hipStream_t st) 
 
 template <int MODE>
 static void launch_mg_mode(const LaunchArgs &la, int prec, hipStream_t st) {
-  const int g = padded_grid(la.total);
+  const int g = la.grid();
   if (prec == 0) stencil_kernel<double, double, MODE><<<g, Tile<double>::THREADS, 0, st>>>(la);
   else stencil_kernel<float, float, MODE><<<g, Tile<float>::THREADS, 0, st>>>(la);
 }
