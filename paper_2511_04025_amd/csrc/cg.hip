@@ -197,7 +197,8 @@ __global__ __launch_bounds__(VEC_THREADS) void fold_kernel(LaunchArgs la) {
   for (int k = 0; k < NRHS; ++k) {
     const bool sel = mode == RES_RECOMPUTE ? st->active[k] != 0 : st->ff[k] > s->ffloor * s->ffloor;
     const double a = sel ? st->alpha[k] : 0.0;
-    const T *p = (const T *)s->p[st->pcur[k]] + (long long)k * 3 * nn;
+    // the multigrid CG keeps the parity of its direction apart from that of r
+    const T *p = (const T *)s->p[s->mgd ? st->mgpar[k] : st->pcur[k]] + (long long)k * 3 * nn;
     T *x = (T *)s->x + (long long)k * 3 * nn;
     double *x64 = s->x64 + (long long)k * 3 * nn;
     for (int c = 0; c < 3; ++c) {

@@ -75,7 +75,7 @@ struct CgState {
   double rho[NRHS];       // r^T D^-1 r of the current residual
   double rho_prev[NRHS];  // the previous one (for a replaced residual's beta)
   double rho_mg[NRHS];    // multigrid CG: r . z at the start of the last iteration
-  double alpha[NRHS];     // step length of the update still to be applied to x, r
+  double alpha[NRHS];     // step length of the update still to be applied to x, r (multigrid: to x)
   double beta[NRHS];      // coefficient of the next direction update
   double rr[NRHS];        // ||r||^2 (recursive, or true after a recompute)
   double ff[NRHS];        // ||f||^2
@@ -86,7 +86,7 @@ struct CgState {
   int active[NRHS];       // 1 while load case k iterates
   int status[NRHS];
   int iters[NRHS];
-  int pcur[NRHS];         // which of the two r, p, q buffer sets is current
+  int pcur[NRHS];         // which of the two r, p, q buffer sets is current (multigrid: r only)
   int mgpar[NRHS];        // multigrid CG: which p buffer holds the current direction
   int no_keep[NRHS];      // selective multigrid CG: restart after every replacement (set by a stall)
   int stag[NRHS];         // selective CG: replacements since the true residual last fell by 1 %
@@ -142,10 +142,12 @@ struct SlotDev {
   // CG vectors [6][3][nn] (float mixed / double FP64).  r, p and q are double
   // buffered: a CG pass reads set pcur[k] of load case k and writes the other
   void *r[2], *p[2], *q[2], *x;
-  // multigrid, voxel level: the pre-smoother's second Chebyshev direction
-  // [6][3][nn] (the only one stored) and the coefficients 1 / theta, c1, c2
+  // multigrid, voxel level: z = V r [6][3][nn], the first coarse level's
+  // solution [6][3][nn / 8] that the post-smoothing pass interpolates, and the
+  // smoother's 1 / theta
   void *mgd;
-  double mgc[3];
+  const void *mgxc;
+  double mgc;
   double *x64;          // FP64 solution accumulator (mixed); == x for FP64
   double *partials;     // [NRHS][maxparts][PSTRIDE]
   CgState *st;
@@ -165,16 +167,13 @@ struct Segment {
 };
 
 // Fused voxel-level passes of the multigrid-preconditioned CG (stencil kernel)
-enum { SMG_DIR = 0, SMG_STEP1 = 1, SMG_POST = 2, SMG_LAST = 3, SMG_RES = 4, SMG_POST1 = 5 };
-// Chebyshev degree of the voxel level's smoother (1 or 2; the coarse levels
-// take 2).  Dense multigrid (SHH_MG_DEG0): degree 1 costs about 1 % more CG
-// iterations at 128^3 and saves two of the five voxel-level operator passes
-// of an iteration (20 % faster).  Selective solve (SHH_SEL_DEG0): degree 2,
-// since with degree 1 the FP32 culled solve of some designs stalls above the
-// tolerance (FP64 converges).  The other degree is a build option.
-#ifndef SHH_MG_DEG0
-#define SHH_MG_DEG0 1
-#endif
+enum { SMG_DIR = 0, SMG_PRE = 1, SMG_POST = 2 };
+// Chebyshev degree of the voxel level's smoother (the coarse levels take 2).
+// Dense multigrid: degree 1, which costs about 1 % more CG iterations at 128^3
+// than degree 2 and saves two of the five voxel-level operator passes of an
+// iteration (20 % faster).  Selective solve (SHH_SEL_DEG0): degree 2, since
+// with degree 1 the FP32 culled solve of some designs stalls above the
+// tolerance (FP64 converges); the other degree is a build option.
 #ifndef SHH_SEL_DEG0
 #define SHH_SEL_DEG0 2
 #endif

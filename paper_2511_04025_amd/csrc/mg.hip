@@ -565,17 +565,13 @@ __global__ __launch_bounds__(256) void mg_coarsest_kernel(MgBatch B) {
   }
 }
 
-// Degree-2 Chebyshev smoothing of A x = b at level l:
+// Degree-2 Chebyshev smoothing of A x = b on the coarse levels:
 //   d = D^-1 b / theta;  r = b - A d;  d' = c1 d + c2 D^-1 r;  x = d + d'
 //   (pre-smoother; the restriction takes r - A d');  after the coarse
 //   correction r = b - A x;  d = D^-1 r / theta;  x += d;
 //   x += c1 d + c2 D^-1 (r - A d)  (post-smoother).
 // Every step after an operator application runs in that pass's output stage
-// (the stencil kernel's multigrid modes at the voxel level, mg_epilogue on
-// the coarse levels); this sweep is the first step, d = D^-1 b / theta, on
-// the coarse levels, and at the voxel level the pending CG update
-// x_cg += alpha p, b = r -= alpha q (q = K p), so that b is the new CG
-// residual (the stencil pass after it forms d itself).
+// (mg_epilogue); this sweep is the first step, d = D^-1 b / theta.
 template <typename T>
 __global__ __launch_bounds__(VEC_THREADS) void mg_vec_kernel(MgBatch B, int l) {
   const SlotDev *s = B.slot[blockIdx.z];
@@ -586,28 +582,10 @@ __global__ __launch_bounds__(VEC_THREADS) void mg_vec_kernel(MgBatch B, int l) {
   const long long i0 = (long long)blockIdx.x * CHUNK;
   const long long i1 = min(i0 + (long long)CHUNK, nn);
   const long long vb = (long long)k * 3 * nn;
-  T *b = (T *)L.b + vb;
-  if (l == 0) {
-    const T a = (T)s->st->alpha[k];
-    if (a == T(0)) return;
-    // (the same pass with every load of a thread's four nodes ahead of its
-    // stores measured 5 % slower: this one keeps more waves in flight)
-    T *xcg = (T *)s->x + vb;
-    const T *pcg = (const T *)s->p[s->st->mgpar[k]] + vb;
-    const T *q = (const T *)L.q + vb;
-    for (long long i = i0 + threadIdx.x; i < i1; i += VEC_THREADS)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const long long j = c * nn + i;
-        xcg[j] = xcg[j] + a * pcg[j];
-        b[j] = b[j] - a * q[j];
-      }
-    return;
-  }
   const T ith = (T)L.inv_theta;
   SHH_GLOBAL T *d = to_global((T *)L.d) + vb;
   const SHH_GLOBAL T *Dv = to_global((const T *)L.Dinv);
-  const SHH_GLOBAL T *bg = to_global((const T *)b);
+  const SHH_GLOBAL T *bg = to_global((const T *)L.b) + vb;
   constexpr int PER = CHUNK / VEC_THREADS;
   T dv[PER][3], bv[PER][3];
 #pragma unroll
@@ -637,6 +615,10 @@ __global__ __launch_bounds__(VEC_THREADS) void mg_vec_kernel(MgBatch B, int l) {
 //            beta = rho' / (rho the last iteration started from)
 //   ALPHA:   alpha = rho / p . K p; the new direction becomes current
 //   BETA:    rho' = r . z, ||r||^2 -> convergence; beta = rho' / rho
+// After a V-cycle (all but ALPHA) the residual buffer that its pre-smoothing
+// pass wrote becomes current.  alpha stays set after BETA, whatever the load
+// case's state: x += alpha p is applied by the next direction pass or, where
+// none follows, before the next FP64 residual.
 __global__ __launch_bounds__(VEC_THREADS) void mg_scalar_kernel(MgBatch B, int phase) {
   __shared__ double red[2 * 16];
   const SlotDev *s = B.slot[blockIdx.z];
@@ -646,13 +628,9 @@ __global__ __launch_bounds__(VEC_THREADS) void mg_scalar_kernel(MgBatch B, int p
   double tot[2];
   sum_partials<2, PSTRIDE>(parts, s->ntiles[s->prec], tot, red, VEC_THREADS);
   if (threadIdx.x != 0) return;
-  // the direction pass ran for the active load cases only: their new
-  // direction becomes current
-  if (!st->active[k]) {
-    st->alpha[k] = 0.0;
-    st->beta[k] = 0.0;
-    return;
-  }
+  // the passes before this ran for the active load cases only
+  if (!st->active[k]) return;
+  if (phase != MGS_ALPHA) st->pcur[k] ^= 1;
   if (phase == MGS_RESTART || phase == MGS_REPLACE) {
     // (the replacement's residual phase has since overwritten rho and beta
     // with the Jacobi recurrences; rho_mg kept the iteration's own rho)
@@ -681,7 +659,6 @@ __global__ __launch_bounds__(VEC_THREADS) void mg_scalar_kernel(MgBatch B, int p
   } else {
     const double rho_n = tot[0], rr = tot[1];
     st->iters[k] += 1;
-    st->alpha[k] = 0.0;
     st->rr[k] = rr;
     const double rel = sqrt(rr / st->ff[k]);
     st->rel[k] = rel;

@@ -10,8 +10,8 @@
 // the coarse element's 8 corner values to child f's corners), and on level 1
 // K_f = E_f K_0, so K_E = sum_f E_f G_f with G_f = Q_f^T K_0 Q_f.  Coarse
 // element matrices are assembled into 27-point nodal stencils of 3 x 3 blocks
-// for the smoother and residual sweeps.  Smoothing is Chebyshev (degree 2)
-// on D^-1 A over [h / 33, h], h an upper bound of lambda_max: on the voxel
+// for the smoother and residual sweeps.  Smoothing is Chebyshev (degree 2; 1
+// on the voxel level of the dense solve) on D^-1 A over [h / 33, h], h an upper bound of lambda_max: on the voxel
 // level the element bound lambda_max(diag(K_0)^-1 K_0), on coarse levels
 // 1.2 x a power-iteration estimate; the coarsest level (at most 8^3 nodes) is
 // solved with a dense inverse of its operator made nonsingular on the three
@@ -41,9 +41,10 @@ struct MgLevel {
   void *S, *Dinv;
   // V-cycle vectors [NRHS][3][nn]: right-hand side, iterate, residual,
   // Chebyshev direction, operator output (on levels >= 1 the fused sweeps
-  // keep the next direction and the post-smoothing iterate there).  Level 0 aliases the slot's CG
-  // vectors (b = r[0], x = r[1] (z), r = q[1], q = q[0]) except d, which
-  // has a buffer of its own (the CG direction alternates between p[0] and p[1]).
+  // keep the next direction and the post-smoothing iterate there).  Level 0 has
+  // r (the slot's q[1]: the residual to restrict) and d (a buffer of its own:
+  // z = V r in the dense solve, the first direction in the selective one); its
+  // passes take the slot's other CG vectors by name.
   void *b, *x, *r, *d, *q;
   void *Ke;             // setup only: element matrices [nn][24][24] (levels >= 1)
   double inv_theta, c1, c2;  // Chebyshev coefficients

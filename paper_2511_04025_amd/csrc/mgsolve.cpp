@@ -290,37 +290,32 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
   hipEvent_t e0 = nullptr;
   auto tb = [&](bool on) -> int { return (on && timer) ? timer->timed_begin(&e0) : (e0 = nullptr, 0); };
   auto te = [&](int kind) -> int { return (e0 && timer) ? timer->timed_end(e0, kind) : 0; };
-  auto vec = [&]() -> int {
-    if ((rc = tb(l == 0))) return rc;
-    SHH_HIP(mg_launch_vec(B, l, nch_max, prec, st));
-    return te(SHH_PROF_MG_UPDATE);
-  };
-  // an operator pass with the Chebyshev sweep after it fused in: the voxel
-  // level's stencil passes, the coarse levels' stored-stencil passes
-  auto app = [&](int src0, int ep) -> int {
-    if (l == 0) return apply0(smooth, src0);
+  if (l == 0) {
+    // voxel level: one smoothing step each side.  The pre-smoothing pass also
+    // applies the CG's residual update and leaves the residual to restrict;
+    // the post-smoothing pass interpolates the coarse correction itself.
+    if ((rc = apply0(smooth, SMG_PRE))) return rc;
+    if ((rc = tb(true))) return rc;
+    SHH_HIP(mg_launch_restrict(B, l, nn_next_max, prec, st));
+    if ((rc = te(SHH_PROF_MG_RESTRICT))) return rc;
+    if ((rc = vcycle(smooth, l + 1, st, timer, apply0))) return rc;
+    return apply0(smooth, SMG_POST);
+  }
+  // an operator pass with the Chebyshev sweep after it fused in
+  auto app = [&](int ep) -> int {
     if ((rc = tb(l == 1))) return rc;
     SHH_HIP(mg_launch_apply(B, l, 0, nn_max, all_even, prec, st, 1, ep));
     return te(SHH_PROF_MG_APPLY1);
   };
-  // pre-smoother (at the voxel level INIT also applies the pending CG
-  // update); with degree 2 the second pass leaves r - A d1, the residual to
-  // restrict, in r.  Degree-1 smoothing at the voxel level: the first step
-  // alone (its r is the residual to restrict), and after the correction one
-  // pass that leaves z = x + D r / theta
-  const bool deg1 = l == 0 && SHH_MG_DEG0 == 1;
-  if ((rc = vec()) || (rc = app(MG_SRC_STEP1, MGE_STEP1)) || (!deg1 && (rc = app(MG_SRC_RES, MGE_RES)))) return rc;
+  // pre-smoother; its second pass leaves r - A d1, the residual to restrict, in r
+  SHH_HIP(mg_launch_vec(B, l, nch_max, prec, st));
+  if ((rc = app(MGE_STEP1)) || (rc = app(MGE_RES))) return rc;
   // coarse-grid correction
-  if ((rc = tb(l == 0))) return rc;
   SHH_HIP(mg_launch_restrict(B, l, nn_next_max, prec, st));
-  if ((rc = te(SHH_PROF_MG_RESTRICT))) return rc;
   if ((rc = vcycle(smooth, l + 1, st, timer, apply0))) return rc;
-  if ((rc = tb(l == 0))) return rc;
   SHH_HIP(mg_launch_prolong(B, l, nn_next_max, prec, st));
-  if ((rc = te(SHH_PROF_MG_PROLONG))) return rc;
   // post-smoother
-  if (deg1) return app(MG_SRC_POST1, MGE_NONE);
-  if ((rc = app(MG_SRC_POST, MGE_POST)) || (rc = app(MG_SRC_LAST, MGE_LAST))) return rc;
+  if ((rc = app(MGE_POST)) || (rc = app(MGE_LAST))) return rc;
   return SHH_OK;
 }
 
@@ -352,12 +347,9 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
   L0.nn = h.nn;
   L0.nchunks = h.nchunks;
   L0.Dinv = h.Dinv;
-  L0.b = h.r[0];
-  L0.x = h.r[1];
   L0.r = h.q[1];
-  L0.q = h.q[0];
   h.mgd = L0.d;
-  SHH_HIP(hipMemcpyAsync(&s.d_slot->mgd, &h.mgd, sizeof(h.mgd), hipMemcpyHostToDevice, st));
+  h.mgxc = mg.lv[1].x;
   // element matrices of levels >= 1 live in the (not yet used) CG vector region
   {
     char *ke = s.base + s.lay.vec;
@@ -411,13 +403,11 @@ int mg_setup_coefficients(Slot &s, const MgDev &est, double bound0, hipStream_t 
     W.c2 = 2.0 * rho1 / delta;
     // one step, x = D b / theta, where the voxel level smooths with degree 1
     // (the selective solve takes these coefficients for its own voxel level)
-    if (l == 0 && (is_selective(s.opts.solver) ? SHH_SEL_DEG0 : SHH_MG_DEG0) == 1) W.c1 = W.c2 = 0.0;
+    if (l == 0 && (!is_selective(s.opts.solver) || SHH_SEL_DEG0 == 1)) W.c1 = W.c2 = 0.0;
   }
-  // the fused voxel-level sweeps read the coefficients from the slot
-  h.mgc[0] = mg.lv[0].inv_theta;
-  h.mgc[1] = mg.lv[0].c1;
-  h.mgc[2] = mg.lv[0].c2;
-  SHH_HIP(hipMemcpyAsync(&s.d_slot->mgc, h.mgc, sizeof(h.mgc), hipMemcpyHostToDevice, st));
+  // the fused voxel-level passes read theirs from the slot
+  h.mgc = mg.lv[0].inv_theta;
+  SHH_HIP(hipMemcpyAsync(s.d_slot, &h, sizeof(SlotDev), hipMemcpyHostToDevice, st));
   SHH_HIP(hipMemcpyAsync(s.d_mg, &mg, sizeof(MgDev), hipMemcpyHostToDevice, st));
   s.mg_restart = true;
   return SHH_OK;
@@ -540,9 +530,10 @@ int mg_iterate(const std::vector<Slot *> &all, hipStream_t st, Solver *timer, co
     }
     const MgBatch B = batch_of(slots);
     // p = z + beta p, q = K p, partials p . q in one pass; alpha
-    if ((rc = apply0(slots, MG_SRC_DIR))) return rc;
+    if ((rc = apply0(slots, SMG_DIR))) return rc;
     SHH_HIP(mg_launch_scalar(B, MGS_ALPHA, st));
-    // the V-cycle's first sweep applies x += alpha p, r -= alpha q
+    // the V-cycle's first pass applies r -= alpha q; x += alpha p follows in
+    // the next direction pass (or before the next FP64 residual)
     if ((rc = vcycle(slots, 0, st, timer, apply0))) return rc;
     SHH_HIP(mg_launch_scalar(B, MGS_BETA, st));
   }

@@ -372,12 +372,12 @@ int slot_setup_moduli(Slot &s, const void *d_E, int e_dtype, double Es, double E
 // ---------------------------------------------------------------------------
 
 size_t Solver::seg_bytes(int max_slots) {
-  return align256(sizeof(Segment) * (size_t)std::max(max_slots, 1)) * K_NKIND;
+  return align256(sizeof(Segment) * (size_t)std::max(max_slots, 1)) * SEG_TABLES;
 }
 
 void Solver::set_segment_memory(char *d_mem, size_t bytes) {
   seg_mem_ = d_mem;
-  seg_cap_ = bytes / K_NKIND;
+  seg_cap_ = bytes / SEG_TABLES;
   for (auto &v : host_segs_) v.clear();
 }
 
@@ -412,7 +412,7 @@ int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_r
     g.slot = s->d_slot;
     g.first = first;
     g.flag = flag;
-    const bool mg_apply = (k >= K_MG_DIR && k <= K_MG_LAST);
+    const bool mg_apply = (k >= K_MG_DIR && k <= K_MG_POST);
     const bool per_tile = (k == K_STENCIL || k == K_RESID || mg_apply);
     const bool scalar = (k == K_SCAL_IT || k == K_SCAL_RES);
     // the CG pass and the operator compute in the vector precision, the residual always in FP64
@@ -585,24 +585,20 @@ int Solver::iterate(const std::vector<Slot *> &all, int iters) {
 int Solver::iterate_mg(const std::vector<Slot *> &slots, int iters) {
   int rc;
   // voxel-level operator over all the given slots, one launch
-  MgApply0 apply0 = [this](const std::vector<Slot *> &ss, int src) -> int {
-    // (the degree-1 post-smoothing pass takes the last sweep's segments and
-    // profile kind: it replaces it)
-    static const Kind kinds[6] = {K_MG_DIR, K_MG_RES, K_MG_STEP1, K_MG_POST, K_MG_LAST, K_MG_LAST};
-    static const int ops[6] = {SMG_DIR, SMG_RES, SMG_STEP1, SMG_POST, SMG_LAST, SMG_POST1};
-    static const int prof[6] = {SHH_PROF_MG_DIR, SHH_PROF_MG_RES, SHH_PROF_MG_STEP1, SHH_PROF_MG_POST,
-                                SHH_PROF_MG_LAST, SHH_PROF_MG_LAST};
-    if (src < 0 || src > MG_SRC_POST1) return SHH_INVALID_ARG;
+  MgApply0 apply0 = [this](const std::vector<Slot *> &ss, int op) -> int {
+    static const Kind kinds[3] = {K_MG_DIR, K_MG_PRE, K_MG_POST};
+    static const int prof[3] = {SHH_PROF_MG_DIR, SHH_PROF_MG_STEP1, SHH_PROF_MG_LAST};
+    if (op < SMG_DIR || op > SMG_POST) return SHH_INVALID_ARG;
     LaunchArgs la;
     int r;
     // segments of the load cases still running at the last read-back; the
     // kernels also skip those that stopped since
-    if ((r = build(kinds[src], ss, 0, false, la))) return r;
+    if ((r = build(kinds[op], ss, 0, false, la))) return r;
     if (la.total == 0) return SHH_OK;
     hipEvent_t e0 = nullptr;
     if ((r = timed_begin(&e0))) return r;
-    SHH_HIP(launch_stencil_mg(la, ss[0]->host.prec, ops[src], st_));
-    return timed_end(e0, prof[src]);
+    SHH_HIP(launch_stencil_mg(la, ss[0]->host.prec, op, st_));
+    return timed_end(e0, prof[op]);
   };
   for (int it = 0; it < iters; ++it) {
     if ((rc = mg_iterate(slots, st_, this, apply0))) return rc;

@@ -90,12 +90,7 @@ int mg_setup(Slot &s, hipStream_t st);
 // i's own status (a slot that fails is left out of the remaining steps) and
 // only HIP errors are returned.
 int mg_setup(const std::vector<Slot *> &slots, hipStream_t st, std::vector<int> *rcs = nullptr);
-// Voxel-level operator launches of the multigrid iteration: the CG direction
-// pass (p_j = z + beta p_{j-1} into the other p buffer, q[0] = K p_j, partials
-// p_j . q); r - K d for the stored Chebyshev direction (the residual the
-// restriction takes, in place of r); the operator fused with the Chebyshev
-// sweep after it (pre-smoother step 1, post-smoother steps 1 and 2)
-enum { MG_SRC_DIR = 0, MG_SRC_RES = 1, MG_SRC_STEP1 = 2, MG_SRC_POST = 3, MG_SRC_LAST = 4, MG_SRC_POST1 = 5 };
+// Voxel-level launch of the multigrid iteration (SMG_DIR, SMG_PRE or SMG_POST)
 class Solver;
 using MgApply0 = std::function<int(const std::vector<Slot *> &, int)>;
 // one multigrid-preconditioned CG iteration of every load case of the slots
@@ -147,9 +142,10 @@ class Solver {
 
  private:
   bool timing_ = true;
-  enum Kind { K_STENCIL = 0, K_RESID, K_FINISH, K_FOLD, K_ZERO, K_SCAL_IT, K_SCAL_RES, K_MG_DIR, K_MG_RES,
-              K_MG_STEP1, K_MG_POST, K_MG_LAST,
-              K_NKIND };
+  enum Kind { K_STENCIL = 0, K_RESID, K_FINISH, K_FOLD, K_ZERO, K_SCAL_IT, K_SCAL_RES, K_MG_DIR, K_MG_PRE,
+              K_MG_POST, K_NKIND };
+  static constexpr int SEG_TABLES = 12;  // room in a workspace's segment region
+  static_assert(K_NKIND <= SEG_TABLES, "one table per kind");
   int residual(const std::vector<Slot *> &slots, int mode);
   int iterate_mg(const std::vector<Slot *> &slots, int iters);
   int build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs &la);

@@ -50,8 +50,7 @@
 
 namespace shh {
 
-enum { MODE_PCG = 0, MODE_RESID = 1, MODE_APPLY = 2, MODE_MGDIR = 3, MODE_MGSTEP1 = 4, MODE_MGPOST = 5,
-       MODE_MGLAST = 6, MODE_MGRES = 7, MODE_MGPOST1 = 8 };
+enum { MODE_PCG = 0, MODE_RESID = 1, MODE_APPLY = 2, MODE_MGDIR = 3, MODE_MGPRE = 4, MODE_MGPOST = 5 };
 
 #ifndef SHH_STENCIL_WAVES_PER_EU
 #define SHH_STENCIL_WAVES_PER_EU 1
@@ -70,8 +69,12 @@ __device__ __forceinline__ int ring_h(int j) {
   return (2 + j - 2 * HX - (HY - 2)) * HX - 1;
 }
 
+// Registers: two workgroups share a CU up to 128 (FP32) or 168 (FP64).  The FP64
+// pre-smoothing pass fits when told to; the FP64 direction and post-smoothing
+// passes would spill (a 24^3 FP64 solve 27.4 instead of 25.5 ms).
 template <typename TC, typename TS, int MODE>
-__global__ __launch_bounds__(Tile<TC>::THREADS) __attribute__((amdgpu_waves_per_eu(SHH_STENCIL_WAVES_PER_EU)))
+__global__ __launch_bounds__(Tile<TC>::THREADS)
+    __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 && MODE == MODE_MGPRE ? 3 : SHH_STENCIL_WAVES_PER_EU)))
 void stencil_kernel(LaunchArgs la) {
   // tile geometry of this compute precision
   using TT = Tile<TC>;
@@ -82,7 +85,11 @@ void stencil_kernel(LaunchArgs la) {
   __shared__ TC nbuf[2][3][NHALO];
   __shared__ TC ebuf[2][12][NELEMC];
   __shared__ TC mbuf[2][NHALO];  // element moduli, by the halo slot of the element's lower corner
-  __shared__ double red[5 * 16];
+  __shared__ double red[(MODE == MODE_PCG ? 5 : (MODE == MODE_RESID ? 3 : 2)) * 16];
+  // post-smoothing: one plane of the coarse correction around the tile
+  constexpr int CXC = TX / 2 + 2, CYC = TY / 2 + 2, NCO = MODE == MODE_MGPOST ? 3 * CXC * CYC : 1;
+  constexpr int CPT = (NCO + STENCIL_THREADS - 1) / STENCIL_THREADS;
+  __shared__ TC cbuf[NCO];
 
   Work w;
   if (!decode_work(la, w)) return;
@@ -159,11 +166,8 @@ void stencil_kernel(LaunchArgs la) {
   const char *Ebase;
   if constexpr (sizeof(TC) == 8) Ebase = (const char *)s->E64;
   else Ebase = (const char *)s->E32;
-  constexpr bool MGF = MODE >= MODE_MGSTEP1;  // a Chebyshev sweep fused behind the operator
-  // operand staged as D^-1 v / theta (v = b or r: the direction is not stored)
-  constexpr bool MG_SCALED = MODE == MODE_MGSTEP1 || MODE == MODE_MGLAST;
-  constexpr bool MG_NEED_D = MG_SCALED || MODE == MODE_MGPOST1;  // D^-1 at the owned nodes
-  constexpr bool WITH_D = MODE == MODE_PCG || MG_NEED_D;
+  constexpr bool MGF = MODE >= MODE_MGPRE;  // a smoothing step fused behind the operator
+  constexpr bool WITH_D = MODE == MODE_PCG || MGF;
   const uint32_t dOff = WITH_D ? (uint32_t)((const char *)s->Dinv - Ebase) : 0u;
   const rsrc_t rE = make_rsrc(Ebase, WITH_D ? (uint64_t)dOff + (uint64_t)nn * SS : (uint64_t)nn * SC);
 
@@ -174,56 +178,40 @@ void stencil_kernel(LaunchArgs la) {
   const uint64_t vbytesS = 3ull * nn * SS, vbytesL = 3ull * nn * SL;
   // PCG: rA = r_{j-1}, rB = q_{j-1}, rC = p_{j-1}; rR, rQ, rP the new set; rX
   // RESID: rA = FP64 x, rQ = current r.  APPLY: rA = p, rQ = q (or the pair the flag names).
-  // MGDIR (the multigrid CG's direction pass): rA = z, rC = p_{j-1}, rP = p_j, rQ = q.
-  // Fused voxel-level Chebyshev sweeps (q = K v is consumed, not stored); rA
-  // the vector staged over the halo, rAux the owned-node inputs, rR, rP, rX
-  // the outputs:
-  //   STEP1: b (r[0]) staged as d0 = D b / theta;  r = b - q,
-  //          d1 = c1 d0 + c2 D r, x = d0 + d1 -> r (q[1]), d1 (mgd), x (r[1])
-  //          (degree 1: r and x = d0 only)
-  //   POST:  x (r[1]) staged as is; aux b;  r = b - q -> q[1]
-  //   RES:   d1 (mgd) staged as is; aux r (q[1]);  r - q -> q[1] (the
-  //          residual the restriction takes)
-  //   LAST:  r (q[1]) staged as d = D r / theta; aux b, x;
-  //          x + (1 + c1) d + c2 D (r - q) -> r[1], partials b . x, b . b
-  //          (the post-smoother's x + d folded into the last update)
-  //   POST1 (degree-1 smoothing): x (r[1]) staged as is; aux b;
-  //          z = x + D (b - q) / theta -> mgd, partials b . z, b . b
-  constexpr int NAUX = MODE == MODE_MGLAST ? 2 : 1;
-  constexpr int NLOAD = MODE == MODE_MGSTEP1 ? 0 : NAUX;  // auxiliary vectors read
-  rsrc_t rA, rB, rC, rR, rQ, rP, rX, rAux[NAUX];
+  // MGDIR (the multigrid CG's direction pass): rA = z (mgd), rC = p_{j-1}, rP = p_j, rQ = q, rX: the
+  // x update of the iteration before (x += alpha p_{j-1}) rides along, since p_{j-1} is read anyway.
+  // The two smoothing passes (q = K v is consumed, not stored; b = r[pc] before, r[pc ^ 1] after PRE):
+  //   PRE:  staged b' = b - alpha q (the CG update) as d0 = D b' / theta;  r = b' - K d0 (the
+  //         residual the restriction takes) -> q[1], b' -> the other r buffer
+  //   POST: staged x = D b' / theta + P x_c, P the interpolation from level 1;
+  //         z = x + D (b' - K x) / theta -> mgd, partials b' . z, b' . b'
+  // Neither d0 nor x is ever stored: each is formed again from b'.
+  rsrc_t rA, rB, rC, rR, rQ, rP, rX, rD;
   TC alpha = TC(0), beta = TC(0);
-  TC ith = TC(0), c1 = TC(0), c2 = TC(0);
+  TC ith = TC(0);
   if constexpr (MGF) {
-    ith = (TC)s->mgc[0];
-    c1 = (TC)s->mgc[1];
-    c2 = (TC)s->mgc[2];
-    if constexpr (MODE == MODE_MGSTEP1) {
-      rA = make_rsrc((const TS *)s->r[0] + vbase, vbytesS);
+    ith = (TC)s->mgc;
+    const int pc = st->pcur[rhs];
+    if constexpr (MODE == MODE_MGPRE) {
+      alpha = (TC)st->alpha[rhs];
+      rA = make_rsrc((const TS *)s->r[pc] + vbase, vbytesS);
+      rB = make_rsrc((const TS *)s->q[0] + vbase, vbytesS);
+      rX = make_rsrc((const TS *)s->r[pc ^ 1] + vbase, vbytesS);
       rR = make_rsrc((const TS *)s->q[1] + vbase, vbytesS);
-      rP = make_rsrc((const TS *)s->mgd + vbase, vbytesS);
-      rX = make_rsrc((const TS *)s->r[1] + vbase, vbytesS);
-    } else if constexpr (MODE == MODE_MGPOST || MODE == MODE_MGRES) {
-      rA = make_rsrc((const TS *)(MODE == MODE_MGPOST ? s->r[1] : s->mgd) + vbase, vbytesS);
-      rAux[0] = make_rsrc((const TS *)(MODE == MODE_MGPOST ? s->r[0] : s->q[1]) + vbase, vbytesS);
-      rR = make_rsrc((const TS *)s->q[1] + vbase, vbytesS);
-    } else if constexpr (MODE == MODE_MGPOST1) {
-      rA = make_rsrc((const TS *)s->r[1] + vbase, vbytesS);
-      rAux[0] = make_rsrc((const TS *)s->r[0] + vbase, vbytesS);
-      rX = make_rsrc((const TS *)s->mgd + vbase, vbytesS);
     } else {
-      rA = make_rsrc((const TS *)s->q[1] + vbase, vbytesS);
-      rAux[0] = make_rsrc((const TS *)s->r[0] + vbase, vbytesS);
-      rAux[NAUX - 1] = make_rsrc((const TS *)s->r[1] + vbase, vbytesS);
-      rX = make_rsrc((const TS *)s->r[1] + vbase, vbytesS);
+      const uint64_t cnn = (uint64_t)nn >> 3;
+      rA = make_rsrc((const TS *)s->r[pc ^ 1] + vbase, vbytesS);
+      rB = make_rsrc((const TS *)s->mgxc + (long long)rhs * 3 * cnn, 3ull * cnn * SS);
+      rX = make_rsrc((const TS *)s->mgd + vbase, vbytesS);
     }
   } else if constexpr (MODE == MODE_MGDIR) {
     const int pc = st->mgpar[rhs];
-    // z: the last post-smoothing pass leaves it in r[1] (degree 2) or mgd
-    rA = make_rsrc((const TS *)(SHH_MG_DEG0 == 1 ? s->mgd : s->r[1]) + vbase, vbytesS);
+    rA = make_rsrc((const TS *)s->mgd + vbase, vbytesS);
     rC = make_rsrc((const TS *)s->p[pc] + vbase, vbytesS);
     rP = make_rsrc((const TS *)s->p[pc ^ 1] + vbase, vbytesS);
     rQ = make_rsrc((const TS *)s->q[0] + vbase, vbytesS);
+    rX = make_rsrc((const TS *)s->x + vbase, vbytesS);
+    alpha = (TC)st->alpha[rhs];
     beta = (TC)st->beta[rhs];
   } else if constexpr (MODE == MODE_PCG) {
     const int pc = st->pcur[rhs];
@@ -240,27 +228,8 @@ void stencil_kernel(LaunchArgs la) {
     rA = make_rsrc(s->x64 + vbase, vbytesL);
     rQ = make_rsrc((const TS *)s->r[st->pcur[rhs]] + vbase, vbytesS);
   } else {
-    // flag 0: p[0] -> q[0]; otherwise 1 + src + 8 dst over (r0, r1, p0, p1, q0, q1, x, mgd)
-    const void *src = s->p[0];
-    void *dst = s->q[0];
-    if (w.flag > 0) {
-      auto pick = [&](int i) -> void * {
-        switch (i) {
-          case 0: return s->r[0];
-          case 1: return s->r[1];
-          case 2: return s->p[0];
-          case 3: return s->p[1];
-          case 4: return s->q[0];
-          case 5: return s->q[1];
-          case 6: return s->x;
-          default: return s->mgd;
-        }
-      };
-      src = pick((w.flag - 1) & 7);
-      dst = pick(((w.flag - 1) >> 3) & 7);
-    }
-    rA = make_rsrc((const TS *)src + vbase, vbytesL);
-    rQ = make_rsrc((const TS *)dst + vbase, vbytesS);
+    rA = make_rsrc((const TS *)s->p[0] + vbase, vbytesL);
+    rQ = make_rsrc((const TS *)s->q[0] + vbase, vbytesS);
   }
   const bool zero_x = (MODE == MODE_RESID) && (w.flag == RES_INIT);
 
@@ -269,8 +238,37 @@ void stencil_kernel(LaunchArgs la) {
   // owned-node values kept from staging to output (two steps later), by
   // parity of the step that staged them: z, D^-1 and p of the node
   TC own_z[2][3], own_p[2][3], own_d[2];
-  // fused sweeps: the owned node's auxiliary inputs, by the same parity
-  TC own_aux[2][NAUX][3];
+  // pending update of the CG: nothing to apply after a (re)start
+  const bool upd = (MODE == MODE_MGDIR || MODE == MODE_MGPRE) && alpha != TC(0);
+
+  // Post-smoothing, the coarse correction at the staged nodes: fine node x
+  // takes the mean of the coarse nodes floor(x / 2) and floor((x + 1) / 2) per
+  // axis (the same node twice where x is even).  z0 is even, so the planes
+  // alternate odd, even, ... from z0 - 1; an odd plane 2 Z + 1 brings in coarse
+  // plane Z + 1, which is loaded two steps ahead (one value per thread), put in
+  // LDS one step ahead and kept interpolated in x-y (cxy) for the even plane
+  // after it.  Interpolating from global memory at the time of use instead
+  // costs 24 registers in flight.
+  const int nc = n >> 1;
+  const uint32_t cplane = (uint32_t)nc * (uint32_t)nc;
+  TC cxy[2][3], raw_cc[CPT];
+  uint32_t coff[CPT];
+  int cpos[2][4];
+  auto issue_c = [&](int Z) {
+    if constexpr (MODE == MODE_MGPOST) {
+      const uint32_t pz = (uint32_t)wrap1(Z, nc) * cplane * SS;
+#pragma unroll
+      for (int k = 0; k < CPT; ++k)
+        if (tid + k * STENCIL_THREADS < NCO) raw_cc[k] = (TC)bload<TS>(rB, coff[k], pz);
+    }
+  };
+  auto write_c = [&]() {
+    if constexpr (MODE == MODE_MGPOST) {
+#pragma unroll
+      for (int k = 0; k < CPT; ++k)
+        if (tid + k * STENCIL_THREADS < NCO) cbuf[tid + k * STENCIL_THREADS] = raw_cc[k];
+    }
+  };
 
   // ---- plane staging, split into issue (loads into registers), finish
   //      (combine, store to LDS) and commit (store owned values) so that the
@@ -278,7 +276,7 @@ void stencil_kernel(LaunchArgs la) {
   //      work.
   //      Node planes z0-1 .. z1 are touched, so a single wrap suffices.
   TL raw_a[2][3];
-  TS raw_b[2][3], raw_c[2][3], raw_d[2], raw_x[3], raw_aux[NAUX][3];
+  TS raw_b[2][3], raw_c[2][3], raw_d[2], raw_x[3];
   TC raw_e[2];
   // node plane z, and the element layer z - 1 below it
   auto issue = [&](int z) {
@@ -305,21 +303,22 @@ void stencil_kernel(LaunchArgs la) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) raw_a[k][c] = zero_x ? 0.0 : bload<TL>(rA, hoL[k], pz * SL + cL[c]);
       } else if constexpr (MGF) {
-        if constexpr (MG_NEED_D) raw_d[k] = bload<TS>(rE, hoS[k], dOff + pz * SS);
+        raw_d[k] = bload<TS>(rE, hoS[k], dOff + pz * SS);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) raw_a[k][c] = bload<TS>(rA, hoS[k], pz * SS + cS[c]);
-        if (k == 0 && is_out && ownz) {
-#pragma unroll
-          for (int a = 0; a < NLOAD; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) raw_aux[a][c] = bload<TS>(rAux[a], hoS[0], pz * SS + cS[c]);
+        for (int c = 0; c < 3; ++c) {
+          raw_a[k][c] = bload<TS>(rA, hoS[k], pz * SS + cS[c]);
+          if constexpr (MODE == MODE_MGPRE) raw_b[k][c] = upd ? bload<TS>(rB, hoS[k], pz * SS + cS[c]) : TS(0);
         }
       } else if constexpr (MODE == MODE_MGDIR) {
         // beta = 0 starts a new direction: the old one is not read
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           raw_a[k][c] = bload<TS>(rA, hoS[k], pz * SS + cS[c]);
-          raw_c[k][c] = beta != TC(0) ? bload<TS>(rC, hoS[k], pz * SS + cS[c]) : TS(0);
+          raw_c[k][c] = upd || beta != TC(0) ? bload<TS>(rC, hoS[k], pz * SS + cS[c]) : TS(0);
+        }
+        if (k == 0 && is_out && ownz && upd) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) raw_x[c] = bload<TS>(rX, hoS[0], pz * SS + cS[c]);
         }
       } else {
 #pragma unroll
@@ -349,7 +348,17 @@ void stencil_kernel(LaunchArgs la) {
       const bool ownz = z >= z0 && z < z1;
       if (is_out && ownz) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) bstore<TS>(out_p[c], rP, hoS[0], pz * SS + cS[c]);
+        for (int c = 0; c < 3; ++c) {
+          bstore<TS>(out_p[c], rP, hoS[0], pz * SS + cS[c]);
+          if (upd) bstore<TS>(out_x[c], rX, hoS[0], pz * SS + cS[c]);
+        }
+      }
+    } else if constexpr (MODE == MODE_MGPRE) {
+      const uint32_t pz = (uint32_t)wrap1(z, n) * plane;
+      const bool ownz = z >= z0 && z < z1;
+      if (is_out && ownz) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) bstore<TS>(out_x[c], rX, hoS[0], pz * SS + cS[c]);
       }
     }
   };
@@ -386,25 +395,39 @@ void stencil_kernel(LaunchArgs la) {
           own_d[b] = dk;
         }
       } else if constexpr (MGF) {
-        TC v[3];
+        const TC dk = (TC)raw_d[k] * ith;
+        TC bv[3], v[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          v[c] = (TC)raw_a[k][c];
-          if constexpr (MG_SCALED) v[c] = (TC)raw_d[k] * v[c] * ith;
-          nbuf[b][c][hslot[k]] = v[c];
+          bv[c] = (TC)raw_a[k][c];
+          if constexpr (MODE == MODE_MGPRE) bv[c] -= alpha * (TC)raw_b[k][c];
+          v[c] = dk * bv[c];
         }
+        if constexpr (MODE == MODE_MGPOST) {
+          if constexpr (b == 0) {  // odd plane: the coarse plane above it comes in
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const TC *cb = cbuf + c * CXC * CYC;
+              const TC up = TC(0.25) * ((cb[cpos[k][0]] + cb[cpos[k][1]]) + (cb[cpos[k][2]] + cb[cpos[k][3]]));
+              v[c] += TC(0.5) * (cxy[k][c] + up);
+              cxy[k][c] = up;
+            }
+          } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c] += cxy[k][c];
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nbuf[b][c][hslot[k]] = v[c];
         if (k == 0 && is_out && ownz) {
-          // own_p: the staged value, own_z: the vector it came from
+          // own_p: the staged value, own_z: b'
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             own_p[b][c] = v[c];
-            own_z[b][c] = (TC)raw_a[0][c];
+            own_z[b][c] = bv[c];
+            out_x[c] = (TS)bv[c];
           }
-          if constexpr (MG_NEED_D) own_d[b] = (TC)raw_d[0];
-#pragma unroll
-          for (int a = 0; a < NLOAD; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) own_aux[b][a][c] = (TC)raw_aux[a][c];
+          own_d[b] = dk;
         }
       } else if constexpr (MODE == MODE_MGDIR) {
         TC pn[3];
@@ -417,6 +440,7 @@ void stencil_kernel(LaunchArgs la) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             out_p[c] = (TS)pn[c];
+            out_x[c] = (TS)((TC)raw_x[c] + alpha * (TC)raw_c[0][c]);
             own_p[b][c] = pn[c];
           }
         }
@@ -454,8 +478,39 @@ void stencil_kernel(LaunchArgs la) {
   TC A[NB][3][4], Bc[NB][3][4];
 
   // prologue: planes z0-1 and z0 staged, plane z0+1 in flight
+  if constexpr (MODE == MODE_MGPOST) {
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+      const int i = tid + k * STENCIL_THREADS, r = i % (CXC * CYC);
+      coff[k] = (((uint32_t)(i / (CXC * CYC)) * nc) * cplane + (uint32_t)wrapi(y0 / 2 - 1 + r / CXC, nc) * nc +
+                 (uint32_t)wrapi(x0 / 2 - 1 + r % CXC, nc)) * SS;
+    }
+    issue_c(z0 / 2);
+    // coarse plane z0 / 2 - 1 straight from memory, once per workgroup
+    const uint32_t pz = (uint32_t)wrap1(z0 / 2 - 1, nc) * cplane * SS;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (!hval[k]) continue;
+      const int hx = hslot[k] % HX, hy = hslot[k] / HX;
+      const int cx[2] = {(hx + 1) >> 1, (hx >> 1) + 1}, cy[2] = {(hy + 1) >> 1, (hy >> 1) + 1};
+      TC v[4][3];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        cpos[k][j] = cy[j >> 1] * CXC + cx[j & 1];
+        const uint32_t o = ((uint32_t)wrapi(y0 / 2 - 1 + cy[j >> 1], nc) * nc +
+                            (uint32_t)wrapi(x0 / 2 - 1 + cx[j & 1], nc)) * SS;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[j][c] = (TC)bload<TS>(rB, o, pz + (uint32_t)c * cplane * nc * SS);
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) cxy[k][c] = TC(0.25) * ((v[0][c] + v[1][c]) + (v[2][c] + v[3][c]));
+    }
+    write_c();
+  }
   issue(z0 - 1);
+  if constexpr (MODE == MODE_MGPOST) __syncthreads();
   finish(z0 - 1, B0{});
+  issue_c(z0 / 2 + 1);
   issue(z0);
   commit(z0 - 1);
   __syncthreads();
@@ -467,6 +522,7 @@ void stencil_kernel(LaunchArgs la) {
       for (int m = 0; m < 4; ++m) Bc[0][c][m] = TC(0);
   }
   finish(z0, B1{});
+  write_c();
   const int S = z1 - z0 + 1;  // element layers z0-1 .. z1-1
   if (S > 1) issue(z0 + 1);
   commit(z0);
@@ -481,7 +537,7 @@ void stencil_kernel(LaunchArgs la) {
     const int kk = z0 - 1 + sl;
     // the owned values of output plane kk (staged two steps ago, same parity)
     // before this step's staging replaces them
-    TC oz[3], op[3], od = TC(0), oa[NAUX][3];
+    TC oz[3], op[3], od = TC(0);
     if constexpr (MODE == MODE_PCG) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -498,11 +554,7 @@ void stencil_kernel(LaunchArgs la) {
         op[c] = own_p[b][c];
         oz[c] = own_z[b][c];
       }
-      if constexpr (MG_NEED_D) od = own_d[b];
-#pragma unroll
-      for (int a = 0; a < NLOAD; ++a)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) oa[a][c] = own_aux[b][a][c];
+      od = own_d[b];
     }
     if (is_elem) {
       constexpr int ib = NB == 2 ? b : 0, ibn = NB == 2 ? bn : 0;
@@ -551,6 +603,8 @@ void stencil_kernel(LaunchArgs la) {
     }
     // stage node plane kk+2 (its loads were issued a step ago), issue kk+3
     if (sl + 1 < S) finish(z0 + sl + 1, bc);
+    if constexpr (b == 0) issue_c((z0 + sl + 4) / 2);  // the upper coarse plane of z0 + sl + 3
+    else write_c();
     if (sl + 2 < S) issue(z0 + sl + 2);
     if (sl + 1 < S) commit(z0 + sl + 1);
     __syncthreads();
@@ -580,43 +634,18 @@ void stencil_kernel(LaunchArgs la) {
           bstore<TS>((TS)qv[c], rQ, ooff, pk + cS[c]);
           acc[0] += (double)op[c] * (double)qv[c];
         }
-      } else if constexpr (MODE == MODE_MGSTEP1) {
-        // op = d0, oz = b
+      } else if constexpr (MODE == MODE_MGPRE) {
+        // oz = b'
+#pragma unroll
+        for (int c = 0; c < 3; ++c) bstore<TS>((TS)(oz[c] - qv[c]), rR, ooff, pk + cS[c]);
+      } else if constexpr (MODE == MODE_MGPOST) {
+        // op = x, oz = b', od = D / theta
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const TC rv = oz[c] - qv[c];
-          bstore<TS>((TS)rv, rR, ooff, pk + cS[c]);
-          if constexpr (SHH_MG_DEG0 == 1) {
-            bstore<TS>((TS)op[c], rX, ooff, pk + cS[c]);  // one step: x = d0
-          } else {
-            const TC d1 = c1 * op[c] + c2 * od * rv;
-            bstore<TS>((TS)d1, rP, ooff, pk + cS[c]);
-            bstore<TS>((TS)(op[c] + d1), rX, ooff, pk + cS[c]);
-          }
-        }
-      } else if constexpr (MODE == MODE_MGPOST || MODE == MODE_MGRES) {
-        // oa[0] = b (POST) or r (RES)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) bstore<TS>((TS)(oa[0][c] - qv[c]), rR, ooff, pk + cS[c]);
-      } else if constexpr (MODE == MODE_MGPOST1) {
-        // op = x, oa = b
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const TC zv = op[c] + od * (oa[0][c] - qv[c]) * ith;
+          const TC zv = op[c] + od * (oz[c] - qv[c]);
           bstore<TS>((TS)zv, rX, ooff, pk + cS[c]);
-          const double b64 = (double)oa[0][c];
+          const double b64 = (double)oz[c];
           acc[0] += b64 * (double)zv;
-          acc[1] += b64 * b64;
-        }
-      } else if constexpr (MODE == MODE_MGLAST) {
-        // op = d, oz = r, oa = b, x
-        const TC c1p = TC(1) + c1;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const TC xv = oa[1][c] + c1p * op[c] + c2 * od * (oz[c] - qv[c]);
-          bstore<TS>((TS)xv, rX, ooff, pk + cS[c]);
-          const double b64 = (double)oa[0][c];
-          acc[0] += b64 * (double)xv;
           acc[1] += b64 * b64;
         }
       } else if constexpr (MODE == MODE_RESID) {
@@ -647,7 +676,7 @@ void stencil_kernel(LaunchArgs la) {
 #pragma unroll
       for (int i = 0; i < 5; ++i) parts[i] = acc[i];
     }
-  } else if constexpr (MODE == MODE_MGLAST || MODE == MODE_MGPOST1) {
+  } else if constexpr (MODE == MODE_MGPOST) {
     double a2[2] = {acc[0], acc[1]};
     block_sum<2>(a2, red, STENCIL_THREADS);
     if (tid == 0) {
@@ -701,18 +730,16 @@ static void launch_mg_mode(const LaunchArgs &la, int prec, hipStream_t st) {
 
 // Voxel-level passes of the multigrid-preconditioned CG, in the vector
 // precision: SMG_DIR the CG direction p_j = z + beta p_{j-1} (into the other
-// p buffer), q = K p_j and per-tile partials p_j . q; SMG_STEP1 / SMG_POST /
-// SMG_LAST / SMG_RES / SMG_POST1 the operator with the Chebyshev sweep that
-// consumes its output (LAST and POST1: per-tile partials b . z, b . b).
+// p buffer) with the x update of the iteration before, q = K p_j and per-tile
+// partials p_j . q; SMG_PRE the CG's residual update and the pre-smoothing
+// step; SMG_POST the coarse correction and the post-smoothing step (per-tile
+// partials b . z, b . b).
 hipError_t launch_stencil_mg(const LaunchArgs &la, int prec, int op, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
   switch (op) {
     case SMG_DIR: launch_mg_mode<MODE_MGDIR>(la, prec, st); break;
-    case SMG_STEP1: launch_mg_mode<MODE_MGSTEP1>(la, prec, st); break;
+    case SMG_PRE: launch_mg_mode<MODE_MGPRE>(la, prec, st); break;
     case SMG_POST: launch_mg_mode<MODE_MGPOST>(la, prec, st); break;
-    case SMG_LAST: launch_mg_mode<MODE_MGLAST>(la, prec, st); break;
-    case SMG_RES: launch_mg_mode<MODE_MGRES>(la, prec, st); break;
-    case SMG_POST1: launch_mg_mode<MODE_MGPOST1>(la, prec, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

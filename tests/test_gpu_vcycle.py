@@ -1,0 +1,47 @@
+"""The V-cycle's fused passes at the sizes where their tiles can go wrong: one
+tile with more nodes than the grid, remainders in x and y, runs of two planes,
+hierarchies that end after one level.  A pass that drops or doubles a node at a
+tile edge leaves C^H right and only slows CG down, so the iteration counts are
+what is checked: the expected sums over the six load cases are those of the
+unfused passes (one kernel per vector update and transfer), and a rounding of
+the last digits can move a load case's count by one."""
+import numpy as np
+import pytest
+
+from gpu_helpers import assert_ch_close
+from paper_2511_04025_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# n: (FP64 at 1e-10, mixed at 1e-6)
+COUNTS = {6: (290, 174), 10: (289, 174), 12: (283, 164), 14: (280, 163), 16: (240, 147), 20: (302, 180),
+          24: (217, 132), 28: (221, 133), 40: (218, 141), 48: (257, 170), 56: (210, 133), 64: (196, 122),
+          80: (242, 153), 96: (190, 126), 112: (183, 123), 128: (225, 151), 160: (192, 128)}
+
+
+def design(n):
+    return wl.random_design(7000 + n, n, N=16, vf=0.2, E_void=1e-2)
+
+
+@pytest.mark.parametrize("n", sorted(COUNTS))
+def test_iteration_counts(n):
+    from paper_2511_04025_amd import api
+    C = {}
+    for k, (precision, rtol) in enumerate((("fp64", 1e-10), ("mixed", 1e-6))):
+        print(f"vcycle {n}^3 {precision}", flush=True)
+        r = api.homogenize(design(n), precision=precision, rtol=rtol, solver="mg")
+        assert r["status"] == 0
+        assert abs(int(np.sum(r["iters"])) - COUNTS[n][k]) <= 6, (r["iters"], COUNTS[n][k])
+        C[precision] = r["C"]
+    assert_ch_close(C["mixed"], C["fp64"], 1e-4)
+
+
+def test_mixed_batch_equals_single_designs():
+    # different z-run lengths and uneven shares of the launch in one batch
+    from paper_2511_04025_amd import api
+    designs = [design(n) for n in (96, 16, 64, 6, 128, 40)]
+    print("vcycle mixed batch", flush=True)
+    batch = api.homogenize_batch(designs, precision="mixed", rtol=1e-6, solver="mg")
+    for d, rb in zip(designs, batch):
+        rs = api.homogenize(d, precision="mixed", rtol=1e-6, solver="mg")
+        assert np.array_equal(rs["C"], rb["C"]) and np.array_equal(rs["iters"], rb["iters"])
