@@ -25,8 +25,9 @@ namespace shh {
 // The all-sum mode m = 0 of each component is a rigid translation: its
 // diagonal entry is zero (every term carries S along some axis) and no
 // coupling touches it, so h[c][0] is never read and y[c][0] is exactly zero.
+// hex_unit is the element of unit modulus, hex_apply scales by the modulus e.
 template <typename T, typename KP>
-__host__ __device__ __forceinline__ void hex_apply(KP kop, const T (&h)[3][8], T (&y)[3][8], T e) {
+__host__ __device__ __forceinline__ void hex_unit(KP kop, const T (&h)[3][8], T (&y)[3][8]) {
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     y[c][0] = T(0);
@@ -54,6 +55,11 @@ __host__ __device__ __forceinline__ void hex_apply(KP kop, const T (&h)[3][8], T
   SHH_COUPLE(0, 2, 1)
   SHH_COUPLE(1, 2, 0)
 #undef SHH_COUPLE
+}
+
+template <typename T, typename KP>
+__host__ __device__ __forceinline__ void hex_apply(KP kop, const T (&h)[3][8], T (&y)[3][8], T e) {
+  hex_unit<T>(kop, h, y);
 #pragma unroll
   for (int c = 0; c < 3; ++c)
 #pragma unroll

@@ -143,8 +143,8 @@ static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 // where 32 left the third round at 6 %).  It depends on the grid and precision
 // alone, so a design's result does not depend on its batch.
 static int tz_for(int n, int prec) {
-  constexpr long long places = 512;
   const int w = prec == SHH_PREC_FP64 ? 0 : 1;
+  const long long places = w ? 256 * (1024 / Tile<float>::THREADS) : 512;
   const int X = w ? Tile<float>::X : Tile<double>::X, Y = w ? Tile<float>::Y : Tile<double>::Y;
   const long long tiles = (long long)((n + X - 1) / X) * ((n + Y - 1) / Y) * NRHS;
   int best = 2;

@@ -52,13 +52,6 @@ namespace shh {
 
 enum { MODE_PCG = 0, MODE_RESID = 1, MODE_APPLY = 2, MODE_MGDIR = 3, MODE_MGPRE = 4, MODE_MGPOST = 5 };
 
-#ifndef SHH_STENCIL_WAVES_PER_EU
-#define SHH_STENCIL_WAVES_PER_EU 1
-#endif
-#ifndef SHH_CARRY_DB
-#define SHH_CARRY_DB 0
-#endif
-
 // Halo-tile index of ring node j: the bottom row, the top row, then the left
 // and right columns between them.
 template <int HX, int HY>
@@ -69,12 +62,15 @@ __device__ __forceinline__ int ring_h(int j) {
   return (2 + j - 2 * HX - (HY - 2)) * HX - 1;
 }
 
-// Registers: two workgroups share a CU up to 128 (FP32) or 168 (FP64).  The FP64
-// pre-smoothing pass fits when told to; the FP64 direction and post-smoothing
-// passes would spill (a 24^3 FP64 solve 27.4 instead of 25.5 ms).
+// Waves per SIMD that the compiler aims at.  Two workgroups share a CU up to 128
+// registers (FP32, four waves) or 168 (FP64, three).  The FP64 pre-smoothing pass
+// fits when told to; the FP64 direction and post-smoothing passes would spill (a
+// 24^3 FP64 solve 27.4 instead of 25.5 ms).
+template <typename TC, int MODE>
+constexpr int WPE = sizeof(TC) == 4 ? 4 : (MODE == MODE_MGPRE ? 3 : 1);
 template <typename TC, typename TS, int MODE>
 __global__ __launch_bounds__(Tile<TC>::THREADS)
-    __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 && MODE == MODE_MGPRE ? 3 : SHH_STENCIL_WAVES_PER_EU)))
+    __attribute__((amdgpu_waves_per_eu(WPE<TC, MODE>)))
 void stencil_kernel(LaunchArgs la) {
   // tile geometry of this compute precision
   using TT = Tile<TC>;
@@ -121,9 +117,15 @@ void stencil_kernel(LaunchArgs la) {
   using TL = typename std::conditional<MODE == MODE_RESID, double, TS>::type;
   constexpr uint32_t SL = sizeof(TL), SS = sizeof(TS), SC = sizeof(TC);
 
-  // element-column role
+  // element-column role.  In FP32 every thread runs the element work (the last
+  // wave is there anyway) and only its stores are masked: values defined under a
+  // branch and carried around the loop cost a register copy each, a fifth of the
+  // loop's vector instructions.  The FP64 kernels and the Jacobi CG pass keep the
+  // branch: without it their registers pass the limit for two workgroups on a CU.
+  constexpr bool BRANCH = sizeof(TC) == 8 || MODE == MODE_PCG;
   const bool is_elem = tid < NELEMC;
-  const int ecx = tid % EXC, ecy = tid / EXC;
+  const int ecol = is_elem ? tid : NELEMC - 1;
+  const int ecx = ecol % EXC, ecy = ecol / EXC;
   // output role (also the owner of the node in the PCG update)
   const int ox = tid % TX, oy = tid / TX;
   const bool is_out = tid < NINT && x0 + ox < n && y0 + oy < n;
@@ -133,7 +135,7 @@ void stencil_kernel(LaunchArgs la) {
   // The element moduli of a layer are staged with a node plane: element
   // column (ecx, ecy) is the voxel whose lower corner is halo node (ecx, ecy),
   // so the thread staging that node loads the voxel's E_e at the same offset
-  // (hel).  Keeping every global load in the staging batch means the element
+  // (hel; without the branch the last row and column ride along).  Keeping every global load in the staging batch means the element
   // work never waits on the memory counter, which retires in issue order.
   bool hval[2], hel[2];
   int hslot[2];
@@ -157,6 +159,10 @@ void stencil_kernel(LaunchArgs la) {
     hoC[k] = o * SC;
     hel[k] = hval[k] && hx < EXC && hy < EYC;
   }
+
+  // every thread's first slot holds a node
+  static_assert(STENCIL_THREADS <= NHALO, "slot 0 is never empty");
+  auto stages = [&](int k) { return !BRANCH && k == 0 ? true : hval[k]; };
 
   const SHH_CONST TC *kop;
   if constexpr (sizeof(TC) == 8) kop = (const SHH_CONST TC *)s->kop64;
@@ -285,8 +291,8 @@ void stencil_kernel(LaunchArgs la) {
     const bool ownz = z >= z0 && z < z1;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      if (!hval[k]) continue;
-      if (hel[k]) raw_e[k] = bload<TC>(rE, hoC[k], pe * SC);
+      if (!stages(k)) continue;
+      if (!BRANCH || hel[k]) raw_e[k] = bload<TC>(rE, hoC[k], pe * SC);
       if constexpr (MODE == MODE_PCG) {
         raw_d[k] = bload<TS>(rE, hoS[k], dOff + pz * SS);
 #pragma unroll
@@ -368,8 +374,8 @@ void stencil_kernel(LaunchArgs la) {
     const bool ownz = z >= z0 && z < z1;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      if (!hval[k]) continue;
-      if (hel[k]) mbuf[b][hslot[k]] = raw_e[k];
+      if (!stages(k)) continue;
+      if (!BRANCH || hel[k]) mbuf[b][hslot[k]] = raw_e[k];
       if constexpr (MODE == MODE_PCG) {
         const TC dk = (TC)raw_d[k];
         TC rn[3], zn[3], pn[3];
@@ -380,19 +386,24 @@ void stencil_kernel(LaunchArgs la) {
           pn[c] = beta * (TC)raw_c[k][c] + zn[c];
           nbuf[b][c][hslot[k]] = pn[c];
         }
-        if (k == 0 && is_out && ownz) {
+        if (k == 0 && (!BRANCH || (is_out && ownz))) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             out_r[c] = (TS)rn[c];
             out_p[c] = (TS)pn[c];
             out_x[c] = (TS)((TC)raw_x[c] + alpha * (TC)raw_c[0][c]);
-            const double r64 = (double)rn[c];
-            acc[0] += r64 * (double)zn[c];
-            acc[1] += r64 * r64;
             own_z[b][c] = zn[c];
             own_p[b][c] = pn[c];
           }
           own_d[b] = dk;
+          if (is_out && ownz) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const double r64 = (double)rn[c];
+              acc[0] += r64 * (double)zn[c];
+              acc[1] += r64 * r64;
+            }
+          }
         }
       } else if constexpr (MGF) {
         const TC dk = (TC)raw_d[k] * ith;
@@ -419,7 +430,7 @@ void stencil_kernel(LaunchArgs la) {
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c) nbuf[b][c][hslot[k]] = v[c];
-        if (k == 0 && is_out && ownz) {
+        if (k == 0 && (!BRANCH || (is_out && ownz))) {
           // own_p: the staged value, own_z: b'
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
@@ -436,7 +447,7 @@ void stencil_kernel(LaunchArgs la) {
           pn[c] = (TC)raw_a[k][c] + beta * (TC)raw_c[k][c];
           nbuf[b][c][hslot[k]] = pn[c];
         }
-        if (k == 0 && is_out && ownz) {
+        if (k == 0 && (!BRANCH || (is_out && ownz))) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             out_p[c] = (TS)pn[c];
@@ -470,12 +481,8 @@ void stencil_kernel(LaunchArgs la) {
 
   // Values carried from one element layer to the next: the x-y Hadamard
   // coefficients of the lower node plane (A) and the upper-plane half of the
-  // layer below (Bc).  With SHH_CARRY_DB (FP32 only) they
-  // are double-buffered by layer parity (index b of the step that reads them),
-  // which spares the register copies of the two-step unrolled loop at the
-  // cost of 24 more registers.
-  constexpr int NB = (SHH_CARRY_DB && sizeof(TC) == 4) ? 2 : 1;
-  TC A[NB][3][4], Bc[NB][3][4];
+  // layer below (Bc).
+  TC A[3][4], Bc[3][4];
 
   // prologue: planes z0-1 and z0 staged, plane z0+1 in flight
   if constexpr (MODE == MODE_MGPOST) {
@@ -490,7 +497,7 @@ void stencil_kernel(LaunchArgs la) {
     const uint32_t pz = (uint32_t)wrap1(z0 / 2 - 1, nc) * cplane * SS;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      if (!hval[k]) continue;
+      if (!stages(k)) continue;
       const int hx = hslot[k] % HX, hy = hslot[k] / HX;
       const int cx[2] = {(hx + 1) >> 1, (hx >> 1) + 1}, cy[2] = {(hy + 1) >> 1, (hy >> 1) + 1};
       TC v[4][3];
@@ -514,12 +521,12 @@ void stencil_kernel(LaunchArgs la) {
   issue(z0);
   commit(z0 - 1);
   __syncthreads();
-  if (is_elem) {
-    xy_hadamard(B0{}, A[0]);
+  if (!BRANCH || is_elem) {
+    xy_hadamard(B0{}, A);
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int m = 0; m < 4; ++m) Bc[0][c][m] = TC(0);
+      for (int m = 0; m < 4; ++m) Bc[c][m] = TC(0);
   }
   finish(z0, B1{});
   write_c();
@@ -556,9 +563,7 @@ void stencil_kernel(LaunchArgs la) {
       }
       od = own_d[b];
     }
-    if (is_elem) {
-      constexpr int ib = NB == 2 ? b : 0, ibn = NB == 2 ? bn : 0;
-      const TC (&Ac)[3][4] = A[ib];
+    if (!BRANCH || is_elem) {
       TC An[3][4];
       xy_hadamard(BN{}, An);
       // layer kk's modulus was staged with node plane kk+1
@@ -566,40 +571,60 @@ void stencil_kernel(LaunchArgs la) {
       TC h[3][8], y[3][8];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        h[c][0] = TC(0);  // rigid mode: not read by hex_apply
+        h[c][0] = TC(0);  // rigid mode: not read by hex_unit
 #pragma unroll
-        for (int m = 1; m < 4; ++m) h[c][m] = Ac[c][m] + An[c][m];
+        for (int m = 1; m < 4; ++m) h[c][m] = A[c][m] + An[c][m];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) h[c][m + 4] = An[c][m] - Ac[c][m];
+        for (int m = 0; m < 4; ++m) h[c][m + 4] = An[c][m] - A[c][m];
       }
       if constexpr (MODE == MODE_RESID) add_chi<TC>(rhs, h);
-      hex_apply<TC>(kop, h, y, e);
-      if (sl > 0) {
-        // lower node plane kk: this layer's lower half completes the upper
-        // half carried from the layer below; store its four x-y corners
-        const TC (&Bacc)[3][4] = Bc[ib];
+      // lower node plane kk: this layer's lower half completes the upper half
+      // carried from the layer below (Bc); its four x-y corners go to LDS
+      // (y[c][0] == 0)
+      auto corners = [&](int c, TC L0, TC L1, TC L2, TC L3) {
+        const TC u0 = L0 - L1, u1 = L0 + L1, v0 = L2 - L3, v1 = L2 + L3;
+        ebuf[b][c * 4 + 0][tid] = u0 - v0;
+        ebuf[b][c * 4 + 1][tid] = u1 - v1;
+        ebuf[b][c * 4 + 2][tid] = u0 + v0;
+        ebuf[b][c * 4 + 3][tid] = u1 + v1;
+      };
+      if constexpr (BRANCH) {
+        hex_apply<TC>(kop, h, y, e);
+        if (sl > 0) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            corners(c, Bc[c][0] - y[c][4], Bc[c][1] + (y[c][1] - y[c][5]), Bc[c][2] + (y[c][2] - y[c][6]),
+                    Bc[c][3] + (y[c][3] - y[c][7]));
+        }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const TC L0 = Bacc[c][0] - y[c][4];  // y[c][0] == 0
-          const TC L1 = Bacc[c][1] + (y[c][1] - y[c][5]);
-          const TC L2 = Bacc[c][2] + (y[c][2] - y[c][6]);
-          const TC L3 = Bacc[c][3] + (y[c][3] - y[c][7]);
-          const TC u0 = L0 - L1, u1 = L0 + L1, v0 = L2 - L3, v1 = L2 + L3;
-          ebuf[b][c * 4 + 0][tid] = u0 - v0;
-          ebuf[b][c * 4 + 1][tid] = u1 - v1;
-          ebuf[b][c * 4 + 2][tid] = u0 + v0;
-          ebuf[b][c * 4 + 3][tid] = u1 + v1;
+          Bc[c][0] = y[c][4];
+#pragma unroll
+          for (int m = 1; m < 4; ++m) Bc[c][m] = y[c][m] + y[c][m + 4];
+        }
+      } else {
+        // the modulus scales the halves in the same multiply-add
+        hex_unit<TC>(kop, h, y);
+        TC L[3][4];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          L[c][0] = Bc[c][0] - e * y[c][4];
+          Bc[c][0] = e * y[c][4];
+#pragma unroll
+          for (int m = 1; m < 4; ++m) {
+            L[c][m] = Bc[c][m] + e * (y[c][m] - y[c][m + 4]);
+            Bc[c][m] = e * (y[c][m] + y[c][m + 4]);
+          }
+        }
+        if (sl > 0 && is_elem) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) corners(c, L[c][0], L[c][1], L[c][2], L[c][3]);
         }
       }
-      TC (&Bnew)[3][4] = Bc[ibn];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        Bnew[c][0] = y[c][4];
+      for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int m = 1; m < 4; ++m) Bnew[c][m] = y[c][m] + y[c][m + 4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) A[ibn][c][m] = An[c][m];
-      }
+        for (int m = 0; m < 4; ++m) A[c][m] = An[c][m];
     }
     // stage node plane kk+2 (its loads were issued a step ago), issue kk+3
     if (sl + 1 < S) finish(z0 + sl + 1, bc);
