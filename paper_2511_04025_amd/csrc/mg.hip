@@ -139,13 +139,9 @@ __global__ __launch_bounds__(256) void mg_stencil_kernel(const MgDev *mg, int l)
 // operator, transfer and coarsest solve (levels >= 1)
 // ---------------------------------------------------------------------------
 
-// q = A_l v (v = x or d of the level) for RHS load cases per thread: RHS =
-// NRHS (one thread per node; the stencil is read once for all load cases) on
-// large levels of odd size (even ones take the pair form below), RHS = 1 (one
-// thread per node and load case: six times the threads, so latency overlaps)
-// on small ones.
 // The coarse-level Chebyshev sweep that follows an operator pass, applied
 // to q = A_l v at node v, load case k (entry j = (3 k + c) nn + v):
+// (degree-2 Chebyshev smoothing of A x = b from x = 0, then of the corrected x):
 //   MGE_NONE:  q = A v
 //   MGE_STEP1: (v = d0) r = b - q;  d1 = c1 d0 + c2 D^-1 r;  x = d0 + d1;  d1 into q
 //   MGE_RES:   (v = d1, in q) r -= q: the residual the restriction takes
@@ -225,16 +221,127 @@ __device__ __forceinline__ const T *mg_operand(const MgLevel &L, int src) {
   else return (const T *)(src == 0 ? L.x : L.d);
 }
 
-template <typename T, int RHS, int EP>
-__global__ __launch_bounds__(256) void mg_apply_kernel(MgBatch B, int l, int src, int live) {
+// q = A_l v (v = x or d of the level) on levels of at most 32^3 nodes, where a
+// pass is bound by the latency of a thread's chain of gathers and not by
+// bytes: the 27 offsets of 64 nodes are split over the G waves of a workgroup
+// (a wave takes 27 / G offsets, its loads in flight together), which meet in
+// LDS; then wave g finishes rows g, g + G, ... of the RHS * 3 (load case,
+// component) rows.  One thread per node and load case walking all 27 offsets
+// took 12 us a pass at 6^3 as at 24^3 (one design).  G = 3 (planes) with all
+// six load cases reads the stencil once; G = 9 (rows) with two load cases per
+// workgroup gives the smallest levels enough threads.  Both add the offsets in
+// the same order -- rows of three, planes of three rows, three planes -- so a
+// design's result does not depend on the launch it shares.
+template <typename T>
+__device__ __forceinline__ T mg_fma(T a, T b, T c) {
+  if constexpr (sizeof(T) == 4) return __builtin_fmaf(a, b, c);
+  else return __builtin_fma(a, b, c);
+}
+
+// p[r][c] += the three offsets of row (dz, dy) of the stencil at node v, zero
+// rows left out; wrapped neighbours x - 1, x, x + 1 of plane row zy
+template <typename T, int RHS>
+__device__ __forceinline__ void mg_row(const SHH_GLOBAL T *S, const SHH_GLOBAL T *in, long long nn, unsigned v,
+                                       unsigned zy, const unsigned (&xs)[3], int row, const bool (&act)[RHS],
+                                       T (&p)[RHS][3]) {
+  T blk[3][9], val[3][RHS][3];
+#pragma unroll
+  for (int o = 0; o < 3; ++o) {
+    const int w = row * 3 + o;  // uniform over the wave
+    const unsigned u = zy + xs[o];
+    const bool lower = w < 13;  // A[v][u] = A[u][v]^T, stored at u for offset 26 - w
+    const SHH_GLOBAL T *Sw = S + (long long)((lower ? 13 - w : w - 13) * 9) * nn + (lower ? u : v);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) blk[o][k] = Sw[k * nn];
+#pragma unroll
+    for (int r = 0; r < RHS; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c)  // an inactive load case reads one broadcast value
+        val[o][r][c] = in[((long long)r * 3 + c) * nn + (act[r] ? u : 0u)];
+  }
+#pragma unroll
+  for (int r = 0; r < RHS; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) p[r][c] = T(0);
+#pragma unroll
+  for (int o = 0; o < 3; ++o) {
+    if (row * 3 + o < 13) {
+#pragma unroll
+      for (int r = 0; r < RHS; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) p[r][c] = mg_fma<T>(blk[o][3 * k + c], val[o][r][k], p[r][c]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < RHS; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) p[r][c] = mg_fma<T>(blk[o][3 * c + k], val[o][r][k], p[r][c]);
+    }
+  }
+}
+
+// the 27 / G offsets of group g into LDS partials part[g][3 r + c][lane]
+template <typename T, int RHS, int G>
+__device__ __forceinline__ void mg_split_sum(const MgLevel &L, const T *operand, unsigned v, int g,
+                                             const bool (&act)[RHS], bool zero_row, T (*part)[RHS * 3][64]) {
+  const int n = L.n, lane = threadIdx.x & 63;
+  const SHH_GLOBAL T *S = to_global((const T *)L.S), *in = to_global(operand);
+  const unsigned row = v / (unsigned)n;
+  const int x = int(v - row * (unsigned)n), y = int(row % (unsigned)n), z = int(row / (unsigned)n);
+  const unsigned xs[3] = {unsigned(wrap1(x - 1, n)), unsigned(x), unsigned(wrap1(x + 1, n))};
+  T acc[RHS][3];
+#pragma unroll
+  for (int r = 0; r < RHS; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[r][c] = T(0);
+  if (!zero_row) {
+    if constexpr (G == 9) {
+      const int dz = g / 3 - 1, dy = g % 3 - 1;
+      mg_row<T, RHS>(S, in, L.nn, v, unsigned(wrap1(z + dz, n) * n + wrap1(y + dy, n)) * n, xs, g, act, acc);
+    } else {
+      const unsigned zo = unsigned(wrap1(z + g - 1, n) * n);
+#pragma unroll 1  // three rows in flight would spill
+      for (int j = 0; j < 3; ++j) {
+        T p[RHS][3];
+        mg_row<T, RHS>(S, in, L.nn, v, (zo + unsigned(wrap1(y + j - 1, n))) * n, xs, 3 * g + j, act, p);
+#pragma unroll
+        for (int r = 0; r < RHS; ++r)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) acc[r][c] = j == 0 ? p[r][c] : acc[r][c] + p[r][c];
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < RHS; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) part[g][3 * r + c][lane] = acc[r][c];
+}
+
+template <typename T, int RHS, int G>
+__device__ __forceinline__ T mg_split_total(T (*part)[RHS * 3][64], int q, int lane) {
+  if constexpr (G == 9) {
+    T s[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      s[k] = (part[3 * k][q][lane] + part[3 * k + 1][q][lane]) + part[3 * k + 2][q][lane];
+    return (s[0] + s[1]) + s[2];
+  } else {
+    return (part[0][q][lane] + part[1][q][lane]) + part[2][q][lane];
+  }
+}
+
+// grid x = 64-node blocks, y = groups of RHS load cases, z = slot
+template <typename T, int RHS, int G, int EP>
+__global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) void mg_apply_split_kernel(MgBatch B, int l, int src, int live) {
+  __shared__ T part[G][RHS * 3][64];
+  constexpr int IT = (RHS * 3 + G - 1) / G;
   const MgLevel &L = B.mg[blockIdx.z]->lv[l];
   const long long nn = L.nn;
-  // node indices fit 32 bits (n <= 512); 64-bit divisions are slow
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (unsigned)nn * (NRHS / RHS)) return;
-  const unsigned r0u = t / (unsigned)nn;
-  const long long v = t - r0u * (unsigned)nn;
-  const int r0 = int(r0u) * RHS;
+  if ((long long)blockIdx.x * 64 >= nn) return;
+  const int r0 = blockIdx.y * RHS;
   // live: load cases that have converged (or broken down) are skipped, as in
   // the voxel-level passes (Sec. 4.2.2: per-right-hand-side convergence)
   bool act[RHS];
@@ -245,68 +352,41 @@ __global__ __launch_bounds__(256) void mg_apply_kernel(MgBatch B, int l, int src
     any = any || act[r];
   }
   if (!any) return;
-  const int n = L.n;
-  const unsigned row = unsigned(v) / (unsigned)n;
-  const int x = int(unsigned(v) - row * (unsigned)n), y = int(row % (unsigned)n), z = int(row / (unsigned)n);
-  const SHH_GLOBAL T *S = to_global((const T *)L.S);
+  const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool inr = blockIdx.x * 64 + lane < (unsigned)nn;
+  const unsigned v = inr ? blockIdx.x * 64 + lane : 0u;
   const SHH_GLOBAL T *Dv = to_global((const T *)L.Dinv);
-  const SHH_GLOBAL T *in = to_global(mg_operand<T, EP>(L, src)) + (long long)r0 * 3 * nn;
-  T acc[RHS][3];
-#pragma unroll
-  for (int r = 0; r < RHS; ++r)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) acc[r][c] = T(0);
   // a node with a zero diagonal has a zero row (every element around it
   // culled): A v = 0 there without reading its stencil
-  const bool zero_row = Dv[v] == T(0);
-  // three offsets per trip: their loads are in flight together (measured
-  // faster than one; more waves per SIMD or fewer load cases per thread are
-  // slower, the stencil reads then miss the caches more)
-  if (!zero_row) {
-#pragma unroll 3
-    for (int w = 0; w < 27; ++w) {
-      const int dx = w % 3 - 1, dy = (w / 3) % 3 - 1, dz = w / 9 - 1;
-      const long long u = ((long long)wrap1(z + dz, n) * n + wrap1(y + dy, n)) * n + wrap1(x + dx, n);
-      T blk[9];
-      if (w >= 13) {
+  mg_split_sum<T, RHS, G>(L, mg_operand<T, EP>(L, src) + (long long)r0 * 3 * nn, v, g, act, Dv[v] == T(0), part);
+  // the inputs of this thread's share of the fused sweep, loaded before the
+  // waves meet
+  const MgEpi<T> E = mg_epi<T>(L);
+  T dv[IT], ein[IT][3];
+  bool mine[IT];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) blk[k] = S[((w - 13) * 9 + k) * nn + v];
-      } else {
-        // A[v][u] = A[u][v]^T, stored at u for offset 26 - w
+  for (int i = 0; i < IT; ++i) {
+    const int q = g + i * G;
+    bool on = false;  // uniform over the wave
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-          for (int cp = 0; cp < 3; ++cp) blk[3 * c + cp] = S[((13 - w) * 9 + 3 * cp + c) * nn + u];
-      }
-#pragma unroll
-      for (int r = 0; r < RHS; ++r) {
-        if (!act[r]) continue;
-        const SHH_GLOBAL T *vr = in + (long long)r * 3 * nn;
-        const T u0 = vr[u], u1 = vr[nn + u], u2 = vr[2 * nn + u];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[r][c] += blk[3 * c] * u0 + blk[3 * c + 1] * u1 + blk[3 * c + 2] * u2;
-      }
+    for (int r = 0; r < RHS; ++r) on = on || (q / 3 == r && act[r]);
+    mine[i] = inr && on;
+    if (mine[i]) {
+      dv[i] = Dv[(long long)(q % 3) * nn + v];
+      mg_epi_load<T, EP>(E, ((long long)r0 * 3 + q) * nn + v, ein[i]);
     }
   }
-  const MgEpi<T> E = mg_epi<T>(L);
-  T dv[3], ein[RHS][3][3];
+  __syncthreads();
 #pragma unroll
-  for (int c = 0; c < 3; ++c) dv[c] = Dv[(long long)c * nn + v];
-#pragma unroll
-  for (int r = 0; r < RHS; ++r)
-    if (act[r])
-#pragma unroll
-      for (int c = 0; c < 3; ++c) mg_epi_load<T, EP>(E, ((long long)(r0 + r) * 3 + c) * nn + v, ein[r][c]);
-#pragma unroll
-  for (int r = 0; r < RHS; ++r)
-    if (act[r])
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        mg_epilogue<T, EP>(E, ((long long)(r0 + r) * 3 + c) * nn + v, dv[c], acc[r][c], ein[r][c]);
+  for (int i = 0; i < IT; ++i) {
+    const int q = g + i * G;
+    if (mine[i])
+      mg_epilogue<T, EP>(E, ((long long)r0 * 3 + q) * nn + v, dv[i], mg_split_total<T, RHS, G>(part, q, lane), ein[i]);
+  }
 }
 
-// q = A_l v as above, all six load cases, for two z-adjacent nodes per thread
-// (even n; the form the large levels take): the vector values of the two
+// q = A_l v on levels of more than 32^3 nodes, all six load cases, for two
+// z-adjacent nodes per thread (every smoothing level is even): the vector values of the two
 // planes between them are loaded once for both (12 % faster per launch than
 // one node per thread).  Occupancy 2 waves per SIMD in FP32 (230 registers;
 // holding it to 3 waves spills).  An inactive load case's gathers read one
@@ -418,7 +498,9 @@ template <typename T> struct Pair2 { using type = T __attribute__((ext_vector_ty
 // two-wide load; the odd node 2X - 1 is the pair of the lane below (a
 // shuffle), loaded only where that lane holds another row or wave.  Node
 // indices fit 32 bits (n <= 512): 64-bit divisions would cost more than the
-// kernel's memory traffic.
+// kernel's memory traffic.  Where the coarse level is smoothed, its first
+// Chebyshev direction d = D^-1 b / theta is written along (a sweep of its own
+// before).
 template <typename T>
 __global__ __launch_bounds__(256) void mg_restrict_kernel(MgBatch B, int l) {
   using T2 = typename Pair2<T>::type;
@@ -444,6 +526,13 @@ __global__ __launch_bounds__(256) void mg_restrict_kernel(MgBatch B, int l) {
     for (int oy = 0; oy < 3; ++oy)
       rowo[3 * oz + oy] =
           (unsigned(wrap1(2 * Z + oz - 1, nf)) * unsigned(nf) + unsigned(wrap1(2 * Y + oy - 1, nf))) * unsigned(nf);
+  const bool smooth = l + 1 < mg->L;
+  const SHH_GLOBAL T *Dc = to_global((const T *)C.Dinv);
+  T dv[3] = {T(0), T(0), T(0)};
+  if (smooth) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dv[c] = Dc[(long long)c * C.nn + I];
+  }
   T2 v[9][3];
 #pragma unroll
   for (int o = 0; o < 9; ++o)
@@ -467,9 +556,16 @@ __global__ __launch_bounds__(256) void mg_restrict_kernel(MgBatch B, int l) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) acc[c] += wyz * (v[o][c].x + T(0.5) * (v[o][c].y + left[o][c]));
   }
-  SHH_GLOBAL T *b = to_global((T *)C.b) + (long long)k * 3 * C.nn;
+  const long long cnn = C.nn;  // read once: the stores below might alias it
+  const T ith = (T)C.inv_theta;
+  SHH_GLOBAL T *b = to_global((T *)C.b) + (long long)k * 3 * cnn;
+  SHH_GLOBAL T *d = to_global((T *)C.d) + (long long)k * 3 * cnn;
 #pragma unroll
-  for (int c = 0; c < 3; ++c) b[(long long)c * C.nn + I] = acc[c];
+  for (int c = 0; c < 3; ++c) b[c * cnn + I] = acc[c];
+  if (smooth) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) d[c * cnn + I] = dv[c] * acc[c] * ith;
+  }
 }
 
 // x_l += P x_{l+1}: fine node 2I + a, a in {0, 1}^3, takes the coarse nodes
@@ -540,71 +636,48 @@ __global__ __launch_bounds__(256) void mg_prolong_kernel(MgBatch B, int l) {
       }
 }
 
-// Coarsest level: x = Mc b per load case (one workgroup per load case; four
-// lanes share a row and combine their partial sums by shuffles).
+// Coarsest level: x = Mc b for all load cases.  Sixteen lanes share a row (its
+// 3 n_c^3 entries are read once, coalesced) and combine their partial sums by
+// shuffles; a workgroup takes 16 rows.  (One workgroup per load case, four
+// lanes a row, took 33 us at 4^3: 192 rows in three rounds of 48 dependent
+// uncoalesced loads.)
 template <typename T>
 __global__ __launch_bounds__(256) void mg_coarsest_kernel(MgBatch B) {
   const MgDev *mg = B.mg[blockIdx.z];
   const MgLevel &L = mg->lv[mg->L];
-  const int k = blockIdx.x;
-  if (!B.slot[blockIdx.z]->st->active[k]) return;
   const int nd = mg->ndof_c;
+  if ((int)blockIdx.x * 16 >= nd) return;
+  const int *active = B.slot[blockIdx.z]->st->active;
+  bool act[NRHS];
+  bool any = false;
+#pragma unroll
+  for (int k = 0; k < NRHS; ++k) {
+    act[k] = active[k] != 0;
+    any = any || act[k];
+  }
+  if (!any) return;
   const long long nn = L.nn;
-  const double *M = mg->Mc;
-  const T *b = (const T *)L.b + (long long)k * 3 * nn;
-  T *x = (T *)L.x + (long long)k * 3 * nn;
-  const int part = threadIdx.x & 3;
-  for (int row0 = 0; row0 < nd; row0 += 64) {
-    const int row = row0 + (threadIdx.x >> 2);
-    double acc = 0.0;
-    if (row < nd)
-      for (int j = part; j < nd; j += 4) acc += (double)M[(long long)row * nd + j] * (double)b[(j % 3) * nn + j / 3];
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    if (row < nd && part == 0) x[(row % 3) * nn + row / 3] = (T)acc;
-  }
-}
-
-// Degree-2 Chebyshev smoothing of A x = b on the coarse levels:
-//   d = D^-1 b / theta;  r = b - A d;  d' = c1 d + c2 D^-1 r;  x = d + d'
-//   (pre-smoother; the restriction takes r - A d');  after the coarse
-//   correction r = b - A x;  d = D^-1 r / theta;  x += d;
-//   x += c1 d + c2 D^-1 (r - A d)  (post-smoother).
-// Every step after an operator application runs in that pass's output stage
-// (mg_epilogue); this sweep is the first step, d = D^-1 b / theta.
-template <typename T>
-__global__ __launch_bounds__(VEC_THREADS) void mg_vec_kernel(MgBatch B, int l) {
-  const SlotDev *s = B.slot[blockIdx.z];
-  const MgLevel &L = B.mg[blockIdx.z]->lv[l];
-  const int k = blockIdx.y;
-  const long long nn = L.nn;
-  if (blockIdx.x >= (unsigned)L.nchunks || !s->st->active[k]) return;
-  const long long i0 = (long long)blockIdx.x * CHUNK;
-  const long long i1 = min(i0 + (long long)CHUNK, nn);
-  const long long vb = (long long)k * 3 * nn;
-  const T ith = (T)L.inv_theta;
-  SHH_GLOBAL T *d = to_global((T *)L.d) + vb;
-  const SHH_GLOBAL T *Dv = to_global((const T *)L.Dinv);
-  const SHH_GLOBAL T *bg = to_global((const T *)L.b) + vb;
-  constexpr int PER = CHUNK / VEC_THREADS;
-  T dv[PER][3], bv[PER][3];
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4), part = threadIdx.x & 15;
+  const double *M = mg->Mc + (long long)min(row, nd - 1) * nd;
+  const T *b = (const T *)L.b;
+  double acc[NRHS];
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const long long i = i0 + threadIdx.x + u * VEC_THREADS;
-    if (i < i1)
+  for (int k = 0; k < NRHS; ++k) acc[k] = 0.0;
+#pragma unroll 4
+  for (int j = part; j < nd; j += 16) {
+    const double m = M[j];
+    const int at = (j % 3) * (int)nn + j / 3;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        dv[u][c] = Dv[c * nn + i];
-        bv[u][c] = bg[c * nn + i];
-      }
+    for (int k = 0; k < NRHS; ++k) acc[k] += m * (double)b[k * 3 * (int)nn + at];
   }
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const long long i = i0 + threadIdx.x + u * VEC_THREADS;
-    if (i < i1)
+  for (int k = 0; k < NRHS; ++k)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) d[c * nn + i] = dv[u][c] * bv[u][c] * ith;
-  }
+    for (int off = 8; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off, 64);
+  T *x = (T *)L.x;
+#pragma unroll
+  for (int k = 0; k < NRHS; ++k)
+    if (part == k && row < nd && act[k]) x[(k * 3 + row % 3) * (int)nn + row / 3] = (T)acc[k];
 }
 
 // CG scalars of the multigrid-preconditioned solve (one workgroup per load
@@ -680,70 +753,93 @@ __global__ __launch_bounds__(VEC_THREADS) void mg_scalar_kernel(MgBatch B, int p
   }
 }
 
-// Power iteration for lambda_max(D^-1 A) at a coarse level l, on load case 0
-// of x, for a batch of slots (grid z = slot):
-//   phase 0: x = a fixed pseudo-random vector
-//   phase 1: partial x.q and x.D x (the Rayleigh quotient x.A x / x.D x of
-//            D^-1 A, self-adjoint in the D inner product), then x = D^-1 q
-//            (q = A x) and partial ||x||^2
-//   phase 2: x *= the level's pw_scale
+// Power iteration for lambda_max(D^-1 A) of every coarse smoothing level of a
+// batch of slots (grid z = slot), on load case 0, the level's x and q taking
+// turns as the vector.  One launch is one step of all levels: a level's blocks
+// of 64 nodes follow those of the level above it.  (Four launches per step and
+// level before: the steps of a single 128^3 design took 4.8 of its 9 ms of setup.)
+//   step:   x' = s D^-1 A x with s the last step's 1 / ||x||, and partial sums
+//           of x.A x, x.D x (their ratio is the Rayleigh quotient of D^-1 A,
+//           self-adjoint in the D inner product) and ||x'||^2
+//   reduce: the partials of each level; the largest quotient into lmax
+__device__ __forceinline__ int mg_power_level(const MgDev *mg, int &block, int &first) {
+  first = 0;
+  for (int l = 1; l < mg->L; ++l) {
+    const int nb = int((mg->lv[l].nn + 63) / 64);
+    if (block < nb) return l;
+    block -= nb;
+    first += nb;
+  }
+  return 0;
+}
+
 template <typename T>
-__global__ __launch_bounds__(VEC_THREADS) void mg_power_kernel(MgBatch B, int l, int phase) {
+__global__ __launch_bounds__(256) void mg_power_init_kernel(MgBatch B, int l) {
+  if (l >= B.mg[blockIdx.z]->L) return;
+  const MgLevel &L = B.mg[blockIdx.z]->lv[l];
+  const unsigned j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= 3 * (unsigned)L.nn) return;
+  uint32_t h = j * 2654435761u + 0x9e3779b9u;
+  h ^= h >> 16;
+  h *= 0x85ebca6bu;
+  h ^= h >> 13;
+  ((T *)L.x)[j] = (T)((double)(h & 0xffffff) / 16777216.0 - 0.5);
+}
+
+template <typename T>
+__global__ __launch_bounds__(192) void mg_power_step_kernel(MgBatch B, int step) {
+  __shared__ T part[3][3][64];
   __shared__ double red[3 * 16];
   const SlotDev *s = B.slot[blockIdx.z];
+  int block = blockIdx.x, first;
+  const int l = mg_power_level(B.mg[blockIdx.z], block, first);
+  if (l == 0) return;
   const MgLevel &L = B.mg[blockIdx.z]->lv[l];
   const long long nn = L.nn;
-  if (blockIdx.x >= (unsigned)L.nchunks) return;
-  const long long i0 = (long long)blockIdx.x * CHUNK;
-  const long long i1 = min(i0 + (long long)CHUNK, nn);
-  T *x = (T *)L.x;
-  const T *q = (const T *)L.q;
+  const T *x = (const T *)(step & 1 ? L.q : L.x);
+  T *xn = (T *)(step & 1 ? L.x : L.q);
+  const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool inr = (unsigned)block * 64 + lane < (unsigned)nn;
+  const unsigned v = inr ? block * 64 + lane : 0u;
   const T *Dv = (const T *)L.Dinv;
+  const bool act[1] = {true};
+  mg_split_sum<T, 1, 3>(L, x, v, g, act, Dv[v] == T(0), part);
+  __syncthreads();
   double acc[3] = {0.0, 0.0, 0.0};
-  for (long long i = i0 + threadIdx.x; i < i1; i += VEC_THREADS) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const long long j = c * nn + i;
-      if (phase == 0) {
-        uint32_t h = (uint32_t)j * 2654435761u + 0x9e3779b9u;
-        h ^= h >> 16;
-        h *= 0x85ebca6bu;
-        h ^= h >> 13;
-        x[j] = (T)((double)(h & 0xffffff) / 16777216.0 - 0.5);
-      } else if (phase == 1) {
-        const T di = Dv[j];
-        const double xo = (double)x[j], qo = (double)q[j];
-        acc[1] += xo * qo;
-        acc[2] += di != T(0) ? xo * xo / (double)di : 0.0;
-        const T v = di * q[j];
-        x[j] = v;
-        acc[0] += (double)v * (double)v;
-      } else {
-        x[j] = (T)((double)x[j] * L.pw_scale);
-      }
-    }
+  if (inr) {  // wave g finishes component g
+    const long long j = g * nn + v;
+    const T qv = mg_split_total<T, 1, 3>(part, g, lane), di = Dv[j];
+    const double xo = (double)x[j];
+    acc[1] = xo * (double)qv;
+    acc[2] = di != T(0) ? xo * xo / (double)di : 0.0;
+    const T w = (T)((double)(di * qv) * L.pw_scale);
+    xn[j] = w;
+    acc[0] = (double)w * (double)w;
   }
-  if (phase == 1) {
-    block_sum<3>(acc, red, VEC_THREADS);
-    if (threadIdx.x == 0) {
-      s->partials[blockIdx.x * PSTRIDE] = acc[0];
-      s->partials[blockIdx.x * PSTRIDE + 1] = acc[1];
-      s->partials[blockIdx.x * PSTRIDE + 2] = acc[2];
-    }
+  block_sum<3>(acc, red, 192);
+  if (threadIdx.x == 0) {
+    double *p = s->partials + (long long)(first + block) * PSTRIDE;
+    p[0] = acc[0];
+    p[1] = acc[1];
+    p[2] = acc[2];
   }
 }
 
-// After power phase 1: reduce the partials (one workgroup per slot), keep the
-// largest Rayleigh quotient in lmax and the normalization for phase 2 (a
-// vanishing or non-finite step leaves lmax = -1, which the host reports as a
-// breakdown).
-__global__ __launch_bounds__(VEC_THREADS) void mg_power_reduce_kernel(MgBatch B, int l) {
+// grid x = level - 1, z = slot: reduce the partials, keep the largest Rayleigh
+// quotient in lmax and the normalization for the next step (a vanishing or
+// non-finite step leaves lmax = -1, which the host reports as a breakdown).
+__global__ __launch_bounds__(VEC_THREADS) void mg_power_reduce_kernel(MgBatch B) {
   __shared__ double red[3 * 16];
   const SlotDev *s = B.slot[blockIdx.z];
+  const int l = blockIdx.x + 1;
   // the slot's own descriptor in device memory, written only here
-  MgLevel &L = const_cast<MgDev *>(B.mg[blockIdx.z])->lv[l];
+  MgDev *mg = const_cast<MgDev *>(B.mg[blockIdx.z]);
+  if (l >= mg->L) return;
+  int first = 0;
+  for (int k = 1; k < l; ++k) first += int((mg->lv[k].nn + 63) / 64);
+  MgLevel &L = mg->lv[l];
   double tot[3];
-  sum_partials<3, PSTRIDE>(s->partials, L.nchunks, tot, red, VEC_THREADS);
+  sum_partials<3, PSTRIDE>(s->partials + (long long)first * PSTRIDE, int((L.nn + 63) / 64), tot, red, VEC_THREADS);
   if (threadIdx.x != 0) return;
   const double nrm = sqrt(tot[0]);
   if (!(nrm > 0.0) || !isfinite(nrm) || !(tot[2] > 0.0) || L.lmax < 0.0) {
@@ -878,46 +974,42 @@ hipError_t mg_launch_stencil(const MgDev *d_mg, int l, long long nn, int prec, h
   return hipGetLastError();
 }
 
-// whether mg_launch_apply takes the all-load-cases-per-thread variant
-bool mg_apply_wide(long long nn_max) { return nn_max > 32768; }
+// whether a level takes the two-nodes-per-thread form (the choice is made
+// design by design: its sums run in another order)
+bool mg_apply_wide(long long nn) { return nn > 32768; }
 
 namespace {
-template <int EP>
-void launch_apply_ep(const MgBatch &B, int l, int src, long long nn_max, bool even, int prec, hipStream_t st,
-                     int live) {
-  if (mg_apply_wide(nn_max) && even) {
-    const dim3 g(blocks_for(nn_max / 2, 256), 1, B.count);
-    if (prec == 0) mg_apply_pair_kernel<double, EP><<<g, 256, 0, st>>>(B, l, src, live);
-    else mg_apply_pair_kernel<float, EP><<<g, 256, 0, st>>>(B, l, src, live);
-  } else if (mg_apply_wide(nn_max)) {
-    const dim3 g(blocks_for(nn_max, 256), 1, B.count);
-    if (prec == 0) mg_apply_kernel<double, NRHS, EP><<<g, 256, 0, st>>>(B, l, src, live);
-    else mg_apply_kernel<float, NRHS, EP><<<g, 256, 0, st>>>(B, l, src, live);
+template <typename T, int EP>
+void launch_apply_ep(const MgBatch &B, int l, int src, long long nn_max, bool wide, hipStream_t st, int live) {
+  if (wide) {
+    mg_apply_pair_kernel<T, EP><<<dim3(blocks_for(nn_max / 2, 256), 1, B.count), 256, 0, st>>>(B, l, src, live);
+  } else if (nn_max > 4096) {
+    constexpr int R = sizeof(T) == 4 ? NRHS : 2;  // FP64: six cases would not fit the registers
+    mg_apply_split_kernel<T, R, 3, EP>
+        <<<dim3(blocks_for(nn_max, 64), NRHS / R, B.count), 192, 0, st>>>(B, l, src, live);
   } else {
-    const dim3 g(blocks_for(nn_max * NRHS, 256), 1, B.count);
-    if (prec == 0) mg_apply_kernel<double, 1, EP><<<g, 256, 0, st>>>(B, l, src, live);
-    else mg_apply_kernel<float, 1, EP><<<g, 256, 0, st>>>(B, l, src, live);
+    mg_apply_split_kernel<T, 2, 9, EP>
+        <<<dim3(blocks_for(nn_max, 64), NRHS / 2, B.count), 576, 0, st>>>(B, l, src, live);
+  }
+}
+template <typename T>
+void launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, hipStream_t st, int live, int ep) {
+  switch (ep) {
+    case MGE_STEP1: launch_apply_ep<T, MGE_STEP1>(B, l, src, nn_max, wide, st, live); break;
+    case MGE_RES: launch_apply_ep<T, MGE_RES>(B, l, src, nn_max, wide, st, live); break;
+    case MGE_POST: launch_apply_ep<T, MGE_POST>(B, l, src, nn_max, wide, st, live); break;
+    case MGE_LAST: launch_apply_ep<T, MGE_LAST>(B, l, src, nn_max, wide, st, live); break;
+    default: launch_apply_ep<T, MGE_NONE>(B, l, src, nn_max, wide, st, live); break;
   }
 }
 }  // namespace
 
-hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool even, int prec,
+// nn_max: the largest of the level over the batch; wide: every design of the
+// batch takes the two-nodes-per-thread form (mg_apply_wide), else none does
+hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, int prec,
                            hipStream_t st, int live, int ep) {
-  switch (ep) {
-    case MGE_STEP1: launch_apply_ep<MGE_STEP1>(B, l, src, nn_max, even, prec, st, live); break;
-    case MGE_RES: launch_apply_ep<MGE_RES>(B, l, src, nn_max, even, prec, st, live); break;
-    case MGE_POST: launch_apply_ep<MGE_POST>(B, l, src, nn_max, even, prec, st, live); break;
-    case MGE_LAST: launch_apply_ep<MGE_LAST>(B, l, src, nn_max, even, prec, st, live); break;
-    default: launch_apply_ep<MGE_NONE>(B, l, src, nn_max, even, prec, st, live); break;
-  }
-  return hipGetLastError();
-}
-
-// q = A_l v for load case 0 only (the setup's power iteration)
-hipError_t mg_launch_apply_case0(const MgBatch &B, int l, long long nn_max, int prec, hipStream_t st) {
-  const dim3 g(blocks_for(nn_max, 256), 1, B.count);
-  if (prec == 0) mg_apply_kernel<double, 1, MGE_NONE><<<g, 256, 0, st>>>(B, l, 0, 0);
-  else mg_apply_kernel<float, 1, MGE_NONE><<<g, 256, 0, st>>>(B, l, 0, 0);
+  if (prec == 0) launch_apply<double>(B, l, src, nn_max, wide, st, live, ep);
+  else launch_apply<float>(B, l, src, nn_max, wide, st, live, ep);
   return hipGetLastError();
 }
 
@@ -936,33 +1028,33 @@ hipError_t mg_launch_prolong(const MgBatch &B, int l, long long nn_coarse_max, i
   return hipGetLastError();
 }
 
-hipError_t mg_launch_coarsest(const MgBatch &B, int prec, hipStream_t st) {
-  const dim3 g(NRHS, 1, B.count);
+hipError_t mg_launch_coarsest(const MgBatch &B, int ndof_max, int prec, hipStream_t st) {
+  const dim3 g(blocks_for(ndof_max, 16), 1, B.count);
   if (prec == 0) mg_coarsest_kernel<double><<<g, 256, 0, st>>>(B);
   else mg_coarsest_kernel<float><<<g, 256, 0, st>>>(B);
   return hipGetLastError();
 }
-
-hipError_t mg_launch_vec(const MgBatch &B, int l, int nchunks_max, int prec, hipStream_t st) {
-  const dim3 g((unsigned)nchunks_max, NRHS, B.count);
-  if (prec == 0) mg_vec_kernel<double><<<g, VEC_THREADS, 0, st>>>(B, l);
-  else mg_vec_kernel<float><<<g, VEC_THREADS, 0, st>>>(B, l);
-  return hipGetLastError();
-}
-
 
 hipError_t mg_launch_scalar(const MgBatch &B, int phase, hipStream_t st) {
   mg_scalar_kernel<<<dim3(NRHS, 1, B.count), VEC_THREADS, 0, st>>>(B, phase);
   return hipGetLastError();
 }
 
-hipError_t mg_launch_power(const MgBatch &B, int l, int phase, int nchunks_max, int prec, hipStream_t st) {
-  if (phase == 3) {
-    mg_power_reduce_kernel<<<dim3(1, 1, B.count), VEC_THREADS, 0, st>>>(B, l);
-  } else if (prec == 0) {
-    mg_power_kernel<double><<<dim3((unsigned)nchunks_max, 1, B.count), VEC_THREADS, 0, st>>>(B, l, phase);
-  } else {
-    mg_power_kernel<float><<<dim3((unsigned)nchunks_max, 1, B.count), VEC_THREADS, 0, st>>>(B, l, phase);
+// the start vector of level l (l = 1, 2, ... in turn), then `steps` steps of all levels;
+// blocks_max: the most 64-node blocks over a design's levels; levels: the most levels
+hipError_t mg_launch_power_init(const MgBatch &B, int l, long long nn_max, int prec, hipStream_t st) {
+  const dim3 g(blocks_for(3 * nn_max, 256), 1, B.count);
+  if (prec == 0) mg_power_init_kernel<double><<<g, 256, 0, st>>>(B, l);
+  else mg_power_init_kernel<float><<<g, 256, 0, st>>>(B, l);
+  return hipGetLastError();
+}
+
+hipError_t mg_launch_power(const MgBatch &B, int steps, long long blocks_max, int levels, int prec, hipStream_t st) {
+  const dim3 g((unsigned)blocks_max, 1, B.count), gr((unsigned)levels, 1, B.count);
+  for (int k = 0; k < steps; ++k) {
+    if (prec == 0) mg_power_step_kernel<double><<<g, 192, 0, st>>>(B, k);
+    else mg_power_step_kernel<float><<<g, 192, 0, st>>>(B, k);
+    mg_power_reduce_kernel<<<gr, VEC_THREADS, 0, st>>>(B);
   }
   return hipGetLastError();
 }

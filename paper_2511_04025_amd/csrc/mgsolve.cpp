@@ -28,17 +28,16 @@ hipError_t mg_launch_stencil(const MgDev *d_mg, int l, long long nn, int prec, h
 hipError_t mg_launch_coarse_inverse(const MgBatch &B, int prec, hipStream_t st);
 // live = 1: skip the load cases whose CG has stopped (state read on the device)
 // ep: the Chebyshev sweep fused into the output stage (MGE_*)
-hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool even, int prec,
+hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, int prec,
                            hipStream_t st, int live, int ep);
-hipError_t mg_launch_apply_case0(const MgBatch &B, int l, long long nn_max, int prec, hipStream_t st);
-bool mg_apply_wide(long long nn_max);
+bool mg_apply_wide(long long nn);
 hipError_t mg_launch_restrict(const MgBatch &B, int l, long long nn_coarse_max, int prec,
                               hipStream_t st);
 hipError_t mg_launch_prolong(const MgBatch &B, int l, long long nn_coarse_max, int prec, hipStream_t st);
-hipError_t mg_launch_coarsest(const MgBatch &B, int prec, hipStream_t st);
-hipError_t mg_launch_vec(const MgBatch &B, int l, int nchunks_max, int prec, hipStream_t st);
+hipError_t mg_launch_coarsest(const MgBatch &B, int ndof_max, int prec, hipStream_t st);
 hipError_t mg_launch_scalar(const MgBatch &B, int phase, hipStream_t st);
-hipError_t mg_launch_power(const MgBatch &B, int l, int phase, int nchunks_max, int prec, hipStream_t st);
+hipError_t mg_launch_power_init(const MgBatch &B, int l, long long nn_max, int prec, hipStream_t st);
+hipError_t mg_launch_power(const MgBatch &B, int steps, long long blocks_max, int levels, int prec, hipStream_t st);
 
 namespace {
 
@@ -272,18 +271,15 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
   const int prec = slots[0]->host.prec;
   std::vector<Slot *> coarse, smooth;
   for (Slot *s : slots) (s->mg.L == l ? coarse : smooth).push_back(s);
-  if (!coarse.empty()) SHH_HIP(mg_launch_coarsest(batch_of(coarse), prec, st));
+  if (!coarse.empty()) {
+    int nd = 0;
+    for (Slot *s : coarse) nd = std::max(nd, s->mg.ndof_c);
+    SHH_HIP(mg_launch_coarsest(batch_of(coarse), nd, prec, st));
+  }
   if (smooth.empty()) return SHH_OK;
   const MgBatch B = batch_of(smooth);
-  long long nn_max = 0, nn_next_max = 0;
-  int nch_max = 0;
-  bool all_even = true;  // the two-nodes-per-thread operator form needs even n
-  for (Slot *s : smooth) {
-    nn_max = std::max(nn_max, s->mg.lv[l].nn);
-    nn_next_max = std::max(nn_next_max, s->mg.lv[l + 1].nn);
-    nch_max = std::max(nch_max, s->mg.lv[l].nchunks);
-    all_even = all_even && s->mg.lv[l].n % 2 == 0;
-  }
+  long long nn_next_max = 0;
+  for (Slot *s : smooth) nn_next_max = std::max(nn_next_max, s->mg.lv[l + 1].nn);
   int rc;
   // when profiling, the voxel level's launches and the first coarse level's
   // operator are timed by kernel family (the rest is small)
@@ -302,13 +298,20 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
     return apply0(smooth, SMG_POST);
   }
   // an operator pass with the Chebyshev sweep after it fused in
+  std::vector<Slot *> by_form[2];  // one launch per form of the operator
+  for (Slot *s : smooth) by_form[mg_apply_wide(s->mg.lv[l].nn)].push_back(s);
   auto app = [&](int ep) -> int {
     if ((rc = tb(l == 1))) return rc;
-    SHH_HIP(mg_launch_apply(B, l, 0, nn_max, all_even, prec, st, 1, ep));
+    for (int w = 0; w < 2; ++w) {
+      if (by_form[w].empty()) continue;
+      long long nn = 0;
+      for (Slot *s : by_form[w]) nn = std::max(nn, s->mg.lv[l].nn);
+      SHH_HIP(mg_launch_apply(batch_of(by_form[w]), l, 0, nn, w == 1, prec, st, 1, ep));
+    }
     return te(SHH_PROF_MG_APPLY1);
   };
-  // pre-smoother; its second pass leaves r - A d1, the residual to restrict, in r
-  SHH_HIP(mg_launch_vec(B, l, nch_max, prec, st));
+  // pre-smoother (the restriction to this level left its first direction in d);
+  // its second pass leaves r - A d1, the residual to restrict, in r
   if ((rc = app(MGE_STEP1)) || (rc = app(MGE_RES))) return rc;
   // coarse-grid correction
   SHH_HIP(mg_launch_restrict(B, l, nn_next_max, prec, st));
@@ -355,6 +358,7 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
     char *ke = s.base + s.lay.vec;
     size_t used = 0;
     for (int l = 1; l < count; ++l) {
+      mg.lv[l].pw_scale = 1.0;
       mg.lv[l].Ke = ke + used;
       used = a256(used + (size_t)mg.lv[l].nn * 576 * ts);
     }
@@ -446,31 +450,28 @@ int mg_setup(const std::vector<Slot *> &all, hipStream_t st, std::vector<int> *r
     SHH_HIP(mg_launch_coarse_inverse(batch_of(part), prec, st));
   }
   // lambda_max(D^-1 A) of every coarse smoothing level by power iteration
-  // on load case 0, entirely on the device and batched over the slots that
-  // have the level (phase 0 start, then per step: apply, phase 1 sweep,
-  // reduction, phase 2 normalization); one read-back at the end.  The voxel
-  // level needs none: it takes the rigorous bound.
-  for (int l = 1; l < max_l; ++l) {
-    std::vector<Slot *> at;
-    for (Slot *s : slots)
-      if (s->mg.L > l) at.push_back(s);
-    for (size_t b0 = 0; b0 < at.size(); b0 += MG_MAXB) {
-      const std::vector<Slot *> part(at.begin() + b0, at.begin() + std::min(at.size(), b0 + MG_MAXB));
-      const MgBatch B = batch_of(part);
-      long long nn = 0;
-      int nch = 0;
-      for (Slot *s : part) {
-        nn = std::max(nn, s->mg.lv[l].nn);
-        nch = std::max(nch, s->mg.lv[l].nchunks);
-      }
-      SHH_HIP(mg_launch_power(B, l, 0, nch, prec, st));
-      for (int it = 0; it < POWER_ITERS; ++it) {
-        SHH_HIP(mg_launch_apply_case0(B, l, nn, prec, st));
-        SHH_HIP(mg_launch_power(B, l, 1, nch, prec, st));
-        SHH_HIP(mg_launch_power(B, l, 3, nch, prec, st));
-        SHH_HIP(mg_launch_power(B, l, 2, nch, prec, st));
-      }
+  // on load case 0, entirely on the device, all levels of all slots together;
+  // one read-back at the end.  The voxel level needs none: it takes the
+  // rigorous bound.
+  for (size_t b0 = 0; b0 < slots.size() && max_l > 1; b0 += MG_MAXB) {
+    const std::vector<Slot *> part(slots.begin() + b0, slots.begin() + std::min(slots.size(), b0 + MG_MAXB));
+    const MgBatch B = batch_of(part);
+    long long blocks_max = 0;
+    for (Slot *s : part) {
+      long long nb = 0;
+      for (int l = 1; l < s->mg.L; ++l) nb += (s->mg.lv[l].nn + 63) / 64;
+      blocks_max = std::max(blocks_max, nb);
+      // the steps' partials lie in the slot's reduction scratch
+      if (nb > (long long)NRHS * s->host.maxparts) return SHH_WORKSPACE_TOO_SMALL;
     }
+    if (blocks_max == 0) continue;
+    for (int l = 1; l < max_l; ++l) {
+      long long nn = 0;
+      for (Slot *s : part)
+        if (s->mg.L > l) nn = std::max(nn, s->mg.lv[l].nn);
+      if (nn > 0) SHH_HIP(mg_launch_power_init(B, l, nn, prec, st));
+    }
+    SHH_HIP(mg_launch_power(B, POWER_ITERS, blocks_max, max_l - 1, prec, st));
   }
   std::vector<MgDev> est(slots.size());
   for (size_t i = 0; i < slots.size(); ++i)
@@ -502,7 +503,8 @@ int mg_apply_level(Slot &s, int l, const void *d_v, void *d_q, hipStream_t st) {
   const MgLevel &L = s.mg.lv[l];
   const size_t bytes = (size_t)NRHS * 3 * L.nn * (s.host.prec == SHH_PREC_FP64 ? 8 : 4);
   SHH_HIP(hipMemcpyAsync(L.x, d_v, bytes, hipMemcpyDeviceToDevice, st));
-  SHH_HIP(mg_launch_apply(batch_of({&s}), l, 0, L.nn, L.n % 2 == 0, s.host.prec, st, 0, MGE_NONE));
+  // (the odd coarsest level is small: never the two-nodes-per-thread form)
+  SHH_HIP(mg_launch_apply(batch_of({&s}), l, 0, L.nn, mg_apply_wide(L.nn), s.host.prec, st, 0, MGE_NONE));
   SHH_HIP(hipMemcpyAsync(d_q, L.q, bytes, hipMemcpyDeviceToDevice, st));
   SHH_HIP(hipStreamSynchronize(st));
   return SHH_OK;

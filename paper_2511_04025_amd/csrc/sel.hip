@@ -1152,9 +1152,20 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_restrict_kernel(const SelB
       for (int o = 0; o < 3 * NRHS; ++o) acc[o] += w * v[o];
     }
   }
-  T *b1 = (T *)S->b1;
+  // with the level's first Chebyshev direction d = D^-1 b / theta where it is
+  // smoothed (not the coarsest)
+  T *b1 = (T *)S->b1, *dir1 = (T *)S->dir1;
+  T dv[3] = {T(0), T(0), T(0)};
+  if (dir1) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dv[c] = ((const T *)S->dinv1)[c * nn1 + I] * (T)S->inv_theta1;
+  }
 #pragma unroll
   for (int o = 0; o < 3 * NRHS; ++o) b1[(long long)o * nn1 + I] = acc[o];
+  if (dir1) {
+#pragma unroll
+    for (int o = 0; o < 3 * NRHS; ++o) dir1[(long long)o * nn1 + I] = dv[o % 3] * acc[o];
+  }
 }
 
 // z += P x1 at the active nodes: per axis, an even fine index has one coarse

@@ -61,13 +61,16 @@ struct SelDev {
   // the compact lists, the coarse levels on the dense hierarchy built from the
   // culled moduli.  Chebyshev coefficients of the voxel level, the V-cycle's
   // vectors (node-major, working precision) and the first coarse level's
-  // right-hand side and iterate ([6][3][n1^3], dense)
+  // right-hand side and iterate ([6][3][n1^3], dense), its first Chebyshev
+  // direction (null where that level is the coarsest), D^-1 and 1 / theta
   int mg;
   int n1;
   long long nn1;
   double inv_theta, c1, c2;
   void *d0, *d1, *xv, *rv;
-  void *b1, *x1;
+  void *b1, *x1, *dir1;
+  const void *dinv1;
+  double inv_theta1;
 };
 
 // operator pass flavours

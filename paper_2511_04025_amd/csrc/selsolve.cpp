@@ -402,6 +402,9 @@ int sel_start(const std::vector<Slot *> &in, hipStream_t st) {
       h.nn1 = M.lv[1].nn;
       h.b1 = M.lv[1].b;
       h.x1 = M.lv[1].x;
+      h.dir1 = M.L > 1 ? M.lv[1].d : nullptr;
+      h.dinv1 = M.lv[1].Dinv;
+      h.inv_theta1 = M.lv[1].inv_theta;
       h.d0 = M.lv[0].d;  // the dense level-0 direction buffer: [6][3][n^3] >= [n_a][18]
     }
   }
