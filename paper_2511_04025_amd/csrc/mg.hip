@@ -851,93 +851,155 @@ __global__ __launch_bounds__(VEC_THREADS) void mg_power_reduce_kernel(MgBatch B)
   L.pw_scale = 1.0 / nrm;
 }
 
-// The coarsest level's dense inverse, in one workgroup: assemble the
-// operator from the stored stencil blocks (row 3 v + c gathers every block of
-// node v, the lower offsets transposed from the neighbours), add gamma / nn to
-// each component's constant block (gamma = mean diagonal; this makes the
-// operator nonsingular on the rigid translations and leaves its inverse on
-// the range equal to the pseudo-inverse), then invert in place by
-// Gauss-Jordan elimination (the matrix is symmetric positive definite, so no
-// pivoting).  FP64 throughout.
-// One workgroup per design of the batch (grid x).
+// The coarsest level's dense inverse, FP64: assemble the operator from the
+// stored stencil blocks (row 3 v + c gathers every block of node v, the lower
+// offsets transposed from the neighbours), add gamma / nn to each component's
+// constant block (gamma = mean diagonal; this makes the operator nonsingular
+// on the rigid translations and leaves its inverse on the range equal to the
+// pseudo-inverse), then invert in place by Gauss-Jordan elimination over blocks
+// of 32 (the matrix is symmetric positive definite, so no pivoting):
+//   P = A_kk^-1;  R_j = P A_kj, C_i = A_ik (panel kernel, into scratch);
+//   A_kk = P, A_kj = R_j, A_ik = -C_i P, A_ij -= C_i R_j (update kernel).
+// One workgroup sweeping the whole matrix in global memory row by row took
+// 1.8 ms at 4^3 (192 rows) and grew with the cube: 7^3 has 1029.
+// Grid z = slot throughout.
+constexpr int IB = 32;  // block edge
+struct InvScratch {
+  double *P, *R, *Cc, *mean;  // [IB][IB], [blocks][IB][IB] twice, the mean diagonal
+  __device__ InvScratch(double *base, int nblk) : P(base), R(base + IB * IB), Cc(R + nblk * IB * IB),
+                                                  mean(Cc + nblk * IB * IB) {}
+};
+
 template <typename T>
-__global__ __launch_bounds__(1024) void mg_coarse_inverse_kernel(MgBatch B) {
+__global__ __launch_bounds__(256) void mg_inv_assemble_kernel(MgBatch B) {
   __shared__ double red[16];
-  const MgDev *mg = B.mg[blockIdx.x];
+  const MgDev *mg = B.mg[blockIdx.z];
   const MgLevel &L = mg->lv[mg->L];
-  const int n = L.n, m = mg->ndof_c;
-  const long long nn = L.nn;
+  const int n = L.n, m = mg->ndof_c, nn = int(L.nn);
+  if ((int)blockIdx.x * 4 >= m) return;
   const T *S = (const T *)L.S;
-  double *A = mg->Mc;
-  for (long long k = threadIdx.x; k < (long long)m * m; k += blockDim.x) A[k] = 0.0;
-  __syncthreads();
-  for (int row = threadIdx.x; row < m; row += blockDim.x) {
-    const long long v = row / 3;
-    const int c = row % 3;
-    const int x = int(v % n), y = int((v / n) % n), z = int(v / ((long long)n * n));
-    for (int w = 0; w < 27; ++w) {
-      const int dx = w % 3 - 1, dy = (w / 3) % 3 - 1, dz = w / 9 - 1;
-      const long long u = ((long long)wrap1(z + dz, n) * n + wrap1(y + dy, n)) * n + wrap1(x + dx, n);
-#pragma unroll
-      for (int cp = 0; cp < 3; ++cp) {
-        const double a = w >= 13 ? (double)S[((w - 13) * 9 + 3 * c + cp) * nn + v]
-                                  : (double)S[((13 - w) * 9 + 3 * cp + c) * nn + u];
-        A[(long long)row * m + 3 * u + cp] += a;
-      }
-    }
-  }
-  __syncthreads();
   double acc[1] = {0.0};
-  for (int i = threadIdx.x; i < m; i += blockDim.x) acc[0] += A[(long long)i * m + i];
-  block_sum<1>(acc, red, blockDim.x);
+  for (int i = threadIdx.x; i < m; i += 256) acc[0] += (double)S[4 * (i % 3) * nn + i / 3];
+  block_sum<1>(acc, red, 256);
   if (threadIdx.x == 0) red[0] = acc[0];
   __syncthreads();
-  const double add = red[0] / m / double(nn);
-  const double mean_diag = red[0] / m;
-  for (long long k = threadIdx.x; k < (long long)m * m; k += blockDim.x) {
-    const int i = int(k / m), j = int(k % m);
-    if (i % 3 == j % 3) A[k] += add;
+  const double mean_diag = red[0] / m, add = mean_diag / double(nn);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *InvScratch((double *)mg->inv, (m + IB - 1) / IB).mean = mean_diag;
+  // one wave per row: the constant blocks, then the 81 stencil entries on top
+  // (27 distinct neighbours: n >= 3)
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= m) return;
+  const int v = row / 3, c = row % 3;
+  double *A = mg->Mc + (long long)row * m;
+  const int x = v % n, y = (v / n) % n, z = v / (n * n);
+  for (int j = lane; j < m; j += 64) {
+    const int u = j / 3, cp = j % 3;
+    // offset of u from v on the periodic grid, if within one node
+    auto off = [n](int a, int b) {
+      const int d = a - b;
+      return d == n - 1 ? -1 : (d == 1 - n ? 1 : d);
+    };
+    const int dx = off(u % n, x), dy = off((u / n) % n, y), dz = off(u / (n * n), z);
+    double a = c == cp ? add : 0.0;
+    if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1) {
+      const int w = (dz + 1) * 9 + (dy + 1) * 3 + dx + 1;
+      a += w >= 13 ? (double)S[((w - 13) * 9 + 3 * c + cp) * nn + v] : (double)S[((13 - w) * 9 + 3 * cp + c) * nn + u];
+    }
+    A[j] = a;
+  }
+}
+
+// Step k, grid x = block t: every workgroup inverts A_kk for itself (one
+// barrier per pivot), block k stores it, the others their R_t and C_t.  A pivot
+// at or below 1e-12 of the mean diagonal is a vanishing pivot of the (positive
+// semidefinite) Schur complement: the dof is a null direction beyond the rigid
+// translations (nodes whose elements are all culled, pieces that float at this
+// level).  It is taken out -- row and column zero, in P and hence in R, C P and
+// the updates -- so the result stays a symmetric generalized inverse.  Never
+// taken on the floored operator.
+__global__ __launch_bounds__(256) void mg_inv_panel_kernel(MgBatch B, int k) {
+  __shared__ double P[IB][IB + 1], M[IB][IB + 1], rowp[2][IB], colp[2][IB];
+  const MgDev *mg = B.mg[blockIdx.z];
+  const int m = mg->ndof_c, nblk = (m + IB - 1) / IB, t = blockIdx.x;
+  if (k >= nblk || t >= nblk) return;
+  InvScratch W((double *)mg->inv, nblk);
+  const double *A = mg->Mc;
+  const double floor_ = 1e-12 * *W.mean;
+  const int bk = min(IB, m - k * IB), bt = min(IB, m - t * IB);
+  const int i = threadIdx.x >> 3, j0 = (threadIdx.x & 7) * 4;
+  double a[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)  // past the matrix: the identity
+    a[e] = i < bk && j0 + e < bk ? A[(long long)(k * IB + i) * m + k * IB + j0 + e] : (i == j0 + e ? 1.0 : 0.0);
+  for (int p = 0; p < bk; ++p) {
+    const int b = p & 1;
+    if (i == p)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rowp[b][j0 + e] = a[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (j0 + e == p) colp[b][i] = a[e];
+    __syncthreads();
+    const double piv = rowp[b][p], f = colp[b][i];
+    const bool ok = piv > floor_;
+    const double inv = ok ? 1.0 / piv : 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = j0 + e;
+      const double r = j == p ? inv : rowp[b][j] * inv;
+      if (!ok) a[e] = i == p || j == p ? 0.0 : a[e];
+      else a[e] = i == p ? r : (j == p ? 0.0 : a[e]) - f * r;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (t == k) W.P[i * IB + j0 + e] = a[e];
+    P[i][j0 + e] = a[e];
+  }
+  if (t == k) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    M[i][j0 + e] = i < bk && j0 + e < bt ? A[(long long)(k * IB + i) * m + t * IB + j0 + e] : 0.0;
+    W.Cc[(t * IB + i) * IB + j0 + e] = i < bt && j0 + e < bk ? A[(long long)(t * IB + i) * m + k * IB + j0 + e] : 0.0;
   }
   __syncthreads();
-  // column k of the current matrix and the normalized pivot row, kept in LDS
-  // while the other rows are updated (each wave sweeps rows, its lanes the
-  // columns)
-  __shared__ double colk[3 * MG_MAX_COARSE * MG_MAX_COARSE * MG_MAX_COARSE];
-  __shared__ double rowk[3 * MG_MAX_COARSE * MG_MAX_COARSE * MG_MAX_COARSE];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  for (int k = 0; k < m; ++k) {
-    const double piv = A[(long long)k * m + k];
-    if (!(piv > 1e-12 * mean_diag)) {
-      // a vanishing pivot of the (positive semidefinite) Schur complement: the
-      // dof is a null direction beyond the rigid translations (nodes whose
-      // elements are all culled, pieces that float at this level).  It is
-      // taken out -- row and column k zero -- so the result stays a symmetric
-      // generalized inverse.  Never taken on the floored operator.
-      __syncthreads();
-      for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        A[(long long)i * m + k] = 0.0;
-        A[(long long)k * m + i] = 0.0;
-      }
-      __syncthreads();
-      continue;
-    }
-    for (int i = threadIdx.x; i < m; i += blockDim.x) colk[i] = A[(long long)i * m + k];
-    __syncthreads();
-    for (int j = threadIdx.x; j < m; j += blockDim.x) {
-      const long long kj = (long long)k * m + j;
-      const double v = j == k ? 1.0 / piv : A[kj] / piv;
-      A[kj] = v;
-      rowk[j] = v;
+  double r[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int q = 0; q < bk; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] += P[i][q] * M[q][j0 + e];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) W.R[(t * IB + i) * IB + j0 + e] = r[e];
+}
+
+__global__ __launch_bounds__(256) void mg_inv_update_kernel(MgBatch B, int k) {
+  __shared__ double X[IB][IB + 1], Y[IB][IB + 1];
+  const MgDev *mg = B.mg[blockIdx.z];
+  const int m = mg->ndof_c, nblk = (m + IB - 1) / IB, tj = blockIdx.x, ti = blockIdx.y;
+  if (k >= nblk || tj >= nblk || ti >= nblk) return;
+  InvScratch W((double *)mg->inv, nblk);
+  const int bi = min(IB, m - ti * IB), bj = min(IB, m - tj * IB), bk = min(IB, m - k * IB);
+  const int i = threadIdx.x >> 3, j0 = (threadIdx.x & 7) * 4;
+  const double *src = ti == k ? (tj == k ? W.P : W.R + tj * IB * IB) : nullptr;
+  const double *right = tj == k ? W.P : W.R + tj * IB * IB;
+  if (!src) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      X[i][j0 + e] = W.Cc[(ti * IB + i) * IB + j0 + e];
+      Y[i][j0 + e] = right[i * IB + j0 + e];
     }
     __syncthreads();
-    // rows i != k: A[i][j] -= f_i A[k][j] (j != k), A[i][k] = -f_i / piv
-    for (int i = wave; i < m; i += nwaves) {
-      if (i == k) continue;
-      const double f = colk[i];
-      double *Ai = A + (long long)i * m;
-      for (int j = lane; j < m; j += 64) Ai[j] = (j == k ? 0.0 : Ai[j]) - f * rowk[j];
-    }
-    __syncthreads();
+  }
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  if (!src)
+    for (int q = 0; q < bk; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += X[i][q] * Y[q][j0 + e];
+  double *A = mg->Mc;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (i >= bi || j0 + e >= bj) continue;
+    double &o = A[(long long)(ti * IB + i) * m + tj * IB + j0 + e];
+    o = src ? src[i * IB + j0 + e] : (tj == k ? 0.0 : o) - acc[e];
   }
 }
 
@@ -961,9 +1023,20 @@ hipError_t mg_launch_elemc(const MgDev *d_mg, int l, long long nn_next, int prec
   return hipGetLastError();
 }
 
-hipError_t mg_launch_coarse_inverse(const MgBatch &B, int prec, hipStream_t st) {
-  if (prec == 0) mg_coarse_inverse_kernel<double><<<B.count, 1024, 0, st>>>(B);
-  else mg_coarse_inverse_kernel<float><<<B.count, 1024, 0, st>>>(B);
+size_t mg_inverse_scratch_bytes(int ndof) {
+  const size_t nblk = (ndof + IB - 1) / IB;
+  return sizeof(double) * ((2 * nblk + 1) * IB * IB + 1);
+}
+
+hipError_t mg_launch_coarse_inverse(const MgBatch &B, int ndof_max, int prec, hipStream_t st) {
+  const dim3 ga(blocks_for(ndof_max, 4), 1, B.count);
+  if (prec == 0) mg_inv_assemble_kernel<double><<<ga, 256, 0, st>>>(B);
+  else mg_inv_assemble_kernel<float><<<ga, 256, 0, st>>>(B);
+  const unsigned nblk = blocks_for(ndof_max, IB);
+  for (unsigned k = 0; k < nblk; ++k) {
+    mg_inv_panel_kernel<<<dim3(nblk, 1, B.count), 256, 0, st>>>(B, k);
+    mg_inv_update_kernel<<<dim3(nblk, nblk, B.count), 256, 0, st>>>(B, k);
+  }
   return hipGetLastError();
 }
 

@@ -57,6 +57,7 @@ struct MgDev {
   int ndof_c;           // 3 n_L^3
   void *G;              // [8][24][24] child Galerkin matrices of K_0 (T)
   double *Mc;           // [ndof_c][ndof_c] coarsest inverse (FP64), dof 3 node + c
+  void *inv;            // setup only: scratch of the inversion
   MgLevel lv[MG_MAXL];
 };
 

@@ -25,7 +25,8 @@ namespace shh {
 hipError_t mg_launch_elem1(const SlotDev *d_slot, const MgDev *d_mg, long long nn1, int prec, hipStream_t st);
 hipError_t mg_launch_elemc(const MgDev *d_mg, int l, long long nn_next, int prec, hipStream_t st);
 hipError_t mg_launch_stencil(const MgDev *d_mg, int l, long long nn, int prec, hipStream_t st);
-hipError_t mg_launch_coarse_inverse(const MgBatch &B, int prec, hipStream_t st);
+size_t mg_inverse_scratch_bytes(int ndof);
+hipError_t mg_launch_coarse_inverse(const MgBatch &B, int ndof_max, int prec, hipStream_t st);
 // live = 1: skip the load cases whose CG has stopped (state read on the device)
 // ep: the Chebyshev sweep fused into the output stage (MGE_*)
 hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, int prec,
@@ -362,6 +363,9 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
       mg.lv[l].Ke = ke + used;
       used = a256(used + (size_t)mg.lv[l].nn * 576 * ts);
     }
+    // the inversion's scratch takes their place once the stencils are built
+    used = std::max(used, mg_inverse_scratch_bytes(mg.ndof_c));
+    mg.inv = ke;
     if (used > 7 * s.lay.vec_bytes) return SHH_WORKSPACE_TOO_SMALL;
   }
   // child Galerkin matrices of this Poisson ratio's K_0 and the voxel-level
@@ -443,11 +447,12 @@ int mg_setup(const std::vector<Slot *> &all, hipStream_t st, std::vector<int> *r
     max_l = std::max(max_l, all[i]->mg.L);
   }
   if (slots.empty()) return SHH_OK;
-  // the coarsest levels' dense inverses, one workgroup per slot (a launch
-  // per slot ran them one after another: 1.8 ms each)
+  // the coarsest levels' dense inverses
   for (size_t b0 = 0; b0 < slots.size(); b0 += MG_MAXB) {
     const std::vector<Slot *> part(slots.begin() + b0, slots.begin() + std::min(slots.size(), b0 + MG_MAXB));
-    SHH_HIP(mg_launch_coarse_inverse(batch_of(part), prec, st));
+    int nd = 0;
+    for (Slot *s : part) nd = std::max(nd, s->mg.ndof_c);
+    SHH_HIP(mg_launch_coarse_inverse(batch_of(part), nd, prec, st));
   }
   // lambda_max(D^-1 A) of every coarse smoothing level by power iteration
   // on load case 0, entirely on the device, all levels of all slots together;

@@ -45,3 +45,23 @@ def test_mixed_batch_equals_single_designs():
     for d, rb in zip(designs, batch):
         rs = api.homogenize(d, precision="mixed", rtol=1e-6, solver="mg")
         assert np.array_equal(rs["C"], rb["C"]) and np.array_equal(rs["iters"], rb["iters"])
+
+
+# n: the largest FP64 iteration count with the coarsest grid inverted by plain
+# sequential elimination
+INVERSE = {6: 45, 8: 47, 10: 40, 14: 42, 28: 39, 40: 53}
+
+
+@pytest.mark.parametrize("n", sorted(INVERSE))
+def test_coarsest_inverse_block_edges(n):
+    # coarsest grids of 3^3, 4^3, 5^3 and 7^3 nodes: 81, 192, 375 and 1029 rows
+    # in blocks of 32.  A wrong block shows in the iteration count, which
+    # rounding can move by one; C^H within the usual FP64 bar of the Jacobi path
+    from paper_2511_04025_amd import api
+    d = wl.random_design(7100 + n, n, N=12, vf=0.25, E_void=1e-2)
+    print(f"coarsest inverse {n}^3", flush=True)
+    mg = api.homogenize(d, precision="fp64", rtol=1e-10, solver="mg")
+    ja = api.homogenize(d, precision="fp64", rtol=1e-10, solver="jacobi")
+    assert mg["status"] == 0 and ja["status"] == 0
+    assert_ch_close(mg["C"], ja["C"], 1e-7)
+    assert abs(int(mg["iters"].max()) - INVERSE[n]) <= 1
