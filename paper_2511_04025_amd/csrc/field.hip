@@ -5,10 +5,10 @@
 // Field evaluation is the exact regrouping of Eq. (6): expanding
 //   cos 2 pi h (x - x_j) = cos 2 pi h x cos 2 pi h x_j + sin 2 pi h x sin 2 pi h x_j
 // in all three axes turns the charge sum into a tensor of (2K+1)^3 real
-// coefficients over the 1D basis {1, cos 2 pi h s, sin 2 pi h s}, which a
-// workgroup contracts with the basis values of one z plane (a (2K+1)^2 plane
-// tensor in LDS) and then with its x and y basis values.  FP64 throughout, so
-// the hard threshold decides voxel for voxel like the FP64 oracle.
+// coefficients over the 1D basis {1, cos 2 pi h s, sin 2 pi h s}, which is
+// contracted with the basis values of each z plane (a (2K+1)^2 plane tensor),
+// then of each row y, then of each voxel x.  FP64 throughout, so the hard
+// threshold decides voxel for voxel like the FP64 oracle.
 #include <algorithm>
 
 #include "common.hpp"
@@ -20,31 +20,34 @@ namespace shh {
 __device__ __forceinline__ int basis_h(int u) { return (u + 1) >> 1; }
 
 // ---- trig coefficient tensor of the field -----------------------------------
-__global__ void coef_kernel(SlotDev *s) {
+// one wave per coefficient, the lanes over the charges (one thread per
+// coefficient walking the charges took 34 us at 48 charges: a handful of
+// waves, each a chain of sincospi calls)
+__global__ __launch_bounds__(256) void coef_kernel(SlotDev *s) {
   const int K = s->K, nb = s->nb, N = s->N, K1 = K + 1;
-  const int total = nb * nb * nb;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-    const int u = e / (nb * nb), v = (e / nb) % nb, w = e % nb;
-    const int h = basis_h(u), k = basis_h(v), l = basis_h(w);
-    double out = 0.0;
-    if (h + k + l > 0) {
-      const int zeros = (h == 0) + (k == 0) + (l == 0);
-      const double wgt = zeros == 0 ? 1.0 : (zeros == 1 ? 0.5 : 0.25);
-      const double a = s->alpha ? s->alpha[(h * K1 + k) * K1 + l] : 1.0;
-      const double c = a * wgt / double(h * h + k * k + l * l);
-      double acc = 0.0;
-      for (int j = 0; j < N; ++j) {
-        const double *ch = s->charges + 4 * j;
-        double tx = 1.0, ty = 1.0, tz = 1.0, sn, cs;
-        if (u > 0) { sincospi(2.0 * h * ch[0], &sn, &cs); tx = (u & 1) ? cs : sn; }
-        if (v > 0) { sincospi(2.0 * k * ch[1], &sn, &cs); ty = (v & 1) ? cs : sn; }
-        if (w > 0) { sincospi(2.0 * l * ch[2], &sn, &cs); tz = (w & 1) ? cs : sn; }
-        acc += ch[3] * tx * ty * tz;
-      }
-      out = c * acc;
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (e >= nb * nb * nb) return;
+  const int u = e / (nb * nb), v = (e / nb) % nb, w = e % nb;
+  const int h = basis_h(u), k = basis_h(v), l = basis_h(w);
+  double out = 0.0;
+  if (h + k + l > 0) {
+    const int zeros = (h == 0) + (k == 0) + (l == 0);
+    const double wgt = zeros == 0 ? 1.0 : (zeros == 1 ? 0.5 : 0.25);
+    const double a = s->alpha ? s->alpha[(h * K1 + k) * K1 + l] : 1.0;
+    const double c = a * wgt / double(h * h + k * k + l * l);
+    double acc = 0.0;
+    for (int j = lane; j < N; j += 64) {
+      const double *ch = s->charges + 4 * j;
+      double tx = 1.0, ty = 1.0, tz = 1.0, sn, cs;
+      if (u > 0) { sincospi(2.0 * h * ch[0], &sn, &cs); tx = (u & 1) ? cs : sn; }
+      if (v > 0) { sincospi(2.0 * k * ch[1], &sn, &cs); ty = (v & 1) ? cs : sn; }
+      if (w > 0) { sincospi(2.0 * l * ch[2], &sn, &cs); tz = (w & 1) ? cs : sn; }
+      acc += ch[3] * tx * ty * tz;
     }
-    s->coef[e] = out;
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    out = c * acc;
   }
+  if (lane == 0) s->coef[e] = out;
 }
 
 // basis value and derivative at voxel center (i + 1/2)/n
@@ -57,80 +60,113 @@ __device__ __forceinline__ void basis_at(int u, int i, int n, double &val, doubl
   if (u & 1) { val = cs; der = -w * sn; } else { val = sn; der = w * cs; }
 }
 
-// ---- field + gradient on one z plane; 64 x 4 voxels per workgroup ------------
-__global__ __launch_bounds__(256) void field_kernel(SlotDev *s) {
-  __shared__ double P[MAXB * MAXB], Pz[MAXB * MAXB];
-  __shared__ double Xv[64][MAXB], Xd[64][MAXB], Yv[4][MAXB], Yd[4][MAXB];
-  __shared__ double red[16];
-  const int n = s->n, nb = s->nb;
-  const int x0 = blockIdx.x * 64, y0 = blockIdx.y * 4, z = blockIdx.z;
-  const int tid = threadIdx.x;
-  // plane tensors P[u][v] = sum_w coef[u][v][w] Z_w(z), Pz with Z_w'(z)
-  for (int e = tid; e < nb * nb; e += 256) {
-    double a = 0.0, b = 0.0;
-    for (int w = 0; w < nb; ++w) {
-      double zv, zd;
-      basis_at(w, z, n, zv, zd);
-      const double c = s->coef[e * nb + w];
-      a += c * zv;
-      b += c * zd;
-    }
-    P[e] = a;
-    Pz[e] = b;
-  }
-  for (int e = tid; e < 64 * nb; e += 256) {
-    const int i = e / nb, u = e % nb;
-    double v = 0.0, d = 0.0;
-    if (x0 + i < n) basis_at(u, x0 + i, n, v, d);
-    Xv[i][u] = v;
-    Xd[i][u] = d;
-  }
-  if (tid < 4 * nb) {
-    const int j = tid / nb, u = tid % nb;
-    double v = 0.0, d = 0.0;
-    if (y0 + j < n) basis_at(u, y0 + j, n, v, d);
-    Yv[j][u] = v;
-    Yd[j][u] = d;
+// Tables of the field synthesis, in the slot's reduction scratch: the 1D basis
+// at the voxel centers (values, derivatives: [n][nb] each, the same on every
+// axis) and per z plane the plane tensors P[u][v] = sum_w coef[u][v][w] Z_w(z)
+// and Pz (with Z_w'): [n][2][nb^2].  One workgroup per plane.  (Formed by every
+// workgroup of the synthesis before, with 820 sincospi per 256 voxels.)
+__host__ __device__ inline long long field_table_doubles(int n, int nb) {
+  return (long long)n * (2 * nb + 2 * nb * nb);
+}
+
+__global__ __launch_bounds__(64) void field_tables_kernel(SlotDev *s) {
+  __shared__ double zv[MAXB], zd[MAXB];
+  const int n = s->n, nb = s->nb, z = blockIdx.x;
+  double *val = s->partials, *der = val + n * nb, *planes = der + n * nb + (long long)z * 2 * nb * nb;
+  for (int u = threadIdx.x; u < nb; u += 64) {
+    double v, d;
+    basis_at(u, z, n, v, d);
+    zv[u] = val[z * nb + u] = v;
+    zd[u] = der[z * nb + u] = d;
   }
   __syncthreads();
-  const int i = tid & 63, j = tid >> 6;
-  const int x = x0 + i, y = y0 + j;
+  for (int e = threadIdx.x; e < nb * nb; e += 64) {
+    double a = 0.0, b = 0.0;
+    for (int w = 0; w < nb; ++w) {
+      const double c = s->coef[e * nb + w];
+      a += c * zv[w];
+      b += c * zd[w];
+    }
+    planes[e] = a;
+    planes[nb * nb + e] = b;
+  }
+}
+
+// ---- field + gradient: 64 x FIELD_ROWS voxels of one z plane per workgroup ---
+// The row tensors (sum over v, three per u) are formed once per row in LDS; a
+// voxel then takes 4 NB multiply-adds.  Bound by its 32 B of output per voxel:
+// 23 us at 128^3 (every voxel summed over v itself before: 114 us).
+constexpr int FIELD_ROWS = 16;
+template <int NB>
+__global__ __launch_bounds__(256) void field_kernel(SlotDev *s) {
+  __shared__ double R[FIELD_ROWS][3][NB];
+  __shared__ double red[4];
+  const int n = s->n;
+  const int x = blockIdx.x * 64 + (threadIdx.x & 63), y0 = blockIdx.y * FIELD_ROWS, z = blockIdx.z;
+  const int wave = threadIdx.x >> 6;
+  const double *val = s->partials, *der = val + n * NB, *P = der + n * NB + (long long)z * 2 * NB * NB;
+  for (int e = threadIdx.x; e < FIELD_ROWS * NB; e += 256) {
+    const int j = e / NB, u = e % NB, y = min(y0 + j, n - 1);
+    double t = 0.0, ty = 0.0, tz = 0.0;
+    for (int v = 0; v < NB; ++v) {
+      const double Yv = val[y * NB + v], pv = P[u * NB + v];
+      t += pv * Yv;
+      ty += pv * der[y * NB + v];
+      tz += P[NB * NB + u * NB + v] * Yv;
+    }
+    R[j][0][u] = t;
+    R[j][1][u] = ty;
+    R[j][2][u] = tz;
+  }
+  const int xc = min(x, n - 1);
+  double Xv[NB], Xd[NB];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    Xv[u] = val[xc * NB + u];
+    Xd[u] = der[xc * NB + u];
+  }
+  __syncthreads();
+  const long long nn = s->nn;
+  double *oF = s->F, *oG = s->G;
   double gn = 0.0;
-  if (x < n && y < n) {
+  for (int j = wave; j < FIELD_ROWS; j += 4) {
+    const int y = y0 + j;
+    if (x >= n || y >= n) break;
     double F = 0.0, Gx = 0.0, Gy = 0.0, Gz = 0.0;
-    for (int u = 0; u < nb; ++u) {
-      double t = 0.0, ty = 0.0, tz = 0.0;
-      for (int v = 0; v < nb; ++v) {
-        const double pv = P[u * nb + v];
-        t += pv * Yv[j][v];
-        ty += pv * Yd[j][v];
-        tz += Pz[u * nb + v] * Yv[j][v];
-      }
-      F += Xv[i][u] * t;
-      Gx += Xd[i][u] * t;
-      Gy += Xv[i][u] * ty;
-      Gz += Xv[i][u] * tz;
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      F += Xv[u] * R[j][0][u];
+      Gx += Xd[u] * R[j][0][u];
+      Gy += Xv[u] * R[j][1][u];
+      Gz += Xv[u] * R[j][2][u];
     }
     const long long idx = ((long long)z * n + y) * n + x;
-    s->F[idx] = F;
-    s->G[idx] = Gx;
-    s->G[s->nn + idx] = Gy;
-    s->G[2 * s->nn + idx] = Gz;
-    gn = sqrt(Gx * Gx + Gy * Gy + Gz * Gz);
+    oF[idx] = F;
+    oG[idx] = Gx;
+    oG[nn + idx] = Gy;
+    oG[2 * nn + idx] = Gz;
+    gn = fmax(gn, sqrt(Gx * Gx + Gy * Gy + Gz * Gz));
   }
   // workgroup max, then a bitwise atomic max (non-negative doubles order as integers)
   for (int off = 32; off > 0; off >>= 1) gn = fmax(gn, __shfl_xor(gn, off, 64));
-  if ((tid & 63) == 0) red[tid >> 6] = gn;
+  if ((threadIdx.x & 63) == 0) red[wave] = gn;
   __syncthreads();
-  if (tid == 0) {
+  if (threadIdx.x == 0) {
     const double m = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
     atomicMax(&s->st->gmax_bits, (unsigned long long)__double_as_longlong(m));
   }
 }
 
+// ---- hard step: bins of the order-statistic search (below) -------------------
+constexpr int SEL_BITS = 11, SEL_BINS = 1 << SEL_BITS, SEL_PASSES = 6;  // 6 x 11 >= 64
+
 // ---- distance d = |F - c| / max(||grad F||, 1e-12 max ||grad F||) ------------
 __global__ __launch_bounds__(256) void distance_kernel(SlotDev *s) {
   const long long nn = s->nn;
+  // the order-statistic search that may follow counts into zeroed bins (the
+  // tables of the synthesis were here)
+  const long long first = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  for (long long i = first; i < 2 * SEL_BINS; i += (long long)gridDim.x * blockDim.x) ((unsigned *)s->partials)[i] = 0u;
   const double gmax = __longlong_as_double((long long)s->st->gmax_bits);
   const double gmin = 1e-12 * gmax;
   const int mode = s->dist_mode;
@@ -150,85 +186,82 @@ __global__ __launch_bounds__(256) void distance_kernel(SlotDev *s) {
   }
 }
 
-// ---- hard step: k-th smallest distance by a 16-way search over bit patterns --
-// Non-negative doubles (and +inf) order like their bit patterns.  Two searches
-// run together: the k1-th and k2-th smallest values (1-based), each the
-// smallest pattern v with count(d <= v) >= k inside its range [lo, hi].  Each
-// launch counts the elements at or below 15 pivots splitting each range into
-// 16 parts and keeps the part that holds the answer; a range of width w
-// leaves at most w / 16 + 1, so 17 launches finish the 63-bit start.
-constexpr int SEL_WAYS = 16, SEL_LAUNCHES = 18;
-
-__device__ __forceinline__ unsigned long long sel_pivot(unsigned long long lo, unsigned long long w, int i) {
-  // lo + floor(w (i + 1) / 16) without overflow
-  return lo + (w / SEL_WAYS) * (i + 1) + ((w % SEL_WAYS) * (i + 1)) / SEL_WAYS;
-}
-
-__global__ __launch_bounds__(256) void select_count_kernel(SlotDev *s, long long k1, long long k2,
-                                                           int nblocks) {
-  constexpr int NP = SEL_WAYS - 1;
-  __shared__ double red[2 * NP * 16];
+// ---- hard step: the k1-th and k2-th smallest distance (1-based) ---------------
+// Non-negative doubles (and +inf) order like their bit patterns.  A radix
+// search from the top: pass p counts, among the elements that share the digits
+// found so far, the next 11 bits (per search: the two ranks may part), in LDS
+// bins that go to global bins; the last workgroup finds the digit that holds
+// the rank and clears the bins.  Six passes over d (a 16-way search by counting
+// against 15 pivots per rank took 18 launches of 32 us at 128^3; these take
+// 8 us each).  State: sel_lo the digits found, sel_hi the rank left below them.
+__global__ __launch_bounds__(256) void select_pass_kernel(SlotDev *s, int pass, long long k1, long long k2,
+                                                          int nblocks) {
+  __shared__ unsigned bins[2][SEL_BINS];
+  __shared__ unsigned scan[2][256];
   __shared__ int lastflag;
   CgState *st = s->st;
-  const unsigned long long lo[2] = {st->sel_lo[0], st->sel_lo[1]};
-  const unsigned long long hi[2] = {st->sel_hi[0], st->sel_hi[1]};
-  if (lo[0] >= hi[0] && lo[1] >= hi[1]) return;  // both found (every workgroup sees the same)
-  unsigned long long m[2][NP];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < NP; ++i) m[j][i] = sel_pivot(lo[j], hi[j] - lo[j], i);
-  unsigned c[2][NP];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < NP; ++i) c[j][i] = 0u;
+  // 64 = 5 x 11 + 9: the first digit has 9 bits
+  const int shift = SEL_BITS * (SEL_PASSES - 1 - pass);
+  const unsigned long long pre[2] = {pass ? st->sel_lo[0] : 0ull, pass ? st->sel_lo[1] : 0ull};
+  const bool same = pre[0] == pre[1];  // one count serves both
+  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += 256) (&bins[0][0])[i] = 0u;
+  __syncthreads();
   const long long nn = s->nn;
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < nn;
-       e += (long long)nblocks * blockDim.x) {
+  const int hi = shift + SEL_BITS;  // bits above the digit (none in the first pass)
+  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < nn; e += (long long)nblocks * 256) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(s->d[e]);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int i = 0; i < NP; ++i) c[j][i] += b <= m[j][i] ? 1u : 0u;
+    const unsigned dig = unsigned(b >> shift) & (SEL_BINS - 1);
+    const unsigned long long top = pass ? b >> hi : 0ull;
+    if (top == (pass ? pre[0] >> hi : 0ull)) atomicAdd(&bins[0][dig], 1u);
+    if (!same && top == pre[1] >> hi) atomicAdd(&bins[1][dig], 1u);
   }
-  double v[2 * NP];  // exact: counts stay far below 2^53
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < NP; ++i) v[j * NP + i] = double(c[j][i]);
-  block_sum<2 * NP>(v, red, 256);
-  double *parts = s->partials;
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int i = 0; i < 2 * NP; ++i) parts[32 * blockIdx.x + i] = v[i];
+  __syncthreads();
+  unsigned *g = (unsigned *)s->partials;
+  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += 256)
+    if (const unsigned c = (&bins[0][0])[i]) atomicAdd(&g[i], c);
+  __syncthreads();
   if (!arrive_last(&st->cnt[6], nblocks, &lastflag)) return;
-  double tot[2 * NP];
-  sum_partials<2 * NP, 32>(parts, nblocks, tot, red, 256);
-  if (threadIdx.x == 0) {
-    const double kk[2] = {double(k1), double(k2)};
+  // thread t owns bins [8 t, 8 t + 8) of each search
+  constexpr int PER = SEL_BINS / 256;
+  unsigned c[2][PER];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (lo[j] >= hi[j]) continue;
-      // the first pivot whose count reaches k bounds the answer from above;
-      // the pivot before it (or lo) from below
-      unsigned long long nlo = lo[j], nhi = hi[j];
-      bool found = false;
+  for (int j = 0; j < 2; ++j) {
+    unsigned sum = 0;
 #pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        if (found) continue;
-        if (tot[j * NP + i] >= kk[j]) {
-          nhi = m[j][i];
-          found = true;
-        } else {
-          nlo = m[j][i] + 1;
-        }
-      }
-      st->sel_lo[j] = nlo;
-      st->sel_hi[j] = nhi;
+    for (int i = 0; i < PER; ++i) {
+      const int at = (same ? 0 : j) * SEL_BINS + threadIdx.x * PER + i;
+      c[j][i] = __hip_atomic_load(&g[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sum += c[j][i];
     }
-    st->cnt[6] = 0;
+    scan[j][threadIdx.x] = sum;
   }
+  __syncthreads();
+  for (int off = 1; off < 256; off <<= 1) {
+    unsigned v[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) v[j] = threadIdx.x >= (unsigned)off ? scan[j][threadIdx.x - off] : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) scan[j][threadIdx.x] += v[j];
+    __syncthreads();
+  }
+  const unsigned long long rank[2] = {pass ? st->sel_hi[0] : (unsigned long long)k1,
+                                      pass ? st->sel_hi[1] : (unsigned long long)k2};
+  __syncthreads();  // every thread has read the state before one rewrites it
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    unsigned long long below = threadIdx.x ? scan[j][threadIdx.x - 1] : 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (below < rank[j] && rank[j] <= below + c[j][i]) {  // exactly one bin holds the rank
+        st->sel_lo[j] = pre[j] | ((unsigned long long)(threadIdx.x * PER + i) << shift);
+        st->sel_hi[j] = rank[j] - below;
+      }
+      below += c[j][i];
+    }
+  }
+  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += 256) g[i] = 0u;
+  if (threadIdx.x == 0) st->cnt[6] = 0;
 }
 
 // t from the two order statistics; k = round(vf n^3).
@@ -428,10 +461,27 @@ static int grid_for(long long nn, int cap) {
   return int(g);
 }
 
-hipError_t launch_field(SlotDev *d_slot, int n, int nb, hipStream_t st) {
-  coef_kernel<<<(nb * nb * nb + 255) / 256, 256, 0, st>>>(d_slot);
-  dim3 g((n + 63) / 64, (n + 3) / 4, n);
-  field_kernel<<<g, 256, 0, st>>>(d_slot);
+hipError_t launch_coef(SlotDev *d_slot, int nb, hipStream_t st) {
+  coef_kernel<<<(nb * nb * nb + 3) / 4, 256, 0, st>>>(d_slot);
+  return hipGetLastError();
+}
+
+// scratch: doubles in the slot's reduction scratch
+hipError_t launch_field(SlotDev *d_slot, int n, int nb, long long scratch, hipStream_t st) {
+  if (scratch < field_table_doubles(n, nb)) return hipErrorInvalidValue;
+  hipError_t rc = launch_coef(d_slot, nb, st);
+  if (rc != hipSuccess) return rc;
+  field_tables_kernel<<<n, 64, 0, st>>>(d_slot);
+  const dim3 g((n + 63) / 64, (n + FIELD_ROWS - 1) / FIELD_ROWS, n);
+  switch (nb) {
+    case 3: field_kernel<3><<<g, 256, 0, st>>>(d_slot); break;
+    case 5: field_kernel<5><<<g, 256, 0, st>>>(d_slot); break;
+    case 7: field_kernel<7><<<g, 256, 0, st>>>(d_slot); break;
+    case 9: field_kernel<9><<<g, 256, 0, st>>>(d_slot); break;
+    case 11: field_kernel<11><<<g, 256, 0, st>>>(d_slot); break;
+    case 13: field_kernel<13><<<g, 256, 0, st>>>(d_slot); break;
+    default: return hipErrorInvalidValue;  // K is 1 to MAXK
+  }
   const long long nn = (long long)n * n * n;
   distance_kernel<<<grid_for(nn, 8192), 256, 0, st>>>(d_slot);
   return hipGetLastError();
@@ -440,11 +490,12 @@ hipError_t launch_field(SlotDev *d_slot, int n, int nb, hipStream_t st) {
 int reduce_blocks(long long nn) { return grid_for(nn, 1024); }
 
 hipError_t launch_select_hard(SlotDev *d_slot, long long nn, long long k, hipStream_t st) {
-  // 32 elements per thread: fewer partials for the last workgroup to sum
-  const int nbk = (int)std::max(1LL, std::min(2048LL, (nn + 8191) / 8192));
+  // one workgroup per CU at most, 16 elements per thread at least: every
+  // workgroup adds its bins to the global ones
+  const int nbk = (int)std::max(1LL, std::min(256LL, (nn + 4095) / 4096));
   const long long k1 = k <= 0 ? 1 : (k >= nn ? nn : k);
   const long long k2 = k <= 0 ? 1 : (k >= nn ? nn : k + 1);
-  for (int it = 0; it < SEL_LAUNCHES; ++it) select_count_kernel<<<nbk, 256, 0, st>>>(d_slot, k1, k2, nbk);
+  for (int p = 0; p < SEL_PASSES; ++p) select_pass_kernel<<<nbk, 256, 0, st>>>(d_slot, p, k1, k2, nbk);
   select_finish_kernel<<<1, 1, 0, st>>>(d_slot, k);
   return hipGetLastError();
 }
@@ -486,11 +537,6 @@ hipError_t launch_moduli_copy(SlotDev *d_slot, long long nn, const void *E, int 
 hipError_t launch_dinv(SlotDev *d_slot, long long nn, int prec, hipStream_t st) {
   if (prec == 0) dinv_kernel<double><<<grid_for(nn, 8192), 256, 0, st>>>(d_slot);
   else dinv_kernel<float><<<grid_for(nn, 8192), 256, 0, st>>>(d_slot);
-  return hipGetLastError();
-}
-
-hipError_t launch_coef(SlotDev *d_slot, int nb, hipStream_t st) {
-  coef_kernel<<<(nb * nb * nb + 255) / 256, 256, 0, st>>>(d_slot);
   return hipGetLastError();
 }
 

@@ -9,7 +9,8 @@ enum { RES_INIT = 0, RES_RECOMPUTE = 1, RES_FINAL = 2 };
 enum { PH_ITER = 0, PH_MEAN = 2, PH_RESID = 3 };
 
 // field.hip (single slot per launch; d_slot is the device copy of the slot)
-hipError_t launch_field(SlotDev *d_slot, int n, int nb, hipStream_t st);
+// scratch: doubles of the slot's reduction scratch (the synthesis keeps its tables there)
+hipError_t launch_field(SlotDev *d_slot, int n, int nb, long long scratch, hipStream_t st);
 int reduce_blocks(long long nn);
 hipError_t launch_select_hard(SlotDev *d_slot, long long nn, long long k, hipStream_t st);
 hipError_t launch_minmax_d(SlotDev *d_slot, long long nn, hipStream_t st);

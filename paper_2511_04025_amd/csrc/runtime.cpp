@@ -328,10 +328,6 @@ int slot_init(Slot &s, char *base, hipStream_t st) {
     // min / max of the distance bit patterns, reduced with atomicMin / atomicMax
     init.sel_lo[0] = ~0ull;
     init.sel_hi[0] = 0ull;
-  } else {
-    // bisection range of the order-statistic search: [0, +inf]
-    init.sel_lo[0] = init.sel_lo[1] = 0ull;
-    init.sel_hi[0] = init.sel_hi[1] = 0x7FF0000000000000ull;
   }
   SHH_HIP(hipMemcpyAsync(s.d_slot, &h, sizeof(SlotDev), hipMemcpyHostToDevice, st));
   SHH_HIP(hipMemcpyAsync(s.d_state, &init, sizeof(CgState), hipMemcpyHostToDevice, st));
@@ -347,7 +343,7 @@ int slot_init(Slot &s, char *base, hipStream_t st) {
 
 int slot_setup_field(Slot &s, double *beta_out, hipStream_t st) {
   const SlotDev &h = s.host;
-  SHH_HIP(launch_field(s.d_slot, h.n, h.nb, st));
+  SHH_HIP(launch_field(s.d_slot, h.n, h.nb, (long long)NRHS * h.maxparts * PSTRIDE, st));
   if (h.mode_t == 1) {
     const long long k = (long long)std::floor(h.target_vf * double(h.nn) + 0.5);
     SHH_HIP(launch_select_hard(s.d_slot, h.nn, k, st));
