@@ -193,15 +193,15 @@ __global__ __launch_bounds__(256) void adj_thickness_kernel(const double *t_part
 // dL/dalpha_hkl from dL/dcoef: coef[u][v][w] = sum_hkl alpha_hkl w_hkl / (h^2+k^2+l^2)
 // sum_j q_j T_u(x_j) T_v(y_j) T_w(z_j), the charge-side basis T pairing cos
 // with cos and sin with sin, so dL/dalpha_hkl sums dL/dcoef over the (at most
-// 8) basis triples of mode (h, k, l) against the charges' products.  One
-// thread per mode.
+// 8) basis triples of mode (h, k, l) against the charges' products.  One wave
+// per mode, the lanes over the charges (one thread per mode: 40 us).
 __global__ __launch_bounds__(256) void adj_alpha_kernel(SlotDev *s, const double *dcoef, double *out) {
   const int K = s->K, K1 = K + 1, nb = s->nb, N = s->N;
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+  const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (m >= K1 * K1 * K1) return;
   const int h = m / (K1 * K1), k = (m / K1) % K1, l = m % K1;
   if (h + k + l == 0) {
-    out[m] = 0.0;
+    if (lane == 0) out[m] = 0.0;
     return;
   }
   const int zeros = (h == 0) + (k == 0) + (l == 0);
@@ -209,32 +209,31 @@ __global__ __launch_bounds__(256) void adj_alpha_kernel(SlotDev *s, const double
   // basis indices of the mode per axis: u = 0 (h = 0), else 2h - 1 (cos) and 2h (sin)
   const int hu[3] = {h, k, l};
   double acc = 0.0;
-  for (int j = 0; j < N; ++j) {
+  // (order 0 has the one function 1: its second term counts 0)
+  double D[2][2][2];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const int a = t >> 2, b = (t >> 1) & 1, c = t & 1;
+    const int u = hu[0] ? 2 * hu[0] - 1 + a : 0, v = hu[1] ? 2 * hu[1] - 1 + b : 0, w = hu[2] ? 2 * hu[2] - 1 + c : 0;
+    D[a][b][c] = dcoef[(u * nb + v) * nb + w];
+  }
+  for (int j = lane; j < N; j += 64) {
     const double *ch = s->charges + 4 * j;
     double T[3][2];
-    int nu_[3], u0[3];
+#pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-      if (hu[ax] == 0) {
-        nu_[ax] = 1;
-        u0[ax] = 0;
-        T[ax][0] = 1.0;
-      } else {
-        nu_[ax] = 2;
-        u0[ax] = 2 * hu[ax] - 1;
-        double sn, cs;
-        sincospi(2.0 * hu[ax] * ch[ax], &sn, &cs);
-        T[ax][0] = cs;
-        T[ax][1] = sn;
-      }
+      double sn, cs;
+      sincospi(2.0 * hu[ax] * ch[ax], &sn, &cs);
+      T[ax][0] = hu[ax] ? cs : 1.0;
+      T[ax][1] = hu[ax] ? sn : 0.0;
     }
     double sj = 0.0;
-    for (int a = 0; a < nu_[0]; ++a)
-      for (int b = 0; b < nu_[1]; ++b)
-        for (int c = 0; c < nu_[2]; ++c)
-          sj += dcoef[((u0[0] + a) * nb + (u0[1] + b)) * nb + (u0[2] + c)] * T[0][a] * T[1][b] * T[2][c];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) sj += D[t >> 2][(t >> 1) & 1][t & 1] * T[0][t >> 2] * T[1][(t >> 1) & 1] * T[2][t & 1];
     acc += ch[3] * sj;
   }
-  out[m] = wgt * acc;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if (lane == 0) out[m] = wgt * acc;
 }
 
 // 1D basis table at the voxel centers: val[i][u], der[i][u]
@@ -389,7 +388,7 @@ hipError_t launch_adjoint(SlotDev *d_slot, int n, int nb, int N, int K, const do
   adj_coef_kernel<<<(nb * nb * nb + 127) / 128, 128, 0, st>>>(n, nb, planes, val, der, dcoef);
   adj_charges_kernel<<<N, 256, 0, st>>>(d_slot, dcoef, d_out);
   const int K1 = K + 1;
-  if (d_alpha_out) adj_alpha_kernel<<<(K1 * K1 * K1 + 255) / 256, 256, 0, st>>>(d_slot, dcoef, d_alpha_out);
+  if (d_alpha_out) adj_alpha_kernel<<<(K1 * K1 * K1 + 3) / 4, 256, 0, st>>>(d_slot, dcoef, d_alpha_out);
   return hipGetLastError();
 }
 
@@ -398,7 +397,7 @@ hipError_t launch_coef_adjoint(SlotDev *d_slot, int N, int K, const double *d_dc
                                double *d_alpha_out, hipStream_t st) {
   adj_charges_kernel<<<N, 256, 0, st>>>(d_slot, d_dcoef, d_out);
   const int K1 = K + 1;
-  if (d_alpha_out) adj_alpha_kernel<<<(K1 * K1 * K1 + 255) / 256, 256, 0, st>>>(d_slot, d_dcoef, d_alpha_out);
+  if (d_alpha_out) adj_alpha_kernel<<<(K1 * K1 * K1 + 3) / 4, 256, 0, st>>>(d_slot, d_dcoef, d_alpha_out);
   return hipGetLastError();
 }
 

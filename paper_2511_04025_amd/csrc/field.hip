@@ -10,6 +10,7 @@
 // then of each row y, then of each voxel x.  FP64 throughout, so the hard
 // threshold decides voxel for voxel like the FP64 oracle.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -383,56 +384,6 @@ __device__ __forceinline__ double decode_modulus(const void *E, long long i, dou
   else return ((const double *)E)[i];
 }
 
-// Copy, round, and record the volume fraction: the solid share of the code
-// (DT = 0), else mean(E) / max(E) (the bitwise max is taken beforehand).
-template <int DT>
-__global__ __launch_bounds__(256) void moduli_copy_kernel(SlotDev *s, const void *E, double Es, double Ev,
-                                                          int nblocks) {
-  __shared__ double red[16];
-  __shared__ int lastflag;
-  CgState *st = s->st;
-  const long long nn = s->nn;
-  double v[1] = {0.0};
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nn;
-       i += (long long)nblocks * blockDim.x) {
-    const double e = decode_modulus<DT>(E, i, Es, Ev);
-    s->E64[i] = e;
-    if (s->E32) s->E32[i] = (float)e;
-    if constexpr (DT == 0) v[0] += ((const unsigned char *)E)[i] ? 1.0 : 0.0;
-    else v[0] += e;
-  }
-  block_sum<1>(v, red, 256);
-  if (threadIdx.x == 0) s->partials[4 * blockIdx.x] = v[0];
-  if (!arrive_last(&st->cnt[6], nblocks, &lastflag)) return;
-  double tot[1];
-  sum_partials<1>(s->partials, nblocks, tot, red, 256);
-  if (threadIdx.x == 0) {
-    const double emax = __longlong_as_double((long long)st->gmax_bits);
-    st->Emax = emax;
-    if constexpr (DT == 0) st->V = tot[0] / double(nn);
-    else st->V = emax > 0.0 ? tot[0] / double(nn) / emax : 0.0;
-    st->t = 0.0;
-    st->cnt[6] = 0;
-  }
-}
-
-template <int DT>
-__global__ __launch_bounds__(256) void max_bits_kernel(SlotDev *s, const void *E, double Es, double Ev) {
-  const long long nn = s->nn;
-  unsigned long long mx = 0ull;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nn;
-       i += (long long)gridDim.x * blockDim.x) {
-    const double e = decode_modulus<DT>(E, i, Es, Ev);
-    const unsigned long long b = e > 0.0 ? (unsigned long long)__double_as_longlong(e) : 0ull;
-    mx = b > mx ? b : mx;
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned long long c = __shfl_xor(mx, off, 64);
-    mx = c > mx ? c : mx;
-  }
-  if ((threadIdx.x & 63) == 0) atomicMax(&s->st->gmax_bits, mx);
-}
-
 // ---- inverse Jacobi diagonal: ((lambda + 4 mu)/9 * sum of the 8 incident E_e)^-1 --
 template <typename T>
 __global__ __launch_bounds__(256) void dinv_kernel(SlotDev *s) {
@@ -450,6 +401,67 @@ __global__ __launch_bounds__(256) void dinv_kernel(SlotDev *s) {
                        ((at(x, y, zm) + at(xm, y, zm)) + (at(x, ym, zm) + at(xm, ym, zm)));
     const double dg = c * sum;
     Dinv[i] = (T)(dg > 0.0 ? 1.0 / dg : 0.0);
+  }
+}
+
+// Moduli given directly: copy, round, the Jacobi diagonal (from the source grid)
+// and the volume fraction -- the solid share of the code (DT = 0), else mean(E)
+// / max(E) -- in one pass.  (The maximum by 4,096 atomics on one word, the copy
+// and the diagonal one after another took 87 us at 101^3.)
+template <int DT, typename T>
+__global__ __launch_bounds__(256) void moduli_kernel(SlotDev *s, const void *E, double Es, double Ev, int nblocks) {
+  __shared__ double red[16];
+  __shared__ int lastflag;
+  CgState *st = s->st;
+  const int n = s->n;
+  const long long nn = s->nn;
+  const double cd = (s->lam + 4.0 * s->mu) / 9.0;
+  double *oE = s->E64;
+  float *oE32 = s->E32;
+  T *Dinv = (T *)s->Dinv;
+  double v[1] = {0.0}, mx = 0.0;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nn;
+       i += (long long)nblocks * blockDim.x) {
+    const unsigned row = unsigned(i) / unsigned(n);  // n <= 512: node indices fit 32 bits
+    const int x = int(unsigned(i) - row * unsigned(n)), y = int(row % unsigned(n)), z = int(row / unsigned(n));
+    const int xm = x == 0 ? n - 1 : x - 1, ym = y == 0 ? n - 1 : y - 1, zm = z == 0 ? n - 1 : z - 1;
+    auto at = [&](int a, int b, int c) { return decode_modulus<DT>(E, ((long long)c * n + b) * n + a, Es, Ev); };
+    const double e = at(x, y, z);
+    const double sum = ((e + at(xm, y, z)) + (at(x, ym, z) + at(xm, ym, z))) +
+                       ((at(x, y, zm) + at(xm, y, zm)) + (at(x, ym, zm) + at(xm, ym, zm)));
+    oE[i] = e;
+    if (oE32) oE32[i] = (float)e;
+    const double dg = cd * sum;
+    Dinv[i] = (T)(dg > 0.0 ? 1.0 / dg : 0.0);
+    if constexpr (DT == 0) v[0] += ((const unsigned char *)E)[i] ? 1.0 : 0.0;
+    else v[0] += e;
+    mx = e > mx ? e : mx;  // a NaN or negative modulus never counts
+  }
+  block_sum<1>(v, red, 256);
+  for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s->partials[4 * blockIdx.x] = v[0];
+    s->partials[4 * blockIdx.x + 1] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  }
+  if (!arrive_last(&st->cnt[6], nblocks, &lastflag)) return;
+  double tot[1];
+  sum_partials<1>(s->partials, nblocks, tot, red, 256);
+  double m = 0.0;
+  for (int k = threadIdx.x; k < nblocks; k += 256) m = fmax(m, s->partials[4 * k + 1]);
+  for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double emax = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    st->Emax = emax;
+    if constexpr (DT == 0) st->V = tot[0] / double(nn);
+    else st->V = emax > 0.0 ? tot[0] / double(nn) / emax : 0.0;
+    st->t = 0.0;
+    st->cnt[6] = 0;
   }
 }
 
@@ -518,19 +530,17 @@ hipError_t launch_occupancy(SlotDev *d_slot, long long nn, double *beta_out, hip
   return hipGetLastError();
 }
 
-hipError_t launch_moduli_copy(SlotDev *d_slot, long long nn, const void *E, int e_dtype, double Es, double Ev,
-                              hipStream_t st) {
-  const int g = grid_for(nn, 1024), nbk = reduce_blocks(nn);
-  if (e_dtype == 0) {
-    max_bits_kernel<0><<<g, 256, 0, st>>>(d_slot, E, Es, Ev);
-    moduli_copy_kernel<0><<<nbk, 256, 0, st>>>(d_slot, E, Es, Ev, nbk);
-  } else if (e_dtype == 1) {
-    max_bits_kernel<1><<<g, 256, 0, st>>>(d_slot, E, Es, Ev);
-    moduli_copy_kernel<1><<<nbk, 256, 0, st>>>(d_slot, E, Es, Ev, nbk);
-  } else {
-    max_bits_kernel<2><<<g, 256, 0, st>>>(d_slot, E, Es, Ev);
-    moduli_copy_kernel<2><<<nbk, 256, 0, st>>>(d_slot, E, Es, Ev, nbk);
-  }
+hipError_t launch_moduli(SlotDev *d_slot, long long nn, const void *E, int e_dtype, double Es, double Ev, int prec,
+                         hipStream_t st) {
+  const int nbk = reduce_blocks(nn);
+  auto go = [&](auto dt) {
+    constexpr int DT = decltype(dt)::value;
+    if (prec == 0) moduli_kernel<DT, double><<<nbk, 256, 0, st>>>(d_slot, E, Es, Ev, nbk);
+    else moduli_kernel<DT, float><<<nbk, 256, 0, st>>>(d_slot, E, Es, Ev, nbk);
+  };
+  if (e_dtype == 0) go(std::integral_constant<int, 0>{});
+  else if (e_dtype == 1) go(std::integral_constant<int, 1>{});
+  else go(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

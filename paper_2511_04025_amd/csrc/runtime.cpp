@@ -358,8 +358,7 @@ int slot_setup_field(Slot &s, double *beta_out, hipStream_t st) {
 
 int slot_setup_moduli(Slot &s, const void *d_E, int e_dtype, double Es, double Ev, hipStream_t st) {
   const SlotDev &h = s.host;
-  SHH_HIP(launch_moduli_copy(s.d_slot, h.nn, d_E, e_dtype, Es, Ev, st));
-  SHH_HIP(launch_dinv(s.d_slot, h.nn, h.prec, st));
+  SHH_HIP(launch_moduli(s.d_slot, h.nn, d_E, e_dtype, Es, Ev, h.prec, st));
   return SHH_OK;
 }
 
