@@ -85,16 +85,17 @@ int prepare_slot(Slot &s, const shh_design *d, const shh_opts *o, void *d_ws, si
 int solve_all(Solver &sv, std::vector<Slot *> slots, int check_every, int max_iter) {
   SHH_TRY(sv.start(slots));
   long long guard = 0;
-  const long long guard_max = (long long)max_iter * 4 + 64 * (long long)check_every + 1024;
+  const long long guard_max = (long long)max_iter * 4 + 64 * (long long)std::max(check_every, 16) + 1024;
   while (!slots.empty()) {
-    SHH_TRY(sv.iterate(slots, check_every));
+    const int iters = next_poll(slots, check_every);
+    SHH_TRY(sv.iterate(slots, iters));
     std::vector<Slot *> done;
     SHH_TRY(sv.poll(slots, done));
     std::vector<Slot *> rest;
     for (Slot *s : slots)
       if (!s->finished) rest.push_back(s);
     slots.swap(rest);
-    guard += check_every;
+    guard += iters;
     if (guard > guard_max) {
       for (Slot *s : slots) s->status = SHH_NOT_CONVERGED;
       break;
@@ -231,12 +232,13 @@ int32_t shh_field(const shh_design *design, void *d_ws, size_t ws_bytes, double 
   hipStream_t st = (hipStream_t)hip_stream;
   Slot s;
   SHH_TRY(prepare_slot(s, design, &o, d_ws, ws_bytes, nullptr));
-  SHH_TRY(slot_init(s, s.base, st));
-  SHH_TRY(slot_setup_field(s, d_beta, st));
-  const size_t nb = sizeof(double) * (size_t)s.host.nn;
-  if (d_F) SHH_HIP(hipMemcpyAsync(d_F, s.host.F, nb, hipMemcpyDeviceToDevice, st));
-  if (d_G) SHH_HIP(hipMemcpyAsync(d_G, s.host.G, 3 * nb, hipMemcpyDeviceToDevice, st));
-  if (d_d) SHH_HIP(hipMemcpyAsync(d_d, s.host.d, nb, hipMemcpyDeviceToDevice, st));
+  // the field kernels write the caller's arrays where given
+  SHH_TRY(slot_init(s, s.base, st, [&](SlotDev &h) {
+    if (d_F) h.F = d_F;
+    if (d_G) h.G = d_G;
+    if (d_d) h.d = d_d;
+  }));
+  SHH_TRY(slot_setup_field(s, d_beta, st, false));
   SHH_HIP(hipMemcpyAsync(&s.state, s.d_state, sizeof(CgState), hipMemcpyDeviceToHost, st));
   SHH_HIP(hipStreamSynchronize(st));
   if (out) {
@@ -286,10 +288,20 @@ int32_t shh_workspace_bytes_operator(int32_t n, int32_t precision, size_t *bytes
   return SHH_OK;
 }
 
-// Slot over a workspace with moduli copied from d_E (scale taken from max E).
+// A grid needs a positive, finite largest modulus; the selective solve culls
+// zero moduli and takes an all-zero grid as an empty cell.
+static bool moduli_ok(const Slot &s) {
+  const double emax = s.state.Emax;
+  return std::isfinite(emax) && (emax > 0.0 || (is_selective(s.opts.solver) && emax == 0.0));
+}
+
+// Slot over a workspace with moduli copied from d_E.  For a solve (vectors) the
+// scale is read back from max E; an operator call gives its vectors in `adjust`
+// and checks the moduli with its own read-back at the end (operator_finish).
 static int moduli_slot(Slot &s, int32_t n, const void *d_E, double nu, const shh_opts *o, void *d_ws,
                        size_t ws_bytes, hipStream_t st, char **seg_mem, bool vectors,
-                       int e_dtype = SHH_EDTYPE_F64, double Es = 0.0, double Ev = 0.0) {
+                       int e_dtype = SHH_EDTYPE_F64, double Es = 0.0, double Ev = 0.0,
+                       const std::function<void(SlotDev &)> &adjust = nullptr, const OperatorSegment *op = nullptr) {
   if (n < 2 || n > 512 || !d_E || !(nu > -1.0 && nu < 0.5)) return SHH_INVALID_ARG;
   if (e_dtype != SHH_EDTYPE_U8 && e_dtype != SHH_EDTYPE_F32 && e_dtype != SHH_EDTYPE_F64) return SHH_INVALID_ARG;
   if (e_dtype == SHH_EDTYPE_U8 && !(Es > 0.0 && std::isfinite(Es) && Ev >= 0.0 && Ev <= Es)) return SHH_INVALID_ARG;
@@ -297,20 +309,34 @@ static int moduli_slot(Slot &s, int32_t n, const void *d_E, double nu, const shh
   oo.save_for_backward = 0;
   const shh_design d = stiffness_design(n, nu);
   SHH_TRY(prepare_slot(s, &d, &oo, d_ws, ws_bytes, seg_mem, vectors));
-  SHH_TRY(slot_init(s, s.base, st));
+  SHH_TRY(slot_init(s, s.base, st, adjust, op));
   // a culled voxel of the selective solve carries nothing, whatever E_void says
   SHH_TRY(slot_setup_moduli(s, d_E, e_dtype, Es, is_selective(oo.solver) ? 0.0 : Ev, st));
+  if (!vectors) return SHH_OK;
   SHH_HIP(hipMemcpyAsync(&s.state, s.d_state, sizeof(CgState), hipMemcpyDeviceToHost, st));
   SHH_HIP(hipStreamSynchronize(st));
+  if (!moduli_ok(s)) return SHH_INVALID_ARG;
   const double emax = s.state.Emax;
-  // the selective solve culls zero moduli; an all-zero grid is an empty cell
-  const bool sel = is_selective(oo.solver);
-  if (!std::isfinite(emax) || !(emax > 0.0 || (sel && emax == 0.0))) return SHH_INVALID_ARG;
   s.host.E = emax;
   s.host.ffloor = 1e-12 * emax * std::sqrt(3.0 * double(s.host.nn));
   SHH_HIP(hipMemcpyAsync(s.d_slot, &s.host, sizeof(SlotDev), hipMemcpyHostToDevice, st));
   SHH_HIP(hipStreamSynchronize(st));
   return SHH_OK;
+}
+
+// The launch of an operator call: its segment was uploaded with the slot.
+static LaunchArgs operator_launch(const Slot &s, const OperatorSegment &op) {
+  LaunchArgs la{(const Segment *)(s.base + s.lay.alpha), 1, s.host.ntiles[op.tiling] * op.nrhs};
+  la.split_evenly();
+  return la;
+}
+
+// Waits for an operator call and says whether its moduli were valid.
+static int operator_finish(Slot &s, hipStream_t st) {
+  SHH_HIP(hipMemcpyAsync(&s.state, s.d_state, sizeof(CgState), hipMemcpyDeviceToHost, st));
+  SHH_HIP(hipStreamSynchronize(st));
+  s.upload.clear();
+  return moduli_ok(s) ? SHH_OK : SHH_INVALID_ARG;
 }
 
 int32_t shh_homogenize_stiffness(int32_t n, const double *d_E, double nu, const shh_opts *opts,
@@ -372,24 +398,15 @@ int32_t shh_apply_stiffness(int32_t n, int32_t precision, const double *d_E, dou
   SHH_TRY(normalize_opts(&o, &o));
   hipStream_t st = (hipStream_t)hip_stream;
   Slot s;
-  char *seg_mem = nullptr;
-  SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, &seg_mem, false));
-  s.host.p[0] = const_cast<void *>(d_p);
-  s.host.q[0] = d_q;
-  SHH_HIP(hipMemcpyAsync(s.d_slot, &s.host, sizeof(SlotDev), hipMemcpyHostToDevice, st));
-  Segment g;
-  std::memset(&g, 0, sizeof(g));
-  g.slot = s.d_slot;
-  g.first = 0;
-  g.nrhs = nrhs;
-  for (int r = 0; r < nrhs; ++r) g.rhs[r] = r;
-  g.nblocks = s.host.ntiles[precision == SHH_PREC_MIXED ? 1 : 0] * nrhs;
-  SHH_HIP(hipMemcpyAsync(seg_mem, &g, sizeof(g), hipMemcpyHostToDevice, st));
-  LaunchArgs la{(const Segment *)seg_mem, 1, g.nblocks};
-  la.split_evenly();
-  SHH_HIP(launch_stencil_apply(la, precision, st));
-  SHH_HIP(hipStreamSynchronize(st));
-  return SHH_OK;
+  const OperatorSegment op{precision == SHH_PREC_MIXED ? 1 : 0, nrhs, 0};
+  SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, nullptr, false, SHH_EDTYPE_F64, 0.0, 0.0,
+                      [&](SlotDev &h) {
+                        h.p[0] = const_cast<void *>(d_p);
+                        h.q[0] = d_q;
+                      },
+                      &op));
+  SHH_HIP(launch_stencil_apply(operator_launch(s, op), precision, st));
+  return operator_finish(s, st);
 }
 
 int32_t shh_mg_operator(int32_t n, int32_t precision, const double *d_E, double nu, int32_t level,
@@ -423,23 +440,11 @@ int32_t shh_load_vectors(int32_t n, const double *d_E, double nu, double *d_f, v
   SHH_TRY(normalize_opts(&o, &o));
   hipStream_t st = (hipStream_t)hip_stream;
   Slot s;
-  char *seg_mem = nullptr;
-  SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, &seg_mem, false));
-  s.host.r[0] = d_f;
-  SHH_HIP(hipMemcpyAsync(s.d_slot, &s.host, sizeof(SlotDev), hipMemcpyHostToDevice, st));
-  Segment g;
-  std::memset(&g, 0, sizeof(g));
-  g.slot = s.d_slot;
-  g.nrhs = NRHS;
-  for (int r = 0; r < NRHS; ++r) g.rhs[r] = r;
-  g.nblocks = s.host.ntiles[0] * NRHS;  // FP64 residual kernel
-  g.flag = RES_INIT;
-  SHH_HIP(hipMemcpyAsync(seg_mem, &g, sizeof(g), hipMemcpyHostToDevice, st));
-  LaunchArgs la{(const Segment *)seg_mem, 1, g.nblocks};
-  la.split_evenly();
-  SHH_HIP(launch_stencil_resid(la, SHH_PREC_FP64, st));
-  SHH_HIP(hipStreamSynchronize(st));
-  return SHH_OK;
+  const OperatorSegment op{0, NRHS, RES_INIT};  // FP64 residual kernel
+  SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, nullptr, false, SHH_EDTYPE_F64, 0.0, 0.0,
+                      [&](SlotDev &h) { h.r[0] = d_f; }, &op));
+  SHH_HIP(launch_stencil_resid(operator_launch(s, op), SHH_PREC_FP64, st));
+  return operator_finish(s, st);
 }
 
 int32_t shh_energy(int32_t n, const double *d_E, double nu, const double *d_u, double CH[36], void *d_ws,
@@ -453,12 +458,10 @@ int32_t shh_energy(int32_t n, const double *d_E, double nu, const double *d_u, d
   SHH_TRY(normalize_opts(&o, &o));
   hipStream_t st = (hipStream_t)hip_stream;
   Slot s;
-  SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, nullptr, false));
-  s.host.x64 = const_cast<double *>(d_u);
-  SHH_HIP(hipMemcpyAsync(s.d_slot, &s.host, sizeof(SlotDev), hipMemcpyHostToDevice, st));
+  SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, nullptr, false, SHH_EDTYPE_F64, 0.0, 0.0,
+                      [&](SlotDev &h) { h.x64 = const_cast<double *>(d_u); }));
   SHH_HIP(launch_energy(s.d_slot, s.host.nn, st));
-  SHH_HIP(hipMemcpyAsync(&s.state, s.d_state, sizeof(CgState), hipMemcpyDeviceToHost, st));
-  SHH_HIP(hipStreamSynchronize(st));
+  SHH_TRY(operator_finish(s, st));
   for (int i = 0; i < 36; ++i) CH[i] = s.state.C[i];
   return SHH_OK;
 }
@@ -669,6 +672,7 @@ int32_t shh_field_points(const shh_design *design, int32_t npts, const double *d
   SHH_HIP(launch_coef(s.d_slot, s.host.nb, st));
   SHH_HIP(launch_points_field(s.d_slot, s.host.nb, npts, d_pts, d_F, d_G, st));
   SHH_HIP(hipStreamSynchronize(st));
+  s.upload.clear();
   return SHH_OK;
 }
 
@@ -697,6 +701,7 @@ int32_t shh_field_points_grad(const shh_design *design, int32_t npts, const doub
   SHH_HIP(hipMemcpyAsync(job.host.data(), d_out, sizeof(double) * (4 * (size_t)Nx + job.nalpha),
                          hipMemcpyDeviceToHost, st));
   SHH_HIP(hipStreamSynchronize(st));
+  s.upload.clear();
   grad_unpack(job, dL_dpos, dL_dq, dL_dalpha, nullptr);
   return SHH_OK;
 }

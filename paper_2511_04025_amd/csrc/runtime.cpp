@@ -125,8 +125,42 @@ int normalize_opts(const shh_opts *in, shh_opts *out) {
   // (near-)null modes, which the FP32 recursion turns into residual drift
   if (out->recompute_every == 0 && out->precision == SHH_PREC_MIXED)
     out->recompute_every = out->solver == SHH_SOLVER_SELECTIVE ? 10 : 50;
-  if (out->check_every == 0) out->check_every = 16;
   return SHH_OK;
+}
+
+// Iterations until the next look at the slots' states where the caller set no
+// period: until the last load case is due at its rate of convergence (since the
+// last look, or from the start), at least 2 and at most 16 -- 64 in a solve of
+// hundreds of iterations while the end is far (an early estimate says little: the
+// residual of the first iterations hardly falls).  A fixed 16 ran up to 15 empty
+// iterations after the last load case stopped: a twentieth of a 48^3 solve.  The
+// arithmetic does not depend on it.
+int next_poll(const std::vector<Slot *> &slots, int fixed) {
+  if (fixed > 0) return fixed;
+  double left = 0.0;
+  int done = 0;
+  for (Slot *s : slots) {
+    const CgState &c = s->state;
+    int it = 0;
+    double v = -1e300;
+    for (int k = 0; k < NRHS; ++k) {
+      if (!c.active[k]) continue;
+      it = std::max(it, c.iters[k]);
+      v = std::max(v, c.rel[k] > 0.0 && std::isfinite(c.rel[k]) ? std::log(c.rel[k] / s->host.rtol) : 0.0);
+    }
+    if (it <= 0 || v <= 0.0) {  // not started, or about to stop
+      left = std::max(left, it <= 0 ? 16.0 : 2.0);
+      continue;
+    }
+    done = std::max(done, it);
+    const double all = (std::log(1.0 / s->host.rtol) - v) / it;
+    const double recent = it > s->polled_at ? (s->polled_log - v) / (it - s->polled_at) : 0.0;
+    const double rate = s->polled_at > 0 && recent > 0.0 ? recent : all;
+    left = std::max(left, rate > 0.0 ? v / rate : 16.0);
+    s->polled_at = it;
+    s->polled_log = v;
+  }
+  return std::max(2, std::min(left > 128.0 && done > 128 ? 64 : 16, int(std::min(left, 1e6)) + 1));
 }
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -253,7 +287,8 @@ static void element_operator(double nu, double kop[KOP_N]) {
   }
 }
 
-int slot_init(Slot &s, char *base, hipStream_t st) {
+int slot_init(Slot &s, char *base, hipStream_t st, const std::function<void(SlotDev &)> &adjust,
+              const OperatorSegment *op) {
   const shh_design &d = s.design.d;
   const int prec = s.opts.precision;
   s.base = base;
@@ -314,13 +349,6 @@ int slot_init(Slot &s, char *base, hipStream_t st) {
   h.st = (CgState *)(base + L.state);
   s.d_slot = (SlotDev *)(base + L.slotdev);
   s.d_state = h.st;
-  std::vector<double> ch(4 * (size_t)h.N);
-  for (int j = 0; j < h.N; ++j) {
-    ch[4 * j] = d.pos[3 * j];
-    ch[4 * j + 1] = d.pos[3 * j + 1];
-    ch[4 * j + 2] = d.pos[3 * j + 2];
-    ch[4 * j + 3] = d.q[j];
-  }
   CgState init;
   std::memset(&init, 0, sizeof(init));
   init.t = d.thickness;
@@ -329,19 +357,41 @@ int slot_init(Slot &s, char *base, hipStream_t st) {
     init.sel_lo[0] = ~0ull;
     init.sel_hi[0] = 0ull;
   }
-  SHH_HIP(hipMemcpyAsync(s.d_slot, &h, sizeof(SlotDev), hipMemcpyHostToDevice, st));
-  SHH_HIP(hipMemcpyAsync(s.d_state, &init, sizeof(CgState), hipMemcpyHostToDevice, st));
-  SHH_HIP(hipMemcpyAsync(h.charges, ch.data(), sizeof(double) * ch.size(), hipMemcpyHostToDevice, st));
-  if (h.alpha) {
-    const int K1 = d.K + 1;
-    SHH_HIP(hipMemcpyAsync(h.alpha, d.alpha, sizeof(double) * K1 * K1 * K1, hipMemcpyHostToDevice, st));
+  if (adjust) adjust(h);
+  // descriptor, state, charges and alpha lie one after the other at the
+  // region's start: one copy (four and a wait took 40 us of a call)
+  const size_t K13 = (size_t)(d.K + 1) * (d.K + 1) * (d.K + 1);
+  if (!s.upload.empty()) SHH_HIP(hipStreamSynchronize(s.upload_stream));
+  s.upload.assign(L.alpha + (d.alpha ? sizeof(double) * K13 : (op ? sizeof(Segment) : 0)), 0);
+  s.upload_stream = st;
+  char *up = s.upload.data();
+  std::memcpy(up + L.slotdev, &h, sizeof(SlotDev));
+  std::memcpy(up + L.state, &init, sizeof(CgState));
+  double *ch = (double *)(up + L.charges);
+  for (int j = 0; j < h.N; ++j) {
+    ch[4 * j] = d.pos[3 * j];
+    ch[4 * j + 1] = d.pos[3 * j + 1];
+    ch[4 * j + 2] = d.pos[3 * j + 2];
+    ch[4 * j + 3] = d.q[j];
   }
-  // the host vectors above are released at return: wait for the copies
-  SHH_HIP(hipStreamSynchronize(st));
+  if (d.alpha) {
+    std::memcpy(up + L.alpha, d.alpha, sizeof(double) * K13);
+  } else if (op) {
+    static_assert(sizeof(Segment) <= 8 * sizeof(double), "fits the weights of the smallest K");
+    Segment g;
+    std::memset(&g, 0, sizeof(g));
+    g.slot = s.d_slot;
+    g.nrhs = op->nrhs;
+    for (int r = 0; r < op->nrhs; ++r) g.rhs[r] = r;
+    g.flag = op->flag;
+    g.nblocks = h.ntiles[op->tiling] * op->nrhs;
+    std::memcpy(up + L.alpha, &g, sizeof(g));
+  }
+  SHH_HIP(hipMemcpyAsync(base, up, s.upload.size(), hipMemcpyHostToDevice, st));
   return SHH_OK;
 }
 
-int slot_setup_field(Slot &s, double *beta_out, hipStream_t st) {
+int slot_setup_field(Slot &s, double *beta_out, hipStream_t st, bool solve) {
   const SlotDev &h = s.host;
   SHH_HIP(launch_field(s.d_slot, h.n, h.nb, (long long)NRHS * h.maxparts * PSTRIDE, st));
   if (h.mode_t == 1) {
@@ -352,7 +402,7 @@ int slot_setup_field(Slot &s, double *beta_out, hipStream_t st) {
     SHH_HIP(launch_bisect_steps(s.d_slot, h.nn, 200, st));
   }
   SHH_HIP(launch_occupancy(s.d_slot, h.nn, beta_out, st));
-  SHH_HIP(launch_dinv(s.d_slot, h.nn, h.prec, st));
+  if (solve) SHH_HIP(launch_dinv(s.d_slot, h.nn, h.prec, st));
   return SHH_OK;
 }
 

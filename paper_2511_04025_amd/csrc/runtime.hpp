@@ -64,7 +64,19 @@ struct Slot {
   bool mg_keep_dir = false;     // ... or, after a residual replacement, p = z + beta p
   int sel_active_nodes = 0;     // selective solve: active nodes
   std::shared_ptr<SelHost> sel; // selective solve: descriptor and progress between steps
+  int polled_at = 0;            // next_poll: iterations and log(residual / rtol) at the last look
+  double polled_log = 0.0;
   bool timing = true;           // launch timing allowed (false: the no-allocation entry point)
+  // host image of the slot's parameter block, read by the upload's copy until
+  // the stream has been waited for (the destructor waits if nothing else did)
+  std::vector<char> upload;
+  hipStream_t upload_stream = nullptr;
+  Slot() = default;
+  Slot(const Slot &) = delete;
+  Slot &operator=(const Slot &) = delete;
+  ~Slot() {
+    if (!upload.empty()) (void)hipStreamSynchronize(upload_stream);
+  }
 };
 
 // the culled solve of Sec. 4.2 (either preconditioner)
@@ -79,6 +91,7 @@ void sym_image(int g, const double *p, double *v);
 void sym_fold(int g, const double *gv, double *gp);
 int charge_count(const shh_design *d);
 int normalize_opts(const shh_opts *in, shh_opts *out);
+int next_poll(const std::vector<Slot *> &slots, int fixed);
 Layout make_layout(int n, int N, int K, int prec, bool save, bool vectors = true, int solver = 0);
 // bytes of the multigrid region of an n^3 slot (levels >= 1, coarsest inverse, descriptors)
 size_t mg_region_bytes(int n, int prec);
@@ -105,10 +118,18 @@ int mg_vcycle_coarse(const std::vector<Slot *> &slots, hipStream_t st);
 int mg_apply_level(Slot &s, int l, const void *d_v, void *d_q, hipStream_t st);
 void copy_design(const shh_design *src, DesignCopy &dst);
 
-// Fill the slot descriptor for a region and upload it (+ charges, alpha, zeroed state).
-int slot_init(Slot &s, char *base, hipStream_t st);
-// Field, distance, thickness, occupancy, Jacobi diagonal (steps 1-2).
-int slot_setup_field(Slot &s, double *beta_out, hipStream_t st);
+// Fill the slot descriptor for a region and upload it (+ charges, alpha, zeroed
+// state) in one copy that the caller need not wait for; `adjust` may change the
+// descriptor first.  An operator call's one launch segment goes along, in the
+// place of the spectral weights (which such a slot does not have).
+struct OperatorSegment {
+  int tiling, nrhs, flag;
+};
+int slot_init(Slot &s, char *base, hipStream_t st, const std::function<void(SlotDev &)> &adjust = nullptr,
+              const OperatorSegment *op = nullptr);
+// Field, distance, thickness, occupancy (steps 1-2) and, for a solve, the
+// Jacobi diagonal.
+int slot_setup_field(Slot &s, double *beta_out, hipStream_t st, bool solve = true);
 // Moduli given directly instead of steps 1-2 (e_dtype as SHH_EDTYPE_*; Es, Ev
 // the solid and void moduli of the byte code).
 int slot_setup_moduli(Slot &s, const void *d_E, int e_dtype, double Es, double Ev, hipStream_t st);

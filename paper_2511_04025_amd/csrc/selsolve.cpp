@@ -503,7 +503,7 @@ int sel_step(const std::vector<Slot *> &in, int iters, hipStream_t st) {
   // from a restart, at most 8 times); a slot past the iteration guard stops
   std::vector<Slot *> check, done;
   for (Slot *s : live) {
-    const long long guard = 4LL * s->opts.max_iter + 64LL * std::max(1, s->opts.check_every) + 1024;
+    const long long guard = 4LL * s->opts.max_iter + 64LL * std::max(16, s->opts.check_every) + 1024;
     if (all_stopped(s->state) || H(s).launched > guard) check.push_back(s);
   }
   if (!check.empty()) {
@@ -513,7 +513,7 @@ int sel_step(const std::vector<Slot *> &in, int iters, hipStream_t st) {
     for (Slot *s : check) {
       SelHost &x = H(s);
       ++x.finals;
-      const long long guard = 4LL * s->opts.max_iter + 64LL * std::max(1, s->opts.check_every) + 1024;
+      const long long guard = 4LL * s->opts.max_iter + 64LL * std::max(16, s->opts.check_every) + 1024;
       if (all_stopped(s->state) || x.finals >= 8 || x.launched > guard) {
         done.push_back(s);
         continue;
@@ -567,7 +567,7 @@ int sel_solve(const std::vector<Slot *> &all, hipStream_t st) {
     for (Slot *s : all)
       if (!s->sel->done) live.push_back(s);
     if (live.empty()) return SHH_OK;
-    if ((rc = sel_step(live, std::max(1, live[0]->opts.check_every), st))) return rc;
+    if ((rc = sel_step(live, next_poll(live, live[0]->opts.check_every), st))) return rc;
   }
 }
 

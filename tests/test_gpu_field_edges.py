@@ -1,0 +1,99 @@
+"""Field, order-statistic, point and given-moduli kernels at the sizes where
+they can go wrong: every truncation order, grids below and just past a tile,
+ranks at both ends, many equal distances, point counts around a workgroup."""
+import numpy as np
+import pytest
+
+from gpu_helpers import torch
+from oracle import field as fld
+from paper_2511_04025_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+# FP64 sums of at most 13^3 terms per charge: 1e-12 of the largest value, as the
+# existing comparisons with the oracle
+@pytest.mark.parametrize("K,n", [(1, 2), (2, 3), (3, 17), (3, 64), (4, 16), (5, 33), (6, 15), (6, 65)])
+def test_field_every_order(K, n):
+    from paper_2511_04025_amd import api
+    rng = np.random.default_rng(100 * K + n)
+    d = wl.random_design(40 + K, n, N=5 + 60 * (n == 17), vf=0.3).with_(K=K, alpha=rng.uniform(0.5, 1.5, (K + 1,) * 3))
+    print(f"field K {K} n {n}", flush=True)
+    r = api.field(d)
+    F, G = fld.field_and_gradient(d.pos, d.q, n, K=K, alpha=d.alpha)
+    assert np.max(np.abs(r["F"].cpu().numpy().ravel() - np.ravel(F))) <= 1e-12 * np.abs(F).max()
+    pts = (np.stack(np.meshgrid(*[np.arange(n)] * 3, indexing="ij"), -1).reshape(-1, 3)[:, ::-1] + 0.5) / n
+    Fp, Gp = api.field_points(d, pts[:777].copy(), gradient=True)
+    m = min(777, n ** 3)
+    assert np.max(np.abs(Fp.cpu().numpy() - r["F"].cpu().numpy().ravel()[:m])) <= 1e-12 * np.abs(F).max()
+    g = r["G"].cpu().numpy().reshape(3, -1)
+    assert np.max(np.abs(Gp.cpu().numpy() - g[:, :m])) <= 1e-12 * np.abs(g).max()
+
+
+@pytest.mark.parametrize("n,vf", [(2, 0.5), (3, 0.99), (17, 1e-5), (17, 0.99999), (16, 0.5), (64, 0.137), (101, 0.05)])
+def test_thickness_is_the_midpoint_of_two_order_statistics(n, vf):
+    # exact: the rule on the distances that the call returns; mirrored charges
+    # make many of them equal
+    from paper_2511_04025_amd import api
+    d = wl.random_design(50 + n, n, N=4, vf=vf).with_(symmetry="mirror" if n == 16 else 0)
+    print(f"thickness n {n} vf {vf}", flush=True)
+    r = api.field(d)
+    s = np.sort(r["d"].cpu().numpy().ravel())
+    k = int(np.floor(vf * n ** 3 + 0.5))
+    t = 0.5 * s[0] if k <= 0 else (2.0 * s[-1] + 1.0 if k >= n ** 3 else 0.5 * (s[k - 1] + s[k]))
+    assert r["t"] == t
+    assert np.array_equal(r["beta"].cpu().numpy(), (r["d"].cpu().numpy() < t).astype(float))
+
+
+@pytest.mark.parametrize("M", [1, 31, 32, 33, 257])
+@pytest.mark.parametrize("K", [2, 3, 4, 6])
+def test_points_around_a_workgroup(M, K):
+    from paper_2511_04025_amd import api
+    d = wl.random_design(60 + K, 8, N=70, vf=0.2).with_(K=K)
+    rng = np.random.default_rng(M)
+    pts, w = rng.random((M, 3)), rng.standard_normal(M)
+    print(f"points {M} K {K}", flush=True)
+    F = api.field_points(d, pts)
+    Fo = fld.field_at_points(pts, d.pos, d.q, K=K)
+    assert np.max(np.abs(F.cpu().numpy() - Fo)) <= 1e-12 * np.abs(Fo).max()
+    # F is linear in q and in alpha: sum_j q_j dL/dq_j = sum alpha dL/dalpha = L
+    dpos, dq, dal = api.field_points_grad(d, pts, w)
+    L = float(w @ Fo)
+    scale = float(np.abs(w) @ np.abs(Fo)) + np.abs(dq).sum() + np.abs(dal).sum()
+    assert abs(dq @ d.q - L) <= 1e-12 * scale and abs(dal.sum() - L) <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("n", [2, 5, 33])
+@pytest.mark.parametrize("dtype", ["uint8", "float32", "float64"])
+def test_given_moduli(n, dtype):
+    # volume fraction and validity from the one pass over the moduli
+    from paper_2511_04025_amd import api
+    rng = np.random.default_rng(n)
+    E = rng.uniform(0.2, 3.0, (n, n, n))
+    E[0, 0, 0] = 0.0
+    print(f"moduli n {n} {dtype}", flush=True)
+    if dtype == "uint8":
+        u = (E > 1.0).astype(np.uint8)
+        r = api.homogenize_field(torch.tensor(u, device="cuda"), 0.3, E_solid=2.0, E_void=0.5, precision="fp64")
+        assert abs(r["V"] - u.mean()) <= 1e-14
+        return
+    Et = torch.tensor(E, dtype=getattr(torch, dtype), device="cuda")
+    r = api.homogenize_field(Et, 0.3, precision="fp64")
+    e = Et.double().cpu().numpy()
+    assert abs(r["V"] - e.mean() / e.max()) <= 1e-14
+    for bad in (torch.zeros_like(Et), -Et, torch.full_like(Et, float("inf"))):
+        with pytest.raises(Exception):
+            api.homogenize_field(bad.contiguous(), 0.3, precision="fp64")
+
+
+def test_operator_refuses_invalid_moduli():
+    from paper_2511_04025_amd import api
+    n = 9
+    p = torch.randn((2, 3, n, n, n), dtype=torch.float64, device="cuda")
+    for v in (0.0, -1.0, float("inf"), float("nan")):
+        E = torch.full((n, n, n), v, dtype=torch.float64, device="cuda")
+        with pytest.raises(Exception):
+            api.apply_stiffness(E, p, 0.3)
+    E = torch.ones((n, n, n), dtype=torch.float64, device="cuda")
+    q = api.apply_stiffness(E, p, 0.3)
+    assert torch.isfinite(q).all()
