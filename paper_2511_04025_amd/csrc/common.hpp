@@ -348,14 +348,14 @@ __device__ __forceinline__ T bload(rsrc_t r, uint32_t voff, uint32_t soff) {
 #define SHH_STORE_AUX 2
 #endif
 
-template <typename T>
+template <typename T, int AUX = SHH_STORE_AUX>
 __device__ __forceinline__ void bstore(T v, rsrc_t r, uint32_t voff, uint32_t soff) {
   static_assert(sizeof(T) == 4 || sizeof(T) == 8, "32- or 64-bit elements");
   if constexpr (sizeof(T) == 4)
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, SHH_STORE_AUX);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, AUX);
   else
     __builtin_amdgcn_raw_buffer_store_b64(
-        __builtin_bit_cast(uint32_t __attribute__((ext_vector_type(2))), v), r, voff, soff, SHH_STORE_AUX);
+        __builtin_bit_cast(uint32_t __attribute__((ext_vector_type(2))), v), r, voff, soff, AUX);
 }
 
 template <typename T>

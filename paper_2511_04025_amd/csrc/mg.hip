@@ -796,19 +796,21 @@ __global__ __launch_bounds__(192) void mg_power_step_kernel(MgBatch B, int step)
   if (l == 0) return;
   const MgLevel &L = B.mg[blockIdx.z]->lv[l];
   const long long nn = L.nn;
-  const T *x = (const T *)(step & 1 ? L.q : L.x);
-  T *xn = (T *)(step & 1 ? L.x : L.q);
+  // a level without a stencil has A x in q already and keeps its vector in x
+  const bool have = l == 1 && B.mg[blockIdx.z]->l1free;
+  const T *x = (const T *)(!have && step & 1 ? L.q : L.x);
+  T *xn = (T *)(have || step & 1 ? L.x : L.q);
   const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool inr = (unsigned)block * 64 + lane < (unsigned)nn;
   const unsigned v = inr ? block * 64 + lane : 0u;
   const T *Dv = (const T *)L.Dinv;
   const bool act[1] = {true};
-  mg_split_sum<T, 1, 3>(L, x, v, g, act, Dv[v] == T(0), part);
+  if (!have) mg_split_sum<T, 1, 3>(L, x, v, g, act, Dv[v] == T(0), part);
   __syncthreads();
   double acc[3] = {0.0, 0.0, 0.0};
   if (inr) {  // wave g finishes component g
     const long long j = g * nn + v;
-    const T qv = mg_split_total<T, 1, 3>(part, g, lane), di = Dv[j];
+    const T qv = have ? ((const T *)L.q)[j] : mg_split_total<T, 1, 3>(part, g, lane), di = Dv[j];
     const double xo = (double)x[j];
     acc[1] = xo * (double)qv;
     acc[2] = di != T(0) ? xo * xo / (double)di : 0.0;
@@ -1047,8 +1049,9 @@ hipError_t mg_launch_stencil(const MgDev *d_mg, int l, long long nn, int prec, h
   return hipGetLastError();
 }
 
-// whether a level takes the two-nodes-per-thread form (the choice is made
-// design by design: its sums run in another order)
+// whether a level takes the large-level form: two nodes per thread, or level 1
+// in mixed precision from the moduli (the choice is made design by design: the
+// sums run in another order)
 bool mg_apply_wide(long long nn) { return nn > 32768; }
 
 namespace {
@@ -1113,7 +1116,7 @@ hipError_t mg_launch_scalar(const MgBatch &B, int phase, hipStream_t st) {
   return hipGetLastError();
 }
 
-// the start vector of level l (l = 1, 2, ... in turn), then `steps` steps of all levels;
+// the start vector of level l (l = 1, 2, ... in turn), then step k of all levels;
 // blocks_max: the most 64-node blocks over a design's levels; levels: the most levels
 hipError_t mg_launch_power_init(const MgBatch &B, int l, long long nn_max, int prec, hipStream_t st) {
   const dim3 g(blocks_for(3 * nn_max, 256), 1, B.count);
@@ -1122,13 +1125,11 @@ hipError_t mg_launch_power_init(const MgBatch &B, int l, long long nn_max, int p
   return hipGetLastError();
 }
 
-hipError_t mg_launch_power(const MgBatch &B, int steps, long long blocks_max, int levels, int prec, hipStream_t st) {
+hipError_t mg_launch_power(const MgBatch &B, int k, long long blocks_max, int levels, int prec, hipStream_t st) {
   const dim3 g((unsigned)blocks_max, 1, B.count), gr((unsigned)levels, 1, B.count);
-  for (int k = 0; k < steps; ++k) {
-    if (prec == 0) mg_power_step_kernel<double><<<g, 192, 0, st>>>(B, k);
-    else mg_power_step_kernel<float><<<g, 192, 0, st>>>(B, k);
-    mg_power_reduce_kernel<<<gr, VEC_THREADS, 0, st>>>(B);
-  }
+  if (prec == 0) mg_power_step_kernel<double><<<g, 192, 0, st>>>(B, k);
+  else mg_power_step_kernel<float><<<g, 192, 0, st>>>(B, k);
+  mg_power_reduce_kernel<<<gr, VEC_THREADS, 0, st>>>(B);
   return hipGetLastError();
 }
 

@@ -35,7 +35,7 @@ struct MgLevel {
   int n;
   int nchunks;          // CHUNK-node chunks of the level (vector kernels)
   long long nn;
-  // levels >= 1: nodal stencil [14 * 9][nn] (block of offset w >= 13, entry (c, c')
+  // levels >= 1 (level 1 not where it runs from the moduli): nodal stencil [14 * 9][nn] (block of offset w >= 13, entry (c, c')
   // at ((w - 13) * 9 + 3 c + c') * nn),
   // inverse diagonal [3][nn]; level 0 uses the slot's matrix-free operator and D^-1 [nn]
   void *S, *Dinv;
@@ -54,6 +54,7 @@ struct MgLevel {
 
 struct MgDev {
   int L;                // index of the coarsest level
+  int l1free;           // level 1 runs from the moduli (mg1.hip), without a stencil
   int ndof_c;           // 3 n_L^3
   void *G;              // [8][24][24] child Galerkin matrices of K_0 (T)
   double *Mc;           // [ndof_c][ndof_c] coarsest inverse (FP64), dof 3 node + c

@@ -32,13 +32,15 @@ hipError_t mg_launch_coarse_inverse(const MgBatch &B, int ndof_max, int prec, hi
 hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, int prec,
                            hipStream_t st, int live, int ep);
 bool mg_apply_wide(long long nn);
+hipError_t mg_launch_l1(const MgBatch &B, int n_max, int nrhs, hipStream_t st, int live, int ep);
+hipError_t mg_launch_l1_diag(const SlotDev *d_slot, const MgDev *d_mg, long long nn, hipStream_t st);
 hipError_t mg_launch_restrict(const MgBatch &B, int l, long long nn_coarse_max, int prec,
                               hipStream_t st);
 hipError_t mg_launch_prolong(const MgBatch &B, int l, long long nn_coarse_max, int prec, hipStream_t st);
 hipError_t mg_launch_coarsest(const MgBatch &B, int ndof_max, int prec, hipStream_t st);
 hipError_t mg_launch_scalar(const MgBatch &B, int phase, hipStream_t st);
 hipError_t mg_launch_power_init(const MgBatch &B, int l, long long nn_max, int prec, hipStream_t st);
-hipError_t mg_launch_power(const MgBatch &B, int steps, long long blocks_max, int levels, int prec, hipStream_t st);
+hipError_t mg_launch_power(const MgBatch &B, int k, long long blocks_max, int levels, int prec, hipStream_t st);
 
 namespace {
 
@@ -57,6 +59,12 @@ constexpr int POWER_ITERS = 30;  // power steps per coarse level
 #ifndef SHH_CHEB_COARSE
 #define SHH_CHEB_COARSE 1.2
 #endif
+
+// From 34^3 nodes level 1 runs from the moduli in FP32 (mg1.hip; the FP64
+// element would not fit the registers); below, its stored stencil stays in the
+// caches and the split passes are faster: 128^3 designs 60.8 -> 55.0 ms, while a
+// 48^3 grid's 24^3 level takes 4 us a pass from the stencil.
+bool level1_free(int prec, long long nn) { return prec == SHH_PREC_MIXED && mg_apply_wide(nn); }
 
 // Lay out the multigrid region at `base` (nullptr: sizing only).  Fills the
 // level descriptors' persistent buffers, G and Mc.
@@ -84,7 +92,7 @@ size_t carve(char *base, int n, int prec, MgDev *mg, char **d_mgdev) {
   for (int l = 1; l < count; ++l) {
     nl /= 2;
     const long long nn = nl * nl * nl;
-    char *S = take(MG_STENCIL * nn * ts);
+    char *S = l == 1 && level1_free(prec, nn) ? nullptr : take(MG_STENCIL * nn * ts);
     char *D = take(3 * nn * ts);
     char *v[5];
     for (int k = 0; k < 5; ++k) v[k] = take((size_t)NRHS * 3 * nn * ts);
@@ -299,15 +307,22 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
     return apply0(smooth, SMG_POST);
   }
   // an operator pass with the Chebyshev sweep after it fused in
-  std::vector<Slot *> by_form[2];  // one launch per form of the operator
-  for (Slot *s : smooth) by_form[mg_apply_wide(s->mg.lv[l].nn)].push_back(s);
+  std::vector<Slot *> by_form[3];  // one launch per form of the operator
+  for (Slot *s : smooth)
+    by_form[l == 1 && s->mg.l1free ? 2 : int(mg_apply_wide(s->mg.lv[l].nn))].push_back(s);
   auto app = [&](int ep) -> int {
     if ((rc = tb(l == 1))) return rc;
-    for (int w = 0; w < 2; ++w) {
+    for (int w = 0; w < 3; ++w) {
       if (by_form[w].empty()) continue;
+      const MgBatch Bw = batch_of(by_form[w]);
       long long nn = 0;
-      for (Slot *s : by_form[w]) nn = std::max(nn, s->mg.lv[l].nn);
-      SHH_HIP(mg_launch_apply(batch_of(by_form[w]), l, 0, nn, w == 1, prec, st, 1, ep));
+      int n = 0;
+      for (Slot *s : by_form[w]) {
+        nn = std::max(nn, s->mg.lv[l].nn);
+        n = std::max(n, s->mg.lv[l].n);
+      }
+      if (w == 2) SHH_HIP(mg_launch_l1(Bw, n, NRHS, st, 1, ep));
+      else SHH_HIP(mg_launch_apply(Bw, l, 0, nn, w == 1, prec, st, 1, ep));
     }
     return te(SHH_PROF_MG_APPLY1);
   };
@@ -372,12 +387,14 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
   // Chebyshev bound (host work of about 1 ms, kept per element operator)
   std::vector<double> G;
   nu_constants(h.kop64, bound0, G);
+  mg.l1free = level1_free(prec, mg.lv[1].nn);
   int rc;
   if ((rc = upload(G, mg.G, prec, st))) return rc;
   SHH_HIP(hipMemcpyAsync(s.d_mg, &mg, sizeof(MgDev), hipMemcpyHostToDevice, st));
   SHH_HIP(mg_launch_elem1(s.d_slot, s.d_mg, mg.lv[1].nn, prec, st));
   for (int l = 1; l + 1 < count; ++l) SHH_HIP(mg_launch_elemc(s.d_mg, l, mg.lv[l + 1].nn, prec, st));
-  for (int l = 1; l < count; ++l) SHH_HIP(mg_launch_stencil(s.d_mg, l, mg.lv[l].nn, prec, st));
+  if (mg.l1free) SHH_HIP(mg_launch_l1_diag(s.d_slot, s.d_mg, mg.lv[1].nn, st));
+  for (int l = mg.l1free ? 2 : 1; l < count; ++l) SHH_HIP(mg_launch_stencil(s.d_mg, l, mg.lv[l].nn, prec, st));
   return SHH_OK;  // the coarsest inverse follows, batched over the slots (mg_setup)
 }
 
@@ -476,7 +493,17 @@ int mg_setup(const std::vector<Slot *> &all, hipStream_t st, std::vector<int> *r
         if (s->mg.L > l) nn = std::max(nn, s->mg.lv[l].nn);
       if (nn > 0) SHH_HIP(mg_launch_power_init(B, l, nn, prec, st));
     }
-    SHH_HIP(mg_launch_power(B, POWER_ITERS, blocks_max, max_l - 1, prec, st));
+    std::vector<Slot *> l1;
+    int n1 = 0;
+    for (Slot *s : part)
+      if (s->mg.l1free) {
+        l1.push_back(s);
+        n1 = std::max(n1, s->mg.lv[1].n);
+      }
+    for (int k = 0; k < POWER_ITERS; ++k) {
+      if (!l1.empty()) SHH_HIP(mg_launch_l1(batch_of(l1), n1, 1, st, 0, MGE_NONE));
+      SHH_HIP(mg_launch_power(B, k, blocks_max, max_l - 1, prec, st));
+    }
   }
   std::vector<MgDev> est(slots.size());
   for (size_t i = 0; i < slots.size(); ++i)
@@ -509,7 +536,8 @@ int mg_apply_level(Slot &s, int l, const void *d_v, void *d_q, hipStream_t st) {
   const size_t bytes = (size_t)NRHS * 3 * L.nn * (s.host.prec == SHH_PREC_FP64 ? 8 : 4);
   SHH_HIP(hipMemcpyAsync(L.x, d_v, bytes, hipMemcpyDeviceToDevice, st));
   // (the odd coarsest level is small: never the two-nodes-per-thread form)
-  SHH_HIP(mg_launch_apply(batch_of({&s}), l, 0, L.nn, mg_apply_wide(L.nn), s.host.prec, st, 0, MGE_NONE));
+  if (l == 1 && s.mg.l1free) SHH_HIP(mg_launch_l1(batch_of({&s}), L.n, NRHS, st, 0, MGE_NONE));
+  else SHH_HIP(mg_launch_apply(batch_of({&s}), l, 0, L.nn, mg_apply_wide(L.nn), s.host.prec, st, 0, MGE_NONE));
   SHH_HIP(hipMemcpyAsync(d_q, L.q, bytes, hipMemcpyDeviceToDevice, st));
   SHH_HIP(hipStreamSynchronize(st));
   return SHH_OK;

@@ -65,3 +65,22 @@ def test_coarsest_inverse_block_edges(n):
     assert mg["status"] == 0 and ja["status"] == 0
     assert_ch_close(mg["C"], ja["C"], 1e-7)
     assert abs(int(mg["iters"].max()) - INVERSE[n]) <= 1
+
+
+@pytest.mark.parametrize("n", [80, 96, 112, 128, 160])
+def test_level_one_from_moduli_matches_the_stored_stencil(n):
+    # coarse grids of 40^3 to 80^3: both tile shapes, with and without a
+    # remainder in x, y and z.  FP64 keeps the stored stencil (held to the
+    # oracle's Galerkin product elsewhere); in FP32 a row sums 8 elements of 24
+    # terms after two 3-level transforms, at most ~100 roundings of 6e-8 of the
+    # largest term
+    import torch
+    from paper_2511_04025_amd import api
+    m = n // 2
+    g = torch.Generator(device="cuda").manual_seed(n)
+    E = torch.where(torch.rand(n, n, n, device="cuda", generator=g) < 0.3, 1.0, 1e-3).double()
+    V = torch.randn(6, 3, m, m, m, device="cuda", generator=g)
+    print(f"level one {n}^3", flush=True)
+    ref = api.mg_operator(E, V.double(), 0.3, 1, "fp64")
+    got = api.mg_operator(E, V, 0.3, 1, "mixed").double()
+    assert float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
