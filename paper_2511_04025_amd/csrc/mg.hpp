@@ -35,9 +35,9 @@ struct MgLevel {
   int n;
   int nchunks;          // CHUNK-node chunks of the level (vector kernels)
   long long nn;
-  // levels >= 1 (level 1 not where it runs from the moduli): nodal stencil [14 * 9][nn] (block of offset w >= 13, entry (c, c')
-  // at ((w - 13) * 9 + 3 c + c') * nn),
-  // inverse diagonal [3][nn]; level 0 uses the slot's matrix-free operator and D^-1 [nn]
+  // levels >= 1: nodal stencil [14 * 9][nn] (block of offset w >= 13, entry
+  // (c, c') at ((w - 13) * 9 + 3 c + c') * nn; none on level 1 where it runs
+  // from the moduli), inverse diagonal [3][nn]; level 0 uses the slot's matrix-free operator and D^-1 [nn]
   void *S, *Dinv;
   // V-cycle vectors [NRHS][3][nn]: right-hand side, iterate, residual,
   // Chebyshev direction, operator output (on levels >= 1 the fused sweeps
@@ -55,6 +55,7 @@ struct MgLevel {
 struct MgDev {
   int L;                // index of the coarsest level
   int l1free;           // level 1 runs from the moduli (mg1.hip), without a stencil
+  int tail;             // level run with the coarsest one in a single launch (mgtail.hip), or -1
   int ndof_c;           // 3 n_L^3
   void *G;              // [8][24][24] child Galerkin matrices of K_0 (T)
   double *Mc;           // [ndof_c][ndof_c] coarsest inverse (FP64), dof 3 node + c

@@ -33,6 +33,8 @@ hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, b
                            hipStream_t st, int live, int ep);
 bool mg_apply_wide(long long nn);
 hipError_t mg_launch_l1(const MgBatch &B, int n_max, int nrhs, hipStream_t st, int live, int ep);
+int mg_tail_level(int coarsest, int n_last);
+hipError_t mg_launch_tail(const MgBatch &B, int l, int prec, hipStream_t st);
 hipError_t mg_launch_l1_diag(const SlotDev *d_slot, const MgDev *d_mg, long long nn, hipStream_t st);
 hipError_t mg_launch_restrict(const MgBatch &B, int l, long long nn_coarse_max, int prec,
                               hipStream_t st);
@@ -278,8 +280,13 @@ MgBatch batch_of(const std::vector<Slot *> &slots) {
 // levels; slots whose coarsest level is l take the dense solve there.
 int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *timer, const MgApply0 &apply0) {
   const int prec = slots[0]->host.prec;
-  std::vector<Slot *> coarse, smooth;
-  for (Slot *s : slots) (s->mg.L == l ? coarse : smooth).push_back(s);
+  std::vector<Slot *> coarse, smooth, tail;
+  for (Slot *s : slots) {
+    if (s->mg.L == l) coarse.push_back(s);
+    else if (s->mg.tail == l) tail.push_back(s);
+    else smooth.push_back(s);
+  }
+  if (!tail.empty()) SHH_HIP(mg_launch_tail(batch_of(tail), l, prec, st));
   if (!coarse.empty()) {
     int nd = 0;
     for (Slot *s : coarse) nd = std::max(nd, s->mg.ndof_c);
@@ -329,10 +336,15 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
   // pre-smoother (the restriction to this level left its first direction in d);
   // its second pass leaves r - A d1, the residual to restrict, in r
   if ((rc = app(MGE_STEP1)) || (rc = app(MGE_RES))) return rc;
-  // coarse-grid correction
-  SHH_HIP(mg_launch_restrict(B, l, nn_next_max, prec, st));
+  // coarse-grid correction (a tail below this level restricts and prolongs
+  // by itself)
+  std::vector<Slot *> step;
+  for (Slot *s : smooth)
+    if (s->mg.tail != l + 1) step.push_back(s);
+  const MgBatch Bs = batch_of(step);
+  if (!step.empty()) SHH_HIP(mg_launch_restrict(Bs, l, nn_next_max, prec, st));
   if ((rc = vcycle(smooth, l + 1, st, timer, apply0))) return rc;
-  SHH_HIP(mg_launch_prolong(B, l, nn_next_max, prec, st));
+  if (!step.empty()) SHH_HIP(mg_launch_prolong(Bs, l, nn_next_max, prec, st));
   // post-smoother
   if ((rc = app(MGE_POST)) || (rc = app(MGE_LAST))) return rc;
   return SHH_OK;
@@ -388,6 +400,7 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
   std::vector<double> G;
   nu_constants(h.kop64, bound0, G);
   mg.l1free = level1_free(prec, mg.lv[1].nn);
+  mg.tail = mg_tail_level(mg.L, mg.lv[mg.L - 1].n);
   int rc;
   if ((rc = upload(G, mg.G, prec, st))) return rc;
   SHH_HIP(hipMemcpyAsync(s.d_mg, &mg, sizeof(MgDev), hipMemcpyHostToDevice, st));

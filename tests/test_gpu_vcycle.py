@@ -84,3 +84,19 @@ def test_level_one_from_moduli_matches_the_stored_stencil(n):
     ref = api.mg_operator(E, V.double(), 0.3, 1, "fp64")
     got = api.mg_operator(E, V, 0.3, 1, "mixed").double()
     assert float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("precision,rtol", [("fp64", 1e-10), ("mixed", 3e-6)])
+@pytest.mark.parametrize("solver", ["mg", "selective"])
+@pytest.mark.parametrize("n", [12, 24, 48])
+def test_last_levels_in_one_launch(n, solver, precision, rtol):
+    # 3 x 2^k grids: the 6^3 and 3^3 levels run in one launch, as level 1 (fed
+    # and read by the voxel level, 12^3) or below it; the V-cycle must stay a
+    # symmetric preconditioner that converges to the Jacobi solution
+    from paper_2511_04025_amd import api
+    d = wl.random_design(7200 + n, n, N=12, vf=0.25, E_void=0.0 if solver != "mg" else 1e-2)
+    print(f"last levels {n}^3 {solver} {precision}", flush=True)
+    mg = api.homogenize(d, precision=precision, rtol=rtol, solver=solver)
+    ja = api.homogenize(d, precision="fp64", rtol=1e-10, solver="selective-jacobi" if solver != "mg" else "jacobi")
+    assert mg["status"] == 0 and ja["status"] == 0
+    assert_ch_close(mg["C"], ja["C"], 1e-7 if precision == "fp64" else 1e-4)
