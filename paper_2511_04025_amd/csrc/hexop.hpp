@@ -82,6 +82,23 @@ __device__ __forceinline__ void add_chi(int k, T (&h)[3][8]) {
   }
 }
 
+// The same for a load case known at run time: nine additions (of zero but for
+// one or two).  The switch above keeps h in memory then (64 bytes of scratch a
+// thread in the residual pass).
+template <typename T>
+__device__ __forceinline__ void add_chi_any(int k, T (&h)[3][8]) {
+  const T d23 = k == 3 ? T(2) : T(0), d13 = k == 4 ? T(2) : T(0), d12 = k == 5 ? T(2) : T(0);
+  h[0][1] += k == 0 ? T(4) : T(0);
+  h[1][2] += k == 1 ? T(4) : T(0);
+  h[2][4] += k == 2 ? T(4) : T(0);
+  h[1][4] += d23;
+  h[2][2] += d23;
+  h[0][4] += d13;
+  h[2][1] += d13;
+  h[0][2] += d12;
+  h[1][1] += d12;
+}
+
 // 8-point Hadamard transform of corner values v[a], a = ax | ay << 1 | az << 2:
 // out[m] = sum_a prod_axis (s ? 1 : 2 a_axis - 1) v[a]
 template <typename T>

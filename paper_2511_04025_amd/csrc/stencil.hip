@@ -577,7 +577,7 @@ void stencil_kernel(LaunchArgs la) {
 #pragma unroll
         for (int m = 0; m < 4; ++m) h[c][m + 4] = An[c][m] - A[c][m];
       }
-      if constexpr (MODE == MODE_RESID) add_chi<TC>(rhs, h);
+      if constexpr (MODE == MODE_RESID) add_chi_any<TC>(rhs, h);
       // lower node plane kk: this layer's lower half completes the upper half
       // carried from the layer below (Bc); its four x-y corners go to LDS
       // (y[c][0] == 0)
