@@ -10,33 +10,35 @@ namespace shh {
 // setup
 // ---------------------------------------------------------------------------
 
+// Element matrices are kept entry by entry ([24][24][elements]: neighbouring
+// threads, which hold neighbouring elements, read and write neighbouring
+// words) and formed row by row (grid y).  The 128^3 hierarchy takes 0.17 ms in
+// these kernels and 0.03 in the stencils; with the matrices one after the other
+// and the stencil summed in memory it took 1.16 and 0.40.
+
 // Level-1 element matrices: K_E = sum_f E_f G_f over the 8 voxels of coarse
-// element E.  One thread per (element, row).
+// element E.
 template <typename T>
 __global__ __launch_bounds__(256) void mg_elem1_kernel(const SlotDev *s, const MgDev *mg) {
   const MgLevel &c = mg->lv[1];
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= c.nn * 24) return;
-  const long long E = t / 24;
-  const int i = int(t % 24);
-  const int nc = c.n, nf = s->n;
-  const int X = int(E % nc), Y = int((E / nc) % nc), Z = int(E / ((long long)nc * nc));
+  const unsigned E = blockIdx.x * 256 + threadIdx.x;
+  if (E >= (unsigned)c.nn) return;
+  const int i = blockIdx.y, nc = c.n, nf = s->n;
+  const int X = int(E % nc), Y = int((E / nc) % nc), Z = int(E / ((unsigned)nc * nc));
   const double *Ef = s->E64;
-  const T *G = (const T *)mg->G;
+  const T *G = (const T *)mg->G + i * 24;
   double row[24];
 #pragma unroll
   for (int j = 0; j < 24; ++j) row[j] = 0.0;
   for (int f = 0; f < 8; ++f) {
     const int fx = f & 1, fy = (f >> 1) & 1, fz = f >> 2;
-    const long long fe = ((long long)(2 * Z + fz) * nf + (2 * Y + fy)) * nf + (2 * X + fx);
-    const double e = Ef[fe];
-    const T *g = G + (f * 24 + i) * 24;
+    const double e = Ef[((long long)(2 * Z + fz) * nf + (2 * Y + fy)) * nf + (2 * X + fx)];
 #pragma unroll
-    for (int j = 0; j < 24; ++j) row[j] += e * (double)g[j];
+    for (int j = 0; j < 24; ++j) row[j] += e * (double)G[f * 576 + j];
   }
-  T *K = (T *)c.Ke + E * 576 + i * 24;
+  T *K = (T *)c.Ke + (long long)i * 24 * c.nn + E;
 #pragma unroll
-  for (int j = 0; j < 24; ++j) K[j] = (T)row[j];
+  for (int j = 0; j < 24; ++j) K[j * c.nn] = (T)row[j];
 }
 
 // Trilinear weight of coarse corner a at fine corner b of child f (per axis:
@@ -53,86 +55,140 @@ __device__ __forceinline__ double qweight(int f, int b, int a) {
   return w;
 }
 
-// Level l + 1 element matrices from level l: K_E = sum_f Q_f^T K_f Q_f.
-// One thread per (coarse element, row i = 3 a + c).
+// G2[f] = Q_f2^T G_f1 Q_f2 for the 64 voxels f = 4 (4 z + y) + x of a level-2
+// element (child f2 of it, child f1 of that one), FP64.
+template <typename T>
+__global__ __launch_bounds__(192) void mg_g2_kernel(const MgDev *mg) {
+  const int f = blockIdx.x, x = f & 3, y = (f >> 2) & 3, z = f >> 4;
+  const int f1 = (x & 1) | ((y & 1) << 1) | ((z & 1) << 2), f2 = (x >> 1) | ((y >> 1) << 1) | ((z >> 1) << 2);
+  const T *G = (const T *)mg->G + f1 * 576;
+  for (int t = threadIdx.x; t < 576; t += 192) {
+    const int i = t / 24, j = t % 24, a = i / 3, ci = i % 3, ap = j / 3, cj = j % 3;
+    double sum = 0.0;
+    for (int b = 0; b < 8; ++b) {
+      const double qa = qweight(f2, b, a);
+      if (qa == 0.0) continue;
+      for (int bp = 0; bp < 8; ++bp) sum += qa * qweight(f2, bp, ap) * (double)G[(3 * b + ci) * 24 + 3 * bp + cj];
+    }
+    mg->G2[f * 576 + t] = sum;
+  }
+}
+
+// Level-2 element matrices from the 64 voxels of an element, where level 1 keeps
+// no element matrices (it runs from the moduli).
+template <typename T>
+__global__ __launch_bounds__(256) void mg_elem2_kernel(const SlotDev *s, const MgDev *mg) {
+  const MgLevel &c = mg->lv[2];
+  const unsigned E = blockIdx.x * 256 + threadIdx.x;
+  if (E >= (unsigned)c.nn) return;
+  const int i = blockIdx.y, nc = c.n, nf = s->n;
+  const int X = int(E % nc), Y = int((E / nc) % nc), Z = int(E / ((unsigned)nc * nc));
+  const SHH_CONST double *G2 = to_const((const double *)mg->G2) + i * 24;
+  double row[24];
+#pragma unroll
+  for (int j = 0; j < 24; ++j) row[j] = 0.0;
+  for (int yz = 0; yz < 16; ++yz) {
+    const double *Ef = s->E64 + ((long long)(4 * Z + (yz >> 2)) * nf + 4 * Y + (yz & 3)) * nf + 4 * X;
+    double e[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) e[k] = Ef[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int j = 0; j < 24; ++j) row[j] += e[k] * G2[(4 * yz + k) * 576 + j];
+  }
+  T *K = (T *)c.Ke + (long long)i * 24 * c.nn + E;
+#pragma unroll
+  for (int j = 0; j < 24; ++j) K[j * c.nn] = (T)row[j];
+}
+
+// Level l + 1 element matrices from level l: K_E = sum_f Q_f^T K_f Q_f.  Eight
+// lanes share a row, one child each (one thread per row took 300 us at 16^3:
+// 648 loads in turn).
 template <typename T>
 __global__ __launch_bounds__(256) void mg_elemc_kernel(const MgDev *mg, int l) {
   const MgLevel &fl = mg->lv[l];
   const MgLevel &cl = mg->lv[l + 1];
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= cl.nn * 24) return;
-  const long long E = t / 24;
-  const int i = int(t % 24);
-  const int a = i / 3, ci = i % 3;
+  const unsigned t = blockIdx.x * 256 + threadIdx.x, E = t >> 3;
+  const int f = t & 7;
+  if (E >= (unsigned)cl.nn) return;  // all eight lanes of an element or none
+  const int i = blockIdx.y, a = i / 3, ci = i % 3;
   const int nc = cl.n, nf = fl.n;
-  const int X = int(E % nc), Y = int((E / nc) % nc), Z = int(E / ((long long)nc * nc));
-  const T *Kf = (const T *)fl.Ke;
-  double row[24];
+  const int X = int(E % nc), Y = int((E / nc) % nc), Z = int(E / ((unsigned)nc * nc));
+  const long long fnn = fl.nn, cnn = cl.nn;
+  const T *K = (const T *)fl.Ke + ((long long)(2 * Z + (f >> 2)) * nf + (2 * Y + ((f >> 1) & 1))) * nf + (2 * X + (f & 1));
+  // w = Q_f[:, i]^T K_f: rows 3 b' + ci of K_f weighted by q(f, b', a)
+  double w[24];
 #pragma unroll
-  for (int j = 0; j < 24; ++j) row[j] = 0.0;
-  for (int f = 0; f < 8; ++f) {
-    const int fx = f & 1, fy = (f >> 1) & 1, fz = f >> 2;
-    const long long fe = ((long long)(2 * Z + fz) * nf + (2 * Y + fy)) * nf + (2 * X + fx);
-    const T *K = Kf + fe * 576;
-    // w = Q_f[:, i]^T K_f: rows 3 b' + ci of K_f weighted by q(f, b', a)
-    double w[24];
+  for (int j = 0; j < 24; ++j) w[j] = 0.0;
+  for (int bp = 0; bp < 8; ++bp) {
+    const double q = qweight(f, bp, a);
+    if (q == 0.0) continue;
+    const T *kr = K + (3 * bp + ci) * 24 * fnn;
 #pragma unroll
-    for (int j = 0; j < 24; ++j) w[j] = 0.0;
-    for (int bp = 0; bp < 8; ++bp) {
-      const double q = qweight(f, bp, a);
-      if (q == 0.0) continue;
-      const T *kr = K + (3 * bp + ci) * 24;
+    for (int j = 0; j < 24; ++j) w[j] += q * (double)kr[j * fnn];
+  }
+  // row = w Q_f: column 3 a' + c sums w[3 b + c] q(f, b, a'); then over the children
+  T *out = (T *)cl.Ke + (long long)i * 24 * cnn + E;
 #pragma unroll
-      for (int j = 0; j < 24; ++j) w[j] += q * (double)kr[j];
+  for (int ap = 0; ap < 8; ++ap) {
+    double row[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const double q = qweight(f, b, ap);
+#pragma unroll
+      for (int cc = 0; cc < 3; ++cc) row[cc] += q * w[3 * b + cc];
     }
-    // row += w Q_f: column 3 a' + c of the result sums w[3 b + c] q(f, b, a')
-    for (int ap = 0; ap < 8; ++ap) {
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const double q = qweight(f, b, ap);
+    for (int cc = 0; cc < 3; ++cc) {
 #pragma unroll
-        for (int cc = 0; cc < 3; ++cc) row[3 * ap + cc] += q * w[3 * b + cc];
-      }
+      for (int off = 1; off < 8; off <<= 1) row[cc] += __shfl_xor(row[cc], off, 64);
+      if (f == ap) out[(3 * ap + cc) * cnn] = (T)row[cc];
     }
   }
-  T *out = (T *)cl.Ke + E * 576 + i * 24;
-#pragma unroll
-  for (int j = 0; j < 24; ++j) out[j] = (T)row[j];
 }
 
 // Nodal stencil of level l from its element matrices (the 14 stored offsets),
 // and D^-1.  Node v is corner a of element v - a; entry (v, v - a + b)
-// gathers K_e[a][b].
+// gathers K_e[a][b].  One thread per (node, stored offset: grid y); the
+// corners a that have a corner b = a + offset in their element add up.
 template <typename T>
 __global__ __launch_bounds__(256) void mg_stencil_kernel(const MgDev *mg, int l) {
   const MgLevel &L = mg->lv[l];
-  const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= L.nn) return;
-  const int n = L.n;
-  const int x = int(v % n), y = int((v / n) % n), z = int(v / ((long long)n * n));
+  const unsigned v = blockIdx.x * 256 + threadIdx.x;
+  if (v >= (unsigned)L.nn) return;
+  const int n = L.n, k = blockIdx.y, w = 13 + k;
+  const long long nn = L.nn;
+  const int dz = w / 9 - 1, dy = (w / 3) % 3 - 1, dx = w % 3 - 1;
+  const int x = int(v % n), y = int((v / n) % n), z = int(v / ((unsigned)n * n));
   const T *Ke = (const T *)L.Ke;
-  T *S = (T *)L.S;
-  for (int k = 0; k < MG_STENCIL; ++k) S[k * L.nn + v] = T(0);
+  T acc[9];
+#pragma unroll
+  for (int e = 0; e < 9; ++e) acc[e] = T(0);
   double diag[3] = {0.0, 0.0, 0.0};
   for (int a = 0; a < 8; ++a) {
     const int ax = a & 1, ay = (a >> 1) & 1, az = a >> 2;
-    const long long e = ((long long)wrapi(z - az, n) * n + wrapi(y - ay, n)) * n + wrapi(x - ax, n);
-    const T *K = Ke + e * 576;
-    for (int b = 0; b < 8; ++b) {
-      const int bx = b & 1, by = (b >> 1) & 1, bz = b >> 2;
-      const int w = ((bz - az + 1) * 3 + (by - ay + 1)) * 3 + (bx - ax + 1);
-      if (w < 13) continue;  // stored by the neighbour, transposed
-      for (int c = 0; c < 3; ++c)
-        for (int cp = 0; cp < 3; ++cp) {
-          const T kv = K[(3 * a + c) * 24 + 3 * b + cp];
-          T *dst = S + ((w - 13) * 9 + 3 * c + cp) * L.nn + v;
-          *dst = *dst + kv;
-          if (b == a && cp == c) diag[c] += (double)kv;
-        }
-    }
+    const int bx = ax + dx, by = ay + dy, bz = az + dz;
+    if ((bx | by | bz) & ~1) continue;  // each is 0 or 1
+    const int b = bx | (by << 1) | (bz << 2);
+    const T *K = Ke + (3 * a * 24 + 3 * b) * nn + ((long long)wrapi(z - az, n) * n + wrapi(y - ay, n)) * n +
+                 wrapi(x - ax, n);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int cp = 0; cp < 3; ++cp) {
+        const T kv = K[(c * 24 + cp) * nn];
+        acc[3 * c + cp] += kv;
+        if (cp == c) diag[c] += (double)kv;
+      }
   }
+  T *S = (T *)L.S + (long long)k * 9 * nn + v;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) S[e * nn] = acc[e];
+  if (k != 0) return;
   T *Dinv = (T *)L.Dinv;
-  for (int c = 0; c < 3; ++c) Dinv[c * L.nn + v] = diag[c] > 0.0 ? (T)(1.0 / diag[c]) : T(0);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) Dinv[c * nn + v] = diag[c] > 0.0 ? (T)(1.0 / diag[c]) : T(0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1012,14 +1068,21 @@ __global__ __launch_bounds__(256) void mg_inv_update_kernel(MgBatch B, int k) {
 static unsigned blocks_for(long long count, int per) { return (unsigned)((count + per - 1) / per); }
 
 hipError_t mg_launch_elem1(const SlotDev *d_slot, const MgDev *d_mg, long long nn1, int prec, hipStream_t st) {
-  const unsigned g = blocks_for(nn1 * 24, 256);
+  const dim3 g(blocks_for(nn1, 256), 24);
   if (prec == 0) mg_elem1_kernel<double><<<g, 256, 0, st>>>(d_slot, d_mg);
   else mg_elem1_kernel<float><<<g, 256, 0, st>>>(d_slot, d_mg);
   return hipGetLastError();
 }
 
+// mixed precision only: level 1 has its element matrices in FP64 solves
+hipError_t mg_launch_elem2(const SlotDev *d_slot, const MgDev *d_mg, long long nn2, hipStream_t st) {
+  mg_g2_kernel<float><<<64, 192, 0, st>>>(d_mg);
+  mg_elem2_kernel<float><<<dim3(blocks_for(nn2, 256), 24), 256, 0, st>>>(d_slot, d_mg);
+  return hipGetLastError();
+}
+
 hipError_t mg_launch_elemc(const MgDev *d_mg, int l, long long nn_next, int prec, hipStream_t st) {
-  const unsigned g = blocks_for(nn_next * 24, 256);
+  const dim3 g(blocks_for(nn_next * 8, 256), 24);
   if (prec == 0) mg_elemc_kernel<double><<<g, 256, 0, st>>>(d_mg, l);
   else mg_elemc_kernel<float><<<g, 256, 0, st>>>(d_mg, l);
   return hipGetLastError();
@@ -1043,7 +1106,7 @@ hipError_t mg_launch_coarse_inverse(const MgBatch &B, int ndof_max, int prec, hi
 }
 
 hipError_t mg_launch_stencil(const MgDev *d_mg, int l, long long nn, int prec, hipStream_t st) {
-  const unsigned g = blocks_for(nn, 256);
+  const dim3 g(blocks_for(nn, 256), MG_HALF);
   if (prec == 0) mg_stencil_kernel<double><<<g, 256, 0, st>>>(d_mg, l);
   else mg_stencil_kernel<float><<<g, 256, 0, st>>>(d_mg, l);
   return hipGetLastError();

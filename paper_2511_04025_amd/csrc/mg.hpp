@@ -46,7 +46,7 @@ struct MgLevel {
   // z = V r in the dense solve, the first direction in the selective one); its
   // passes take the slot's other CG vectors by name.
   void *b, *x, *r, *d, *q;
-  void *Ke;             // setup only: element matrices [nn][24][24] (levels >= 1)
+  void *Ke;             // setup only: element matrices [24][24][nn] (levels >= 1, >= 2 with l1free)
   double inv_theta, c1, c2;  // Chebyshev coefficients
   double lmax;               // lambda_max(D^-1 A) estimate (setup: running max of Rayleigh quotients)
   double pw_scale;           // setup: 1 / ||D^-1 A x|| of the last power step
@@ -58,6 +58,7 @@ struct MgDev {
   int tail;             // level run with the coarsest one in a single launch (mgtail.hip), or -1
   int ndof_c;           // 3 n_L^3
   void *G;              // [8][24][24] child Galerkin matrices of K_0 (T)
+  double *G2;           // l1free: [64][24][24] Galerkin matrices of a level-2 element's voxels
   double *Mc;           // [ndof_c][ndof_c] coarsest inverse (FP64), dof 3 node + c
   void *inv;            // setup only: scratch of the inversion
   MgLevel lv[MG_MAXL];

@@ -23,6 +23,7 @@ namespace shh {
   } while (0)
 
 hipError_t mg_launch_elem1(const SlotDev *d_slot, const MgDev *d_mg, long long nn1, int prec, hipStream_t st);
+hipError_t mg_launch_elem2(const SlotDev *d_slot, const MgDev *d_mg, long long nn2, hipStream_t st);
 hipError_t mg_launch_elemc(const MgDev *d_mg, int l, long long nn_next, int prec, hipStream_t st);
 hipError_t mg_launch_stencil(const MgDev *d_mg, int l, long long nn, int prec, hipStream_t st);
 size_t mg_inverse_scratch_bytes(int ndof);
@@ -81,12 +82,16 @@ size_t carve(char *base, int n, int prec, MgDev *mg, char **d_mgdev) {
   };
   char *dev = take(sizeof(MgDev));
   char *G = take(8 * 576 * ts);
+  const bool free1 = count > 2 && level1_free(prec, (long long)(n / 2) * (n / 2) * (n / 2));
+  char *G2 = free1 ? take(64 * 576 * sizeof(double)) : nullptr;
   // the voxel level's stored Chebyshev direction (its other V-cycle vectors
   // alias CG vectors)
   char *d0 = take((size_t)NRHS * 3 * (size_t)n * n * n * ts);
   if (mg) {
     mg->L = count - 1;
     mg->G = G;
+    mg->G2 = (double *)G2;
+    mg->l1free = free1;
     mg->lv[0].d = d0;
   }
   if (d_mgdev) *d_mgdev = dev;
@@ -94,7 +99,7 @@ size_t carve(char *base, int n, int prec, MgDev *mg, char **d_mgdev) {
   for (int l = 1; l < count; ++l) {
     nl /= 2;
     const long long nn = nl * nl * nl;
-    char *S = l == 1 && level1_free(prec, nn) ? nullptr : take(MG_STENCIL * nn * ts);
+    char *S = l == 1 && free1 ? nullptr : take(MG_STENCIL * nn * ts);
     char *D = take(3 * nn * ts);
     char *v[5];
     for (int k = 0; k < 5; ++k) v[k] = take((size_t)NRHS * 3 * nn * ts);
@@ -387,6 +392,7 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
     size_t used = 0;
     for (int l = 1; l < count; ++l) {
       mg.lv[l].pw_scale = 1.0;
+      if (l == 1 && mg.l1free) continue;
       mg.lv[l].Ke = ke + used;
       used = a256(used + (size_t)mg.lv[l].nn * 576 * ts);
     }
@@ -399,15 +405,16 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
   // Chebyshev bound (host work of about 1 ms, kept per element operator)
   std::vector<double> G;
   nu_constants(h.kop64, bound0, G);
-  mg.l1free = level1_free(prec, mg.lv[1].nn);
   mg.tail = mg_tail_level(mg.L, mg.lv[mg.L - 1].n);
   int rc;
   if ((rc = upload(G, mg.G, prec, st))) return rc;
   SHH_HIP(hipMemcpyAsync(s.d_mg, &mg, sizeof(MgDev), hipMemcpyHostToDevice, st));
-  SHH_HIP(mg_launch_elem1(s.d_slot, s.d_mg, mg.lv[1].nn, prec, st));
-  for (int l = 1; l + 1 < count; ++l) SHH_HIP(mg_launch_elemc(s.d_mg, l, mg.lv[l + 1].nn, prec, st));
+  const int first = mg.l1free ? 2 : 1;  // the finest level with element matrices
+  if (mg.l1free) SHH_HIP(mg_launch_elem2(s.d_slot, s.d_mg, mg.lv[2].nn, st));
+  else SHH_HIP(mg_launch_elem1(s.d_slot, s.d_mg, mg.lv[1].nn, prec, st));
+  for (int l = first; l + 1 < count; ++l) SHH_HIP(mg_launch_elemc(s.d_mg, l, mg.lv[l + 1].nn, prec, st));
   if (mg.l1free) SHH_HIP(mg_launch_l1_diag(s.d_slot, s.d_mg, mg.lv[1].nn, st));
-  for (int l = mg.l1free ? 2 : 1; l < count; ++l) SHH_HIP(mg_launch_stencil(s.d_mg, l, mg.lv[l].nn, prec, st));
+  for (int l = first; l < count; ++l) SHH_HIP(mg_launch_stencil(s.d_mg, l, mg.lv[l].nn, prec, st));
   return SHH_OK;  // the coarsest inverse follows, batched over the slots (mg_setup)
 }
 
