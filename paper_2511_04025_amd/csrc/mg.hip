@@ -624,6 +624,69 @@ __global__ __launch_bounds__(256) void mg_restrict_kernel(MgBatch B, int l) {
   }
 }
 
+// b_1 = P^T r_0 from the shares that the FP32 pre-smoothing pass left in r_0
+// (stencil.hip): a coarse node takes its own tile's, and on a tile's first
+// plane, row or column also the last one of the tile before.  One thread per
+// coarse node; d is written as by the restriction.
+__global__ __launch_bounds__(256) void mg_gather_kernel(MgBatch B) {
+  using TT = Tile<float>;
+  constexpr int CX = TT::X / 2, CY = TT::Y / 2;
+  const MgDev *mg = B.mg[blockIdx.z];
+  const SlotDev *s = B.slot[blockIdx.z];
+  const MgLevel &C = mg->lv[1];
+  const unsigned I = blockIdx.x * 256 + threadIdx.x;
+  const int k = blockIdx.y;
+  if (I >= (unsigned)C.nn || !s->st->active[k]) return;
+  const int nc = C.n, cz = s->tz / 2, cols = min(CX, nc) + 1;
+  const int tx = s->tiles_x[1], ty = s->tiles_y[1], runs = s->tiles_z;
+  const unsigned row = I / (unsigned)nc;
+  const int X = int(I - row * (unsigned)nc), Y = int(row % (unsigned)nc), Z = int(row / (unsigned)nc);
+  // tile and place in it, own and (where there is one) the tile before
+  struct Axis {
+    int t[2], at[2], m;
+  };
+  auto axis = [nc](int i, int step, int tiles) {
+    Axis a;
+    a.t[0] = i / step;
+    a.at[0] = i - a.t[0] * step;
+    a.m = a.at[0] == 0 ? 2 : 1;
+    a.t[1] = i == 0 ? tiles - 1 : a.t[0] - 1;
+    a.at[1] = i == 0 ? nc - step * (tiles - 1) : step;
+    return a;
+  };
+  const Axis ax = axis(X, CX, tx), ay = axis(Y, CY, ty), az = axis(Z, cz, runs);
+  const SHH_GLOBAL float *r = to_global((const float *)mg->lv[0].r) + (long long)k * 3 * mg->lv[0].nn;
+  const SHH_GLOBAL float *Dc = to_global((const float *)C.Dinv);
+  const long long cnn = C.nn;
+  const bool smooth = mg->L > 1;
+  float dv[3] = {0.0f, 0.0f, 0.0f}, acc[3] = {0.0f, 0.0f, 0.0f};
+  if (smooth) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dv[c] = Dc[c * cnn + I];
+  }
+  const unsigned cst = (unsigned)((CY + 1) * cols);
+#pragma unroll
+  for (int iz = 0; iz < 2; ++iz)
+#pragma unroll
+    for (int iy = 0; iy < 2; ++iy)
+#pragma unroll
+      for (int ix = 0; ix < 2; ++ix) {
+        if (iz >= az.m || iy >= ay.m || ix >= ax.m) continue;
+        const unsigned tile = unsigned((az.t[iz] * ty + ay.t[iy]) * tx + ax.t[ix]);
+        const unsigned o = (tile * unsigned(cz + 1) + unsigned(az.at[iz])) * 3u * cst + unsigned(ay.at[iy] * cols + ax.at[ix]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[c] += r[o + c * cst];
+      }
+  const float ith = (float)C.inv_theta;
+  SHH_GLOBAL float *b = to_global((float *)C.b) + (long long)k * 3 * cnn;
+  SHH_GLOBAL float *d = to_global((float *)C.d) + (long long)k * 3 * cnn;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    b[c * cnn + I] = acc[c];
+    if (smooth) d[c * cnn + I] = dv[c] * acc[c] * ith;
+  }
+}
+
 // x_l += P x_{l+1}: fine node 2I + a, a in {0, 1}^3, takes the coarse nodes
 // I + i with i_d in {0, a_d}, weight 1/2 per axis with a_d = 1.  One thread
 // per coarse node (grid y = load case) updates its 2 x 2 x 2 fine block as
@@ -1158,6 +1221,18 @@ hipError_t mg_launch_restrict(const MgBatch &B, int l, long long nn_coarse_max, 
   if (prec == 0) mg_restrict_kernel<double><<<g, 256, 0, st>>>(B, l);
   else mg_restrict_kernel<float><<<g, 256, 0, st>>>(B, l);
   return hipGetLastError();
+}
+
+hipError_t mg_launch_gather(const MgBatch &B, long long nn_coarse_max, hipStream_t st) {
+  mg_gather_kernel<<<dim3(blocks_for(nn_coarse_max, 256), NRHS, B.count), 256, 0, st>>>(B);
+  return hipGetLastError();
+}
+
+// bytes of a load case's restriction shares in the pre-smoothing pass (they
+// take the place of its residual)
+size_t mg_share_bytes(int n, int tz, int ntiles) {
+  using TT = Tile<float>;
+  return sizeof(float) * (size_t)ntiles * (tz / 2 + 1) * 3 * (TT::Y / 2 + 1) * (std::min(TT::X, n) / 2 + 1);
 }
 
 hipError_t mg_launch_prolong(const MgBatch &B, int l, long long nn_coarse_max, int prec, hipStream_t st) {

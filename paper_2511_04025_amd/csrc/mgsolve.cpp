@@ -34,6 +34,8 @@ hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, b
                            hipStream_t st, int live, int ep);
 bool mg_apply_wide(long long nn);
 hipError_t mg_launch_l1(const MgBatch &B, int n_max, int nrhs, hipStream_t st, int live, int ep);
+hipError_t mg_launch_gather(const MgBatch &B, long long nn_coarse_max, hipStream_t st);
+size_t mg_share_bytes(int n, int tz, int ntiles);
 int mg_tail_level(int coarsest, int n_last);
 hipError_t mg_launch_tail(const MgBatch &B, int l, int prec, hipStream_t st);
 hipError_t mg_launch_l1_diag(const SlotDev *d_slot, const MgDev *d_mg, long long nn, hipStream_t st);
@@ -313,7 +315,8 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
     // the post-smoothing pass interpolates the coarse correction itself.
     if ((rc = apply0(smooth, SMG_PRE))) return rc;
     if ((rc = tb(true))) return rc;
-    SHH_HIP(mg_launch_restrict(B, l, nn_next_max, prec, st));
+    if (prec == SHH_PREC_FP64) SHH_HIP(mg_launch_restrict(B, l, nn_next_max, prec, st));
+    else SHH_HIP(mg_launch_gather(B, nn_next_max, st));
     if ((rc = te(SHH_PROF_MG_RESTRICT))) return rc;
     if ((rc = vcycle(smooth, l + 1, st, timer, apply0))) return rc;
     return apply0(smooth, SMG_POST);
@@ -384,6 +387,8 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
   L0.nchunks = h.nchunks;
   L0.Dinv = h.Dinv;
   L0.r = h.q[1];
+  if (prec == SHH_PREC_MIXED && mg_share_bytes(n, h.tz, h.ntiles[1]) > sizeof(float) * 3 * (size_t)h.nn)
+    return SHH_UNSUPPORTED;  // no grid: the shares are at most two thirds of the residual
   h.mgd = L0.d;
   h.mgxc = mg.lv[1].x;
   // element matrices of levels >= 1 live in the (not yet used) CG vector region

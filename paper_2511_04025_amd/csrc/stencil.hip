@@ -86,6 +86,12 @@ void stencil_kernel(LaunchArgs la) {
   constexpr int CXC = TX / 2 + 2, CYC = TY / 2 + 2, NCO = MODE == MODE_MGPOST ? 3 * CXC * CYC : 1;
   constexpr int CPT = (NCO + STENCIL_THREADS - 1) / STENCIL_THREADS;
   __shared__ TC cbuf[NCO];
+  // FP32 pre-smoothing: a plane of the residual, summed over z, in a margin of
+  // zeros (one before, two behind)
+  constexpr bool RESTR = MODE == MODE_MGPRE && sizeof(TC) == 4;
+  constexpr int RX = TX + 3, RY = TY + 3, RCX = TX / 2 + 1, RCY = TY / 2 + 1, NRC = 3 * RCX * RCY;
+  static_assert(!RESTR || NRC <= STENCIL_THREADS, "one coarse value a thread");
+  __shared__ TC rbuf[RESTR ? 3 * RX * RY : 1];
 
   Work w;
   if (!decode_work(la, w)) return;
@@ -188,7 +194,8 @@ void stencil_kernel(LaunchArgs la) {
   // x update of the iteration before (x += alpha p_{j-1}) rides along, since p_{j-1} is read anyway.
   // The two smoothing passes (q = K v is consumed, not stored; b = r[pc] before, r[pc ^ 1] after PRE):
   //   PRE:  staged b' = b - alpha q (the CG update) as d0 = D b' / theta;  r = b' - K d0 (the
-  //         residual the restriction takes) -> q[1], b' -> the other r buffer
+  //         residual the restriction takes) -> q[1] (FP32: its restriction's shares), b' -> the
+  //         other r buffer
   //   POST: staged x = D b' / theta + P x_c, P the interpolation from level 1;
   //         z = x + D (b' - K x) / theta -> mgd, partials b' . z, b' . b'
   // Neither d0 nor x is ever stored: each is formed again from b'.
@@ -514,6 +521,33 @@ void stencil_kernel(LaunchArgs la) {
     }
     write_c();
   }
+  // Pre-smoothing, the restriction: a workgroup sums its own nodes' share of
+  // the coarse right-hand side P^T r (coarse planes z0 / 2 .. z1 / 2, RCX x RCY
+  // nodes of each, the last ones shared with the next workgroup) and stores it
+  // where the residual itself went, [tile][coarse plane][3][RCY][coarse columns];
+  // mg_gather_kernel adds the shares.  Over z in registers: an odd plane
+  // completes coarse plane Z and starts Z + 1; over x and y from rbuf.  The
+  // residual's 12 bytes a node and load case are neither written nor read back
+  // by a restriction kernel: one 128^3 design, this pass 149 -> 134 us and the
+  // restriction 42 -> 16.  (FP64 has no registers left for it.)
+  TC zac[3] = {TC(0), TC(0), TC(0)};
+  const int rcols = min(TX, n) / 2 + 1;
+  const int rc = tid / (RCX * RCY), ry = (tid / RCX) % RCY, rx = tid % RCX;
+  const uint32_t rplane = 3u * RCY * (uint32_t)rcols * SS;
+  const uint32_t roff =
+      (uint32_t)tile * (uint32_t)(s->tz / 2 + 1) * rplane + ((uint32_t)((rc * RCY + ry) * rcols) + rx) * SS;
+  auto restrict_store = [&](int Z) {  // coarse plane Z of the run
+    if constexpr (RESTR) {
+      if (tid < NRC && rx < rcols) {
+        const TC *rb = rbuf + (rc * RY + 2 * ry) * RX + 2 * rx;
+        auto row = [&](int y) { return rb[y * RX + 1] + TC(0.5) * (rb[y * RX] + rb[y * RX + 2]); };
+        bstore<TS, 0>((TS)(row(1) + TC(0.5) * (row(0) + row(2))), rR, roff, (uint32_t)Z * rplane);
+      }
+    }
+  };
+  if constexpr (RESTR) {
+    for (int i = tid; i < 3 * RX * RY; i += STENCIL_THREADS) rbuf[i] = TC(0);
+  }
   issue(z0 - 1);
   if constexpr (MODE == MODE_MGPOST) __syncthreads();
   finish(z0 - 1, B0{});
@@ -662,7 +696,15 @@ void stencil_kernel(LaunchArgs la) {
       } else if constexpr (MODE == MODE_MGPRE) {
         // oz = b'
 #pragma unroll
-        for (int c = 0; c < 3; ++c) bstore<TS>((TS)(oz[c] - qv[c]), rR, ooff, pk + cS[c]);
+        for (int c = 0; c < 3; ++c) {
+          const TC rv = oz[c] - qv[c];
+          if constexpr (!RESTR) bstore<TS>((TS)rv, rR, ooff, pk + cS[c]);
+          else if constexpr (b == 1) zac[c] += rv;  // even plane
+          else {
+            rbuf[(c * RY + oy + 1) * RX + ox + 1] = zac[c] + TC(0.5) * rv;
+            zac[c] = TC(0.5) * rv;
+          }
+        }
       } else if constexpr (MODE == MODE_MGPOST) {
         // op = x, oz = b', od = D / theta
 #pragma unroll
@@ -685,6 +727,11 @@ void stencil_kernel(LaunchArgs la) {
         for (int c = 0; c < 3; ++c) bstore<TS>((TS)qv[c], rQ, ooff, pk + cS[c]);
       }
     }
+    // the plane written two barriers ago (an odd plane again writes rbuf after
+    // the next one)
+    if constexpr (RESTR && b == 1) {
+      if (sl > 1) restrict_store((sl - 3) / 2);
+    }
   };
   int sl = 0;
   for (; sl + 1 < S; sl += 2) {
@@ -692,6 +739,17 @@ void stencil_kernel(LaunchArgs la) {
     step(sl + 1, B1{});
   }
   if (sl < S) step(sl, B0{});
+  if constexpr (RESTR) {  // the last whole coarse plane and the share of the one above
+    __syncthreads();
+    restrict_store((z1 - z0) / 2 - 1);
+    __syncthreads();
+    if (is_out) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) rbuf[(c * RY + oy + 1) * RX + ox + 1] = zac[c];
+    }
+    __syncthreads();
+    restrict_store((z1 - z0) / 2);
+  }
 
   // workgroup partials only; the scalar kernel that follows reduces them
   double *parts = w.slot->partials + ((long long)rhs * s->maxparts + tile) * PSTRIDE;
