@@ -160,6 +160,7 @@ __global__ __launch_bounds__(256) void field_kernel(SlotDev *s) {
 
 // ---- hard step: bins of the order-statistic search (below) -------------------
 constexpr int SEL_BITS = 11, SEL_BINS = 1 << SEL_BITS, SEL_PASSES = 6;  // 6 x 11 >= 64
+constexpr int SEL_T = 512;   // threads of a counting workgroup
 
 // ---- distance d = |F - c| / max(||grad F||, 1e-12 max ||grad F||) ------------
 __global__ __launch_bounds__(256) void distance_kernel(SlotDev *s) {
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256) void distance_kernel(SlotDev *s) {
   // the order-statistic search that may follow counts into zeroed bins (the
   // tables of the synthesis were here)
   const long long first = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  for (long long i = first; i < 2 * SEL_BINS; i += (long long)gridDim.x * blockDim.x) ((unsigned *)s->partials)[i] = 0u;
+  for (long long i = first; i < 2 * SEL_BINS * SEL_PASSES; i += (long long)gridDim.x * blockDim.x) ((unsigned *)s->partials)[i] = 0u;
   const double gmax = __longlong_as_double((long long)s->st->gmax_bits);
   const double gmin = 1e-12 * gmax;
   const int mode = s->dist_mode;
@@ -191,90 +192,121 @@ __global__ __launch_bounds__(256) void distance_kernel(SlotDev *s) {
 // Non-negative doubles (and +inf) order like their bit patterns.  A radix
 // search from the top: pass p counts, among the elements that share the digits
 // found so far, the next 11 bits (per search: the two ranks may part), in LDS
-// bins that go to global bins; the last workgroup finds the digit that holds
-// the rank and clears the bins.  Six passes over d (a 16-way search by counting
-// against 15 pivots per rank took 18 launches of 32 us at 128^3; these take
-// 8 us each).  State: sel_lo the digits found, sel_hi the rank left below them.
-__global__ __launch_bounds__(256) void select_pass_kernel(SlotDev *s, int pass, long long k1, long long k2,
-                                                          int nblocks) {
-  __shared__ unsigned bins[2][SEL_BINS];
-  __shared__ unsigned scan[2][256];
-  __shared__ int lastflag;
-  CgState *st = s->st;
-  // 64 = 5 x 11 + 9: the first digit has 9 bits
-  const int shift = SEL_BITS * (SEL_PASSES - 1 - pass);
-  const unsigned long long pre[2] = {pass ? st->sel_lo[0] : 0ull, pass ? st->sel_lo[1] : 0ull};
-  const bool same = pre[0] == pre[1];  // one count serves both
-  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += 256) (&bins[0][0])[i] = 0u;
-  __syncthreads();
-  const long long nn = s->nn;
-  const int hi = shift + SEL_BITS;  // bits above the digit (none in the first pass)
-  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < nn; e += (long long)nblocks * 256) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(s->d[e]);
-    const unsigned dig = unsigned(b >> shift) & (SEL_BINS - 1);
-    const unsigned long long top = pass ? b >> hi : 0ull;
-    if (top == (pass ? pre[0] >> hi : 0ull)) atomicAdd(&bins[0][dig], 1u);
-    if (!same && top == pre[1] >> hi) atomicAdd(&bins[1][dig], 1u);
-  }
-  __syncthreads();
-  unsigned *g = (unsigned *)s->partials;
-  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += 256)
-    if (const unsigned c = (&bins[0][0])[i]) atomicAdd(&g[i], c);
-  __syncthreads();
-  if (!arrive_last(&st->cnt[6], nblocks, &lastflag)) return;
-  // thread t owns bins [8 t, 8 t + 8) of each search
-  constexpr int PER = SEL_BINS / 256;
-  unsigned c[2][PER];
+// bins that go to the pass's global bins.  The next pass finds the digit that
+// holds the rank, every workgroup for itself: with a last-arrival step (a release
+// per workgroup, one workgroup's scan) a pass took 17 us at 128^3 instead of 8.  (A
+// 16-way search by counting against 15 pivots per rank took 18 launches of 32 us.)
+struct SelState {  // at the entry of a pass
+  unsigned long long pre[2];   // the digits found
+  unsigned long long rank[2];  // the rank left below them
+};
+__device__ __forceinline__ unsigned *sel_bins(SlotDev *s, int pass) {
+  return (unsigned *)s->partials + pass * 2 * SEL_BINS;
+}
+__device__ __forceinline__ SelState *sel_state(SlotDev *s, int pass) {
+  return (SelState *)((unsigned *)s->partials + SEL_PASSES * 2 * SEL_BINS) + pass;
+}
+
+// the state at the entry of `pass` (> 0) from that of the pass before and its
+// counts; all threads of a SEL_T workgroup
+__device__ __forceinline__ void sel_advance(SlotDev *s, int pass, SelState &out, SelState *shared_state,
+                                            unsigned (*wave_sum)[SEL_T / 64]) {
+  constexpr int PER = SEL_BINS / SEL_T;
+  const SelState in = *sel_state(s, pass - 1);
+  const unsigned *g = sel_bins(s, pass - 1);
+  const int shift = SEL_BITS * (SEL_PASSES - pass);
+  const bool same = in.pre[0] == in.pre[1];  // one count serves both
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  unsigned c[2][PER], below[2];  // thread t owns bins [PER t, PER t + PER) of each search
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     unsigned sum = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int at = (same ? 0 : j) * SEL_BINS + threadIdx.x * PER + i;
-      c[j][i] = __hip_atomic_load(&g[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      c[j][i] = g[(same ? 0 : j) * SEL_BINS + threadIdx.x * PER + i];
       sum += c[j][i];
     }
-    scan[j][threadIdx.x] = sum;
+    unsigned inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned v = __shfl_up(inc, off, 64);
+      inc += lane >= off ? v : 0u;
+    }
+    if (lane == 63) wave_sum[j][wave] = inc;
+    below[j] = inc - sum;
   }
   __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    unsigned v[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) v[j] = threadIdx.x >= (unsigned)off ? scan[j][threadIdx.x - off] : 0u;
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 2; ++j) scan[j][threadIdx.x] += v[j];
-    __syncthreads();
-  }
-  const unsigned long long rank[2] = {pass ? st->sel_hi[0] : (unsigned long long)k1,
-                                      pass ? st->sel_hi[1] : (unsigned long long)k2};
-  __syncthreads();  // every thread has read the state before one rewrites it
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    unsigned long long below = threadIdx.x ? scan[j][threadIdx.x - 1] : 0u;
+    unsigned long long n = below[j];
+    for (int w = 0; w < wave; ++w) n += wave_sum[j][w];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      if (below < rank[j] && rank[j] <= below + c[j][i]) {  // exactly one bin holds the rank
-        st->sel_lo[j] = pre[j] | ((unsigned long long)(threadIdx.x * PER + i) << shift);
-        st->sel_hi[j] = rank[j] - below;
+      if (n < in.rank[j] && in.rank[j] <= n + c[j][i]) {  // exactly one bin holds the rank
+        shared_state->pre[j] = in.pre[j] | ((unsigned long long)(threadIdx.x * PER + i) << shift);
+        shared_state->rank[j] = in.rank[j] - n;
       }
-      below += c[j][i];
+      n += c[j][i];
     }
   }
-  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += 256) g[i] = 0u;
-  if (threadIdx.x == 0) st->cnt[6] = 0;
+  __syncthreads();
+  out = *shared_state;
+}
+
+__global__ __launch_bounds__(SEL_T) void select_pass_kernel(SlotDev *s, int pass, long long k1, long long k2,
+                                                            int nblocks) {
+  __shared__ unsigned bins[2][SEL_BINS];
+  __shared__ unsigned wave_sum[2][SEL_T / 64];
+  __shared__ SelState entry;
+  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += SEL_T) (&bins[0][0])[i] = 0u;
+  SelState at = {{0ull, 0ull}, {(unsigned long long)k1, (unsigned long long)k2}};
+  if (pass) sel_advance(s, pass, at, &entry, wave_sum);
+  else __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) *sel_state(s, pass) = at;
+  // 64 = 5 x 11 + 9: the first digit has 9 bits
+  const int shift = SEL_BITS * (SEL_PASSES - 1 - pass);
+  const bool same = at.pre[0] == at.pre[1];
+  const long long nn = s->nn;
+  const int hi = shift + SEL_BITS;  // bits above the digit (none in the first pass)
+  constexpr int UN = 4;             // loads in flight per thread
+  const double *d = s->d;
+  const long long stride = (long long)nblocks * SEL_T;
+  for (long long e0 = (long long)blockIdx.x * SEL_T + threadIdx.x; e0 < nn; e0 += UN * stride) {
+    unsigned long long v[UN];
+#pragma unroll
+    for (int j = 0; j < UN; ++j) {
+      const long long e = e0 + j * stride;
+      v[j] = (unsigned long long)__double_as_longlong(d[e < nn ? e : e0]);
+    }
+#pragma unroll
+    for (int j = 0; j < UN; ++j) {
+      if (e0 + j * stride >= nn) break;
+      const unsigned dig = unsigned(v[j] >> shift) & (SEL_BINS - 1);
+      const unsigned long long top = pass ? v[j] >> hi : 0ull;
+      if (top == (pass ? at.pre[0] >> hi : 0ull)) atomicAdd(&bins[0][dig], 1u);
+      if (!same && top == at.pre[1] >> hi) atomicAdd(&bins[1][dig], 1u);
+    }
+  }
+  __syncthreads();
+  unsigned *g = sel_bins(s, pass);
+  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += SEL_T)
+    if (const unsigned c = (&bins[0][0])[i]) atomicAdd(&g[i], c);
 }
 
 // t from the two order statistics; k = round(vf n^3).
-__global__ void select_finish_kernel(SlotDev *s, long long k) {
-  CgState *st = s->st;
-  const double v1 = __longlong_as_double((long long)st->sel_lo[0]);
-  const double v2 = __longlong_as_double((long long)st->sel_lo[1]);
+__global__ __launch_bounds__(SEL_T) void select_finish_kernel(SlotDev *s, long long k) {
+  __shared__ unsigned wave_sum[2][SEL_T / 64];
+  __shared__ SelState entry;
+  SelState at;
+  sel_advance(s, SEL_PASSES, at, &entry, wave_sum);
+  if (threadIdx.x != 0) return;
+  const double v1 = __longlong_as_double((long long)at.pre[0]);
+  const double v2 = __longlong_as_double((long long)at.pre[1]);
   double t;
   if (k <= 0) t = 0.5 * v1;                 // v1 = smallest
   else if (k >= s->nn) t = 2.0 * v2 + 1.0;  // v2 = largest
   else t = 0.5 * (v1 + v2);
-  st->t = t;
+  s->st->t = t;
 }
 
 // ---- logistic: bisection on t until |V(t) - target| <= 1e-12 ------------------
@@ -346,10 +378,13 @@ __global__ __launch_bounds__(256) void bisect_step_kernel(SlotDev *s, int nblock
 }
 
 // ---- occupancy, element moduli and volume fraction ---------------------------
+// (The sums are finished by a kernel of one workgroup: a last-arrival counter
+// needs every workgroup's device-wide release, which writes the L2's dirty lines
+// back.  128^3: 37 us in one kernel, 10 + 4 in two; the given moduli of 101^3 36
+// and 13 + 3.)
 __global__ __launch_bounds__(256) void occupancy_kernel(SlotDev *s, double *beta_out, int nblocks) {
   __shared__ double red[16];
-  __shared__ int lastflag;
-  CgState *st = s->st;
+  const CgState *st = s->st;
   const double t = st->t, kappa = s->kappa, E = s->E, Ev = s->E_void;
   const long long nn = s->nn;
   double v[1] = {0.0};  // V = mean beta over every voxel, culled or not
@@ -365,13 +400,13 @@ __global__ __launch_bounds__(256) void occupancy_kernel(SlotDev *s, double *beta
   }
   block_sum<1>(v, red, 256);
   if (threadIdx.x == 0) s->partials[4 * blockIdx.x] = v[0];
-  if (!arrive_last(&st->cnt[6], nblocks, &lastflag)) return;
+}
+
+__global__ __launch_bounds__(256) void occupancy_sum_kernel(SlotDev *s, int nblocks) {
+  __shared__ double red[16];
   double tot[1];
   sum_partials<1>(s->partials, nblocks, tot, red, 256);
-  if (threadIdx.x == 0) {
-    st->V = tot[0] / double(nn);
-    st->cnt[6] = 0;
-  }
+  if (threadIdx.x == 0) s->st->V = tot[0] / double(s->nn);
 }
 
 // Moduli given directly (solver-only entries).  The source grid is one of
@@ -411,8 +446,6 @@ __global__ __launch_bounds__(256) void dinv_kernel(SlotDev *s) {
 template <int DT, typename T>
 __global__ __launch_bounds__(256) void moduli_kernel(SlotDev *s, const void *E, double Es, double Ev, int nblocks) {
   __shared__ double red[16];
-  __shared__ int lastflag;
-  CgState *st = s->st;
   const int n = s->n;
   const long long nn = s->nn;
   const double cd = (s->lam + 4.0 * s->mu) / 9.0;
@@ -446,7 +479,14 @@ __global__ __launch_bounds__(256) void moduli_kernel(SlotDev *s, const void *E, 
     s->partials[4 * blockIdx.x] = v[0];
     s->partials[4 * blockIdx.x + 1] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
   }
-  if (!arrive_last(&st->cnt[6], nblocks, &lastflag)) return;
+}
+
+// maximum and volume fraction from the workgroups' partials (see the occupancy)
+template <int DT>
+__global__ __launch_bounds__(256) void moduli_sum_kernel(SlotDev *s, int nblocks) {
+  __shared__ double red[16];
+  CgState *st = s->st;
+  const long long nn = s->nn;
   double tot[1];
   sum_partials<1>(s->partials, nblocks, tot, red, 256);
   double m = 0.0;
@@ -461,7 +501,6 @@ __global__ __launch_bounds__(256) void moduli_kernel(SlotDev *s, const void *E, 
     if constexpr (DT == 0) st->V = tot[0] / double(nn);
     else st->V = emax > 0.0 ? tot[0] / double(nn) / emax : 0.0;
     st->t = 0.0;
-    st->cnt[6] = 0;
   }
 }
 
@@ -507,8 +546,8 @@ hipError_t launch_select_hard(SlotDev *d_slot, long long nn, long long k, hipStr
   const int nbk = (int)std::max(1LL, std::min(256LL, (nn + 4095) / 4096));
   const long long k1 = k <= 0 ? 1 : (k >= nn ? nn : k);
   const long long k2 = k <= 0 ? 1 : (k >= nn ? nn : k + 1);
-  for (int p = 0; p < SEL_PASSES; ++p) select_pass_kernel<<<nbk, 256, 0, st>>>(d_slot, p, k1, k2, nbk);
-  select_finish_kernel<<<1, 1, 0, st>>>(d_slot, k);
+  for (int p = 0; p < SEL_PASSES; ++p) select_pass_kernel<<<nbk, SEL_T, 0, st>>>(d_slot, p, k1, k2, nbk);
+  select_finish_kernel<<<1, SEL_T, 0, st>>>(d_slot, k);
   return hipGetLastError();
 }
 
@@ -527,6 +566,7 @@ hipError_t launch_bisect_steps(SlotDev *d_slot, long long nn, int steps, hipStre
 hipError_t launch_occupancy(SlotDev *d_slot, long long nn, double *beta_out, hipStream_t st) {
   const int nbk = reduce_blocks(nn);
   occupancy_kernel<<<nbk, 256, 0, st>>>(d_slot, beta_out, nbk);
+  occupancy_sum_kernel<<<1, 256, 0, st>>>(d_slot, nbk);
   return hipGetLastError();
 }
 
@@ -537,6 +577,7 @@ hipError_t launch_moduli(SlotDev *d_slot, long long nn, const void *E, int e_dty
     constexpr int DT = decltype(dt)::value;
     if (prec == 0) moduli_kernel<DT, double><<<nbk, 256, 0, st>>>(d_slot, E, Es, Ev, nbk);
     else moduli_kernel<DT, float><<<nbk, 256, 0, st>>>(d_slot, E, Es, Ev, nbk);
+    moduli_sum_kernel<DT><<<1, 256, 0, st>>>(d_slot, nbk);
   };
   if (e_dtype == 0) go(std::integral_constant<int, 0>{});
   else if (e_dtype == 1) go(std::integral_constant<int, 1>{});
