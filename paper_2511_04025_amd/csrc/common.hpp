@@ -97,11 +97,6 @@ struct CgState {
   unsigned long long gmax_bits;
   double Emax;
   double C[36];           // homogenized tensor
-  // thickness selection state
-  unsigned long long sel_lo[2], sel_hi[2];  // logistic: min and max of d
-  double bis_lo, bis_hi, bis_V;             // logistic bisection on t
-  int bis_done;
-  int pad_;
 };
 
 struct SlotDev {

@@ -309,36 +309,44 @@ __global__ __launch_bounds__(SEL_T) void select_finish_kernel(SlotDev *s, long l
   s->st->t = t;
 }
 
-// ---- logistic: bisection on t until |V(t) - target| <= 1e-12 ------------------
-__global__ __launch_bounds__(256) void minmax_d_kernel(SlotDev *s) {
-  // reuses sel_lo[0] / sel_hi[0] as min / max bit patterns
-  const long long nn = s->nn;
-  unsigned long long mn = ~0ull, mx = 0ull;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nn;
-       i += (long long)gridDim.x * blockDim.x) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(s->d[i]);
-    mn = b < mn ? b : mn;
-    mx = b > mx ? b : mx;
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned long long a = __shfl_xor(mn, off, 64), c = __shfl_xor(mx, off, 64);
-    mn = a < mn ? a : mn;
-    mx = c > mx ? c : mx;
-  }
-  if ((threadIdx.x & 63) == 0) {
-    atomicMin(&s->st->sel_lo[0], mn);
-    atomicMax(&s->st->sel_hi[0], mx);
-  }
+// ---- logistic: bisection on t until |V(t) - target| <= 1e-12, 200 steps at most ----
+// A pass evaluates the midpoints that its steps can reach (three steps, seven
+// midpoints; on large grids, where a midpoint's logistics cost more than a
+// launch, one) and leaves per-workgroup sums; the next one takes those steps in every workgroup
+// for itself (no last-arrival step, as in the search above), from the state that
+// its predecessor started from: states and sums alternate between two places.
+// The steps are those of the plain bisection.  The field of a logistic design went
+// from 1.55 to 0.63 ms at 96^3 and from 4.31 to 3.14 at 256^3 (200 launches of one
+// step with a last-arrival sum, most of them after the end).
+constexpr int BIS_T = 512, BIS_BLOCKS = 1024, BIS_STEPS = 200;
+// three steps a pass up to 128^3: field with three / one at 96^3 0.63 / 0.83 ms,
+// 128^3 0.95 / 0.96, 160^3 1.51 / 1.23
+constexpr long long BIS_SMALL = 128LL * 128 * 128;
+struct BisState {
+  double lo, hi, t;
+  int done, steps;
+};
+__device__ __forceinline__ double *bis_parts(SlotDev *s, int pass) { return s->partials + (pass & 1) * BIS_BLOCKS * 8; }
+__device__ __forceinline__ BisState *bis_state(SlotDev *s, int pass) {
+  return (BisState *)(s->partials + 2 * BIS_BLOCKS * 8) + (pass & 1);
 }
 
-__global__ void bisect_init_kernel(SlotDev *s) {
-  CgState *st = s->st;
-  const double dmin = __longlong_as_double((long long)st->sel_lo[0]);
-  const double dmax = __longlong_as_double((long long)st->sel_hi[0]);
-  st->bis_lo = dmin - 40.0 / s->kappa;
-  st->bis_hi = dmax + 40.0 / s->kappa;
-  st->bis_done = 0;
-  st->t = 0.5 * (st->bis_lo + st->bis_hi);
+// node i of the tree of midpoints; its lower and upper half continue at 2 i + 1, 2 i + 2
+template <int NODES>
+__device__ __forceinline__ void bis_nodes(const BisState &b, double (&t)[NODES]) {
+  double lo[NODES], hi[NODES];
+  lo[0] = b.lo;
+  hi[0] = b.hi;
+#pragma unroll
+  for (int i = 0; i < NODES; ++i) {
+    t[i] = 0.5 * (lo[i] + hi[i]);
+    if (2 * i + 2 < NODES) {
+      lo[2 * i + 1] = lo[i];
+      hi[2 * i + 1] = t[i];
+      lo[2 * i + 2] = t[i];
+      hi[2 * i + 2] = hi[i];
+    }
+  }
 }
 
 __device__ __forceinline__ double logistic(double kappa, double t, double d) {
@@ -349,32 +357,134 @@ __device__ __forceinline__ double logistic(double kappa, double t, double d) {
   return e / (1.0 + e);
 }
 
-__global__ __launch_bounds__(256) void bisect_step_kernel(SlotDev *s, int nblocks) {
-  __shared__ double red[16];
-  __shared__ int lastflag;
-  CgState *st = s->st;
-  if (st->bis_done) return;
-  const double t = 0.5 * (st->bis_lo + st->bis_hi);
+// min and max of d by workgroup
+__global__ __launch_bounds__(BIS_T) void minmax_d_kernel(SlotDev *s, int nblocks) {
+  __shared__ double red[2][BIS_T / 64];
+  const long long nn = s->nn;
+  double mn = INFINITY, mx = 0.0;  // distances are not negative
+  for (long long i = (long long)blockIdx.x * BIS_T + threadIdx.x; i < nn; i += (long long)nblocks * BIS_T) {
+    const double d = s->d[i];
+    mn = d < mn ? d : mn;
+    mx = d > mx ? d : mx;
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    mn = fmin(mn, __shfl_xor(mn, off, 64));
+    mx = fmax(mx, __shfl_xor(mx, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = mn;
+    red[1][threadIdx.x >> 6] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < BIS_T / 64; ++w) {
+    mn = fmin(mn, red[0][w]);
+    mx = fmax(mx, red[1][w]);
+  }
+  s->partials[8 * blockIdx.x] = mn;
+  s->partials[8 * blockIdx.x + 1] = mx;
+}
+
+__global__ __launch_bounds__(64) void bisect_init_kernel(SlotDev *s, int nblocks) {
+  double mn = INFINITY, mx = 0.0;
+  for (int b = threadIdx.x; b < nblocks; b += 64) {
+    mn = fmin(mn, s->partials[8 * b]);
+    mx = fmax(mx, s->partials[8 * b + 1]);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    mn = fmin(mn, __shfl_xor(mn, off, 64));
+    mx = fmax(mx, __shfl_xor(mx, off, 64));
+  }
+  if (threadIdx.x != 0) return;
+  BisState b;
+  b.lo = mn - 40.0 / s->kappa;
+  b.hi = mx + 40.0 / s->kappa;
+  b.t = 0.5 * (b.lo + b.hi);
+  b.done = 0;
+  b.steps = 0;
+  *bis_state(s, 0) = b;
+}
+
+// the state at the entry of pass > 0: its steps from that of the pass
+// before with its sums; all threads of a BIS_T workgroup
+template <int LEVELS>
+__device__ __forceinline__ BisState bis_advance(SlotDev *s, int pass, int nblocks, double *red, BisState *shared_state) {
+  constexpr int NODES = (1 << LEVELS) - 1;
+  BisState b = *bis_state(s, pass - 1);
+  if (b.done) return b;  // uniform
+  double t[NODES], tot[NODES];
+  bis_nodes<NODES>(b, t);
+  sum_partials<NODES, 8>(bis_parts(s, pass - 1), nblocks, tot, red, BIS_T);
+  if (threadIdx.x == 0) {
+    const double n = double(s->nn), target = s->target_vf;
+    int at = 0;
+#pragma unroll
+    for (int level = 0; level < LEVELS; ++level) {
+      if (b.done) continue;
+      double tt = 0.0, V = 0.0;
+#pragma unroll
+      for (int i = 0; i < NODES; ++i)  // (no indexed registers)
+        if (i == at) {
+          tt = t[i];
+          V = tot[i] / n;
+        }
+      b.t = tt;
+      b.steps += 1;
+      if (fabs(V - target) <= 1e-12) {
+        b.done = 1;
+      } else if (V < target) {
+        b.lo = tt;
+        at = 2 * at + 2;
+      } else {
+        b.hi = tt;
+        at = 2 * at + 1;
+      }
+      if (b.steps == BIS_STEPS) b.done = 1;
+    }
+    *shared_state = b;
+  }
+  __syncthreads();
+  return *shared_state;
+}
+
+template <int LEVELS>
+__global__ __launch_bounds__(BIS_T) void bisect_pass_kernel(SlotDev *s, int pass, int nblocks) {
+  constexpr int NODES = (1 << LEVELS) - 1;
+  __shared__ double red[7 * 16];
+  __shared__ BisState entry;
+  BisState b;
+  if (pass) {
+    b = bis_advance<LEVELS>(s, pass, nblocks, red, &entry);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *bis_state(s, pass) = b;
+  } else {
+    b = *bis_state(s, 0);
+  }
+  if (b.done) return;
+  double t[NODES], v[NODES];
+  bis_nodes<NODES>(b, t);
+#pragma unroll
+  for (int i = 0; i < NODES; ++i) v[i] = 0.0;
   const double kappa = s->kappa;
   const long long nn = s->nn;
-  double v[1] = {0.0};
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nn;
-       i += (long long)nblocks * blockDim.x)
-    v[0] += logistic(kappa, t, s->d[i]);
-  block_sum<1>(v, red, 256);
-  if (threadIdx.x == 0) s->partials[4 * blockIdx.x] = v[0];
-  if (!arrive_last(&st->cnt[6], nblocks, &lastflag)) return;
-  double tot[1];
-  sum_partials<1>(s->partials, nblocks, tot, red, 256);
-  if (threadIdx.x == 0) {
-    const double V = tot[0] / double(nn);
-    st->t = t;
-    st->bis_V = V;
-    if (fabs(V - s->target_vf) <= 1e-12) st->bis_done = 1;
-    else if (V < s->target_vf) st->bis_lo = t;
-    else st->bis_hi = t;
-    st->cnt[6] = 0;
+  for (long long e = (long long)blockIdx.x * BIS_T + threadIdx.x; e < nn; e += (long long)nblocks * BIS_T) {
+    const double d = s->d[e];
+#pragma unroll
+    for (int i = 0; i < NODES; ++i) v[i] += logistic(kappa, t[i], d);
   }
+  __syncthreads();  // the sums above have been read from red
+  block_sum<NODES>(v, red, BIS_T);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int i = 0; i < NODES; ++i) bis_parts(s, pass)[8 * blockIdx.x + i] = v[i];
+  }
+}
+
+template <int LEVELS>
+__global__ __launch_bounds__(BIS_T) void bisect_finish_kernel(SlotDev *s, int passes, int nblocks) {
+  __shared__ double red[7 * 16];
+  __shared__ BisState entry;
+  const BisState b = bis_advance<LEVELS>(s, passes, nblocks, red, &entry);
+  if (threadIdx.x == 0) s->st->t = b.t;
 }
 
 // ---- occupancy, element moduli and volume fraction ---------------------------
@@ -551,15 +661,19 @@ hipError_t launch_select_hard(SlotDev *d_slot, long long nn, long long k, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_minmax_d(SlotDev *d_slot, long long nn, hipStream_t st) {
-  minmax_d_kernel<<<grid_for(nn, 1024), 256, 0, st>>>(d_slot);
-  bisect_init_kernel<<<1, 1, 0, st>>>(d_slot);
-  return hipGetLastError();
+template <int LEVELS>
+static void launch_bisect_levels(SlotDev *d_slot, int nbk, hipStream_t st) {
+  constexpr int passes = (BIS_STEPS + LEVELS - 1) / LEVELS;
+  minmax_d_kernel<<<nbk, BIS_T, 0, st>>>(d_slot, nbk);
+  bisect_init_kernel<<<1, 64, 0, st>>>(d_slot, nbk);
+  for (int p = 0; p < passes; ++p) bisect_pass_kernel<LEVELS><<<nbk, BIS_T, 0, st>>>(d_slot, p, nbk);
+  bisect_finish_kernel<LEVELS><<<1, BIS_T, 0, st>>>(d_slot, passes, nbk);
 }
 
-hipError_t launch_bisect_steps(SlotDev *d_slot, long long nn, int steps, hipStream_t st) {
-  const int nbk = reduce_blocks(nn);
-  for (int it = 0; it < steps; ++it) bisect_step_kernel<<<nbk, 256, 0, st>>>(d_slot, nbk);
+hipError_t launch_bisect(SlotDev *d_slot, long long nn, hipStream_t st) {
+  const long long g = (nn + BIS_T - 1) / BIS_T;
+  if (nn <= BIS_SMALL) launch_bisect_levels<3>(d_slot, (int)std::max(1LL, std::min(256LL, g)), st);
+  else launch_bisect_levels<1>(d_slot, (int)std::min((long long)BIS_BLOCKS, g), st);
   return hipGetLastError();
 }
 

@@ -13,8 +13,7 @@ enum { PH_ITER = 0, PH_MEAN = 2, PH_RESID = 3 };
 hipError_t launch_field(SlotDev *d_slot, int n, int nb, long long scratch, hipStream_t st);
 int reduce_blocks(long long nn);
 hipError_t launch_select_hard(SlotDev *d_slot, long long nn, long long k, hipStream_t st);
-hipError_t launch_minmax_d(SlotDev *d_slot, long long nn, hipStream_t st);
-hipError_t launch_bisect_steps(SlotDev *d_slot, long long nn, int steps, hipStream_t st);
+hipError_t launch_bisect(SlotDev *d_slot, long long nn, hipStream_t st);
 hipError_t launch_occupancy(SlotDev *d_slot, long long nn, double *beta_out, hipStream_t st);
 // e_dtype 0: 1-byte solid/void code (E = Es where nonzero, else Ev); 1: float; 2: double
 hipError_t launch_moduli(SlotDev *d_slot, long long nn, const void *E, int e_dtype, double Es, double Ev, int prec,

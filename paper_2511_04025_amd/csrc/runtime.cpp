@@ -352,11 +352,6 @@ int slot_init(Slot &s, char *base, hipStream_t st, const std::function<void(Slot
   CgState init;
   std::memset(&init, 0, sizeof(init));
   init.t = d.thickness;
-  if (h.mode_t == 2) {
-    // min / max of the distance bit patterns, reduced with atomicMin / atomicMax
-    init.sel_lo[0] = ~0ull;
-    init.sel_hi[0] = 0ull;
-  }
   if (adjust) adjust(h);
   // descriptor, state, charges and alpha lie one after the other at the
   // region's start: one copy (four and a wait took 40 us of a call)
@@ -398,8 +393,7 @@ int slot_setup_field(Slot &s, double *beta_out, hipStream_t st, bool solve) {
     const long long k = (long long)std::floor(h.target_vf * double(h.nn) + 0.5);
     SHH_HIP(launch_select_hard(s.d_slot, h.nn, k, st));
   } else if (h.mode_t == 2) {
-    SHH_HIP(launch_minmax_d(s.d_slot, h.nn, st));
-    SHH_HIP(launch_bisect_steps(s.d_slot, h.nn, 200, st));
+    SHH_HIP(launch_bisect(s.d_slot, h.nn, st));
   }
   SHH_HIP(launch_occupancy(s.d_slot, h.nn, beta_out, st));
   if (solve) SHH_HIP(launch_dinv(s.d_slot, h.nn, h.prec, st));

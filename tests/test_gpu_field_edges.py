@@ -45,6 +45,25 @@ def test_thickness_is_the_midpoint_of_two_order_statistics(n, vf):
     assert np.array_equal(r["beta"].cpu().numpy(), (r["d"].cpu().numpy() < t).astype(float))
 
 
+@pytest.mark.parametrize("n,vf,kappa", [(2, 0.4, 1e7), (3, 0.5, 30.0), (17, 0.01, 50.0), (33, 0.97, 400.0),
+                                        (128, 0.3, 256.0), (130, 0.3, 256.0)])
+def test_logistic_thickness_is_the_bisection(n, vf, kappa):
+    # three steps a pass and, past 128^3, one; (2, 1e7): a step too steep to meet
+    # the target, all 200 steps.  The volume fractions differ from the oracle's by
+    # rounding (1e-15), which can move the end of a bisection that passes 1e-12 by
+    # a step: t to 1e-9, V to the criterion
+    from paper_2511_04025_amd import api
+    d = wl.random_design(70 + n, n, N=6, vf=vf).with_(kappa=kappa)
+    print(f"logistic thickness n {n} vf {vf} kappa {kappa}", flush=True)
+    r = api.field(d)
+    dist = r["d"].cpu().numpy()
+    t = fld.thickness_for_volume(dist, vf, kappa)
+    assert abs(r["t"] - t) <= 1e-9 * max(1.0, abs(t))
+    if n > 2:
+        assert abs(r["V"] - vf) <= 1e-12 + 1e-14
+    assert np.max(np.abs(r["beta"].cpu().numpy() - fld.occupancy(dist, r["t"], kappa))) <= 1e-13
+
+
 @pytest.mark.parametrize("M", [1, 31, 32, 33, 257])
 @pytest.mark.parametrize("K", [2, 3, 4, 6])
 def test_points_around_a_workgroup(M, K):
