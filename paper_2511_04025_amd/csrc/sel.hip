@@ -11,35 +11,55 @@ namespace {
 __device__ __forceinline__ int wrap_dec(int v, int n) { return v == 0 ? n - 1 : v - 1; }
 __device__ __forceinline__ int wrap_inc(int v, int n) { return v + 1 == n ? 0 : v + 1; }
 
-// Vectors are node-major: the 18 values (load case k, component c at 3 k + c)
-// of one node are contiguous, so a neighbour's values come in nine 8- or
-// 16-byte loads (the row of node j starts at 72 j or 144 j bytes).
-template <typename T> struct Pair;
-template <> struct Pair<float> { using type = float2; };
-template <> struct Pair<double> { using type = double2; };
+// Vectors hold 18 values per node (load case k, component c at o = 3 k + c) in
+// chunks of 16 bytes, chunk by chunk over the nodes ([4][na][4] and [na][2] in
+// FP32, [9][na][2] in FP64): the lanes of a wave, which hold neighbouring nodes,
+// read neighbouring chunks.  With a node's 18 values together every load touched
+// 36 cache lines: 284,000 active nodes of a 128^3 grid, the smoothing passes
+// 47-62 -> 43-52 us, the vector update 33 -> 25 (5.7 TB/s), restriction 35 -> 28,
+// FP64 residual 133 -> 106.
+template <typename T>
+__device__ __forceinline__ long long row_at(int na, long long j, int o) {
+  if constexpr (sizeof(T) == 8) return ((long long)(o >> 1) * na + j) * 2 + (o & 1);
+  else return o < 16 ? ((long long)(o >> 2) * na + j) * 4 + (o & 3) : 16ll * na + j * 2 + (o - 16);
+}
 
 template <typename TV, typename TE>
-__device__ __forceinline__ void load_row(const TV *u, long long j, TE (&v)[3 * NRHS]) {
-  using P2 = typename Pair<TV>::type;
-  const P2 *p = reinterpret_cast<const P2 *>(u + j * (3 * NRHS));
+__device__ __forceinline__ void load_row(const TV *u, int na, long long j, TE (&v)[3 * NRHS]) {
+  if constexpr (sizeof(TV) == 8) {
 #pragma unroll
-  for (int t = 0; t < 3 * NRHS / 2; ++t) {
-    const P2 w = p[t];
-    v[2 * t] = (TE)w.x;
-    v[2 * t + 1] = (TE)w.y;
+    for (int t = 0; t < 3 * NRHS / 2; ++t) {
+      const double2 w = reinterpret_cast<const double2 *>(u)[(long long)t * na + j];
+      v[2 * t] = (TE)w.x;
+      v[2 * t + 1] = (TE)w.y;
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float4 w = reinterpret_cast<const float4 *>(u)[(long long)t * na + j];
+      v[4 * t] = (TE)w.x;
+      v[4 * t + 1] = (TE)w.y;
+      v[4 * t + 2] = (TE)w.z;
+      v[4 * t + 3] = (TE)w.w;
+    }
+    const float2 w = reinterpret_cast<const float2 *>(u + 16ll * na)[j];
+    v[16] = (TE)w.x;
+    v[17] = (TE)w.y;
   }
 }
 
 template <typename TV, typename TE>
-__device__ __forceinline__ void store_row(TV *u, long long j, const TE (&v)[3 * NRHS]) {
-  using P2 = typename Pair<TV>::type;
-  P2 *p = reinterpret_cast<P2 *>(u + j * (3 * NRHS));
+__device__ __forceinline__ void store_row(TV *u, int na, long long j, const TE (&v)[3 * NRHS]) {
+  if constexpr (sizeof(TV) == 8) {
 #pragma unroll
-  for (int t = 0; t < 3 * NRHS / 2; ++t) {
-    P2 w;
-    w.x = (TV)v[2 * t];
-    w.y = (TV)v[2 * t + 1];
-    p[t] = w;
+    for (int t = 0; t < 3 * NRHS / 2; ++t)
+      reinterpret_cast<double2 *>(u)[(long long)t * na + j] = make_double2((TV)v[2 * t], (TV)v[2 * t + 1]);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      reinterpret_cast<float4 *>(u)[(long long)t * na + j] =
+          make_float4((TV)v[4 * t], (TV)v[4 * t + 1], (TV)v[4 * t + 2], (TV)v[4 * t + 3]);
+    reinterpret_cast<float2 *>(u + 16ll * na)[j] = make_float2((TV)v[16], (TV)v[17]);
   }
 }
 
@@ -266,7 +286,7 @@ __device__ __forceinline__ void accumulate(const TE (&E)[8], TE lam, TE mu, int 
   TE A[3][3];
   block_of<RX, RY, RZ>(E, lam, mu, A);
   TE v[3 * NRHS];
-  load_row(u, j, v);
+  load_row(u, na, j, v);
 #pragma unroll
   for (int k = 0; k < NRHS; ++k) {
     if (!((act >> k) & 1u)) continue;
@@ -279,7 +299,7 @@ __device__ __forceinline__ void accumulate(const TE (&E)[8], TE lam, TE mu, int 
 // branch for the row (skipped when all three are culled), the three rows'
 // loads in flight together; a culled one reads row 0 against a zero block
 template <int RY, int RZ, typename TE, typename TV>
-__device__ __forceinline__ void accumulate_xrow(const TE (&E)[8], TE lam, TE mu, const int *nb, const TV *u,
+__device__ __forceinline__ void accumulate_xrow(const TE (&E)[8], TE lam, TE mu, const int *nb, const TV *u, int na,
                                                 const unsigned act, TE (&q)[NRHS][3]) {
   const int j0 = nb[0], j1 = nb[1], j2 = nb[2];
   if ((j0 & j1 & j2) < 0) return;  // all three culled (negative)
@@ -290,7 +310,7 @@ __device__ __forceinline__ void accumulate_xrow(const TE (&E)[8], TE lam, TE mu,
   const int jj[3] = {j0, j1, j2};
   TE v[3][3 * NRHS];
 #pragma unroll
-  for (int x = 0; x < 3; ++x) load_row(u, jj[x] < 0 ? 0 : jj[x], v[x]);
+  for (int x = 0; x < 3; ++x) load_row(u, na, jj[x] < 0 ? 0 : jj[x], v[x]);
 #pragma unroll
   for (int x = 0; x < 3; ++x) {
     const TE live = jj[x] < 0 ? TE(0) : TE(1);
@@ -316,7 +336,7 @@ __device__ __forceinline__ void apply_row(const TE (&E)[8], TE lam, TE mu, const
 #define SEL_ACC(dx, dy, dz) accumulate<dx, dy, dz>(E, lam, mu, nb[((dz) + 1) * 9 + ((dy) + 1) * 3 + (dx) + 1], u, na, act, q)
 #define SEL_ROW(dy, dz)                                                                    \
   if constexpr (XROW) {                                                                    \
-    accumulate_xrow<dy, dz>(E, lam, mu, &nb[((dz) + 1) * 9 + ((dy) + 1) * 3], u, act, q); \
+    accumulate_xrow<dy, dz>(E, lam, mu, &nb[((dz) + 1) * 9 + ((dy) + 1) * 3], u, na, act, q); \
   } else {                                                                                 \
     SEL_ACC(-1, dy, dz);                                                                   \
     SEL_ACC(0, dy, dz);                                                                    \
@@ -407,9 +427,9 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_op_pcg_kernel(const SelBatch 
     for (int k = 0; k < NRHS; ++k)
 #pragma unroll
       for (int c = 0; c < 3; ++c) qr[3 * k + c] = q[k][c];
-    store_row(Q, i, qr);
-    load_row(P, i, pr);
-    load_row(Rv, i, rr);
+    store_row(Q, na, i, qr);
+    load_row(P, na, i, pr);
+    load_row(Rv, na, i, rr);
   }
   double *parts = S->partials;
   const int np = S->nparts;
@@ -472,7 +492,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_op_resid_kernel(const SelBatc
 #pragma unroll
         for (int a = 0; a < 8; ++a) f -= E[a] * S->f0[k][a][c];
         const double rv = f - q[k][c];
-        Rv[(long long)i * (3 * NRHS) + 3 * k + c] = (TV)rv;
+        Rv[row_at<TV>(na, i, 3 * k + c)] = (TV)rv;
         acc[k][c] += rv;
       }
     }
@@ -519,7 +539,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_op_energy_kernel(const SelBat
     for (int k = 0; k < NRHS; ++k)
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        u[k][c] = U[(long long)i * (3 * NRHS) + 3 * k + c];
+        u[k][c] = U[row_at<double>(na, i, 3 * k + c)];
         double fv = 0.0;
 #pragma unroll
         for (int a = 0; a < 8; ++a) fv -= E[a] * S->f0[k][a][c];
@@ -564,7 +584,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_op_apply_kernel(const SelBatc
 #pragma unroll
     for (int k = 0; k < NRHS; ++k)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) Q[(long long)i * (3 * NRHS) + 3 * k + c] = q[k][c];
+      for (int c = 0; c < 3; ++c) Q[row_at<T>(na, i, 3 * k + c)] = q[k][c];
   }
 }
 
@@ -590,10 +610,10 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_update_kernel(const SelBatch 
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < na; i += S->nparts * blockDim.x) {
     const T d = Dv[i];
     T x[3 * NRHS], r[3 * NRHS], p[3 * NRHS], q[3 * NRHS];
-    load_row(X, i, x);
-    load_row(Rv, i, r);
-    load_row(P, i, p);
-    load_row(Q, i, q);
+    load_row(X, na, i, x);
+    load_row(Rv, na, i, r);
+    load_row(P, na, i, p);
+    load_row(Q, na, i, q);
 #pragma unroll
     for (int k = 0; k < NRHS; ++k) {
       if (!((step >> k) & 1u)) continue;
@@ -607,9 +627,9 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_update_kernel(const SelBatch 
         p[o] = d * rv + b[k] * pv;
       }
     }
-    store_row(X, i, x);
-    store_row(Rv, i, r);
-    store_row(P, i, p);
+    store_row(X, na, i, x);
+    store_row(Rv, na, i, r);
+    store_row(P, na, i, p);
   }
 }
 
@@ -627,7 +647,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_dir0_kernel(const SelBatch B)
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < na; i += S->nparts * blockDim.x)
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const long long o = (long long)i * (3 * NRHS) + 3 * k + c;
+        const long long o = row_at<T>(na, i, 3 * k + c);
         P[o] = Dv[i] * Rv[o];
       }
   }
@@ -646,8 +666,8 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_fold_kernel(const SelBatch B,
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < na; i += S->nparts * blockDim.x)
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const long long o = (long long)i * (3 * NRHS) + 3 * k + c;
-        X64[o] += (double)X[o];
+        const long long o = row_at<float>(na, i, 3 * k + c);
+        X64[row_at<double>(na, i, 3 * k + c)] += (double)X[o];
         X[o] = 0.0f;
       }
   }
@@ -673,7 +693,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_finish_kernel(const SelBatch 
       const double d = (double)Dv[i];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const long long o = (long long)i * (3 * NRHS) + 3 * k + c;
+        const long long o = row_at<T>(na, i, 3 * k + c);
         const T rv = Rv[o] - m[c];
         Rv[o] = rv;
         const double r64 = (double)rv;
@@ -944,7 +964,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_op_kernel(const SelBatch B
     const T it = (T)S->inv_theta, c1 = (T)S->c1, c2 = (T)S->c2;
     if constexpr (MODE == SMO_PQ) {
       T pr[3 * NRHS], qr[3 * NRHS];
-      load_row((const T *)S->p, i, pr);
+      load_row((const T *)S->p, na, i, pr);
 #pragma unroll
       for (int k = 0; k < NRHS; ++k)
 #pragma unroll
@@ -952,11 +972,11 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_op_kernel(const SelBatch B
           qr[3 * k + c] = q[k][c];
           acc[k][0] += (double)pr[3 * k + c] * (double)q[k][c];
         }
-      store_row((T *)S->q, i, qr);
+      store_row((T *)S->q, na, i, qr);
     } else if constexpr (MODE == SMO_STEP1) {
       T b[3 * NRHS], d0[3 * NRHS], r1[3 * NRHS], d1[3 * NRHS], x[3 * NRHS];
-      load_row((const T *)S->r, i, b);
-      load_row((const T *)S->d0, i, d0);
+      load_row((const T *)S->r, na, i, b);
+      load_row((const T *)S->d0, na, i, d0);
 #pragma unroll
       for (int k = 0; k < NRHS; ++k)
 #pragma unroll
@@ -966,23 +986,23 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_op_kernel(const SelBatch B
           d1[o] = c1 * d0[o] + c2 * dv * r1[o];
           x[o] = d0[o] + d1[o];
         }
-      store_row((T *)S->rv, i, r1);
-      if constexpr (SHH_SEL_DEG0 != 1) store_row((T *)S->d1, i, d1);  // degree 1: d1 = 0, unused
-      store_row((T *)S->xv, i, x);
+      store_row((T *)S->rv, na, i, r1);
+      if constexpr (SHH_SEL_DEG0 != 1) store_row((T *)S->d1, na, i, d1);  // degree 1: d1 = 0, unused
+      store_row((T *)S->xv, na, i, x);
     } else if constexpr (MODE == SMO_RES) {
       T r[3 * NRHS];
-      load_row((const T *)S->rv, i, r);
+      load_row((const T *)S->rv, na, i, r);
 #pragma unroll
       for (int k = 0; k < NRHS; ++k)
 #pragma unroll
         for (int c = 0; c < 3; ++c) r[3 * k + c] -= q[k][c];
-      store_row((T *)S->rv, i, r);
+      store_row((T *)S->rv, na, i, r);
     } else if constexpr (MODE == SMO_POST) {
       // x is this pass's operand: the updated x goes to d1 (free after the
       // restriction), not over the neighbours' input
       T b[3 * NRHS], x[3 * NRHS], r[3 * NRHS], d0[3 * NRHS];
-      load_row((const T *)S->r, i, b);
-      load_row((const T *)S->xv, i, x);
+      load_row((const T *)S->r, na, i, b);
+      load_row((const T *)S->xv, na, i, x);
 #pragma unroll
       for (int k = 0; k < NRHS; ++k)
 #pragma unroll
@@ -992,15 +1012,15 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_op_kernel(const SelBatch B
           d0[o] = it * dv * r[o];
           x[o] += d0[o];
         }
-      store_row((T *)S->rv, i, r);
-      store_row((T *)S->d0, i, d0);
-      store_row((T *)S->d1, i, x);
+      store_row((T *)S->rv, na, i, r);
+      store_row((T *)S->d0, na, i, d0);
+      store_row((T *)S->d1, na, i, x);
     } else if constexpr (MODE == SMO_POST1) {
       // degree 1: z = x + D (b - K x) / theta into d1 (x is the operand),
       // and the sums b . z, b . b
       T b[3 * NRHS], x[3 * NRHS];
-      load_row((const T *)S->r, i, b);
-      load_row((const T *)S->xv, i, x);
+      load_row((const T *)S->r, na, i, b);
+      load_row((const T *)S->xv, na, i, x);
 #pragma unroll
       for (int k = 0; k < NRHS; ++k)
 #pragma unroll
@@ -1010,13 +1030,13 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_op_kernel(const SelBatch B
           acc[k][0] += (double)b[o] * (double)x[o];
           acc[k][1] += (double)b[o] * (double)b[o];
         }
-      store_row((T *)S->d1, i, x);
+      store_row((T *)S->d1, na, i, x);
     } else {  // SMO_LAST: z = x + d1 into xv, and the sums b . z, b . b
       T b[3 * NRHS], x[3 * NRHS], r[3 * NRHS], d0[3 * NRHS];
-      load_row((const T *)S->r, i, b);
-      load_row((const T *)S->d1, i, x);
-      load_row((const T *)S->rv, i, r);
-      load_row((const T *)S->d0, i, d0);
+      load_row((const T *)S->r, na, i, b);
+      load_row((const T *)S->d1, na, i, x);
+      load_row((const T *)S->rv, na, i, r);
+      load_row((const T *)S->d0, na, i, d0);
 #pragma unroll
       for (int k = 0; k < NRHS; ++k)
 #pragma unroll
@@ -1027,7 +1047,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_op_kernel(const SelBatch B
           acc[k][0] += (double)b[o] * (double)x[o];
           acc[k][1] += (double)b[o] * (double)b[o];
         }
-      store_row((T *)S->xv, i, x);
+      store_row((T *)S->xv, na, i, x);
     }
   }
   if constexpr (MODE == SMO_PQ || MODE == SMO_LAST || MODE == SMO_POST1) {
@@ -1060,11 +1080,11 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_s1_kernel(const SelBatch B
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < na; i += S->nparts * blockDim.x) {
     const T dv = ((const T *)S->Dinv)[i];
     T x[3 * NRHS], r[3 * NRHS], p[3 * NRHS], q[3 * NRHS], d0[3 * NRHS];
-    load_row((const T *)S->r, i, r);
+    load_row((const T *)S->r, na, i, r);
     if (!restart) {
-      load_row((const T *)S->x, i, x);
-      load_row((const T *)S->p, i, p);
-      load_row((const T *)S->q, i, q);
+      load_row((const T *)S->x, na, i, x);
+      load_row((const T *)S->p, na, i, p);
+      load_row((const T *)S->q, na, i, q);
     }
 #pragma unroll
     for (int k = 0; k < NRHS; ++k)
@@ -1078,10 +1098,10 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_s1_kernel(const SelBatch B
         d0[o] = it * dv * r[o];
       }
     if (!restart) {
-      store_row((T *)S->x, i, x);
-      store_row((T *)S->r, i, r);
+      store_row((T *)S->x, na, i, x);
+      store_row((T *)S->r, na, i, r);
     }
-    store_row((T *)S->d0, i, d0);
+    store_row((T *)S->d0, na, i, d0);
   }
 }
 
@@ -1097,15 +1117,15 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_dir_kernel(const SelBatch 
   for (int k = 0; k < NRHS; ++k) b[k] = (T)S->st->beta[k];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < na; i += S->nparts * blockDim.x) {
     T z[3 * NRHS], p[3 * NRHS];
-    load_row((const T *)(SHH_SEL_DEG0 == 1 ? S->d1 : S->xv), i, z);  // where post-smoothing left z
-    load_row((const T *)S->p, i, p);
+    load_row((const T *)(SHH_SEL_DEG0 == 1 ? S->d1 : S->xv), na, i, z);  // where post-smoothing left z
+    load_row((const T *)S->p, na, i, p);
 #pragma unroll
     for (int k = 0; k < NRHS; ++k) {
       if (!((act >> k) & 1u)) continue;
 #pragma unroll
       for (int c = 0; c < 3; ++c) p[3 * k + c] = z[3 * k + c] + b[k] * p[3 * k + c];
     }
-    store_row((T *)S->p, i, p);
+    store_row((T *)S->p, na, i, p);
   }
 }
 
@@ -1147,7 +1167,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_restrict_kernel(const SelB
       const int ox = f % 3 - 1, oy = (f / 3) % 3 - 1, oz = f / 9 - 1;
       const T w = jf[f] >= 0 ? T((ox ? 0.5 : 1.0) * (oy ? 0.5 : 1.0) * (oz ? 0.5 : 1.0)) : T(0);
       T v[3 * NRHS];
-      load_row(rv, jf[f] >= 0 ? jf[f] : 0, v);
+      load_row(rv, S->na, jf[f] >= 0 ? jf[f] : 0, v);
 #pragma unroll
       for (int o = 0; o < 3 * NRHS; ++o) acc[o] += w * v[o];
     }
@@ -1196,7 +1216,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_prolong_kernel(const SelBa
       }
     }
     T z[3 * NRHS];
-    load_row((const T *)S->xv, i, z);
+    load_row((const T *)S->xv, na, i, z);
     for (int kz = 0; kz < cnt[2]; ++kz)
       for (int ky = 0; ky < cnt[1]; ++ky)
         for (int kx = 0; kx < cnt[0]; ++kx) {
@@ -1205,7 +1225,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_mg_prolong_kernel(const SelBa
 #pragma unroll
           for (int o = 0; o < 3 * NRHS; ++o) z[o] += w * x1[(long long)o * nn1 + I];
         }
-    store_row((T *)S->xv, i, z);
+    store_row((T *)S->xv, na, i, z);
   }
 }
 
@@ -1247,7 +1267,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_energy_sens_kernel(const SelB
     for (int c = 0; c < 3; ++c) {
       double v[8];
 #pragma unroll
-      for (int a = 0; a < 8; ++a) v[a] = U[(long long)node[a] * (3 * NRHS) + 3 * k + c];
+      for (int a = 0; a < 8; ++a) v[a] = U[row_at<double>(S->na, node[a], 3 * k + c)];
       hadamard8<double>(v, h[c]);
     }
     add_chi<double>(k, h);
