@@ -32,13 +32,13 @@ COPY_CEILING_GBS = 4912.5  # best of five 4 GiB copies (mean 4891.5)
 
 # Measured memory traffic of the dominant kernel relative to its algorithmic
 # bytes (rocprofv3 FETCH_SIZE x 2 and WRITE_SIZE x 1, the factors the 4 GiB
-# stream copy gives; profiles/mg_apply_128_hbm_traffic.md), keyed by kernel
+# stream copy gives; profiles/mg_voxel_128_counters.md), keyed by kernel
 # family.  The counters count L2-to-fabric bytes, last-level-cache hits
 # included, so the figure bounds HBM traffic from above.  It holds only for
 # the kernel sources it was measured on (digest), null otherwise.
 TRAFFIC = {
-    "mg_apply1": {"ratio": 1.87, "sources": ["mg.hip", "mg.hpp", "common.hpp"],
-                  "sha256": "722819f5a030965320042ddc7a7ee96a57fb468c25582d89fd867fff0140f3b0"},
+    "mg_dir": {"ratio": 1.11, "sources": ["stencil.hip", "hexop.hpp"],
+               "sha256": "89cff14f16f412b4e4a33e09fcf39ffc188fb4e0780a711cf793aefa4c295687"},
 }
 
 
@@ -55,31 +55,26 @@ def traffic_ratio(kind):
     return t["ratio"] if h.hexdigest() == t["sha256"] else None
 
 
-def family_bytes(results, n, R, solver, deg0=1):
+def family_bytes(results, n, R, solver, deg0=2):
     """Algorithmic HBM bytes per kernel family over the given results (FP32
     vectors, 12 B per node and load case per vector; a design's per-node data
     -- moduli, D^-1, coarse stencils -- counts once per iteration in which any
     of its load cases runs).  Only the work that each design's iteration
     counts imply is counted: restarted V-cycles after a residual replacement
     are not, so the figures are lower bounds.
-      multigrid voxel level, per (node, load case), with the voxel level's
-      Chebyshev degree deg0 (the library's build option; 1 by default):
-        direction pass  48 (z, p read; p, q written) + 4 E per node
-        pre-smoothing   48 (b staged; r, d1, x written) + 8 (E, D^-1) per node;
-                        degree 1: 36 (b staged; r, x written) + 8
-        r - K d1        36 (d1 staged, r read, r written) + 4 (degree 2 only)
-        post-smoothing  36 (x staged, b read, r written) + 4 (degree 2 only)
-        last sweep      48 (r staged; b, x read; x written) + 8; degree 1 the
-                        one post-smoothing pass: 36 (x staged, b read, z
-                        written) + 8
-        CG update       72 (x, p, b, q read; x, b written)
-        restriction     12 fine read + 12 per coarse node written
-        prolongation    24 fine read and written + 12 per coarse node read
-      first coarse level operator, 4 per iteration, each with the Chebyshev
-        sweep after it in its output stage: 504 B of stencil per coarse node
-        per pass + 36 B of D^-1 per coarse node, and per (coarse node, load
-        case) 60 (d, b read; r, x, d1 written) + 36 (d1, r read; r written)
-        + 60 (x, b read; r, d, x + d written) + 48 (d, x + d, r read; x written)
+      multigrid voxel level, per (node, load case):
+        direction pass  72 (z, p, x read; p, q, x written) + 4 E per node
+        pre-smoothing   36 (r, q read; r written) + 8 (E, D^-1) per node + 12 per
+                        coarse node and load case (the restriction's shares)
+        post-smoothing  24 (r read, z written) + 8 per node + 12 per coarse node
+                        and load case (the correction)
+        restriction     36 per coarse node and load case (shares read; b, d
+                        written) + 12 (D^-1) per coarse node
+      first coarse level operator with the sweeps in its output stage: per
+        coarse node and pass 32 (moduli) from 34^3 nodes, else 504 (stencil),
+        and 12 (D^-1) per sweep that takes it; per (coarse node, load case)
+        from 24^3 nodes two passes, 48 (d, b read; r, x written) + 36 (b, x
+        read; q written); else four, 60 + 36 + 60 + 48
       FP64 residual: 24 (x64) + 12 (r) per (node, load case) + 8 (E) per node,
         every R iterations and once at the end
       Jacobi CG pass: 96 per (node, load case) + 8 per node
@@ -124,19 +119,16 @@ def family_bytes(results, n, R, solver, deg0=1):
         if solver == "jacobi":
             out["cg_pass"] += 96.0 * nn * Ik + 8.0 * nn * Im
             continue
-        out["mg_dir"] += 48.0 * nn * Ik + 4.0 * nn * Im
-        if deg0 == 1:
-            out["mg_step1"] += 36.0 * nn * Ik + 8.0 * nn * Im
-            out["mg_last"] += 36.0 * nn * Ik + 8.0 * nn * Im
+        n1 = n // 2
+        level1 = 32.0 if n1 > 32 else 504.0
+        out["mg_dir"] += 72.0 * nn * Ik + 4.0 * nn * Im
+        out["mg_step1"] += (36.0 * nn + 12.0 * nn1) * Ik + 8.0 * nn * Im
+        out["mg_last"] += (24.0 * nn + 12.0 * nn1) * Ik + 8.0 * nn * Im
+        out["mg_restrict"] += 36.0 * nn1 * Ik + 12.0 * nn1 * Im
+        if n1 >= 24:
+            out["mg_apply1"] += (2 * level1 + 12.0) * nn1 * Im + 84.0 * nn1 * Ik
         else:
-            out["mg_step1"] += 48.0 * nn * Ik + 8.0 * nn * Im
-            out["mg_res"] += 36.0 * nn * Ik + 4.0 * nn * Im
-            out["mg_post"] += 36.0 * nn * Ik + 4.0 * nn * Im
-            out["mg_last"] += 48.0 * nn * Ik + 8.0 * nn * Im
-        out["mg_update"] += 72.0 * nn * Ik
-        out["mg_restrict"] += (12.0 * nn + 12.0 * nn1) * Ik
-        out["mg_prolong"] += (24.0 * nn + 12.0 * nn1) * Ik
-        out["mg_apply1"] += (4 * 504.0 + 36.0) * nn1 * Im + 204.0 * nn1 * Ik
+            out["mg_apply1"] += (4 * level1 + 36.0) * nn1 * Im + 204.0 * nn1 * Ik
     return out
 
 
@@ -434,13 +426,9 @@ def main():
     # per-family roofline: algorithmic bytes implied by the iteration counts
     # over the event-timed milliseconds of that family's launches
     R = args.recompute_every if args.recompute_every > 0 else (10 if args.solver == "selective" else 50)
-    # the voxel level's smoothing degree, from the passes that ran: degree 2
-    # has the r - K d1 pass (dense) or two smoothing passes per transfer
-    # (selective)
-    if args.solver == "selective":
-        deg0 = 2 if fam["sel_mg_smooth"][0] > fam["sel_mg_transfer"][0] else 1
-    else:
-        deg0 = 2 if fam["mg_res"][0] > 0 else 1
+    # the selective solve's voxel-level smoothing degree, from the passes that
+    # ran: degree 2 has two smoothing passes per transfer
+    deg0 = 1 if 0 < fam["sel_mg_smooth"][0] <= fam["sel_mg_transfer"][0] else 2
     fbytes = family_bytes(all_res, args.n, R, args.solver, deg0)
     kernels = {}
     for name, (nl, ms) in fam.items():

@@ -126,7 +126,8 @@ typedef struct {
                                SHH_SOLVER_SELECTIVE -- / 0 FP64; the true residual is
                                always recomputed at the end)                             */
   int32_t save_for_backward;/* keep F, grad F and the solution for shh_grad               */
-  int32_t check_every;      /* host polls convergence every this many iterations (0: 16) */
+  int32_t check_every;      /* host polls convergence every this many iterations (0: when
+                               a load case is due by its rate so far, 2 to 64 apart)     */
   int32_t solver;           /* SHH_SOLVER_JACOBI (0): Jacobi-preconditioned CG, one fused
                                pass per iteration; SHH_SOLVER_MG (1): CG preconditioned by
                                a geometric multigrid V-cycle (Sec. 4.2's solver family:
@@ -330,15 +331,15 @@ int32_t shh_grad_batch(const shh_design *designs, int32_t count, const shh_opts 
    state besides a small cache of constants per Poisson ratio; neither holds
    design data).  Families: */
 #define SHH_PROF_CG_PASS      0  /* Jacobi-PCG: the fused pass, q = K p with the vector updates */
-#define SHH_PROF_MG_DIR       1  /* multigrid CG, voxel level: p = z + beta p, q = K p, p.q     */
-#define SHH_PROF_MG_STEP1     2  /*   operator fused with the first pre-smoothing sweep         */
-#define SHH_PROF_MG_RES       3  /*   r - K d1 (the residual the restriction takes)            */
-#define SHH_PROF_MG_POST      4  /*   operator fused with the first post-smoothing sweep        */
-#define SHH_PROF_MG_LAST      5  /*   operator fused with the last sweep and the r.z partials   */
-#define SHH_PROF_MG_UPDATE    6  /*   CG update x += alpha p, r -= alpha q                     */
-#define SHH_PROF_MG_RESTRICT  7  /*   restriction to the first coarse level                    */
-#define SHH_PROF_MG_PROLONG   8  /*   prolongation from the first coarse level                 */
-#define SHH_PROF_MG_APPLY1    9  /* multigrid, first coarse level: q = A_1 v (27-point blocks)  */
+#define SHH_PROF_MG_DIR       1  /* multigrid CG, voxel level: x += alpha p, p = z + beta p, q = K p, p.q */
+#define SHH_PROF_MG_STEP1     2  /*   r -= alpha q and the pre-smoothing step (FP32: with its restriction) */
+#define SHH_PROF_MG_RES       3  /*   (no launches: the residual is part of the pass before)   */
+#define SHH_PROF_MG_POST      4  /*   (no launches)                                             */
+#define SHH_PROF_MG_LAST      5  /*   coarse correction, post-smoothing step, r.z partials      */
+#define SHH_PROF_MG_UPDATE    6  /*   (no launches: the CG update is part of the passes)        */
+#define SHH_PROF_MG_RESTRICT  7  /*   restriction to the first coarse level (FP32: gathered)   */
+#define SHH_PROF_MG_PROLONG   8  /*   (no launches: part of the post-smoothing pass)            */
+#define SHH_PROF_MG_APPLY1    9  /* multigrid, first coarse level: q = A_1 v with its sweeps    */
 #define SHH_PROF_RESID64     10  /* FP64 residual f - K u (replacement and final check)         */
 #define SHH_PROF_SEL_OP      11  /* selective solve: q = K p on the active nodes, with the sums  */
 #define SHH_PROF_SEL_UPDATE  12  /*   x += alpha p, r -= alpha q, p = D^-1 r + beta p            */
