@@ -357,20 +357,26 @@ __device__ __forceinline__ double logistic(double kappa, double t, double d) {
   return e / (1.0 + e);
 }
 
-// min and max of d by workgroup
-__global__ __launch_bounds__(BIS_T) void minmax_d_kernel(SlotDev *s, int nblocks) {
-  __shared__ double red[2][BIS_T / 64];
-  const long long nn = s->nn;
-  double mn = INFINITY, mx = 0.0;  // distances are not negative
-  for (long long i = (long long)blockIdx.x * BIS_T + threadIdx.x; i < nn; i += (long long)nblocks * BIS_T) {
-    const double d = s->d[i];
-    mn = d < mn ? d : mn;
-    mx = d > mx ? d : mx;
-  }
+// min and max of d by workgroup, as bit patterns (non-negative doubles order like
+// them, +inf and a NaN last)
+__device__ __forceinline__ void wave_minmax(unsigned long long &mn, unsigned long long &mx) {
   for (int off = 32; off > 0; off >>= 1) {
-    mn = fmin(mn, __shfl_xor(mn, off, 64));
-    mx = fmax(mx, __shfl_xor(mx, off, 64));
+    const unsigned long long a = __shfl_xor(mn, off, 64), b = __shfl_xor(mx, off, 64);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
   }
+}
+
+__global__ __launch_bounds__(BIS_T) void minmax_d_kernel(SlotDev *s, int nblocks) {
+  __shared__ unsigned long long red[2][BIS_T / 64];
+  const long long nn = s->nn;
+  unsigned long long mn = ~0ull, mx = 0ull;
+  for (long long i = (long long)blockIdx.x * BIS_T + threadIdx.x; i < nn; i += (long long)nblocks * BIS_T) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(s->d[i]);
+    mn = b < mn ? b : mn;
+    mx = b > mx ? b : mx;
+  }
+  wave_minmax(mn, mx);
   if ((threadIdx.x & 63) == 0) {
     red[0][threadIdx.x >> 6] = mn;
     red[1][threadIdx.x >> 6] = mx;
@@ -378,27 +384,26 @@ __global__ __launch_bounds__(BIS_T) void minmax_d_kernel(SlotDev *s, int nblocks
   __syncthreads();
   if (threadIdx.x != 0) return;
   for (int w = 1; w < BIS_T / 64; ++w) {
-    mn = fmin(mn, red[0][w]);
-    mx = fmax(mx, red[1][w]);
+    mn = red[0][w] < mn ? red[0][w] : mn;
+    mx = red[1][w] > mx ? red[1][w] : mx;
   }
-  s->partials[8 * blockIdx.x] = mn;
-  s->partials[8 * blockIdx.x + 1] = mx;
+  unsigned long long *part = (unsigned long long *)s->partials + 2 * blockIdx.x;
+  part[0] = mn;
+  part[1] = mx;
 }
 
 __global__ __launch_bounds__(64) void bisect_init_kernel(SlotDev *s, int nblocks) {
-  double mn = INFINITY, mx = 0.0;
+  const unsigned long long *part = (const unsigned long long *)s->partials;
+  unsigned long long mn = ~0ull, mx = 0ull;
   for (int b = threadIdx.x; b < nblocks; b += 64) {
-    mn = fmin(mn, s->partials[8 * b]);
-    mx = fmax(mx, s->partials[8 * b + 1]);
+    mn = part[2 * b] < mn ? part[2 * b] : mn;
+    mx = part[2 * b + 1] > mx ? part[2 * b + 1] : mx;
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    mn = fmin(mn, __shfl_xor(mn, off, 64));
-    mx = fmax(mx, __shfl_xor(mx, off, 64));
-  }
+  wave_minmax(mn, mx);
   if (threadIdx.x != 0) return;
   BisState b;
-  b.lo = mn - 40.0 / s->kappa;
-  b.hi = mx + 40.0 / s->kappa;
+  b.lo = __longlong_as_double((long long)mn) - 40.0 / s->kappa;
+  b.hi = __longlong_as_double((long long)mx) + 40.0 / s->kappa;
   b.t = 0.5 * (b.lo + b.hi);
   b.done = 0;
   b.steps = 0;
