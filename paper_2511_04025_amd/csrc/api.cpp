@@ -326,7 +326,7 @@ static int moduli_slot(Slot &s, int32_t n, const void *d_E, double nu, const shh
 
 // The launch of an operator call: its segment was uploaded with the slot.
 static LaunchArgs operator_launch(const Slot &s, const OperatorSegment &op) {
-  LaunchArgs la{(const Segment *)(s.base + s.lay.alpha), 1, s.host.ntiles[op.tiling] * op.nrhs};
+  LaunchArgs la{(const Segment *)(s.base + s.lay.alpha), 1, s.host.ntiles[op.residual ? s.host.wr : s.host.wt] * op.nrhs};
   la.split_evenly();
   return la;
 }
@@ -398,14 +398,14 @@ int32_t shh_apply_stiffness(int32_t n, int32_t precision, const double *d_E, dou
   SHH_TRY(normalize_opts(&o, &o));
   hipStream_t st = (hipStream_t)hip_stream;
   Slot s;
-  const OperatorSegment op{precision == SHH_PREC_MIXED ? 1 : 0, nrhs, 0};
+  const OperatorSegment op{false, nrhs, 0};
   SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, nullptr, false, SHH_EDTYPE_F64, 0.0, 0.0,
                       [&](SlotDev &h) {
                         h.p[0] = const_cast<void *>(d_p);
                         h.q[0] = d_q;
                       },
                       &op));
-  SHH_HIP(launch_stencil_apply(operator_launch(s, op), precision, st));
+  SHH_HIP(launch_stencil_apply(operator_launch(s, op), s.host.wt, st));
   return operator_finish(s, st);
 }
 
@@ -440,10 +440,10 @@ int32_t shh_load_vectors(int32_t n, const double *d_E, double nu, double *d_f, v
   SHH_TRY(normalize_opts(&o, &o));
   hipStream_t st = (hipStream_t)hip_stream;
   Slot s;
-  const OperatorSegment op{0, NRHS, RES_INIT};  // FP64 residual kernel
+  const OperatorSegment op{true, NRHS, RES_INIT};
   SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, nullptr, false, SHH_EDTYPE_F64, 0.0, 0.0,
                       [&](SlotDev &h) { h.r[0] = d_f; }, &op));
-  SHH_HIP(launch_stencil_resid(operator_launch(s, op), SHH_PREC_FP64, st));
+  SHH_HIP(launch_stencil_resid(operator_launch(s, op), SHH_PREC_FP64, s.host.wr, st));
   return operator_finish(s, st);
 }
 

@@ -32,6 +32,9 @@ constexpr int MAXB = 2 * MAXK + 1;  // 1D basis functions per axis: 1, cos, sin 
 #ifndef SHH_F64_TILE_X
 #define SHH_F64_TILE_X 32
 #endif
+#ifndef SHH_F64_TALL_Y
+#define SHH_F64_TALL_Y 14
+#endif
 #ifndef SHH_F64_TILE_Y
 #define SHH_F64_TILE_Y 8
 #endif
@@ -40,12 +43,16 @@ template <typename TC> struct TileDims;
 template <> struct TileDims<float> { static constexpr int X = SHH_F32_TILE_X, Y = SHH_F32_TILE_Y; };
 template <> struct TileDims<double> { static constexpr int X = SHH_F64_TILE_X, Y = SHH_F64_TILE_Y; };
 
-// Index of a compute precision's tiling in the per-slot tile counts.
-template <typename TC> constexpr int tiling_of() { return sizeof(TC) == 4 ? 1 : 0; }
+// Tilings, by their index in the per-slot tile counts: the FP64 kernels have a
+// second, tall one (runtime.cpp::tiling_for says which a slot takes).
+enum { TILING_F64 = 0, TILING_F32 = 1, TILING_F64_TALL = 2, NTILING = 3 };
+template <typename TC, bool TALL> constexpr int tiling_of() {
+  return sizeof(TC) == 4 ? TILING_F32 : (TALL ? TILING_F64_TALL : TILING_F64);
+}
 
-template <typename TC>
+template <typename TC, bool TALL = false>
 struct Tile {
-  static constexpr int X = TileDims<TC>::X, Y = TileDims<TC>::Y;
+  static constexpr int X = TileDims<TC>::X, Y = TALL ? SHH_F64_TALL_Y : TileDims<TC>::Y;
   static constexpr int HX = X + 2, HY = Y + 2;        // node halo tile
   static constexpr int EXC = X + 1, EYC = Y + 1;      // element columns needed by the tile
   static constexpr int NHALO = HX * HY;
@@ -103,7 +110,8 @@ struct SlotDev {
   int n;
   int prec;             // 0 FP64, 1 mixed
   long long nn;         // n^3
-  int tiles_x[2], tiles_y[2], ntiles[2];  // by tiling: [0] FP64-compute, [1] FP32-compute kernels
+  int tiles_x[NTILING], tiles_y[NTILING], ntiles[NTILING];  // by tiling
+  int wt, wr;           // tiling of the slot's operator passes and of its FP64 residual
   int tiles_z, tz;
   int nchunks;
   int K, nb, N;

@@ -22,11 +22,11 @@ hipError_t launch_dinv(SlotDev *d_slot, long long nn, int prec, hipStream_t st);
 
 // stencil.hip (segments of (slot, load case, tile)); the PCG launch is one
 // whole CG iteration of every listed load case
-hipError_t launch_stencil_pcg(const LaunchArgs &la, int prec, hipStream_t st);
-hipError_t launch_stencil_resid(const LaunchArgs &la, int prec, hipStream_t st);
-hipError_t launch_stencil_apply(const LaunchArgs &la, int prec, hipStream_t st);
+hipError_t launch_stencil_pcg(const LaunchArgs &la, int tiling, hipStream_t st);
+hipError_t launch_stencil_resid(const LaunchArgs &la, int prec, int tiling, hipStream_t st);
+hipError_t launch_stencil_apply(const LaunchArgs &la, int tiling, hipStream_t st);
 // multigrid voxel-level passes (op: SMG_DIR, SMG_PRE, SMG_POST)
-hipError_t launch_stencil_mg(const LaunchArgs &la, int prec, int op, hipStream_t st);
+hipError_t launch_stencil_mg(const LaunchArgs &la, int tiling, int op, hipStream_t st);
 
 // cg.hip (segments of (slot, load case, chunk); fold/zero use one case per slot)
 hipError_t launch_finish_resid(const LaunchArgs &la, int prec, hipStream_t st);

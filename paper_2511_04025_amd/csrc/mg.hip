@@ -832,7 +832,7 @@ __global__ __launch_bounds__(VEC_THREADS) void mg_scalar_kernel(MgBatch B, int p
   CgState *st = s->st;
   const double *parts = s->partials + (long long)k * s->maxparts * PSTRIDE;
   double tot[2];
-  sum_partials<2, PSTRIDE>(parts, s->ntiles[s->prec], tot, red, VEC_THREADS);
+  sum_partials<2, PSTRIDE>(parts, s->ntiles[s->wt], tot, red, VEC_THREADS);
   if (threadIdx.x != 0) return;
   // the passes before this ran for the active load cases only
   if (!st->active[k]) return;

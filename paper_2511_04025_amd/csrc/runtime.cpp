@@ -165,6 +165,27 @@ int next_poll(const std::vector<Slot *> &slots, int fixed) {
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
+// The tiling of a slot's operator passes.  FP64: 32 x 14 nodes keep eight waves on
+// a CU (one workgroup; the passes' registers allow no more), 32 x 8 five, or ten where
+// two workgroups fit.  Multigrid takes the tall tile where it costs at most a
+// fifteenth more waves than the other (48^3 12.7 -> 11.0 ms, 64^3 17.4 -> 14.5, 96^3
+// 38.6 -> 29.8), the Jacobi CG where it costs none (25^3 10.4 -> 8.3, 101^3 709 ->
+// 677; flat stays 71^3, where tall took 203 for 187).  Below 25^3 every pass is flat
+// (24^3 multigrid 11.3, tall 11.6).  It depends on the grid and solver alone.
+static int tile_x(int tiling) { return tiling == TILING_F32 ? Tile<float>::X : Tile<double>::X; }
+static int tile_y(int tiling) {
+  return tiling == TILING_F32 ? Tile<float>::Y : (tiling == TILING_F64 ? Tile<double>::Y : Tile<double, true>::Y);
+}
+static int tile_count(int n, int tiling) {
+  return ((n + tile_x(tiling) - 1) / tile_x(tiling)) * ((n + tile_y(tiling) - 1) / tile_y(tiling));
+}
+static int tiling_for(int n, int prec, int solver) {
+  if (prec != SHH_PREC_FP64) return TILING_F32;
+  const int tall = tile_count(n, TILING_F64_TALL) * (Tile<double, true>::THREADS / 64);
+  const int flat = tile_count(n, TILING_F64) * (Tile<double>::THREADS / 64);
+  return n >= 25 && (solver == SHH_SOLVER_MG ? 15 * tall <= 16 * flat : tall <= flat) ? TILING_F64_TALL : TILING_F64;
+}
+
 // z planes per stencil workgroup (the z-march length) of an n^3 grid.  One
 // design's six load cases are tiles x runs x 6 workgroups on 512 places (two
 // workgroups on each of 256 CUs); a workgroup of tz planes takes about tz + 3
@@ -176,11 +197,10 @@ static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 // 24^3 in FP64 27.6 -> 19.9 ms), balanced rounds on larger grids (128^3: 26,
 // where 32 left the third round at 6 %).  It depends on the grid and precision
 // alone, so a design's result does not depend on its batch.
-static int tz_for(int n, int prec) {
-  const int w = prec == SHH_PREC_FP64 ? 0 : 1;
-  const long long places = w ? 256 * (1024 / Tile<float>::THREADS) : 512;
-  const int X = w ? Tile<float>::X : Tile<double>::X, Y = w ? Tile<float>::Y : Tile<double>::Y;
-  const long long tiles = (long long)((n + X - 1) / X) * ((n + Y - 1) / Y) * NRHS;
+static int tz_for(int n, int tiling) {
+  // the tall FP64 tile's LDS leaves one workgroup on a CU
+  const long long places = tiling == TILING_F32 ? 256 * (1024 / Tile<float>::THREADS) : (tiling == TILING_F64 ? 512 : 256);
+  const long long tiles = (long long)tile_count(n, tiling) * NRHS;
   int best = 2;
   double best_cost = -1.0;
   for (int tz = 2; tz <= n + 1 && tz <= 64; tz += 2) {
@@ -199,10 +219,9 @@ Layout make_layout(int n, int N, int K, int prec, bool save, bool vectors, int s
   L.vectors = vectors;
   const long long nn = (long long)n * n * n;
   const int nb = 2 * K + 1;
-  const int tz = tz_for(n, prec), tz_runs = (n + tz - 1) / tz;
-  const int tiles = std::max(((n + Tile<float>::X - 1) / Tile<float>::X) * ((n + Tile<float>::Y - 1) / Tile<float>::Y),
-                             ((n + Tile<double>::X - 1) / Tile<double>::X) * ((n + Tile<double>::Y - 1) / Tile<double>::Y)) *
-                    tz_runs;
+  const int tz = tz_for(n, tiling_for(n, prec, solver)), tz_runs = (n + tz - 1) / tz;
+  int tiles = 0;
+  for (int w = 0; w < NTILING; ++w) tiles = std::max(tiles, tile_count(n, w) * tz_runs);
   const int chunks = int((nn + CHUNK - 1) / CHUNK);
   L.maxparts = std::max(std::max(tiles, chunks), 1024);
   const size_t ts = prec == SHH_PREC_FP64 ? 8 : 4;
@@ -299,13 +318,15 @@ int slot_init(Slot &s, char *base, hipStream_t st, const std::function<void(Slot
   h.n = n;
   h.prec = prec;
   h.nn = (long long)n * n * n;
-  h.tz = tz_for(n, prec);
+  h.wt = tiling_for(n, prec, s.opts.solver);
+  h.wr = prec == SHH_PREC_FP64 ? h.wt : TILING_F64_TALL;  // (mixed, 128^3: a solve 1 % faster than with the flat tile)
+  h.tz = tz_for(n, h.wt);
   h.tiles_z = (n + h.tz - 1) / h.tz;
-  h.tiles_x[0] = (n + Tile<double>::X - 1) / Tile<double>::X;
-  h.tiles_y[0] = (n + Tile<double>::Y - 1) / Tile<double>::Y;
-  h.tiles_x[1] = (n + Tile<float>::X - 1) / Tile<float>::X;
-  h.tiles_y[1] = (n + Tile<float>::Y - 1) / Tile<float>::Y;
-  for (int w = 0; w < 2; ++w) h.ntiles[w] = h.tiles_x[w] * h.tiles_y[w] * h.tiles_z;
+  for (int w = 0; w < NTILING; ++w) {
+    h.tiles_x[w] = (n + tile_x(w) - 1) / tile_x(w);
+    h.tiles_y[w] = (n + tile_y(w) - 1) / tile_y(w);
+    h.ntiles[w] = h.tiles_x[w] * h.tiles_y[w] * h.tiles_z;
+  }
   h.nchunks = int((h.nn + CHUNK - 1) / CHUNK);
   h.K = d.K;
   h.nb = 2 * d.K + 1;
@@ -379,7 +400,7 @@ int slot_init(Slot &s, char *base, hipStream_t st, const std::function<void(Slot
     g.nrhs = op->nrhs;
     for (int r = 0; r < op->nrhs; ++r) g.rhs[r] = r;
     g.flag = op->flag;
-    g.nblocks = h.ntiles[op->tiling] * op->nrhs;
+    g.nblocks = h.ntiles[op->residual ? h.wr : h.wt] * op->nrhs;
     std::memcpy(up + L.alpha, &g, sizeof(g));
   }
   SHH_HIP(hipMemcpyAsync(base, up, s.upload.size(), hipMemcpyHostToDevice, st));
@@ -451,11 +472,13 @@ int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_r
     g.slot = s->d_slot;
     g.first = first;
     g.flag = flag;
-    const bool mg_apply = (k >= K_MG_DIR && k <= K_MG_POST);
-    const bool per_tile = (k == K_STENCIL || k == K_RESID || mg_apply);
+    const bool resid = k == K_RESID || k == K_RESID + K_TALL;
+    const bool per_tile = resid || k == K_STENCIL || k >= K_MG_DIR;
     const bool scalar = (k == K_SCAL_IT || k == K_SCAL_RES);
-    // the CG pass and the operator compute in the vector precision, the residual always in FP64
-    const int tiling = (k == K_STENCIL || mg_apply) ? s->host.prec : 0;
+    // the CG pass and the operator compute in the vector precision, the residual
+    // always in FP64; FP64 slots are launched by tiling
+    const int tiling = resid ? s->host.wr : s->host.wt;
+    if (per_tile && s->host.prec == SHH_PREC_FP64 && (tiling == TILING_F64_TALL) != (k >= K_TALL)) continue;
     const int units = scalar ? 1 : (per_tile ? s->host.ntiles[tiling] : s->host.nchunks);
     if (k == K_FOLD || k == K_ZERO) {
       g.nrhs = 1;
@@ -493,6 +516,15 @@ int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_r
   return SHH_OK;
 }
 
+// A per-tile kind over slots of one precision: [0] the slots of its first tiling,
+// [1] (FP64 only) those of the tall one.
+int Solver::build_tiled(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs (&la)[2]) {
+  la[1] = LaunchArgs{};
+  int rc = build(k, slots, flag, all_rhs, la[0]);
+  if (!rc && slots[0]->host.prec == SHH_PREC_FP64) rc = build(Kind(k + K_TALL), slots, flag, all_rhs, la[1]);
+  return rc;
+}
+
 // Residual f - K x in FP64 (mode RES_INIT: x = 0), mean projection and the
 // scalar update for the given slots.
 int Solver::residual(const std::vector<Slot *> &slots, int mode) {
@@ -506,10 +538,12 @@ int Solver::residual(const std::vector<Slot *> &slots, int mode) {
     if ((rc = build(K_FOLD, slots, mode, true, la))) return rc;
     SHH_HIP(launch_fold(la, prec, st_));
   }
-  if ((rc = build(K_RESID, slots, mode, all, la))) return rc;
+  LaunchArgs lr[2];
+  if ((rc = build_tiled(K_RESID, slots, mode, all, lr))) return rc;
   hipEvent_t e0 = nullptr;
-  if (la.total > 0 && (rc = timed_begin(&e0))) return rc;
-  SHH_HIP(launch_stencil_resid(la, prec, st_));
+  if (lr[0].total + lr[1].total > 0 && (rc = timed_begin(&e0))) return rc;
+  SHH_HIP(launch_stencil_resid(lr[0], prec, prec == SHH_PREC_FP64 ? TILING_F64 : TILING_F64_TALL, st_));
+  SHH_HIP(launch_stencil_resid(lr[1], prec, TILING_F64_TALL, st_));
   if ((rc = timed_end(e0, SHH_PROF_RESID64))) return rc;
   LaunchArgs ls;
   if ((rc = build(K_SCAL_RES, slots, mode, all, ls))) return rc;
@@ -598,14 +632,15 @@ int Solver::iterate(const std::vector<Slot *> &all, int iters) {
   if (!mgs.empty() && (rc = iterate_mg(mgs, iters))) return rc;
   if (slots.empty()) return SHH_OK;
   const int prec = slots[0]->host.prec;
-  LaunchArgs la_s;
-  if ((rc = build(K_STENCIL, slots, 0, false, la_s))) return rc;
+  LaunchArgs la_s[2];
+  if ((rc = build_tiled(K_STENCIL, slots, 0, false, la_s))) return rc;
   LaunchArgs la_c;
   if ((rc = build(K_SCAL_IT, slots, 0, false, la_c))) return rc;
   for (int it = 0; it < iters; ++it) {
     hipEvent_t e0 = nullptr;
-    if (la_s.total > 0 && (rc = timed_begin(&e0))) return rc;
-    SHH_HIP(launch_stencil_pcg(la_s, prec, st_));
+    if (la_s[0].total + la_s[1].total > 0 && (rc = timed_begin(&e0))) return rc;
+    SHH_HIP(launch_stencil_pcg(la_s[0], prec, st_));  // the precision's first tiling has its index
+    SHH_HIP(launch_stencil_pcg(la_s[1], TILING_F64_TALL, st_));
     if ((rc = timed_end(e0, SHH_PROF_CG_PASS))) return rc;
     SHH_HIP(launch_scalar(la_c, PH_ITER, st_));
     std::vector<Slot *> due;
@@ -628,15 +663,16 @@ int Solver::iterate_mg(const std::vector<Slot *> &slots, int iters) {
     static const Kind kinds[3] = {K_MG_DIR, K_MG_PRE, K_MG_POST};
     static const int prof[3] = {SHH_PROF_MG_DIR, SHH_PROF_MG_STEP1, SHH_PROF_MG_LAST};
     if (op < SMG_DIR || op > SMG_POST) return SHH_INVALID_ARG;
-    LaunchArgs la;
+    LaunchArgs la[2];
     int r;
     // segments of the load cases still running at the last read-back; the
     // kernels also skip those that stopped since
-    if ((r = build(kinds[op], ss, 0, false, la))) return r;
-    if (la.total == 0) return SHH_OK;
+    if ((r = build_tiled(kinds[op], ss, 0, false, la))) return r;
+    if (la[0].total + la[1].total == 0) return SHH_OK;
     hipEvent_t e0 = nullptr;
     if ((r = timed_begin(&e0))) return r;
-    SHH_HIP(launch_stencil_mg(la, ss[0]->host.prec, op, st_));
+    SHH_HIP(launch_stencil_mg(la[0], ss[0]->host.prec, op, st_));
+    SHH_HIP(launch_stencil_mg(la[1], TILING_F64_TALL, op, st_));
     return timed_end(e0, prof[op]);
   };
   for (int it = 0; it < iters; ++it) {

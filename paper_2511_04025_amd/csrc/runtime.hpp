@@ -123,7 +123,8 @@ void copy_design(const shh_design *src, DesignCopy &dst);
 // descriptor first.  An operator call's one launch segment goes along, in the
 // place of the spectral weights (which such a slot does not have).
 struct OperatorSegment {
-  int tiling, nrhs, flag;
+  bool residual;  // the FP64 residual pass, not the operator in the slot's precision
+  int nrhs, flag;
 };
 int slot_init(Slot &s, char *base, hipStream_t st, const std::function<void(SlotDev &)> &adjust = nullptr,
               const OperatorSegment *op = nullptr);
@@ -164,11 +165,12 @@ class Solver {
  private:
   bool timing_ = true;
   enum Kind { K_STENCIL = 0, K_RESID, K_FINISH, K_FOLD, K_ZERO, K_SCAL_IT, K_SCAL_RES, K_MG_DIR, K_MG_PRE,
-              K_MG_POST, K_NKIND };
-  static constexpr int SEG_TABLES = 12;  // room in a workspace's segment region
+              K_MG_POST, K_TALL, K_NKIND = 2 * K_TALL };  // K_TALL + k: per-tile kind k of the tall FP64 tiling
+  static constexpr int SEG_TABLES = 20;  // room in a workspace's segment region
   static_assert(K_NKIND <= SEG_TABLES, "one table per kind");
   int residual(const std::vector<Slot *> &slots, int mode);
   int iterate_mg(const std::vector<Slot *> &slots, int iters);
+  int build_tiled(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs (&la)[2]);
   int build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs &la);
   int read_states(const std::vector<Slot *> &slots);
   int final_check(const std::vector<Slot *> &slots);

@@ -68,16 +68,16 @@ __device__ __forceinline__ int ring_h(int j) {
 // 24^3 FP64 solve 27.4 instead of 25.5 ms).
 template <typename TC, int MODE>
 constexpr int WPE = sizeof(TC) == 4 ? 4 : (MODE == MODE_MGPRE ? 3 : 1);
-template <typename TC, typename TS, int MODE>
-__global__ __launch_bounds__(Tile<TC>::THREADS)
+template <typename TC, typename TS, int MODE, bool TALL = false>
+__global__ __launch_bounds__((Tile<TC, TALL>::THREADS))
     __attribute__((amdgpu_waves_per_eu(WPE<TC, MODE>)))
 void stencil_kernel(LaunchArgs la) {
   // tile geometry of this compute precision
-  using TT = Tile<TC>;
+  using TT = Tile<TC, TALL>;
   constexpr int TX = TT::X, TY = TT::Y, HX = TT::HX, HY = TT::HY, EXC = TT::EXC, EYC = TT::EYC;
   constexpr int NHALO = TT::NHALO, NELEMC = TT::NELEMC, STENCIL_THREADS = TT::THREADS;
   constexpr int NINT = TT::NINT, NRING = TT::NRING;
-  constexpr int TW = tiling_of<TC>();
+  constexpr int TW = tiling_of<TC, TALL>();
   __shared__ TC nbuf[2][3][NHALO];
   __shared__ TC ebuf[2][12][NELEMC];
   __shared__ TC mbuf[2][NHALO];  // element moduli, by the halo slot of the element's lower corner
@@ -780,35 +780,36 @@ void stencil_kernel(LaunchArgs la) {
   }
 }
 
-hipError_t launch_stencil_pcg(const LaunchArgs &la, int prec, hipStream_t st) {
+// one mode in a tiling; TS is the vectors' type where the kernel computes in FP64
+template <int MODE, typename TS>
+static hipError_t launch_f64(const LaunchArgs &la, int tiling, hipStream_t st) {
   if (la.total == 0) return hipSuccess;
-  const int g = la.grid();
-  if (prec == 0) stencil_kernel<double, double, MODE_PCG><<<g, Tile<double>::THREADS, 0, st>>>(la);
-  else stencil_kernel<float, float, MODE_PCG><<<g, Tile<float>::THREADS, 0, st>>>(la);
-  return hipGetLastError();
-}
-
-hipError_t launch_stencil_resid(const LaunchArgs &la, int prec, hipStream_t st) {
-  if (la.total == 0) return hipSuccess;
-  const int g = la.grid();
-  if (prec == 0) stencil_kernel<double, double, MODE_RESID><<<g, Tile<double>::THREADS, 0, st>>>(la);
-  else stencil_kernel<double, float, MODE_RESID><<<g, Tile<double>::THREADS, 0, st>>>(la);
-  return hipGetLastError();
-}
-
-hipError_t launch_stencil_apply(const LaunchArgs &la, int prec, hipStream_t st) {
-  if (la.total == 0) return hipSuccess;
-  const int g = la.grid();
-  if (prec == 0) stencil_kernel<double, double, MODE_APPLY><<<g, Tile<double>::THREADS, 0, st>>>(la);
-  else stencil_kernel<float, float, MODE_APPLY><<<g, Tile<float>::THREADS, 0, st>>>(la);
+  if (tiling == TILING_F64_TALL)
+    stencil_kernel<double, TS, MODE, true><<<la.grid(), Tile<double, true>::THREADS, 0, st>>>(la);
+  else
+    stencil_kernel<double, TS, MODE><<<la.grid(), Tile<double>::THREADS, 0, st>>>(la);
   return hipGetLastError();
 }
 
 template <int MODE>
-static void launch_mg_mode(const LaunchArgs &la, int prec, hipStream_t st) {
-  const int g = la.grid();
-  if (prec == 0) stencil_kernel<double, double, MODE><<<g, Tile<double>::THREADS, 0, st>>>(la);
-  else stencil_kernel<float, float, MODE><<<g, Tile<float>::THREADS, 0, st>>>(la);
+static hipError_t launch_mode(const LaunchArgs &la, int tiling, hipStream_t st) {
+  if (tiling != TILING_F32) return launch_f64<MODE, double>(la, tiling, st);
+  if (la.total == 0) return hipSuccess;
+  stencil_kernel<float, float, MODE><<<la.grid(), Tile<float>::THREADS, 0, st>>>(la);
+  return hipGetLastError();
+}
+
+hipError_t launch_stencil_pcg(const LaunchArgs &la, int tiling, hipStream_t st) {
+  return launch_mode<MODE_PCG>(la, tiling, st);
+}
+
+// prec: of the vectors; tiling: an FP64 one
+hipError_t launch_stencil_resid(const LaunchArgs &la, int prec, int tiling, hipStream_t st) {
+  return prec == 0 ? launch_f64<MODE_RESID, double>(la, tiling, st) : launch_f64<MODE_RESID, float>(la, tiling, st);
+}
+
+hipError_t launch_stencil_apply(const LaunchArgs &la, int tiling, hipStream_t st) {
+  return launch_mode<MODE_APPLY>(la, tiling, st);
 }
 
 // Voxel-level passes of the multigrid-preconditioned CG, in the vector
@@ -817,15 +818,13 @@ static void launch_mg_mode(const LaunchArgs &la, int prec, hipStream_t st) {
 // partials p_j . q; SMG_PRE the CG's residual update and the pre-smoothing
 // step; SMG_POST the coarse correction and the post-smoothing step (per-tile
 // partials b . z, b . b).
-hipError_t launch_stencil_mg(const LaunchArgs &la, int prec, int op, hipStream_t st) {
-  if (la.total == 0) return hipSuccess;
+hipError_t launch_stencil_mg(const LaunchArgs &la, int tiling, int op, hipStream_t st) {
   switch (op) {
-    case SMG_DIR: launch_mg_mode<MODE_MGDIR>(la, prec, st); break;
-    case SMG_PRE: launch_mg_mode<MODE_MGPRE>(la, prec, st); break;
-    case SMG_POST: launch_mg_mode<MODE_MGPOST>(la, prec, st); break;
+    case SMG_DIR: return launch_mode<MODE_MGDIR>(la, tiling, st);
+    case SMG_PRE: return launch_mode<MODE_MGPRE>(la, tiling, st);
+    case SMG_POST: return launch_mode<MODE_MGPOST>(la, tiling, st);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace shh

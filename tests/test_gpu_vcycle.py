@@ -116,3 +116,31 @@ def test_last_levels_in_one_launch(n, solver, precision, rtol):
     ja = api.homogenize(d, precision="fp64", rtol=1e-10, solver="selective-jacobi" if solver != "mg" else "jacobi")
     assert mg["status"] == 0 and ja["status"] == 0
     assert_ch_close(mg["C"], ja["C"], 1e-7 if precision == "fp64" else 1e-4)
+
+
+@pytest.mark.parametrize("n", [25, 28, 29, 42, 64])
+def test_tall_fp64_tiles(n):
+    # tiles of 32 x 14 nodes from 25^3: remainders of 11, 0, 1 and 8 rows and of
+    # the 32 columns; K p against the oracle's element sum at nodes around the
+    # tile edges (FP64 sums of 8 x 24 terms: 1e-12 of the largest), and flat and
+    # tall slots in one Jacobi batch
+    import torch
+    from oracle import fem
+    from paper_2511_04025_amd import api
+    rng = np.random.default_rng(n)
+    E, p = rng.uniform(0.1, 1.0, (n, n, n)), rng.standard_normal((6, 3, n, n, n))
+    print(f"tall tiles {n}^3", flush=True)
+    q = api.apply_stiffness(torch.tensor(E, device="cuda"), torch.tensor(p, device="cuda"), 0.3, "fp64").cpu().numpy()
+    edge = [i for i in (0, 1, 12, 13, 14, 15, 27, 28, 31, 32, 33, n - 2, n - 1) if i < n]
+    nodes = np.unique([(z * n + y) * n + x for z in (0, n // 2, n - 1) for y in edge for x in edge])
+    U = p.reshape(6, 3, -1).transpose(2, 1, 0)
+    ref = fem.stiffness_rows(E.ravel(), 0.3, n, lambda ids: U[ids], nodes)
+    got = q.reshape(6, 3, -1)[:, :, nodes].transpose(2, 1, 0)
+    assert np.max(np.abs(got - ref)) <= 1e-12 * np.abs(ref).max()
+    if n > 28:
+        return
+    designs = [wl.random_design(7300 + k, k, N=8, vf=0.3, E_void=1e-1) for k in (n, 24, 10)]
+    batch = api.homogenize_batch(designs, precision="fp64", rtol=1e-8, solver="jacobi")
+    for d, rb in zip(designs, batch):
+        rs = api.homogenize(d, precision="fp64", rtol=1e-8, solver="jacobi")
+        assert rs["status"] == 0 and np.array_equal(rs["C"], rb["C"]) and np.array_equal(rs["iters"], rb["iters"])
