@@ -22,7 +22,7 @@ constexpr int MAXB = 2 * MAXK + 1;  // 1D basis functions per axis: 1, cos, sin 
 // up tz planes in z.  Kernels that compute in FP32 use a wide 64 x 6 tile: its
 // halo ring has 12 side-column nodes per 384 outputs (each of those pulls a
 // whole 128-byte line), 8 waves per workgroup, 2 workgroups per CU.  Kernels
-// that compute in FP64 hold twice the bytes in LDS per node and use 32 x 8.
+// that compute in FP64 hold twice the bytes in LDS per node and use 32 x 8 or 32 x 14.
 #ifndef SHH_F32_TILE_X
 #define SHH_F32_TILE_X 64
 #endif

@@ -219,9 +219,14 @@ Layout make_layout(int n, int N, int K, int prec, bool save, bool vectors, int s
   L.vectors = vectors;
   const long long nn = (long long)n * n * n;
   const int nb = 2 * K + 1;
-  const int tz = tz_for(n, tiling_for(n, prec, solver)), tz_runs = (n + tz - 1) / tz;
-  int tiles = 0;
-  for (int w = 0; w < NTILING; ++w) tiles = std::max(tiles, tile_count(n, w) * tz_runs);
+  // room for the runs of either solver's tiling: an adjoint call may name another
+  // solver than its forward, so nothing before the multigrid region depends on it
+  int runs = 0, tiles = 0;
+  for (int sv : {SHH_SOLVER_JACOBI, SHH_SOLVER_MG}) {
+    const int tz = tz_for(n, tiling_for(n, prec, sv));
+    runs = std::max(runs, (n + tz - 1) / tz);
+  }
+  for (int w = 0; w < NTILING; ++w) tiles = std::max(tiles, tile_count(n, w) * runs);
   const int chunks = int((nn + CHUNK - 1) / CHUNK);
   L.maxparts = std::max(std::max(tiles, chunks), 1024);
   const size_t ts = prec == SHH_PREC_FP64 ? 8 : 4;
@@ -462,23 +467,24 @@ static void split_by_cost(const std::vector<Segment> &segs, const std::vector<in
   }
 }
 
-int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs &la) {
-  std::vector<Segment> segs;
-  std::vector<int> cost;  // of one workgroup of each segment
-  int first = 0;
+// The launch of kind k over the slots' live load cases.  With `tall`, a per-tile
+// kind's FP64 slots of the tall tiling make a launch of their own, its segments
+// behind the others' in the kind's table.
+int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs &la,
+                  LaunchArgs *tall) {
+  std::vector<Segment> segs[2];
+  std::vector<int> cost[2];  // of one workgroup of each segment
+  int first[2] = {0, 0};
   for (Slot *s : slots) {
     Segment g;
     std::memset(&g, 0, sizeof(g));
     g.slot = s->d_slot;
-    g.first = first;
     g.flag = flag;
-    const bool resid = k == K_RESID || k == K_RESID + K_TALL;
-    const bool per_tile = resid || k == K_STENCIL || k >= K_MG_DIR;
+    const bool per_tile = (k == K_STENCIL || k == K_RESID || k == K_MG_DIR || k == K_MG_PRE || k == K_MG_POST);
     const bool scalar = (k == K_SCAL_IT || k == K_SCAL_RES);
-    // the CG pass and the operator compute in the vector precision, the residual
-    // always in FP64; FP64 slots are launched by tiling
-    const int tiling = resid ? s->host.wr : s->host.wt;
-    if (per_tile && s->host.prec == SHH_PREC_FP64 && (tiling == TILING_F64_TALL) != (k >= K_TALL)) continue;
+    // the CG pass and the operator compute in the vector precision, the residual always in FP64
+    const int tiling = k == K_RESID ? s->host.wr : s->host.wt;
+    const int t = tall && s->host.prec == SHH_PREC_FP64 && tiling == TILING_F64_TALL;
     const int units = scalar ? 1 : (per_tile ? s->host.ntiles[tiling] : s->host.nchunks);
     if (k == K_FOLD || k == K_ZERO) {
       g.nrhs = 1;
@@ -492,37 +498,33 @@ int Solver::build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_r
       }
       if (g.nrhs == 0) continue;
     }
+    g.first = first[t];
     g.nblocks = units * g.nrhs;
-    first += g.nblocks;
-    segs.push_back(g);
-    cost.push_back(per_tile ? std::min(s->host.tz, s->host.n) + 3 : 1);
+    first[t] += g.nblocks;
+    segs[t].push_back(g);
+    cost[t].push_back(per_tile ? std::min(s->host.tz, s->host.n) + 3 : 1);
   }
-  la.nseg = int(segs.size());
-  la.total = first;
-  split_by_cost(segs, cost, la);
-  const size_t bytes = sizeof(Segment) * segs.size();
+  const size_t flat = segs[0].size(), bytes = sizeof(Segment) * (flat + segs[1].size());
   if (bytes > seg_cap_) return SHH_WORKSPACE_TOO_SMALL;
   Segment *dst = (Segment *)(seg_mem_ + (size_t)k * seg_cap_);
-  la.segs = dst;
-  if (segs.empty()) return SHH_OK;
+  for (int t = 0; t < (tall ? 2 : 1); ++t) {
+    LaunchArgs &l = t ? *tall : la;
+    l.segs = dst + (t ? flat : 0);
+    l.nseg = int(segs[t].size());
+    l.total = first[t];
+    split_by_cost(segs[t], cost[t], l);
+  }
+  std::vector<Segment> &cur = segs[0];
+  cur.insert(cur.end(), segs[1].begin(), segs[1].end());
+  if (cur.empty()) return SHH_OK;
   auto &prev = host_segs_[k];
-  const bool same = prev.size() == segs.size() &&
-                    std::memcmp(prev.data(), segs.data(), bytes) == 0;
+  const bool same = prev.size() == cur.size() && std::memcmp(prev.data(), cur.data(), bytes) == 0;
   if (!same) {
-    SHH_HIP(hipMemcpyAsync(dst, segs.data(), bytes, hipMemcpyHostToDevice, st_));
+    SHH_HIP(hipMemcpyAsync(dst, cur.data(), bytes, hipMemcpyHostToDevice, st_));
     SHH_HIP(hipStreamSynchronize(st_));
-    prev = segs;
+    prev = cur;
   }
   return SHH_OK;
-}
-
-// A per-tile kind over slots of one precision: [0] the slots of its first tiling,
-// [1] (FP64 only) those of the tall one.
-int Solver::build_tiled(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs (&la)[2]) {
-  la[1] = LaunchArgs{};
-  int rc = build(k, slots, flag, all_rhs, la[0]);
-  if (!rc && slots[0]->host.prec == SHH_PREC_FP64) rc = build(Kind(k + K_TALL), slots, flag, all_rhs, la[1]);
-  return rc;
 }
 
 // Residual f - K x in FP64 (mode RES_INIT: x = 0), mean projection and the
@@ -539,7 +541,7 @@ int Solver::residual(const std::vector<Slot *> &slots, int mode) {
     SHH_HIP(launch_fold(la, prec, st_));
   }
   LaunchArgs lr[2];
-  if ((rc = build_tiled(K_RESID, slots, mode, all, lr))) return rc;
+  if ((rc = build(K_RESID, slots, mode, all, lr[0], &lr[1]))) return rc;
   hipEvent_t e0 = nullptr;
   if (lr[0].total + lr[1].total > 0 && (rc = timed_begin(&e0))) return rc;
   SHH_HIP(launch_stencil_resid(lr[0], prec, prec == SHH_PREC_FP64 ? TILING_F64 : TILING_F64_TALL, st_));
@@ -633,7 +635,7 @@ int Solver::iterate(const std::vector<Slot *> &all, int iters) {
   if (slots.empty()) return SHH_OK;
   const int prec = slots[0]->host.prec;
   LaunchArgs la_s[2];
-  if ((rc = build_tiled(K_STENCIL, slots, 0, false, la_s))) return rc;
+  if ((rc = build(K_STENCIL, slots, 0, false, la_s[0], &la_s[1]))) return rc;
   LaunchArgs la_c;
   if ((rc = build(K_SCAL_IT, slots, 0, false, la_c))) return rc;
   for (int it = 0; it < iters; ++it) {
@@ -667,7 +669,7 @@ int Solver::iterate_mg(const std::vector<Slot *> &slots, int iters) {
     int r;
     // segments of the load cases still running at the last read-back; the
     // kernels also skip those that stopped since
-    if ((r = build_tiled(kinds[op], ss, 0, false, la))) return r;
+    if ((r = build(kinds[op], ss, 0, false, la[0], &la[1]))) return r;
     if (la[0].total + la[1].total == 0) return SHH_OK;
     hipEvent_t e0 = nullptr;
     if ((r = timed_begin(&e0))) return r;

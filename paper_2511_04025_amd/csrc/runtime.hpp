@@ -165,13 +165,13 @@ class Solver {
  private:
   bool timing_ = true;
   enum Kind { K_STENCIL = 0, K_RESID, K_FINISH, K_FOLD, K_ZERO, K_SCAL_IT, K_SCAL_RES, K_MG_DIR, K_MG_PRE,
-              K_MG_POST, K_TALL, K_NKIND = 2 * K_TALL };  // K_TALL + k: per-tile kind k of the tall FP64 tiling
-  static constexpr int SEG_TABLES = 20;  // room in a workspace's segment region
+              K_MG_POST, K_NKIND };
+  static constexpr int SEG_TABLES = 12;  // room in a workspace's segment region
   static_assert(K_NKIND <= SEG_TABLES, "one table per kind");
   int residual(const std::vector<Slot *> &slots, int mode);
   int iterate_mg(const std::vector<Slot *> &slots, int iters);
-  int build_tiled(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs (&la)[2]);
-  int build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs &la);
+  int build(Kind k, const std::vector<Slot *> &slots, int flag, bool all_rhs, LaunchArgs &la,
+            LaunchArgs *tall = nullptr);
   int read_states(const std::vector<Slot *> &slots);
   int final_check(const std::vector<Slot *> &slots);
   hipStream_t st_;

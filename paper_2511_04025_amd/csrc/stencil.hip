@@ -2,7 +2,7 @@
 // (Sec. 4.1, Eq. (7)-(8)), for one load case per workgroup.
 //
 // A workgroup owns a TX x TY tile of nodes in the x-y plane (64 x 6 for FP32
-// compute, 32 x 8 for FP64) and marches up a run of tz planes in z.  Per
+// compute, 32 x 8 or 32 x 14 for FP64) and marches up a run of tz planes in z.  Per
 // element layer it
 //   1. stages the next node plane (tile + one-node periodic halo) in LDS,
 //   2. forms, for each of the (TX+1)(TY+1) element columns, the Hadamard

@@ -144,3 +144,16 @@ def test_tall_fp64_tiles(n):
     for d, rb in zip(designs, batch):
         rs = api.homogenize(d, precision="fp64", rtol=1e-8, solver="jacobi")
         assert rs["status"] == 0 and np.array_equal(rs["C"], rb["C"]) and np.array_equal(rs["iters"], rb["iters"])
+
+
+@pytest.mark.parametrize("sizes", [(48, 24, 28), (24, 20), (28, 48)])
+def test_flat_and_tall_fp64_multigrid_batch(sizes):
+    # the two FP64 tilings make a launch each from one table of segments: 24^3 and
+    # 20^3 flat, 28^3 and 48^3 tall, in batches of both, of one, and of the other
+    from paper_2511_04025_amd import api
+    print(f"FP64 batch {sizes}", flush=True)
+    designs = [wl.random_design(7400 + n, n, N=8, vf=0.3, E_void=1e-4) for n in sizes]
+    batch = api.homogenize_batch(designs, precision="fp64", rtol=1e-8, solver="mg")
+    for d, rb in zip(designs, batch):
+        rs = api.homogenize(d, precision="fp64", rtol=1e-8, solver="mg")
+        assert rs["status"] == 0 and np.array_equal(rs["C"], rb["C"]) and np.array_equal(rs["iters"], rb["iters"])
