@@ -440,7 +440,7 @@ int32_t shh_load_vectors(int32_t n, const double *d_E, double nu, double *d_f, v
   SHH_TRY(normalize_opts(&o, &o));
   hipStream_t st = (hipStream_t)hip_stream;
   Slot s;
-  const OperatorSegment op{true, NRHS, RES_INIT};
+  const OperatorSegment op{true, NRHS, RES_LOAD};
   SHH_TRY(moduli_slot(s, n, d_E, nu, &o, d_ws, ws_bytes, st, nullptr, false, SHH_EDTYPE_F64, 0.0, 0.0,
                       [&](SlotDev &h) { h.r[0] = d_f; }, &op));
   SHH_HIP(launch_stencil_resid(operator_launch(s, op), SHH_PREC_FP64, s.host.wr, st));

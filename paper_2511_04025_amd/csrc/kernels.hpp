@@ -5,7 +5,7 @@
 
 namespace shh {
 
-enum { RES_INIT = 0, RES_RECOMPUTE = 1, RES_FINAL = 2 };
+enum { RES_INIT = 0, RES_RECOMPUTE = 1, RES_FINAL = 2, RES_LOAD = 3 };  // RES_LOAD: f alone, for shh_load_vectors
 enum { PH_ITER = 0, PH_MEAN = 2, PH_RESID = 3 };
 
 // field.hip (single slot per launch; d_slot is the device copy of the slot)

@@ -105,6 +105,11 @@ void stencil_kernel(LaunchArgs la) {
     if (w.flag == RES_RECOMPUTE && !st->active[rhs]) return;
     if (w.flag == RES_FINAL && !(st->ff[rhs] > s->ffloor * s->ffloor)) return;
   }
+  // an operator call on moduli that its caller will refuse leaves the output alone
+  if (MODE == MODE_APPLY || (MODE == MODE_RESID && w.flag == RES_LOAD)) {
+    const double emax = st->Emax;
+    if (!(emax > 0.0 && emax < INFINITY)) return;
+  }
 
   // n <= 512: every byte offset into one load case's [3][n^3] vector fits in
   // 32 bits.  Per-lane offsets are fixed per thread; plane and component
@@ -244,7 +249,7 @@ void stencil_kernel(LaunchArgs la) {
     rA = make_rsrc((const TS *)s->p[0] + vbase, vbytesL);
     rQ = make_rsrc((const TS *)s->q[0] + vbase, vbytesS);
   }
-  const bool zero_x = (MODE == MODE_RESID) && (w.flag == RES_INIT);
+  const bool zero_x = (MODE == MODE_RESID) && (w.flag == RES_INIT || w.flag == RES_LOAD);
 
   // FP64 partial sums: PCG r.z, r.r, p.q, q.z, q.D^-1 q; RESID sums of r
   double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};

@@ -116,3 +116,29 @@ def test_operator_refuses_invalid_moduli():
     E = torch.ones((n, n, n), dtype=torch.float64, device="cuda")
     q = api.apply_stiffness(E, p, 0.3)
     assert torch.isfinite(q).all()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 0.0])
+def test_refused_moduli_leave_the_output_alone(bad):
+    # the moduli are checked on the device, after the pass has been launched
+    import torch
+    from ctypes import c_double, c_size_t
+    from paper_2511_04025_amd import api, binding as B
+    n = 10
+    E = torch.ones((n, n, n), dtype=torch.float64, device="cuda")
+    if np.isinf(bad):
+        E[3, 4, 5] = bad
+    else:
+        E.fill_(bad)  # no modulus above 0
+    for prec, dt in (("fp64", torch.float64), ("mixed", torch.float32)):
+        p = torch.ones((6, 3, n, n, n), dtype=dt, device="cuda")
+        q = torch.full_like(p, 7.0)
+        ws = api.Workspace(api.operator_workspace_bytes(n, prec))
+        code = B.PREC_FP64 if prec == "fp64" else B.PREC_MIXED
+        rc = B.lib().shh_apply_stiffness(n, code, api._ptr(E), c_double(0.3), 6, api._ptr(p), api._ptr(q), ws.ptr,
+                                         c_size_t(ws.nbytes), api._stream())
+        assert rc != 0 and bool((q == 7.0).all())
+    f = torch.full((6, 3, n, n, n), 7.0, dtype=torch.float64, device="cuda")
+    ws = api.Workspace(api.operator_workspace_bytes(n, "fp64"))
+    rc = B.lib().shh_load_vectors(n, api._ptr(E), c_double(0.3), api._ptr(f), ws.ptr, c_size_t(ws.nbytes), api._stream())
+    assert rc != 0 and bool((f == 7.0).all())
