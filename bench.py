@@ -72,9 +72,8 @@ def family_bytes(results, n, R, solver, deg0=2):
                         written) + 12 (D^-1) per coarse node
       first coarse level operator with the sweeps in its output stage: per
         coarse node and pass 32 (moduli) from 34^3 nodes, else 504 (stencil),
-        and 12 (D^-1) per sweep that takes it; per (coarse node, load case)
-        from 24^3 nodes two passes, 48 (d, b read; r, x written) + 36 (b, x
-        read; q written); else four, 60 + 36 + 60 + 48
+        and 12 (D^-1) per sweep that takes it (three of the four passes); per
+        (coarse node, load case) 60 + 36 + 60 + 48
       FP64 residual: 24 (x64) + 12 (r) per (node, load case) + 8 (E) per node,
         every R iterations and once at the end
       Jacobi CG pass: 96 per (node, load case) + 8 per node
@@ -125,10 +124,7 @@ def family_bytes(results, n, R, solver, deg0=2):
         out["mg_step1"] += (36.0 * nn + 12.0 * nn1) * Ik + 8.0 * nn * Im
         out["mg_last"] += (24.0 * nn + 12.0 * nn1) * Ik + 8.0 * nn * Im
         out["mg_restrict"] += 36.0 * nn1 * Ik + 12.0 * nn1 * Im
-        if n1 >= 24:
-            out["mg_apply1"] += (2 * level1 + 12.0) * nn1 * Im + 84.0 * nn1 * Ik
-        else:
-            out["mg_apply1"] += (4 * level1 + 36.0) * nn1 * Im + 204.0 * nn1 * Ik
+        out["mg_apply1"] += (4 * level1 + 36.0) * nn1 * Im + 204.0 * nn1 * Ik
     return out
 
 

@@ -203,9 +203,6 @@ __global__ __launch_bounds__(256) void mg_stencil_kernel(const MgDev *mg, int l)
 //   MGE_RES:   (v = d1, in q) r -= q: the residual the restriction takes
 //   MGE_POST:  (v = x) r = b - q;  d = D^-1 r / theta;  x + d into q
 //   MGE_LAST:  (v = d) x = (x + d, in q) + c1 d + c2 D^-1 (r - q)
-// and of one step each side (degree 1):
-//   MGE_PRE1:  (v = d0) r = b - q, the residual the restriction takes;  x = d0
-//   MGE_POST1: (v = x) x + D^-1 (b - q) / theta into q, the level's result
 // No pass writes the vector its operator reads.
 // The level's vectors and coefficients, read once per thread into scalar
 // registers: a field read after a store would be read again (the store might
@@ -236,12 +233,6 @@ __device__ __forceinline__ void mg_epi_load(const MgEpi<T> &E, long long j, T (&
   if constexpr (EP == MGE_STEP1) {
     in[0] = E.d[j];
     in[1] = E.b[j];
-  } else if constexpr (EP == MGE_PRE1) {
-    in[0] = E.b[j];
-    in[1] = E.d[j];
-  } else if constexpr (EP == MGE_POST1) {
-    in[0] = E.b[j];
-    in[1] = E.x[j];
   } else if constexpr (EP == MGE_RES) {
     in[0] = E.r[j];
   } else if constexpr (EP == MGE_POST) {
@@ -264,11 +255,6 @@ __device__ __forceinline__ void mg_epilogue(const MgEpi<T> &E, long long j, T di
     E.r[j] = rv;
     E.x[j] = d0 + d1;
     E.q[j] = d1;
-  } else if constexpr (EP == MGE_PRE1) {
-    E.r[j] = in[0] - a;
-    E.x[j] = in[1];
-  } else if constexpr (EP == MGE_POST1) {
-    E.q[j] = in[1] + dinv * (in[0] - a) * E.inv_theta;
   } else if constexpr (EP == MGE_RES) {
     E.r[j] = in[0] - a;
   } else if constexpr (EP == MGE_POST) {
@@ -285,9 +271,9 @@ __device__ __forceinline__ void mg_epilogue(const MgEpi<T> &E, long long j, T di
 // the operator's input vector of an epilogue (MGE_NONE: src 0 x, 1 d)
 template <typename T, int EP>
 __device__ __forceinline__ const T *mg_operand(const MgLevel &L, int src) {
-  if constexpr (EP == MGE_STEP1 || EP == MGE_LAST || EP == MGE_PRE1) return (const T *)L.d;
+  if constexpr (EP == MGE_STEP1 || EP == MGE_LAST) return (const T *)L.d;
   else if constexpr (EP == MGE_RES) return (const T *)L.q;
-  else if constexpr (EP == MGE_POST || EP == MGE_POST1) return (const T *)L.x;
+  else if constexpr (EP == MGE_POST) return (const T *)L.x;
   else return (const T *)(src == 0 ? L.x : L.d);
 }
 
@@ -721,7 +707,7 @@ __global__ __launch_bounds__(256) void mg_prolong_kernel(MgBatch B, int l) {
   const int X1 = X + 1 == nc ? 0 : X + 1;
   const unsigned cy[2] = {unsigned(Y), unsigned(Y + 1 == nc ? 0 : Y + 1)};
   const unsigned cz[2] = {unsigned(Z), unsigned(Z + 1 == nc ? 0 : Z + 1)};
-  const SHH_GLOBAL T *xc = to_global((const T *)C.xo) + (long long)k * 3 * cnn;
+  const SHH_GLOBAL T *xc = to_global((const T *)C.x) + (long long)k * 3 * cnn;
   SHH_GLOBAL T *xf = to_global((T *)F.x) + (long long)k * 3 * fnn;
   // every load (coarse values, then the fine pairs) is issued before the
   // first store
@@ -1214,8 +1200,6 @@ void launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide,
     case MGE_STEP1: launch_apply_ep<T, MGE_STEP1>(B, l, src, nn_max, wide, st, live); break;
     case MGE_RES: launch_apply_ep<T, MGE_RES>(B, l, src, nn_max, wide, st, live); break;
     case MGE_POST: launch_apply_ep<T, MGE_POST>(B, l, src, nn_max, wide, st, live); break;
-    case MGE_PRE1: launch_apply_ep<T, MGE_PRE1>(B, l, src, nn_max, wide, st, live); break;
-    case MGE_POST1: launch_apply_ep<T, MGE_POST1>(B, l, src, nn_max, wide, st, live); break;
     case MGE_LAST: launch_apply_ep<T, MGE_LAST>(B, l, src, nn_max, wide, st, live); break;
     default: launch_apply_ep<T, MGE_NONE>(B, l, src, nn_max, wide, st, live); break;
   }

@@ -46,7 +46,6 @@ struct MgLevel {
   // z = V r in the dense solve, the first direction in the selective one); its
   // passes take the slot's other CG vectors by name.
   void *b, *x, *r, *d, *q;
-  void *xo;             // the level's result: x, or q after one smoothing step each side
   void *Ke;             // setup only: element matrices [24][24][nn] (levels >= 1, >= 2 with l1free)
   double inv_theta, c1, c2;  // Chebyshev coefficients
   double lmax;               // lambda_max(D^-1 A) estimate (setup: running max of Rayleigh quotients)
@@ -56,7 +55,6 @@ struct MgLevel {
 struct MgDev {
   int L;                // index of the coarsest level
   int l1free;           // level 1 runs from the moduli (mg1.hip), without a stencil
-  int deg1;             // level 1 smooths by one step each side
   int tail;             // level run with the coarsest one in a single launch (mgtail.hip), or -1
   int ndof_c;           // 3 n_L^3
   void *G;              // [8][24][24] child Galerkin matrices of K_0 (T)
@@ -78,7 +76,7 @@ struct MgBatch {
 enum { MGS_RESTART = 0, MGS_ALPHA = 1, MGS_BETA = 2, MGS_REPLACE = 3 };
 // coarse-level operator passes with the Chebyshev sweep that follows them
 // fused into their output stage (see mg_epilogue)
-enum { MGE_NONE = 0, MGE_STEP1 = 1, MGE_RES = 2, MGE_POST = 3, MGE_LAST = 4, MGE_PRE1 = 5, MGE_POST1 = 6 };
+enum { MGE_NONE = 0, MGE_STEP1 = 1, MGE_RES = 2, MGE_POST = 3, MGE_LAST = 4 };
 
 // Number of levels for an n^3 grid (coarsening while even and above 4^3, so
 // the dense coarsest solve stays at most 8^3 and usually 3^3 or 4^3), or 0

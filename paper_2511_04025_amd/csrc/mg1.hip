@@ -155,7 +155,7 @@ void mg_l1_kernel(MgBatch B, int tiles, int per, int nrhs, int tz, int live) {
   const uint64_t vb = 3ull * cb;
   const long long v0 = (long long)rhs * 3 * L->nn;
   auto vec = [&](void *p) { return make_rsrc((const float *)p + v0, vb); };
-  const rsrc_t rV = vec(EP == MGE_STEP1 || EP == MGE_LAST || EP == MGE_PRE1 ? L->d : (EP == MGE_RES ? L->q : L->x));
+  const rsrc_t rV = vec(EP == MGE_STEP1 || EP == MGE_LAST ? L->d : (EP == MGE_RES ? L->q : L->x));
   const rsrc_t rE = make_rsrc(s->E32, (uint64_t)fplane * nf), rD = make_rsrc(L->Dinv, vb);
   const rsrc_t rB = vec(L->b), rR = vec(L->r), rX = vec(L->x), rQ = vec(L->q), rDir = vec(L->d);
   const float c1 = (float)L->c1, c2 = (float)L->c2, ith = (float)L->inv_theta;
@@ -254,10 +254,10 @@ void mg_l1_kernel(MgBatch B, int tiles, int per, int nrhs, int tz, int live) {
     if (sl > 0 && is_out) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        if constexpr (EP == MGE_STEP1 || EP == MGE_POST || EP == MGE_PRE1 || EP == MGE_POST1) aux[0][c] = bload<float>(rB, ooff, pk + c * cb);
+        if constexpr (EP == MGE_STEP1 || EP == MGE_POST) aux[0][c] = bload<float>(rB, ooff, pk + c * cb);
         if constexpr (EP == MGE_RES || EP == MGE_LAST) aux[0][c] = bload<float>(rR, ooff, pk + c * cb);
         if constexpr (EP == MGE_LAST) aux[1][c] = bload<float>(rQ, ooff, pk + c * cb);
-        if constexpr (EP != MGE_RES && EP != MGE_NONE && EP != MGE_PRE1) dv[c] = bload<float>(rD, ooff, pk + c * cb);
+        if constexpr (EP != MGE_RES && EP != MGE_NONE) dv[c] = bload<float>(rD, ooff, pk + c * cb);
       }
     }
 #pragma unroll
@@ -324,11 +324,6 @@ void mg_l1_kernel(MgBatch B, int tiles, int per, int nrhs, int tz, int live) {
           bstore<float, 0>(r, rR, ooff, o);
           bstore<float, 0>(op[c] + d1, rX, ooff, o);
           bstore<float, 0>(d1, rQ, ooff, o);
-        } else if constexpr (EP == MGE_PRE1) {
-          bstore<float, 0>(aux[0][c] - q, rR, ooff, o);
-          bstore<float, 0>(op[c], rX, ooff, o);
-        } else if constexpr (EP == MGE_POST1) {
-          bstore<float, 0>(op[c] + dv[c] * ith * (aux[0][c] - q), rQ, ooff, o);
         } else if constexpr (EP == MGE_RES) {
           bstore<float, 0>(aux[0][c] - q, rR, ooff, o);
         } else if constexpr (EP == MGE_POST) {
@@ -422,8 +417,6 @@ hipError_t mg_launch_l1(const MgBatch &B, int n_max, int nrhs, hipStream_t st, i
     case MGE_STEP1: launch_l1<MGE_STEP1>(B, n_max, nrhs, live, st); break;
     case MGE_RES: launch_l1<MGE_RES>(B, n_max, nrhs, live, st); break;
     case MGE_POST: launch_l1<MGE_POST>(B, n_max, nrhs, live, st); break;
-    case MGE_PRE1: launch_l1<MGE_PRE1>(B, n_max, nrhs, live, st); break;
-    case MGE_POST1: launch_l1<MGE_POST1>(B, n_max, nrhs, live, st); break;
     case MGE_LAST: launch_l1<MGE_LAST>(B, n_max, nrhs, live, st); break;
     default: launch_l1<MGE_NONE>(B, n_max, nrhs, live, st); break;
   }

@@ -71,17 +71,6 @@ constexpr int POWER_ITERS = 30;  // power steps per coarse level
 // 48^3 grid's 24^3 level takes 4 us a pass from the stencil.
 bool level1_free(int prec, long long nn) { return prec == SHH_PREC_MIXED && mg_apply_wide(nn); }
 
-// Level 1 of the floored solve smooths by one step each side (degree 1, like
-// its voxel level) from this many nodes an edge: two operator passes of its four
-// fall away for 3 to 15 % more iterations (mixed: 128^3 51.1 -> 47.1 ms, 256^3
-// 785 -> 702, 48^3 10.0 -> 9.2; FP64: 128^3 101.7 -> 92.8, 48^3 13.3 -> 12.8).
-// With 20^3 nodes FP64 gained nothing (10.18 -> 10.15), with 12^3 it took 20 % more
-// iterations and more time (11.4 -> 11.6); with the levels below at degree 1 too,
-// 30 % more iterations (128^3 54.5 ms).  The culled solve keeps two steps
-// throughout: one 128^3 design gained 9 %, but a 64^3 design near the limit of
-// FP32 no longer reached 3e-6.
-constexpr int DEG1_MIN = 24;
-
 // Lay out the multigrid region at `base` (nullptr: sizing only).  Fills the
 // level descriptors' persistent buffers, G and Mc.
 size_t carve(char *base, int n, int prec, MgDev *mg, char **d_mgdev) {
@@ -128,7 +117,6 @@ size_t carve(char *base, int n, int prec, MgDev *mg, char **d_mgdev) {
       L.r = v[2];
       L.d = v[3];
       L.q = v[4];
-      L.xo = L.x;
     }
   }
   const long long nc = nl * nl * nl;
@@ -334,19 +322,17 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
     return apply0(smooth, SMG_POST);
   }
   // an operator pass with the Chebyshev sweep after it fused in
-  // (steps: for the designs that smooth by so many)
-  std::vector<Slot *> by_form[3][2];  // one launch per form of the operator and smoother
+  std::vector<Slot *> by_form[3];  // one launch per form of the operator
   for (Slot *s : smooth)
-    by_form[l == 1 && s->mg.l1free ? 2 : int(mg_apply_wide(s->mg.lv[l].nn))][l == 1 && s->mg.deg1 ? 0 : 1].push_back(s);
-  auto app = [&](int ep, int steps) -> int {
+    by_form[l == 1 && s->mg.l1free ? 2 : int(mg_apply_wide(s->mg.lv[l].nn))].push_back(s);
+  auto app = [&](int ep) -> int {
     if ((rc = tb(l == 1))) return rc;
     for (int w = 0; w < 3; ++w) {
-      const std::vector<Slot *> &part = by_form[w][steps - 1];
-      if (part.empty()) continue;
-      const MgBatch Bw = batch_of(part);
+      if (by_form[w].empty()) continue;
+      const MgBatch Bw = batch_of(by_form[w]);
       long long nn = 0;
       int n = 0;
-      for (Slot *s : part) {
+      for (Slot *s : by_form[w]) {
         nn = std::max(nn, s->mg.lv[l].nn);
         n = std::max(n, s->mg.lv[l].n);
       }
@@ -356,14 +342,8 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
     return te(SHH_PROF_MG_APPLY1);
   };
   // pre-smoother (the restriction to this level left its first direction in d);
-  // its last pass leaves the residual to restrict in r.  One step or two: the
-  // designs of a batch may differ on level 1
-  std::vector<Slot *> two;
-  for (Slot *s : smooth)
-    if (!(l == 1 && s->mg.deg1)) two.push_back(s);
-  const bool one = two.size() < smooth.size();
-  if (one && (rc = app(MGE_PRE1, 1))) return rc;
-  if (!two.empty() && ((rc = app(MGE_STEP1, 2)) || (rc = app(MGE_RES, 2)))) return rc;
+  // its second pass leaves r - A d1, the residual to restrict, in r
+  if ((rc = app(MGE_STEP1)) || (rc = app(MGE_RES))) return rc;
   // coarse-grid correction (a tail below this level restricts and prolongs
   // by itself)
   std::vector<Slot *> step;
@@ -374,8 +354,7 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
   if ((rc = vcycle(smooth, l + 1, st, timer, apply0))) return rc;
   if (!step.empty()) SHH_HIP(mg_launch_prolong(Bs, l, nn_next_max, prec, st));
   // post-smoother
-  if (one && (rc = app(MGE_POST1, 1))) return rc;
-  if (!two.empty() && ((rc = app(MGE_POST, 2)) || (rc = app(MGE_LAST, 2)))) return rc;
+  if ((rc = app(MGE_POST)) || (rc = app(MGE_LAST))) return rc;
   return SHH_OK;
 }
 
@@ -408,12 +387,10 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
   L0.nchunks = h.nchunks;
   L0.Dinv = h.Dinv;
   L0.r = h.q[1];
-  mg.deg1 = mg.L > 1 && mg.lv[1].n >= DEG1_MIN && !is_selective(s.opts.solver);
-  if (mg.deg1) mg.lv[1].xo = mg.lv[1].q;
   if (prec == SHH_PREC_MIXED && mg_share_bytes(n, h.tz, h.ntiles[1]) > sizeof(float) * 3 * (size_t)h.nn)
     return SHH_UNSUPPORTED;  // no grid: the shares are at most two thirds of the residual
   h.mgd = L0.d;
-  h.mgxc = mg.lv[1].xo;
+  h.mgxc = mg.lv[1].x;
   // element matrices of levels >= 1 live in the (not yet used) CG vector region
   {
     char *ke = s.base + s.lay.vec;

@@ -401,7 +401,7 @@ int sel_start(const std::vector<Slot *> &in, hipStream_t st) {
       h.n1 = M.lv[1].n;
       h.nn1 = M.lv[1].nn;
       h.b1 = M.lv[1].b;
-      h.x1 = M.lv[1].xo;
+      h.x1 = M.lv[1].x;
       h.dir1 = M.L > 1 ? M.lv[1].d : nullptr;
       h.dinv1 = M.lv[1].Dinv;
       h.inv_theta1 = M.lv[1].inv_theta;

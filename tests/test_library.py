@@ -231,6 +231,20 @@ def test_multigrid_solver_option(lib):
         assert nsj == nj and nsel == (nm if rc_m == B.SHH_OK else nj), n
 
 
+@pytest.mark.parametrize("n,precision,nbytes", [
+    (6, "fp64", 839168), (24, "fp64", 20139008), (48, "fp64", 157383680), (128, "fp64", 2975517184),
+    (6, "mixed", 703232), (24, "mixed", 12421376), (48, "mixed", 95752448), (64, "mixed", 226496256)])
+def test_multigrid_workspaces_do_not_grow(lib, n, precision, nbytes):
+    # a caller may hold workspaces and arenas of sizes asked for once: these are
+    # the bytes of 16 charges at K = 3 with the first release's hierarchy descriptor
+    d = wl.Design(pos=np.zeros((16, 3)), q=np.ones(16), n=n, K=3, thickness=0.1)
+    rc, got = ws_bytes(lib, d, precision, solver="mg")
+    assert rc == B.SHH_OK and got <= nbytes
+    a, o, nb = B.DesignArgs(d), B.make_opts(precision, solver="mg"), c_size_t(0)
+    assert lib.shh_engine_footprint(byref(a.c), byref(o), byref(nb)) == B.SHH_OK
+    assert nb.value <= nbytes - 43264  # less the segment tables and the alignment
+
+
 def test_field_entry_point_validation(lib):
     # argument checks of shh_homogenize_field that return before any device work
     from ctypes import c_double, c_void_p
