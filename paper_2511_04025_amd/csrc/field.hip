@@ -161,6 +161,7 @@ __global__ __launch_bounds__(256) void field_kernel(SlotDev *s) {
 // ---- hard step: bins of the order-statistic search (below) -------------------
 constexpr int SEL_BITS = 11, SEL_BINS = 1 << SEL_BITS, SEL_PASSES = 6;  // 6 x 11 >= 64
 constexpr int SEL_T = 512;   // threads of a counting workgroup
+constexpr unsigned long long INF_BITS = 0x7FF0000000000000ull;
 
 // ---- distance d = |F - c| / max(||grad F||, 1e-12 max ||grad F||) ------------
 __global__ __launch_bounds__(256) void distance_kernel(SlotDev *s) {
@@ -189,13 +190,14 @@ __global__ __launch_bounds__(256) void distance_kernel(SlotDev *s) {
 }
 
 // ---- hard step: the k1-th and k2-th smallest distance (1-based) ---------------
-// Non-negative doubles (and +inf) order like their bit patterns.  A radix
-// search from the top: pass p counts, among the elements that share the digits
-// found so far, the next 11 bits (per search: the two ranks may part), in LDS
-// bins that go to the pass's global bins.  The next pass finds the digit that
-// holds the rank, every workgroup for itself: with a last-arrival step (a release
-// per workgroup, one workgroup's scan) a pass took 17 us at 128^3 instead of 8.  (A
-// 16-way search by counting against 15 pivots per rank took 18 launches of 32 us.)
+// Non-negative doubles (and +inf, which a NaN counts as) order like their bit
+// patterns.  A radix search from the top: pass p counts, among the elements that
+// share the digits found so far, the next 11 bits (per search: the two ranks may
+// part), in LDS bins that go to the pass's global bins.  The next pass finds the
+// digit that holds the rank, every workgroup for itself: with a last-arrival step
+// (a release per workgroup, one workgroup's scan) a pass took 17 us at 128^3
+// instead of 8.  (A 16-way search by counting against 15 pivots per rank took 18
+// launches of 32 us.)
 struct SelState {  // at the entry of a pass
   unsigned long long pre[2];   // the digits found
   unsigned long long rank[2];  // the rank left below them
@@ -281,8 +283,9 @@ __global__ __launch_bounds__(SEL_T) void select_pass_kernel(SlotDev *s, int pass
 #pragma unroll
     for (int j = 0; j < UN; ++j) {
       if (e0 + j * stride >= nn) break;
-      const unsigned dig = unsigned(v[j] >> shift) & (SEL_BINS - 1);
-      const unsigned long long top = pass ? v[j] >> hi : 0ull;
+      const unsigned long long b = v[j] < INF_BITS ? v[j] : INF_BITS;
+      const unsigned dig = unsigned(b >> shift) & (SEL_BINS - 1);
+      const unsigned long long top = pass ? b >> hi : 0ull;
       if (top == (pass ? at.pre[0] >> hi : 0ull)) atomicAdd(&bins[0][dig], 1u);
       if (!same && top == at.pre[1] >> hi) atomicAdd(&bins[1][dig], 1u);
     }

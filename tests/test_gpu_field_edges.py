@@ -45,6 +45,25 @@ def test_thickness_is_the_midpoint_of_two_order_statistics(n, vf):
     assert np.array_equal(r["beta"].cpu().numpy(), (r["d"].cpu().numpy() < t).astype(float))
 
 
+@pytest.mark.parametrize("q", [2e307, 8e307, 1.7e308])
+@pytest.mark.parametrize("vf", [0.02, 0.5, 0.98])
+def test_thickness_counts_a_nan_distance_as_infinite(q, vf):
+    # charges whose field overflows: some distances are infinite and some, from
+    # the difference of infinities, no numbers; a rank among those means t = inf
+    from paper_2511_04025_amd import api
+    n = 12
+    d = wl.Design(pos=np.array([[0.1, 0.2, 0.3], [0.6, 0.55, 0.9]]), q=np.array([q, -q]), n=n, dist_mode=1, target_vf=vf)
+    print(f"overflowing field q {q} vf {vf}", flush=True)
+    r = api.field(d)
+    dist = r["d"].cpu().numpy()
+    s = np.sort(np.where(np.isnan(dist), np.inf, dist).ravel())
+    k = int(np.floor(vf * n ** 3 + 0.5))
+    with np.errstate(over="ignore"):
+        t = 0.5 * (s[k - 1] + s[k])
+    assert r["t"] == t
+    assert np.array_equal(r["beta"].cpu().numpy(), (dist < t).astype(float))
+
+
 @pytest.mark.parametrize("n,vf,kappa", [(2, 0.4, 1e7), (3, 0.5, 30.0), (17, 0.01, 50.0), (33, 0.97, 400.0),
                                         (128, 0.3, 256.0), (130, 0.3, 256.0)])
 def test_logistic_thickness_is_the_bisection(n, vf, kappa):
