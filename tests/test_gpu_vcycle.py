@@ -86,6 +86,27 @@ def test_level_one_from_moduli_matches_the_stored_stencil(n):
     assert float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
 
 
+# (n, nu): rms and largest error of the FP32 product A_1 v with a stencil stored in
+# FP32 (element matrices summed in FP64, rounded once), in units of the largest
+# modulus times the largest entry of v: moduli 0.1 + U[0, 1), v normal
+STORED = {(80, 0.3): (5.69e-8, 7.97e-7), (96, -0.5): (7.69e-8, 1.23e-6), (96, 0.0): (4.56e-8, 7.54e-7),
+          (96, 0.45): (1.28e-7, 1.51e-6), (96, 0.49): (5.58e-7, 6.28e-6), (160, 0.3): (4.85e-8, 7.56e-7)}
+
+
+@pytest.mark.parametrize("n,nu", sorted(STORED))
+def test_level_one_from_moduli_is_no_further_off_than_the_stored_stencil(n, nu):
+    # the moduli enter in FP32 and the element is formed in FP32
+    import torch
+    from paper_2511_04025_amd import api
+    m = n // 2
+    E = (0.1 + torch.rand(n, n, n, generator=torch.Generator().manual_seed(n), dtype=torch.float64)).cuda()
+    V = torch.randn(6, 3, m, m, m, generator=torch.Generator().manual_seed(n + 1), dtype=torch.float64).float().cuda()
+    print(f"level one error {n}^3 nu {nu}", flush=True)
+    d = api.mg_operator(E, V, nu, 1, "mixed").double() - api.mg_operator(E, V.double(), nu, 1, "fp64")
+    d /= float(E.max()) * float(V.abs().max())
+    assert float(d.pow(2).mean().sqrt()) <= STORED[n, nu][0] and float(d.abs().max()) <= STORED[n, nu][1]
+
+
 @pytest.mark.parametrize("n", [32, 40, 48, 64])
 def test_one_step_smoothing_beside_two(n):
     # hierarchies of different depths and operator forms in one batch: the passes
