@@ -1004,7 +1004,10 @@ __global__ __launch_bounds__(256) void mg_inv_assemble_kernel(MgBatch B) {
   block_sum<1>(acc, red, 256);
   if (threadIdx.x == 0) red[0] = acc[0];
   __syncthreads();
-  const double mean_diag = red[0] / m, add = mean_diag / double(nn);
+  // a stencil past the range of FP32 has no inverse: a zero matrix, all of whose
+  // pivots vanish below, leaves the coarsest level out of the cycle
+  const bool finite = isfinite(red[0]);
+  const double mean_diag = finite ? red[0] / m : 0.0, add = mean_diag / double(nn);
   if (blockIdx.x == 0 && threadIdx.x == 0) *InvScratch((double *)mg->inv, (m + IB - 1) / IB).mean = mean_diag;
   // one wave per row: the constant blocks, then the 81 stencil entries on top
   // (27 distinct neighbours: n >= 3)
@@ -1026,7 +1029,7 @@ __global__ __launch_bounds__(256) void mg_inv_assemble_kernel(MgBatch B) {
       const int w = (dz + 1) * 9 + (dy + 1) * 3 + dx + 1;
       a += w >= 13 ? (double)S[((w - 13) * 9 + 3 * c + cp) * nn + v] : (double)S[((13 - w) * 9 + 3 * cp + c) * nn + u];
     }
-    A[j] = a;
+    A[j] = finite ? a : 0.0;
   }
 }
 

@@ -396,7 +396,9 @@ int mg_setup_levels(Slot &s, hipStream_t st, double &bound0) {
     char *ke = s.base + s.lay.vec;
     size_t used = 0;
     for (int l = 1; l < count; ++l) {
-      mg.lv[l].pw_scale = 1.0;
+      // about 1 / ||x|| of the power iteration's start, so that no step multiplies a
+      // vector of entries above 1 (a power of two: the steps round as without it)
+      mg.lv[l].pw_scale = std::exp2(-std::floor(0.5 * std::log2(double(mg.lv[l].nn))));
       if (l == 1 && mg.l1free) continue;
       mg.lv[l].Ke = ke + used;
       used = a256(used + (size_t)mg.lv[l].nn * 576 * ts);

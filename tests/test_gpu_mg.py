@@ -309,3 +309,19 @@ def test_served_engine_vs_oracle_with_staggered_arrivals():
               f"small {small:.2e} frob {frob:.2e}", flush=True)
         assert np.array_equal(r["C"], alone[i]["C"]), i
         assert np.array_equal(r["iters"], alone[i]["iters"]), i
+
+
+@pytest.mark.parametrize("n,scale", [(24, 1e37), (20, 5e37), (24, 5e37), (40, 5e37), (56, 5e37), (80, 2.5e37)])
+def test_moduli_at_the_end_of_fp32(n, scale):
+    # the coarse operators grow by two a level, so their sums come to FP32's range
+    # before the moduli do: the coarsest stencil passes it (all but 24, 1e37), and the
+    # cycle goes on without that level; the power iteration's products stay within.
+    # C^H / scale is that of the same moduli at scale 1 (rtol 1e-6: error its square)
+    from paper_2511_04025_amd import api
+    u = torch.rand(n, n, n, generator=torch.Generator().manual_seed(1), dtype=torch.float64)
+    E = torch.where(u < 0.5, 1.0, 0.5).double().cuda()
+    print(f"large moduli {n}^3 scale {scale}", flush=True)
+    ref = api.homogenize_stiffness(E, 0.3, precision="mixed", rtol=1e-6, solver="mg")
+    r = api.homogenize_stiffness(E * scale, 0.3, precision="mixed", rtol=1e-6, solver="mg")
+    assert r["status"] == 0
+    assert_ch_close(r["C"] / scale, ref["C"], 1e-9)
