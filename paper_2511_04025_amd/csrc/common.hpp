@@ -66,6 +66,16 @@ struct Tile {
   static_assert(THREADS <= 1024, "one workgroup");
 };
 
+// Halo-tile index of ring node j: the bottom row, the top row, then the left
+// and right columns between them.
+template <int HX, int HY>
+__device__ __forceinline__ int ring_h(int j) {
+  if (j < HX) return j;
+  if (j < 2 * HX) return (HY - 1) * HX + (j - HX);
+  if (j < 2 * HX + (HY - 2)) return (1 + j - 2 * HX) * HX;
+  return (2 + j - 2 * HX - (HY - 2)) * HX - 1;
+}
+
 // ---- vector-update chunking ----
 constexpr int CHUNK = 1024;         // nodes per workgroup in the update kernels (4 per thread)
 constexpr int VEC_THREADS = 256;
@@ -97,11 +107,10 @@ struct CgState {
   int mgpar[NRHS];        // multigrid CG: which p buffer holds the current direction
   int no_keep[NRHS];      // selective multigrid CG: restart after every replacement (set by a stall)
   int stag[NRHS];         // selective CG: replacements since the true residual last fell by 1 %
-  unsigned cnt[8];        // last-workgroup counters (0..5 per load case, 6, 7 misc)
+  unsigned arrived;       // last-workgroup counter of the energy form
   double V;               // volume fraction
   double t;               // half-thickness used
-  double gmax;            // max ||grad F|| (stored as bits for atomicMax)
-  unsigned long long gmax_bits;
+  unsigned long long gmax_bits;  // max ||grad F|| (as bits, for atomicMax)
   double Emax;
   double C[36];           // homogenized tensor
 };

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void energy_kernel(SlotDev *s, int nblocks, co
 #pragma unroll
     for (int t = 0; t < 21; ++t) parts[21 * blockIdx.x + t] = acc[t];
   }
-  if (!arrive_last(&s->st->cnt[7], nblocks, &lastflag)) return;
+  if (!arrive_last(&s->st->arrived, nblocks, &lastflag)) return;
   double tot[21];
   sum_partials<21, 21>(parts, nblocks, tot, red, 256);
   if (threadIdx.x == 0) {
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void energy_kernel(SlotDev *s, int nblocks, co
         s->st->C[i * 6 + j] = c;
         s->st->C[j * 6 + i] = c;
       }
-    s->st->cnt[7] = 0;
+    s->st->arrived = 0;
   }
 }
 

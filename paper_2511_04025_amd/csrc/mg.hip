@@ -268,13 +268,12 @@ __device__ __forceinline__ void mg_epilogue(const MgEpi<T> &E, long long j, T di
   }
 }
 
-// the operator's input vector of an epilogue (MGE_NONE: src 0 x, 1 d)
+// the operator's input vector of an epilogue (MGE_NONE: x)
 template <typename T, int EP>
-__device__ __forceinline__ const T *mg_operand(const MgLevel &L, int src) {
+__device__ __forceinline__ const T *mg_operand(const MgLevel &L) {
   if constexpr (EP == MGE_STEP1 || EP == MGE_LAST) return (const T *)L.d;
   else if constexpr (EP == MGE_RES) return (const T *)L.q;
-  else if constexpr (EP == MGE_POST) return (const T *)L.x;
-  else return (const T *)(src == 0 ? L.x : L.d);
+  else return (const T *)L.x;
 }
 
 // q = A_l v (v = x or d of the level) on levels of at most 32^3 nodes, where a
@@ -391,7 +390,7 @@ __device__ __forceinline__ T mg_split_total(T (*part)[RHS * 3][64], int q, int l
 
 // grid x = 64-node blocks, y = groups of RHS load cases, z = slot
 template <typename T, int RHS, int G, int EP>
-__global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) void mg_apply_split_kernel(MgBatch B, int l, int src, int live) {
+__global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) void mg_apply_split_kernel(MgBatch B, int l, int live) {
   __shared__ T part[G][RHS * 3][64];
   constexpr int IT = (RHS * 3 + G - 1) / G;
   const MgLevel &L = B.mg[blockIdx.z]->lv[l];
@@ -414,7 +413,7 @@ __global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) voi
   const SHH_GLOBAL T *Dv = to_global((const T *)L.Dinv);
   // a node with a zero diagonal has a zero row (every element around it
   // culled): A v = 0 there without reading its stencil
-  mg_split_sum<T, RHS, G>(L, mg_operand<T, EP>(L, src) + (long long)r0 * 3 * nn, v, g, act, Dv[v] == T(0), part);
+  mg_split_sum<T, RHS, G>(L, mg_operand<T, EP>(L) + (long long)r0 * 3 * nn, v, g, act, Dv[v] == T(0), part);
   // the inputs of this thread's share of the fused sweep, loaded before the
   // waves meet
   const MgEpi<T> E = mg_epi<T>(L);
@@ -449,7 +448,7 @@ __global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) voi
 // broadcast element instead of branching around them (7 % faster), and the
 // fused sweep loads all of a node's inputs before its first store.
 template <typename T, int EP>
-__global__ __launch_bounds__(256) void mg_apply_pair_kernel(MgBatch B, int l, int src, int live) {
+__global__ __launch_bounds__(256) void mg_apply_pair_kernel(MgBatch B, int l, int live) {
   const MgLevel &L = B.mg[blockIdx.z]->lv[l];
   const long long nn = L.nn;
   const int n = L.n;
@@ -471,7 +470,7 @@ __global__ __launch_bounds__(256) void mg_apply_pair_kernel(MgBatch B, int l, in
   const long long v0 = (long long)z0 * plane + xy;
   const SHH_GLOBAL T *S = to_global((const T *)L.S);
   const SHH_GLOBAL T *Dv = to_global((const T *)L.Dinv);
-  const SHH_GLOBAL T *in = to_global(mg_operand<T, EP>(L, src));
+  const SHH_GLOBAL T *in = to_global(mg_operand<T, EP>(L));
   // nodes with a zero diagonal have a zero row (every element around them
   // culled): A v = 0 there without reading their stencil
   const bool zero_rows = Dv[v0] == T(0) && Dv[v0 + plane] == T(0);
@@ -1185,36 +1184,36 @@ bool mg_apply_wide(long long nn) { return nn > 32768; }
 
 namespace {
 template <typename T, int EP>
-void launch_apply_ep(const MgBatch &B, int l, int src, long long nn_max, bool wide, hipStream_t st, int live) {
+void launch_apply_ep(const MgBatch &B, int l, long long nn_max, bool wide, hipStream_t st, int live) {
   if (wide) {
-    mg_apply_pair_kernel<T, EP><<<dim3(blocks_for(nn_max / 2, 256), 1, B.count), 256, 0, st>>>(B, l, src, live);
+    mg_apply_pair_kernel<T, EP><<<dim3(blocks_for(nn_max / 2, 256), 1, B.count), 256, 0, st>>>(B, l, live);
   } else if (nn_max > 4096) {
     constexpr int R = sizeof(T) == 4 ? NRHS : 2;  // FP64: six cases would not fit the registers
     mg_apply_split_kernel<T, R, 3, EP>
-        <<<dim3(blocks_for(nn_max, 64), NRHS / R, B.count), 192, 0, st>>>(B, l, src, live);
+        <<<dim3(blocks_for(nn_max, 64), NRHS / R, B.count), 192, 0, st>>>(B, l, live);
   } else {
     mg_apply_split_kernel<T, 2, 9, EP>
-        <<<dim3(blocks_for(nn_max, 64), NRHS / 2, B.count), 576, 0, st>>>(B, l, src, live);
+        <<<dim3(blocks_for(nn_max, 64), NRHS / 2, B.count), 576, 0, st>>>(B, l, live);
   }
 }
 template <typename T>
-void launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, hipStream_t st, int live, int ep) {
+void launch_apply(const MgBatch &B, int l, long long nn_max, bool wide, hipStream_t st, int live, int ep) {
   switch (ep) {
-    case MGE_STEP1: launch_apply_ep<T, MGE_STEP1>(B, l, src, nn_max, wide, st, live); break;
-    case MGE_RES: launch_apply_ep<T, MGE_RES>(B, l, src, nn_max, wide, st, live); break;
-    case MGE_POST: launch_apply_ep<T, MGE_POST>(B, l, src, nn_max, wide, st, live); break;
-    case MGE_LAST: launch_apply_ep<T, MGE_LAST>(B, l, src, nn_max, wide, st, live); break;
-    default: launch_apply_ep<T, MGE_NONE>(B, l, src, nn_max, wide, st, live); break;
+    case MGE_STEP1: launch_apply_ep<T, MGE_STEP1>(B, l, nn_max, wide, st, live); break;
+    case MGE_RES: launch_apply_ep<T, MGE_RES>(B, l, nn_max, wide, st, live); break;
+    case MGE_POST: launch_apply_ep<T, MGE_POST>(B, l, nn_max, wide, st, live); break;
+    case MGE_LAST: launch_apply_ep<T, MGE_LAST>(B, l, nn_max, wide, st, live); break;
+    default: launch_apply_ep<T, MGE_NONE>(B, l, nn_max, wide, st, live); break;
   }
 }
 }  // namespace
 
 // nn_max: the largest of the level over the batch; wide: every design of the
 // batch takes the two-nodes-per-thread form (mg_apply_wide), else none does
-hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, int prec,
+hipError_t mg_launch_apply(const MgBatch &B, int l, long long nn_max, bool wide, int prec,
                            hipStream_t st, int live, int ep) {
-  if (prec == 0) launch_apply<double>(B, l, src, nn_max, wide, st, live, ep);
-  else launch_apply<float>(B, l, src, nn_max, wide, st, live, ep);
+  if (prec == 0) launch_apply<double>(B, l, nn_max, wide, st, live, ep);
+  else launch_apply<float>(B, l, nn_max, wide, st, live, ep);
   return hipGetLastError();
 }
 

@@ -98,15 +98,6 @@ struct CoarseTile {
   static_assert(NELEMC <= THREADS && NHALO >= THREADS && NHALO <= 2 * THREADS, "one element, two staged nodes a thread");
 };
 
-// Halo-tile index of ring node j (as in stencil.hip)
-template <int HX, int HY>
-__device__ __forceinline__ int coarse_ring(int j) {
-  if (j < HX) return j;
-  if (j < 2 * HX) return (HY - 1) * HX + (j - HX);
-  if (j < 2 * HX + (HY - 2)) return (1 + j - 2 * HX) * HX;
-  return (2 + j - 2 * HX - (HY - 2)) * HX - 1;
-}
-
 // grid: 8 XCDs x per; logical workgroup = ((slot * tiles + tile) * nrhs + load
 // case); tz: planes a workgroup marches (no sums: the result does not depend on
 // the tiling)
@@ -144,7 +135,7 @@ void mg_l1_kernel(MgBatch B, int tiles, int per, int nrhs, int tz, int live) {
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int j = k == 0 ? tid - TT::NINT : tid + 256 - TT::NINT;
-    const int h = k == 0 && tid < TT::NINT ? (oy + 1) * HX + ox + 1 : coarse_ring<HX, HY>(k == 1 && !ring2 ? 0 : j);
+    const int h = k == 0 && tid < TT::NINT ? (oy + 1) * HX + ox + 1 : ring_h<HX, HY>(k == 1 && !ring2 ? 0 : j);
     hslot[k] = h;
     hoff[k] = ((uint32_t)wrapi(y0 - 1 + h / HX, n) * n + (uint32_t)wrapi(x0 - 1 + h % HX, n)) * 4u;
   }

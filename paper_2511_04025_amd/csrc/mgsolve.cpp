@@ -30,7 +30,7 @@ size_t mg_inverse_scratch_bytes(int ndof);
 hipError_t mg_launch_coarse_inverse(const MgBatch &B, int ndof_max, int prec, hipStream_t st);
 // live = 1: skip the load cases whose CG has stopped (state read on the device)
 // ep: the Chebyshev sweep fused into the output stage (MGE_*)
-hipError_t mg_launch_apply(const MgBatch &B, int l, int src, long long nn_max, bool wide, int prec,
+hipError_t mg_launch_apply(const MgBatch &B, int l, long long nn_max, bool wide, int prec,
                            hipStream_t st, int live, int ep);
 bool mg_apply_wide(long long nn);
 hipError_t mg_launch_l1(const MgBatch &B, int n_max, int nrhs, hipStream_t st, int live, int ep);
@@ -337,7 +337,7 @@ int vcycle(const std::vector<Slot *> &slots, int l, hipStream_t st, Solver *time
         n = std::max(n, s->mg.lv[l].n);
       }
       if (w == 2) SHH_HIP(mg_launch_l1(Bw, n, NRHS, st, 1, ep));
-      else SHH_HIP(mg_launch_apply(Bw, l, 0, nn, w == 1, prec, st, 1, ep));
+      else SHH_HIP(mg_launch_apply(Bw, l, nn, w == 1, prec, st, 1, ep));
     }
     return te(SHH_PROF_MG_APPLY1);
   };
@@ -564,7 +564,7 @@ int mg_apply_level(Slot &s, int l, const void *d_v, void *d_q, hipStream_t st) {
   SHH_HIP(hipMemcpyAsync(L.x, d_v, bytes, hipMemcpyDeviceToDevice, st));
   // (the odd coarsest level is small: never the two-nodes-per-thread form)
   if (l == 1 && s.mg.l1free) SHH_HIP(mg_launch_l1(batch_of({&s}), L.n, NRHS, st, 0, MGE_NONE));
-  else SHH_HIP(mg_launch_apply(batch_of({&s}), l, 0, L.nn, mg_apply_wide(L.nn), s.host.prec, st, 0, MGE_NONE));
+  else SHH_HIP(mg_launch_apply(batch_of({&s}), l, L.nn, mg_apply_wide(L.nn), s.host.prec, st, 0, MGE_NONE));
   SHH_HIP(hipMemcpyAsync(d_q, L.q, bytes, hipMemcpyDeviceToDevice, st));
   SHH_HIP(hipStreamSynchronize(st));
   return SHH_OK;

@@ -52,16 +52,6 @@ namespace shh {
 
 enum { MODE_PCG = 0, MODE_RESID = 1, MODE_APPLY = 2, MODE_MGDIR = 3, MODE_MGPRE = 4, MODE_MGPOST = 5 };
 
-// Halo-tile index of ring node j: the bottom row, the top row, then the left
-// and right columns between them.
-template <int HX, int HY>
-__device__ __forceinline__ int ring_h(int j) {
-  if (j < HX) return j;
-  if (j < 2 * HX) return (HY - 1) * HX + (j - HX);
-  if (j < 2 * HX + (HY - 2)) return (1 + j - 2 * HX) * HX;
-  return (2 + j - 2 * HX - (HY - 2)) * HX - 1;
-}
-
 // Waves per SIMD that the compiler aims at.  Two workgroups share a CU up to 128
 // registers (FP32, four waves) or 168 (FP64, three).  The FP64 pre-smoothing pass
 // fits when told to; the FP64 direction and post-smoothing passes would spill (a
