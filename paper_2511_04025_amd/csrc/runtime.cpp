@@ -166,12 +166,16 @@ int next_poll(const std::vector<Slot *> &slots, int fixed) {
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // The tiling of a slot's operator passes.  FP64: 32 x 14 nodes keep eight waves on
-// a CU (one workgroup; the passes' registers allow no more), 32 x 8 five, or ten where
-// two workgroups fit.  Multigrid takes the tall tile where it costs at most a
-// fifteenth more waves than the other (48^3 12.7 -> 11.0 ms, 64^3 17.4 -> 14.5, 96^3
-// 38.6 -> 29.8), the Jacobi CG where it costs none (25^3 10.4 -> 8.3, 101^3 709 ->
-// 677; flat stays 71^3, where tall took 203 for 187).  Below 25^3 every pass is flat
-// (24^3 multigrid 11.3, tall 11.6).  It depends on the grid and solver alone.
+// a CU (one workgroup; the passes' registers allow no more), 32 x 8 five, or ten
+// where two workgroups fit.  The tall tile pays where it needs no more waves in all
+// than the flat one, since more of them share a halo (ms, flat and tall: multigrid
+// 28^3 5.8 and 5.3, 64^3 17.2 and 14.6, 96^3 34.1 and 27.5; Jacobi 25^3 9.2 and
+// 7.4, 101^3 703 and 674), and in the multigrid, whose passes stage more, up to a
+// tenth more: 48^3 (7 % more waves) 10.3 and 9.1, 32^3 (20 % more) 5.1 and 5.2.
+// The Jacobi CG is even there (7 % more: 45^3 35.5 and 34.8, 71^3 162 and 179; as
+// many: 57^3 69.6 and 72.3).  Below 25^3 a pass is as long as one workgroup, and
+// the flat tile's is the shorter (multigrid 16^3 4.8 and 4.9, 24^3 4.1 and 4.2).
+// It depends on the grid, precision and solver alone.
 static int tile_x(int tiling) { return tiling == TILING_F32 ? Tile<float>::X : Tile<double>::X; }
 static int tile_y(int tiling) {
   return tiling == TILING_F32 ? Tile<float>::Y : (tiling == TILING_F64 ? Tile<double>::Y : Tile<double, true>::Y);
@@ -183,20 +187,20 @@ static int tiling_for(int n, int prec, int solver) {
   if (prec != SHH_PREC_FP64) return TILING_F32;
   const int tall = tile_count(n, TILING_F64_TALL) * (Tile<double, true>::THREADS / 64);
   const int flat = tile_count(n, TILING_F64) * (Tile<double>::THREADS / 64);
-  return n >= 25 && (solver == SHH_SOLVER_MG ? 15 * tall <= 16 * flat : tall <= flat) ? TILING_F64_TALL : TILING_F64;
+  return n >= 25 && (solver == SHH_SOLVER_MG ? 10 * tall <= 11 * flat : tall <= flat) ? TILING_F64_TALL : TILING_F64;
 }
 
 // z planes per stencil workgroup (the z-march length) of an n^3 grid.  One
 // design's six load cases are tiles x runs x 6 workgroups on 512 places (two
-// workgroups on each of 256 CUs); a workgroup of tz planes takes about tz + 3
+// workgroups on each of 256 CUs; 256 with the tall FP64 tile); a workgroup of tz planes takes about tz + 3
 // layer times (two planes of halo and the pipeline's start).  The length is the
 // even one, at most 64, with the smallest sum of the time of one design alone
 // (whole rounds over the places) and twice that in a large batch (rounds
-// shared): short runs where the grid would leave the chip idle (48^3: 6 planes,
-// where 32 ran 96 workgroups: a Jacobi pass at 45^3 61 -> 27 us, a design at
-// 24^3 in FP64 27.6 -> 19.9 ms), balanced rounds on larger grids (128^3: 26,
-// where 32 left the third round at 6 %).  It depends on the grid and precision
-// alone, so a design's result does not depend on its batch.
+// shared): short runs where the grid would leave the chip idle (FP32, 48^3: 6
+// planes, where 32 ran 96 workgroups: a Jacobi pass at 45^3 61 -> 27 us; a design
+// at 24^3 in FP64 27.6 -> 19.9 ms), balanced rounds on larger grids (FP32, 128^3:
+// 26, where 32 left the third round at 6 %).  It depends on the grid, precision and
+// solver alone, so a design's result does not depend on its batch.
 static int tz_for(int n, int tiling) {
   // the tall FP64 tile's LDS leaves one workgroup on a CU
   const long long places = tiling == TILING_F32 ? 256 * (1024 / Tile<float>::THREADS) : (tiling == TILING_F64 ? 512 : 256);
