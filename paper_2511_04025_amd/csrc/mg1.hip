@@ -22,7 +22,10 @@
 // instructions per element and load case).  With it the served batch of eight
 // 128^3 designs went from 676 to 591 ms, its setup from 31 to 20 ms (no stencil
 // to assemble), one 128^3 design from 60.8 to 55.0 ms; and a level keeps 504
-// bytes a node less.
+// bytes a node less.  The product is closer to FP64's than that of the stored
+// stencil, whose entries are rounded before they cancel: rms error at 96^3, random
+// moduli and vectors, nu 0.3, 5.2e-8 -> 3.6e-8 of the largest, nu 0.49 5.6e-7 ->
+// 5.2e-7.
 #include "kernels.hpp"
 #include "mg.hpp"
 

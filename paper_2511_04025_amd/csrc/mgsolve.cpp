@@ -86,8 +86,8 @@ size_t carve(char *base, int n, int prec, MgDev *mg, char **d_mgdev) {
   char *G = take(8 * 576 * ts);
   const bool free1 = count > 2 && level1_free(prec, (long long)(n / 2) * (n / 2) * (n / 2));
   char *G2 = free1 ? take(64 * 576 * sizeof(double)) : nullptr;
-  // the voxel level's stored Chebyshev direction (its other V-cycle vectors
-  // alias CG vectors)
+  // the voxel level's own vector: z = V r in the dense solve, the first Chebyshev
+  // direction in the selective one (its other V-cycle vectors alias CG vectors)
   char *d0 = take((size_t)NRHS * 3 * (size_t)n * n * n * ts);
   if (mg) {
     mg->L = count - 1;

@@ -10,7 +10,9 @@
 // neighbours' values and their transposes by its own value, which LDS carries
 // to the neighbours; then thread (node, component) sums.  12 us (FP64: 23),
 // a third of it the first loads' latency, 1 us (FP64: 3) a pass; one 48^3
-// design 12.1 -> 10.5 ms, a 24^3 one in FP64 14.6 -> 11.8 ms.
+// design 12.1 -> 10.5 ms, a 24^3 one in FP64 14.6 -> 11.8 ms.  In FP64 the blocks
+// take 72 of the 128 registers that 1,024 threads leave, and 13 values go to
+// scratch (48 bytes a thread).
 // The 8^3 -> 4^3 tails of the powers of two keep their launches: there the
 // blocks (258 KB) and the dense inverse (295 KB) come to one compute unit at
 // 25 GB/s, 11 + 17 us, and the whole took 35 us against 45 with the launches'
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(1024) void mg_tail_kernel(MgBatch B, int l, int fin
       const int nf = F.n;
       const SHH_GLOBAL T *rf = to_global((const T *)F.r) + ((long long)rhs * 3 + c) * F.nn;
       const int fx[3] = {x == 0 ? nf - 1 : 2 * x - 1, 2 * x, 2 * x + 1};
-#pragma unroll(sizeof(T) == 4 ? 3 : 1)  // FP64: 27 values beside the blocks would spill
+#pragma unroll(sizeof(T) == 4 ? 3 : 1)  // FP64: no room for 27 values beside the blocks
       for (int oz = 0; oz < 3; ++oz) {
         const int Z = 2 * z + oz - 1;
         T val[3][3];

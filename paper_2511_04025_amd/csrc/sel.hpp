@@ -53,14 +53,17 @@ struct SelDev {
   void *Ec;               // [na] moduli in the working precision
   double *Ec64;           // [na] FP64 moduli (== Ec for the FP64 path)
   void *Dinv;             // [na] inverse Jacobi diagonal (same for the 3 components)
-  void *r, *p, *q, *x;    // [6][3][na] working precision
-  double *x64;            // [6][3][na] FP64 solution accumulator (mixed); == x for FP64
+  // Vectors hold the 18 values of a node (load case k, component c at o = 3 k + c)
+  // in chunks of 16 bytes, chunk by chunk over the nodes: [4][na][4] and [na][2] in
+  // FP32, [9][na][2] in FP64 (value o of node j: sel.hip::row_at)
+  void *r, *p, *q, *x;    // working precision
+  double *x64;            // FP64 solution accumulator (mixed); == x for FP64
   double *partials;       // [6][nparts][SEL_PS]
   CgState *st;
   // multigrid preconditioner (mg != 0): the voxel level's V-cycle steps run on
   // the compact lists, the coarse levels on the dense hierarchy built from the
   // culled moduli.  Chebyshev coefficients of the voxel level, the V-cycle's
-  // vectors (node-major, working precision) and the first coarse level's
+  // vectors (laid out as r, working precision) and the first coarse level's
   // right-hand side and iterate ([6][3][n1^3], dense), its first Chebyshev
   // direction (null where that level is the coarsest), D^-1 and 1 / theta
   int mg;

@@ -303,7 +303,7 @@ int describe(Slot &s) {
 }
 
 // After the compaction (n_a known): workgroup count, partial room, and the
-// multigrid's three extra [n_a][18] vectors after the compact arrays in
+// multigrid's three extra vectors (18 values a node) after the compact arrays in
 // vectors 0-1, then after the partials in vector 5 (Jacobi when a nearly full
 // design leaves no room for them).
 int place(Slot &s) {
@@ -405,7 +405,7 @@ int sel_start(const std::vector<Slot *> &in, hipStream_t st) {
       h.dir1 = M.L > 1 ? M.lv[1].d : nullptr;
       h.dinv1 = M.lv[1].Dinv;
       h.inv_theta1 = M.lv[1].inv_theta;
-      h.d0 = M.lv[0].d;  // the dense level-0 direction buffer: [6][3][n^3] >= [n_a][18]
+      h.d0 = M.lv[0].d;  // the dense level-0 direction buffer: 6 * 3 * n^3 values, at least 18 a node
     }
   }
   run.record(slots, 1);

@@ -53,9 +53,10 @@ namespace shh {
 enum { MODE_PCG = 0, MODE_RESID = 1, MODE_APPLY = 2, MODE_MGDIR = 3, MODE_MGPRE = 4, MODE_MGPOST = 5 };
 
 // Waves per SIMD that the compiler aims at.  Two workgroups share a CU up to 128
-// registers (FP32, four waves) or 168 (FP64, three).  The FP64 pre-smoothing pass
-// fits when told to; the FP64 direction and post-smoothing passes would spill (a
-// 24^3 FP64 solve 27.4 instead of 25.5 ms).
+// registers (FP32, four waves; the post-smoothing pass keeps two values in scratch
+// for it) or 168 (FP64, three).  The FP64 pre-smoothing pass fits when told to; the
+// FP64 direction and post-smoothing passes would spill (a 24^3 FP64 solve 27.4
+// instead of 25.5 ms).
 template <typename TC, int MODE>
 constexpr int WPE = sizeof(TC) == 4 ? 4 : (MODE == MODE_MGPRE ? 3 : 1);
 template <typename TC, typename TS, int MODE, bool TALL = false>
