@@ -273,3 +273,21 @@ def test_point_field_workspace_needs_only_charges(lib):
     a = B.DesignArgs(d)
     nb = c_size_t(0)
     assert lib.shh_workspace_bytes_points(byref(a.c), 0, byref(nb)) == B.SHH_INVALID_ARG
+
+
+def test_traffic_figure_belongs_to_its_sources(monkeypatch, tmp_path):
+    # bench.py's measured traffic ratio holds for the sources whose digest its
+    # profile records beside the counters: a digest that was only brought up to
+    # date in bench.py is not in the profile, and other sources give no figure
+    monkeypatch.syspath_prepend(ROOT)
+    import bench
+    for kind, t in bench.TRAFFIC.items():
+        with open(os.path.join(ROOT, t["profile"])) as f:
+            text = f.read()
+        assert t["sha256"] in text and f"{t['ratio']:.2f}" in text
+    csrc = tmp_path / "paper_2511_04025_amd" / "csrc"
+    csrc.mkdir(parents=True)
+    for f in {f for t in bench.TRAFFIC.values() for f in t["sources"]}:
+        (csrc / f).write_text("changed")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert all(bench.traffic_ratio(kind) is None for kind in bench.TRAFFIC)
